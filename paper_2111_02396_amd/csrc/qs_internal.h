@@ -94,13 +94,20 @@ struct TileArgs {
 };
 
 // ---- batched persistent launch -------------------------------------------
-// Device program of many small circuits, run one trajectory per workgroup
-// iteration.  A circuit whose state fits in LDS (n <= kBatchLdsQubits) keeps
-// it there for the whole trajectory; larger ones stream tiles of a per-
-// workgroup global slot, one pass per sweep.
+// Device program of many small circuits.  A circuit whose state fits in LDS
+// (n <= kBatchLdsQubits) runs one trajectory per workgroup iteration, the
+// state in LDS throughout; larger ones run as tile sweeps over all jobs of a
+// wave, one launch per sweep.
 constexpr int kBatchLdsQubits = 13;
 constexpr int kBatchMaxQubits = 18;
-constexpr int kBatchTileBits = 12;
+constexpr int kBatchTileBits = 13;      // tiles of the larger circuits' sweeps
+constexpr int kBatchWideThreads = 512;
+// The blocks of the larger circuits run in the order of a grouping into
+// 2^12-amplitude tiles that hold bits 0..5.  Blocks on disjoint qubits
+// commute but round differently, so this order is part of the results; the
+// sweeps only cut it into runs that fit a tile.
+constexpr int kBatchOrderBits = 12;
+constexpr int kBatchOrderLowBits = 6;
 constexpr int kBatchMaxSamples = 4096;
 
 struct BatchGate {
@@ -110,10 +117,23 @@ struct BatchGate {
     int m0, m1;              // the block's operations in the member table
 };
 
-struct BatchSweep {
-    int tb;                  // tile bits (tiled circuits); n for resident ones
-    int pos[kMaxTileBits];
-    int g0, g1;              // gate range
+// The same block as a tile sweep reads it (circuits of n > kBatchLdsQubits;
+// kept apart from BatchGate, which the resident kernel carries in registers).
+struct BatchTileGate {
+    int k;
+    int lt[kMaxGateQubits];
+    int lofs;                // float2 offset in the staged matrices
+    int tab[kMaxTileBits];   // LDS byte offset per logical bit (batch_gate_tables)
+};
+
+struct BatchSweep {          // circuits of n > kBatchLdsQubits
+    int pos[kMaxTileBits];   // the tile's kBatchTileBits index bits
+    int g0, g1;              // block range, relative to the circuit's first
+};
+
+// A workgroup's share of a sweep launch: `tiles` tiles of one job.
+struct BatchPart {
+    int job, tile0, tiles;
 };
 
 struct BatchCircuit {
@@ -123,6 +143,7 @@ struct BatchCircuit {
     int n_samples;
     int readout;             // offset of 2n doubles (e0[], e1[]) in the readout pool, or -1
     int g0, n_gates;         // the circuit's blocks (absolute first, count)
+    int tg0;                 // its first entry in tile_gates
     int ch0, nch;            // the circuit's channels in the channel table
     int pool0, pool_len;     // float2 range of the circuit's default matrices in the pool
 };
@@ -156,12 +177,16 @@ struct BatchJob {
     uint64_t seed;           // Philox key
     int64_t out;             // first output sample
     int64_t choices;         // first recorded pick, or -1
+    // n > kBatchLdsQubits: the job's state, its rebuilt matrices and its
+    // matrix table within the wave's buffers
+    int64_t slot, mine, mptr;
 };
 
 struct BatchArgs {
     const BatchCircuit *circs;
     const BatchSweep *sweeps;
     const BatchGate *gates;
+    const BatchTileGate *tile_gates;  // those of the larger circuits
     const BatchJob *jobs;
     const float2 *mats;      // default block matrices
     const double *readout;
@@ -169,13 +194,13 @@ struct BatchArgs {
     const double *pbar;
     const BatchMember *members;
     const double2 *fmats;    // FP64 gate and channel matrices for the members
-    float2 *patched;         // per-workgroup matrices of the blocks a job's picks change
-    int64_t patched_stride;  // float2 entries per workgroup
+    float2 *patched;         // matrices of the blocks a job's picks change
+    int64_t patched_stride;  // float2 entries per workgroup of run_batched
+    const float2 **mptr;     // per job of a wave: its blocks' matrices
     int8_t *choices;         // recorded picks
-    float2 *slots;           // per-workgroup state slots (tiled circuits)
-    int64_t slot_amps;
+    float2 *slots;           // the wave's states
     uint64_t *out;
-    int n_jobs;
+    int n_jobs;              // resident jobs (the first ones)
 };
 
 // Blocks per batched circuit: the job's patched-block flags are one bit each
@@ -282,9 +307,18 @@ struct SelectArgs {
 
 hipError_t launch_select(const SelectArgs &a, hipStream_t st);
 
-// One persistent launch over all jobs; `grid` workgroups, each owning slot
-// blockIdx.x of `slots` when it runs a tiled circuit.
+// One persistent launch over the resident jobs.
 hipError_t launch_batched(const BatchArgs &a, int grid, hipStream_t st);
+
+// The larger jobs of a wave, jobs [job0, job0 + jobs): draws and matrices;
+// sweep `step` of the parts' jobs (each has one); samples.
+hipError_t launch_batch_prepare(const BatchArgs &a, int job0, int jobs, hipStream_t st);
+hipError_t launch_batch_sweep(const BatchArgs &a, const BatchPart *parts, int n_parts, int step, bool k5,
+                              hipStream_t st);
+hipError_t launch_batch_sample(const BatchArgs &a, int job0, int jobs, hipStream_t st);
+
+// Fills g.tab for the sweeps' tile layout.
+void batch_gate_tables(BatchTileGate &g);
 
 // Workgroups the batched launch uses (persistent grid size).
 int batched_grid();

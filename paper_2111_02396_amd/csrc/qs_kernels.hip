@@ -560,11 +560,17 @@ __device__ __forceinline__ void tile_gate_mfma5(float2 *__restrict__ sd, const f
 // log2(NT / 64)), else on VALU from the plain matrix.
 // RK: the launch also accumulates the reduced density matrix of one tile
 // qubit (TileArgs::rdm_out) from every tile after its gates.
-template <int TB, typename Idx, bool K5, int NT, bool RK>
-__global__ __launch_bounds__(NT) void apply_tile(float2 *__restrict__ amp, Idx n_tiles,
-                                                 TileArgs a) {
+//
+// The sweep's description comes through Src: the kernel's own arguments
+// (apply_tile) or tables in device memory (batch_sweep).  Tiles first,
+// first + step, ... below last are this workgroup's.
+// K5V: 5-qubit blocks take the VALU path at any tile width (the batched
+// launch, whose resident states do).
+template <int TB, typename Idx, bool K5, int NT, bool RK, bool K5V, class Src>
+__device__ __forceinline__ void tile_sweep(float2 *__restrict__ amp, Idx first, Idx step, Idx last, const Src &a,
+                                           float2 *__restrict__ sd, float2 *__restrict__ sm) {
     constexpr int NB = ilog2(NT);
-    constexpr bool K5_MFMA = TB >= 9 + NB - 6;
+    constexpr bool K5_MFMA = !K5V && TB >= 9 + NB - 6;
     static_assert(TB >= 10, "the MFMA gates need at least 32 groups per tile");
     static_assert((1 << (TB - 8)) >= NT / 64, "every wavefront needs a 4-qubit batch");
     constexpr int E = 1 << TB;
@@ -573,24 +579,19 @@ __global__ __launch_bounds__(NT) void apply_tile(float2 *__restrict__ amp, Idx n
     // the pair is one 16-byte load or store, and each eight lanes cover one
     // 128-byte line (local bits 0..3 are global bits 0..3).
     constexpr int R = E / (2 * NT);
-    // The tile is a static array (its LDS address is a link-time constant
-    // that folds into the LDS instructions' offsets); the launch's matrices
-    // follow it in dynamic LDS.
-    __shared__ float2 sd[E];
-    extern __shared__ float2 sm[];
-    Idx tile = blockIdx.x;
-    if (tile >= n_tiles) return;  // uniform over the workgroup
+    Idx tile = first;
+    if (tile >= last) return;  // uniform over the workgroup
     Idx off_tid = 0;
 #pragma unroll
     for (int b = 0; b < NB; ++b)
-        if ((threadIdx.x >> b) & 1) off_tid |= Idx(1) << a.pos[b + 1];
+        if ((threadIdx.x >> b) & 1) off_tid |= Idx(1) << a.pos(b + 1);
     Idx off_r[R];
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         Idx o = 0;
 #pragma unroll
         for (int b = NB + 1; b < TB; ++b)
-            if (((r << (NB + 1)) >> b) & 1) o |= Idx(1) << a.pos[b];
+            if (((r << (NB + 1)) >> b) & 1) o |= Idx(1) << a.pos(b);
         off_r[r] = o;
     }
     // First index of tile t: the bits of t spread over the positions the tile
@@ -600,27 +601,27 @@ __global__ __launch_bounds__(NT) void apply_tile(float2 *__restrict__ amp, Idx n
     auto tile_base = [&](Idx t) {
         Idx base = t << kTileLowBits;
 #pragma unroll
-        for (int b = kTileLowBits; b < TB; ++b) base += base & (~Idx(0) << a.pos[b]);
+        for (int b = kTileLowBits; b < TB; ++b) base += base & (~Idx(0) << a.pos(b));
         return base + off_tid;
     };
     // A tile's amplitude pairs.  With init_zero the sweep starts from
     // |0...0> without reading the state: nothing is fetched, and the tile's
     // LDS copy is written from zeros (amplitude 1 at index 0).
     auto fetch = [&](Idx t, float4 (&dst)[R]) {
-        if (a.init_zero) return;
+        if (a.init_zero()) return;
         const Idx base = tile_base(t);
 #pragma unroll
         for (int r = 0; r < R; ++r) dst[r] = *reinterpret_cast<const float4 *>(amp + base + off_r[r]);
     };
     float4 v[R];
     fetch(tile, v);
-    for (int gi = 0; gi < a.n_gates; ++gi) {
-        const int k = a.g[gi].k;
-        const float2 *src = a.g[gi].mat;
-        float2 *dst = sm + a.g[gi].lofs;
+    for (int gi = 0; gi < a.n_gates(); ++gi) {
+        const int k = a.k(gi);
+        const float2 *src = a.mat(gi);
+        float2 *dst = sm + a.lofs(gi);
         int gtab[kMaxTileBits];
 #pragma unroll
-        for (int b = 0; b < kMaxTileBits; ++b) gtab[b] = a.g[gi].tab[b];
+        for (int b = 0; b < kMaxTileBits; ++b) gtab[b] = a.tab(gi, b);
         if (k == 4) {
             stage_frag4<NT>(reinterpret_cast<float *>(dst), src, gtab);
         } else if (k == 3) {
@@ -653,7 +654,7 @@ __global__ __launch_bounds__(NT) void apply_tile(float2 *__restrict__ amp, Idx n
     auto run_tile = [&](Idx t, bool has_prev) {
         __syncthreads();  // the previous tile is out of LDS; matrices staged
         const Idx base = tile_base(t);
-        if (a.init_zero) {
+        if (a.init_zero()) {
             const float one = base == Idx(0) ? 1.f : 0.f;  // index 0 is pair 0 of work-item 0
 #pragma unroll
             for (int r = 0; r < R; ++r) {
@@ -671,33 +672,33 @@ __global__ __launch_bounds__(NT) void apply_tile(float2 *__restrict__ amp, Idx n
 #pragma unroll
             for (int r = 0; r < R; ++r) *reinterpret_cast<float4 *>(amp + prev_base + off_r[r]) = o[r];
         }
-        const Idx next = t + gridDim.x;
-        if (next < n_tiles) fetch(next, v);
+        const Idx next = t + step;
+        if (next < last) fetch(next, v);
         __syncthreads();
-        for (int gi = 0; gi < a.n_gates; ++gi) {
-            const int k = a.g[gi].k;
+        for (int gi = 0; gi < a.n_gates(); ++gi) {
+            const int k = a.k(gi);
             int lt[kMaxGateQubits], tab[kMaxTileBits];
 #pragma unroll
-            for (int b = 0; b < kMaxGateQubits; ++b) lt[b] = a.g[gi].lt[b];
+            for (int b = 0; b < kMaxGateQubits; ++b) lt[b] = a.lt(gi, b);
 #pragma unroll
-            for (int b = 0; b < kMaxTileBits; ++b) tab[b] = a.g[gi].tab[b];
+            for (int b = 0; b < kMaxTileBits; ++b) tab[b] = a.tab(gi, b);
             switch (k) {
-                case 1: tile_gate_small<1, SwizzledTile, NT>(sd, a.g[gi].mat, lt, tab, TB); break;
-                case 2: tile_gate_small<2, SwizzledTile, NT>(sd, a.g[gi].mat, lt, tab, TB); break;
+                case 1: tile_gate_small<1, SwizzledTile, NT>(sd, a.mat(gi), lt, tab, TB); break;
+                case 2: tile_gate_small<2, SwizzledTile, NT>(sd, a.mat(gi), lt, tab, TB); break;
                 case 3:
-                    tile_gate_mfma3<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.g[gi].lofs),
+                    tile_gate_mfma3<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)),
                                                       tab, TB);
                     break;
                 case 4:
-                    tile_gate_mfma4<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.g[gi].lofs),
+                    tile_gate_mfma4<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)),
                                                       tab, TB);
                     break;
                 default:
                     if constexpr (K5 && K5_MFMA)
-                        tile_gate_mfma5<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.g[gi].lofs),
+                        tile_gate_mfma5<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)),
                                                           tab, TB);
                     else if constexpr (K5)
-                        tile_gate_valu<5, SwizzledTile, NT>(sd, sm + a.g[gi].lofs, lt, TB);
+                        tile_gate_valu<5, SwizzledTile, NT>(sd, sm + a.lofs(gi), lt, TB);
                     break;
             }
             __syncthreads();
@@ -712,7 +713,7 @@ __global__ __launch_bounds__(NT) void apply_tile(float2 *__restrict__ amp, Idx n
             // read again from LDS (a rolled loop keeps the registers of the
             // common sweep); the partner across the qubit's bit pc sits at
             // LDS index ^ map(2^pc)
-            const int pc = a.rdm_lt;
+            const int pc = a.rdm_lt();
             const int pm = SwizzledTile::map(1 << pc);
             const int tid_bit = pc >= 1 && pc <= NB ? (int(threadIdx.x) >> (pc - 1)) & 1 : 0;
 #pragma unroll 1
@@ -736,7 +737,7 @@ __global__ __launch_bounds__(NT) void apply_tile(float2 *__restrict__ amp, Idx n
         prev_base = base;
     };
     run_tile(tile, false);
-    for (tile += gridDim.x; tile < n_tiles; tile += gridDim.x) run_tile(tile, true);
+    for (tile += step; tile < last; tile += step) run_tile(tile, true);
 #pragma unroll
     for (int r = 0; r < R; ++r) *reinterpret_cast<float4 *>(amp + prev_base + off_r[r]) = o[r];
     if constexpr (RK) {
@@ -768,7 +769,7 @@ __global__ __launch_bounds__(NT) void apply_tile(float2 *__restrict__ amp, Idx n
                 sr += red[4 * w + 2];
                 si += red[4 * w + 3];
             }
-            double *rec = a.rdm_out + size_t(blockIdx.x) * 8;
+            double *rec = a.rdm_out() + size_t(blockIdx.x) * 8;
             rec[0] = s00;
             rec[1] = 0.0;
             rec[2] = sr;
@@ -779,6 +780,31 @@ __global__ __launch_bounds__(NT) void apply_tile(float2 *__restrict__ amp, Idx n
             rec[7] = 0.0;
         }
     }
+}
+
+// A launch's sweep in the kernel's arguments.
+struct ArgSweep {
+    const TileArgs &a;
+    __device__ __forceinline__ int pos(int b) const { return a.pos[b]; }
+    __device__ __forceinline__ int n_gates() const { return a.n_gates; }
+    __device__ __forceinline__ int init_zero() const { return a.init_zero; }
+    __device__ __forceinline__ int rdm_lt() const { return a.rdm_lt; }
+    __device__ __forceinline__ double *rdm_out() const { return a.rdm_out; }
+    __device__ __forceinline__ int k(int gi) const { return a.g[gi].k; }
+    __device__ __forceinline__ int lt(int gi, int b) const { return a.g[gi].lt[b]; }
+    __device__ __forceinline__ int lofs(int gi) const { return a.g[gi].lofs; }
+    __device__ __forceinline__ int tab(int gi, int b) const { return a.g[gi].tab[b]; }
+    __device__ __forceinline__ const float2 *mat(int gi) const { return a.g[gi].mat; }
+};
+
+template <int TB, typename Idx, bool K5, int NT, bool RK>
+__global__ __launch_bounds__(NT) void apply_tile(float2 *__restrict__ amp, Idx n_tiles, TileArgs a) {
+    // The tile is a static array (its LDS address is a link-time constant
+    // that folds into the LDS instructions' offsets); the launch's matrices
+    // follow it in dynamic LDS.
+    __shared__ float2 sd[1 << TB];
+    extern __shared__ float2 sm[];
+    tile_sweep<TB, Idx, K5, NT, RK, false>(amp, Idx(blockIdx.x), Idx(gridDim.x), n_tiles, ArgSweep{a}, sd, sm);
 }
 
 // ---------------------------------------------------------------- branch selection
@@ -1096,204 +1122,259 @@ __device__ __forceinline__ void fuse_patched(const BatchArgs &A, const BatchJob 
     }
 }
 
-// Persistent launch: each workgroup takes jobs blockIdx.x, + gridDim.x, ...
+// The job's channel draws (one Philox call per channel, Algorithm 2's fast
+// path), recorded when asked; a pick other than the default one flags its
+// block in `mask`, and the flagged blocks' matrices are rebuilt with the
+// job's picks into `mine`, one wavefront per block, by the first four
+// wavefronts (LDS workspaces: 1024 + 64 complex128 each at ws4 and ush4).
+// Ends with a workgroup barrier.
+template <int NT>
+__device__ __forceinline__ void draw_and_patch(const BatchArgs &A, const BatchJob &J, const BatchCircuit &C,
+                                               uint32_t *mask, double2 *ws4, double2 *ush4, float2 *mine) {
+    const int words = (C.n_gates + 31) >> 5;
+    for (int w = threadIdx.x; w < words; w += NT) mask[w] = 0u;
+    __syncthreads();
+    for (int c = threadIdx.x; c < C.nch; c += NT) {
+        const BatchChannel ch = A.chans[C.ch0 + c];
+        const int pick = draw_pick(A.pbar + ch.pbar, ch.nk,
+                                   philox_uniform(J.seed, uint32_t(c), J.traj, J.circ_id, kStreamChannel));
+        if (J.choices >= 0) A.choices[J.choices + c] = int8_t(pick);
+        if (pick != ch.default_pick) atomicOr(&mask[ch.gate >> 5], 1u << (ch.gate & 31));
+    }
+    __syncthreads();
+    const int wave = int(threadIdx.x) >> 6;
+    double2 *ws = ws4 + wave * 1024;
+    double2 *ush = ush4 + wave * 64;
+    for (int w = wave; wave < 4 && w < words; w += 4) {
+        uint32_t bits = __builtin_amdgcn_readfirstlane(mask[w]);
+        while (bits) {
+            const int b = __builtin_ctz(bits);
+            bits &= bits - 1u;
+            fuse_patched(A, J, C, 32 * w + b, ws, ush, mine);
+        }
+    }
+    __syncthreads();
+}
+
+// Samples of a job's final state at `p` (2^n amplitudes): inverse CDF over
+// 256 contiguous chunks whose FP64 sums are scanned in a fixed order; readout
+// flips as in sample_draw.  PIECE amplitudes are loaded at a time (16 for a
+// state in global memory, so that a work-item's 128-byte line is one burst of
+// independent loads; the order of the additions is the same for any PIECE,
+// which divides the chunk length).  `part` is 256 doubles of LDS.
+template <int NT, int PIECE>
+__device__ __forceinline__ void batched_sample(const BatchArgs &A, const BatchJob &J, const BatchCircuit &C,
+                                               const float2 *p, double *part) {
+    const int n = C.n;
+    const int dim = 1 << n;
+    // chunk c = amplitudes [c*L, (c+1)*L), L = dim / 256 (>= 1), the same 256
+    // chunks at either group size
+    const int L = dim >= kBlock ? dim / kBlock : 1;
+    const int chunks = dim >= kBlock ? kBlock : dim;
+    double acc = 0.0;
+    if (int(threadIdx.x) < chunks) {
+        for (int i = 0; i < L; i += PIECE) {
+            float2 v[PIECE];
+#pragma unroll
+            for (int j = 0; j < PIECE; ++j) v[j] = p[threadIdx.x * L + i + j];
+#pragma unroll
+            for (int j = 0; j < PIECE; ++j)
+                acc = fma(double(v[j].x), double(v[j].x), fma(double(v[j].y), double(v[j].y), acc));
+        }
+    }
+    if (int(threadIdx.x) < kBlock) part[threadIdx.x] = acc;
+    __syncthreads();
+    // inclusive prefix of the chunk sums by one wavefront: lane l sums
+    // chunks 4l..4l+3 in order, the lanes' totals are scanned across
+    // the wavefront, and chunk c's prefix is the lane's offset plus its
+    // own running sum (a fixed order, so every launch rounds alike),
+    // then made exactly non-decreasing by a running maximum (the two
+    // summation orders can differ by an ulp where lanes meet)
+    if (threadIdx.x < 64) {
+        const int l = int(threadIdx.x);
+        double p4[4];
+        double run = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            run += 4 * l + i < chunks ? part[4 * l + i] : 0.0;
+            p4[i] = run;
+        }
+        double t = run;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const double u = __shfl_up(t, o);
+            if (l >= o) t += u;
+        }
+        double off = __shfl_up(t, 1);
+        if (l == 0) off = 0.0;
+        double hi = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            p4[i] = fmax(hi, off + p4[i]);
+            hi = p4[i];
+        }
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const double u = __shfl_up(hi, o);
+            if (l >= o) hi = fmax(hi, u);
+        }
+        double below = __shfl_up(hi, 1);
+        if (l == 0) below = 0.0;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (4 * l + i < chunks) part[4 * l + i] = fmax(below, p4[i]);
+    }
+    __syncthreads();
+    const double N = part[chunks - 1];
+    for (int smp = threadIdx.x; smp < C.n_samples; smp += NT) {
+        const double target = philox_uniform(J.seed, uint32_t(smp), J.traj, J.circ_id, kStreamMeasure) * N;
+        int lo = 0, hi = chunks;
+        while (lo < hi) {
+            const int mid = (lo + hi) >> 1;
+            if (target < part[mid]) hi = mid; else lo = mid + 1;
+        }
+        uint32_t x;
+        if (lo >= chunks) {
+            x = uint32_t(dim - 1);
+        } else {
+            double run = lo > 0 ? part[lo - 1] : 0.0;
+            int at = L - 1;
+            for (int i = 0; i < L; i += PIECE) {
+                float2 v[PIECE];
+#pragma unroll
+                for (int j = 0; j < PIECE; ++j) v[j] = p[lo * L + i + j];
+                int found = -1;
+#pragma unroll
+                for (int j = 0; j < PIECE; ++j) {
+                    run += fma(double(v[j].x), double(v[j].x), double(v[j].y) * double(v[j].y));
+                    if (found < 0 && target < run) found = i + j;
+                }
+                if (found >= 0) {
+                    at = found;
+                    break;
+                }
+            }
+            x = uint32_t(lo * L + at);
+        }
+        if (C.readout >= 0) {
+            const double *e0 = A.readout + C.readout;
+            const double *e1 = e0 + n;
+            for (int q = 0; q < n; ++q) {
+                const int bit = int((x >> q) & 1u);
+                const double u = philox_uniform(J.seed, uint32_t(smp * n + q), J.traj, J.circ_id,
+                                                kStreamReadout);
+                if (u < (bit ? e1[q] : e0[q])) x ^= 1u << q;
+            }
+        }
+        A.out[J.out + smp] = x;
+    }
+}
+
+// Persistent launch over the jobs whose state fits in LDS (n <=
+// kBatchLdsQubits): each workgroup takes jobs blockIdx.x, + gridDim.x, ...
 // A job is one trajectory: its channels are drawn, the blocks its picks
 // change are rebuilt, the state starts as |0...0>, the circuit's blocks run
-// with the job's matrices, and the workgroup samples the final state
-// (inverse CDF over 256 contiguous chunks whose FP64 sums are scanned in a
-// fixed order; readout flips as in sample_draw).
+// with the job's matrices, and the workgroup samples the final state.
+// The workgroup's own global stores (the rebuilt matrices) are read back
+// only by its own wavefronts, which share one CU and its L1: the barriers'
+// workgroup-scope ordering suffices, and no device-scope fence (an L2
+// write-back and invalidate on gfx950) is needed.
 template <int NT>
 __global__ __launch_bounds__(NT) void run_batched(BatchArgs A) {
-    constexpr int LNT = ilog2(NT);
     extern __shared__ float2 smem[];
     float2 *sd = smem;                                                   // 2^13 amplitudes
     float *frag = reinterpret_cast<float *>(smem + (1 << kBatchLdsQubits));  // 2048 floats
     float2 *raw = smem + (1 << kBatchLdsQubits) + 1024;                  // 2 x 256 entries
     __shared__ double part[kBlock];
-    float2 *slot = A.slots ? A.slots + size_t(blockIdx.x) * size_t(A.slot_amps) : nullptr;
     float2 *mine = A.patched + size_t(blockIdx.x) * size_t(A.patched_stride);
     uint32_t *mask = reinterpret_cast<uint32_t *>(part);  // blocks the job's picks change
     for (int job = blockIdx.x; job < A.n_jobs; job += gridDim.x) {
         const BatchJob J = A.jobs[job];
         const BatchCircuit C = A.circs[J.circuit];
-        const int n = C.n;
-        const int dim = 1 << n;
-        // the job's channel draws (one Philox call per channel, Algorithm
-        // 2's fast path), recorded when asked; a pick other than the default
-        // one flags its block
-        const int words = (C.n_gates + 31) >> 5;
-        for (int w = threadIdx.x; w < words; w += NT) mask[w] = 0u;
+        const int dim = 1 << C.n;
+        draw_and_patch<NT>(A, J, C, mask, reinterpret_cast<double2 *>(sd), reinterpret_cast<double2 *>(raw), mine);
+        for (int i = threadIdx.x; i < dim; i += NT) sd[i] = make_float2(i == 0 ? 1.f : 0.f, 0.f);
         __syncthreads();
-        for (int c = threadIdx.x; c < C.nch; c += NT) {
-            const BatchChannel ch = A.chans[C.ch0 + c];
-            const int pick = draw_pick(A.pbar + ch.pbar, ch.nk,
-                                       philox_uniform(J.seed, uint32_t(c), J.traj, J.circ_id, kStreamChannel));
-            if (J.choices >= 0) A.choices[J.choices + c] = int8_t(pick);
-            if (pick != ch.default_pick) atomicOr(&mask[ch.gate >> 5], 1u << (ch.gate & 31));
-        }
-        __syncthreads();
-        // the flagged blocks' matrices with the job's picks, one wavefront
-        // per block, by the first four wavefronts (workspace: a quarter of
-        // the LDS state area each)
-        {
-            const int wave = int(threadIdx.x) >> 6;
-            double2 *ws = reinterpret_cast<double2 *>(sd) + wave * 1024;
-            double2 *ush = reinterpret_cast<double2 *>(raw) + wave * 64;
-            for (int w = wave; wave < 4 && w < words; w += 4) {
-                uint32_t bits = __builtin_amdgcn_readfirstlane(mask[w]);
-                while (bits) {
-                    const int b = __builtin_ctz(bits);
-                    bits &= bits - 1u;
-                    fuse_patched(A, J, C, 32 * w + b, ws, ush, mine);
-                }
-            }
-            // The workgroup's own global stores (these copies, the state slot)
-            // are read back only by its own wavefronts, which share one CU and
-            // its L1: the barrier's workgroup-scope ordering suffices, and no
-            // device-scope fence (an L2 write-back and invalidate on gfx950)
-            // is needed anywhere in this kernel.
-            __syncthreads();
-        }
-        // the state: LDS (resident) or the workgroup's slot, each accessed
-        // through its own pointer so that LDS accesses stay LDS instructions
-        const bool res = C.resident != 0;
-        for (int i = threadIdx.x; i < dim; i += NT) {
-            const float2 z = make_float2(i == 0 ? 1.f : 0.f, 0.f);
-            if (res) sd[i] = z;
-            else slot[i] = z;
-        }
-        __syncthreads();
-        for (int si = C.s0; si < C.s1; ++si) {
-            const BatchSweep &S = A.sweeps[si];
-            if (C.resident) {
-                batched_blocks<NT>(A, mask, mine, C, S.g0, S.g1, sd, frag, raw, n);
-                continue;
-            }
-            // tiled: one pass over the slot, tile by tile
-            const int tb = S.tb;
-            const int R = (1 << tb) / NT;
-            int off_tid = 0;
-            for (int b = 0; b < LNT; ++b)
-                if ((threadIdx.x >> b) & 1) off_tid |= 1 << S.pos[b];
-            const int n_tiles = dim >> tb;
-            for (int t = 0; t < n_tiles; ++t) {
-                int base = t;
-                for (int b = 0; b < tb; ++b) {
-                    const int q = S.pos[b];
-                    base = ((base >> q) << (q + 1)) | (base & ((1 << q) - 1));
-                }
-                base += off_tid;
-                for (int r = 0; r < R; ++r) {
-                    int o = 0;
-                    for (int b = LNT; b < tb; ++b)
-                        if (((r << LNT) >> b) & 1) o |= 1 << S.pos[b];
-                    sd[threadIdx.x + (r << LNT)] = slot[base + o];
-                }
-                __syncthreads();
-                batched_blocks<NT>(A, mask, mine, C, S.g0, S.g1, sd, frag, raw, tb);
-                for (int r = 0; r < R; ++r) {
-                    int o = 0;
-                    for (int b = LNT; b < tb; ++b)
-                        if (((r << LNT) >> b) & 1) o |= 1 << S.pos[b];
-                    slot[base + o] = sd[threadIdx.x + (r << LNT)];
-                }
-                __syncthreads();
-            }
-        }
-        // sampling: chunk c = amplitudes [c*L, (c+1)*L), L = dim / 256 (>= 1),
-        // the same 256 chunks at either group size
-        const int L = dim >= kBlock ? dim / kBlock : 1;
-        const int chunks = dim >= kBlock ? kBlock : dim;
-        auto chunk_sum = [&](const float2 *p) {
-            double acc = 0.0;
-            for (int i = 0; i < L; ++i) {
-                const float2 v = p[threadIdx.x * L + i];
-                acc = fma(double(v.x), double(v.x), fma(double(v.y), double(v.y), acc));
-            }
-            return acc;
-        };
-        double acc = 0.0;
-        if (int(threadIdx.x) < chunks) acc = res ? chunk_sum(sd) : chunk_sum(slot);
-        if (int(threadIdx.x) < kBlock) part[threadIdx.x] = acc;
-        __syncthreads();
-        // inclusive prefix of the chunk sums by one wavefront: lane l sums
-        // chunks 4l..4l+3 in order, the lanes' totals are scanned across
-        // the wavefront, and chunk c's prefix is the lane's offset plus its
-        // own running sum (a fixed order, so every launch rounds alike),
-        // then made exactly non-decreasing by a running maximum (the two
-        // summation orders can differ by an ulp where lanes meet)
-        if (threadIdx.x < 64) {
-            const int l = int(threadIdx.x);
-            double p[4];
-            double run = 0.0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                run += 4 * l + i < chunks ? part[4 * l + i] : 0.0;
-                p[i] = run;
-            }
-            double t = run;
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const double u = __shfl_up(t, o);
-                if (l >= o) t += u;
-            }
-            double off = __shfl_up(t, 1);
-            if (l == 0) off = 0.0;
-            double hi = 0.0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                p[i] = fmax(hi, off + p[i]);
-                hi = p[i];
-            }
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const double u = __shfl_up(hi, o);
-                if (l >= o) hi = fmax(hi, u);
-            }
-            double below = __shfl_up(hi, 1);
-            if (l == 0) below = 0.0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (4 * l + i < chunks) part[4 * l + i] = fmax(below, p[i]);
-        }
-        __syncthreads();
-        const double N = part[chunks - 1];
-        for (int smp = threadIdx.x; smp < C.n_samples; smp += NT) {
-            const double target = philox_uniform(J.seed, uint32_t(smp), J.traj, J.circ_id, kStreamMeasure) * N;
-            int lo = 0, hi = chunks;
-            while (lo < hi) {
-                const int mid = (lo + hi) >> 1;
-                if (target < part[mid]) hi = mid; else lo = mid + 1;
-            }
-            uint32_t x;
-            if (lo >= chunks) {
-                x = uint32_t(dim - 1);
-            } else {
-                auto within = [&](const float2 *p) {
-                    double run = lo > 0 ? part[lo - 1] : 0.0;
-                    for (int i = 0; i < L; ++i) {
-                        const float2 v = p[lo * L + i];
-                        run += fma(double(v.x), double(v.x), double(v.y) * double(v.y));
-                        if (target < run) return i;
-                    }
-                    return L - 1;
-                };
-                x = uint32_t(lo * L + (res ? within(sd) : within(slot)));
-            }
-            if (C.readout >= 0) {
-                const double *e0 = A.readout + C.readout;
-                const double *e1 = e0 + n;
-                for (int q = 0; q < n; ++q) {
-                    const int bit = int((x >> q) & 1u);
-                    const double u = philox_uniform(J.seed, uint32_t(smp * n + q), J.traj, J.circ_id,
-                                                    kStreamReadout);
-                    if (u < (bit ? e1[q] : e0[q])) x ^= 1u << q;
-                }
-            }
-            A.out[J.out + smp] = x;
-        }
+        batched_blocks<NT>(A, mask, mine, C, C.g0, C.g0 + C.n_gates, sd, frag, raw, C.n);
+        batched_sample<NT, 1>(A, J, C, sd, part);
         __syncthreads();
     }
+}
+
+// ---- jobs of n > kBatchLdsQubits
+// One workgroup per such job would leave most of the GPU waiting for the
+// widest ones (an 18-qubit, 40-cycle trajectory alone took 45 ms), so their
+// sweeps are launches over all jobs of a wave at once: launch s applies
+// sweep s of every job that has one, a workgroup per one or two tiles of one
+// job, with the tile sweep of apply_tile (FP32 MFMA and the LDS round trips
+// of its blocks bound it, as there).  What a sweep applies, and in which
+// order, is fixed by the circuit's plan, so a job's state does not depend on
+// the jobs beside it.  64 circuits of 12..18 qubits x 16 trajectories: 51 ms
+// with a workgroup per job, 7.8 ms like this (5.5 ms of it sweeps).
+
+// Per job of the wave: draws, rebuilt matrices, and the table of the job's
+// block matrices (default or rebuilt) its sweeps read.
+__global__ __launch_bounds__(kBlock) void batch_prepare(BatchArgs A, int job0) {
+    extern __shared__ float2 smem[];  // 4 x (1024 + 64) complex128
+    __shared__ uint32_t mask[kBatchMaxBlocks / 32];
+    const BatchJob J = A.jobs[job0 + int(blockIdx.x)];
+    const BatchCircuit C = A.circs[J.circuit];
+    float2 *mine = A.patched + J.mine;
+    double2 *ws = reinterpret_cast<double2 *>(smem);
+    draw_and_patch<kBlock>(A, J, C, mask, ws, ws + 4 * 1024, mine);
+    for (int gi = threadIdx.x; gi < C.n_gates; gi += kBlock) {
+        const int mat = A.gates[C.g0 + gi].mat;
+        const bool patched = (mask[gi >> 5] >> (gi & 31)) & 1u;
+        A.mptr[J.mptr + gi] = patched ? mine + (mat - C.pool0) : A.mats + mat;
+    }
+}
+
+// A job's sweep in device tables; uniform, so read through the constant
+// address space (scalar loads).
+struct JobSweep {
+    const __attribute__((address_space(4))) BatchSweep *s;
+    const __attribute__((address_space(4))) BatchTileGate *g;  // the sweep's first gate
+    const __attribute__((address_space(4))) uint64_t *m;   // its matrices' addresses
+    int zero;
+    __device__ __forceinline__ int pos(int b) const { return s->pos[b]; }
+    __device__ __forceinline__ int n_gates() const { return s->g1 - s->g0; }
+    __device__ __forceinline__ int init_zero() const { return zero; }
+    __device__ __forceinline__ int rdm_lt() const { return 0; }
+    __device__ __forceinline__ double *rdm_out() const { return nullptr; }
+    __device__ __forceinline__ int k(int gi) const { return g[gi].k; }
+    __device__ __forceinline__ int lt(int gi, int b) const { return g[gi].lt[b]; }
+    __device__ __forceinline__ int lofs(int gi) const { return g[gi].lofs; }
+    __device__ __forceinline__ int tab(int gi, int b) const { return g[gi].tab[b]; }
+    __device__ __forceinline__ const float2 *mat(int gi) const { return reinterpret_cast<const float2 *>(m[gi]); }
+};
+
+template <bool K5>
+__global__ __launch_bounds__(kBatchWideThreads) void batch_sweep(BatchArgs A, const BatchPart *parts, int step) {
+    __shared__ float2 sd[1 << kBatchTileBits];
+    extern __shared__ float2 sm[];
+    typedef const __attribute__((address_space(4))) BatchPart *Parts;
+    typedef const __attribute__((address_space(4))) BatchJob *Jobs;
+    typedef const __attribute__((address_space(4))) BatchCircuit *Circs;
+    typedef const __attribute__((address_space(4))) BatchSweep *Sweeps;
+    typedef const __attribute__((address_space(4))) BatchTileGate *Gates;
+    typedef const __attribute__((address_space(4))) uint64_t *Words;
+    const Parts P = (Parts)(parts) + blockIdx.x;
+    const Jobs J = (Jobs)(A.jobs) + P->job;
+    const Circs C = (Circs)(A.circs) + J->circuit;
+    JobSweep src;
+    src.s = (Sweeps)(A.sweeps) + C->s0 + step;
+    src.g = (Gates)(A.tile_gates) + C->tg0 + src.s->g0;
+    src.m = (Words)(A.mptr) + J->mptr + src.s->g0;
+    src.zero = step == 0 ? 1 : 0;
+    tile_sweep<kBatchTileBits, uint32_t, K5, kBatchWideThreads, false, true>(
+        A.slots + J->slot, uint32_t(P->tile0), 1u, uint32_t(P->tile0 + P->tiles), src, sd, sm);
+}
+
+__global__ __launch_bounds__(kBlock) void batch_sample(BatchArgs A, int job0) {
+    __shared__ double part[kBlock];
+    const BatchJob J = A.jobs[job0 + int(blockIdx.x)];
+    const BatchCircuit C = A.circs[J.circuit];
+    batched_sample<kBlock, 16>(A, J, C, A.slots + J.slot, part);
 }
 
 // ---------------------------------------------------------------- utility
@@ -1933,6 +2014,47 @@ hipError_t launch_batched(const BatchArgs &a, int grid, hipStream_t st) {
     else
         run_batched<256><<<unsigned(grid), 256, lds, st>>>(a);
     return hipGetLastError();
+}
+
+hipError_t launch_batch_prepare(const BatchArgs &a, int job0, int jobs, hipStream_t st) {
+    const size_t lds = sizeof(double2) * 4 * (1024 + 64);
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&batch_prepare),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (attr != hipSuccess) return attr;
+    if (jobs < 1) return hipErrorInvalidValue;
+    batch_prepare<<<unsigned(jobs), kBlock, lds, st>>>(a, job0);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_sweep(const BatchArgs &a, const BatchPart *parts, int n_parts, int step, bool k5,
+                              hipStream_t st) {
+    const size_t lds = sizeof(float2) * size_t(tile_mat_budget(kBatchTileBits));
+    static const hipError_t attr_k5 = hipFuncSetAttribute(reinterpret_cast<const void *>(&batch_sweep<true>),
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&batch_sweep<false>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (attr_k5 != hipSuccess) return attr_k5;
+    if (attr != hipSuccess) return attr;
+    if (n_parts < 1 || step < 0) return hipErrorInvalidValue;
+    if (k5) batch_sweep<true><<<unsigned(n_parts), kBatchWideThreads, lds, st>>>(a, parts, step);
+    else batch_sweep<false><<<unsigned(n_parts), kBatchWideThreads, lds, st>>>(a, parts, step);
+    return hipGetLastError();
+}
+
+hipError_t launch_batch_sample(const BatchArgs &a, int job0, int jobs, hipStream_t st) {
+    if (jobs < 1) return hipErrorInvalidValue;
+    batch_sample<<<unsigned(jobs), kBlock, 0, st>>>(a, job0);
+    return hipGetLastError();
+}
+
+void batch_gate_tables(BatchTileGate &g) {
+    switch (g.k) {
+        case 1: gate_tables<1, SwizzledTile>(g.lt, g.tab); break;
+        case 2: gate_tables<2, SwizzledTile>(g.lt, g.tab); break;
+        case 3: gate_tables<3, SwizzledTile>(g.lt, g.tab); break;
+        case 4: gate_tables<4, SwizzledTile>(g.lt, g.tab); break;
+        default: gate_tables<5, SwizzledTile>(g.lt, g.tab); break;
+    }
 }
 
 int reduce_blocks_for(int n, int k) {

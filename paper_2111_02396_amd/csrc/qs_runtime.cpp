@@ -2850,11 +2850,13 @@ struct BatchPlanKey {
 struct BatchPlanEntry {
     std::vector<qs::BatchSweep> sweeps;     // gate ranges local to the circuit
     std::vector<qs::BatchGate> gates;       // mat: offset into pool; m0, m1: into members
+    std::vector<qs::BatchTileGate> tile_gates;  // the larger circuits' blocks, as sweeps read them
     std::vector<float2> pool;               // the default matrices of the blocks
     std::vector<qs::BatchChannel> chans;    // pbar: into pbar; unit: into fmats
     std::vector<double> pbar;
     std::vector<qs::BatchMember> members;   // src >= 0: into fmats
     std::vector<double2> fmats;             // FP64 gate and channel matrices of the members
+    bool k5 = false;                        // a sweep holds a 5-qubit block
 };
 constexpr size_t kBatchPlanEntries = 2048;
 std::mutex g_bplan_mu;
@@ -2996,6 +2998,38 @@ class HostPool {
     uint64_t generation_ = 0;
 };
 
+// The blocks in the order of `order`, cut into runs whose qubits fit a tile
+// and whose staged matrices fit its budget.
+std::vector<qs::Sweep> cut_sweeps(const std::vector<qs::Sweep> &order, const std::vector<qs::Block> &blocks) {
+    std::vector<qs::Sweep> out;
+    const uint64_t low = (uint64_t(1) << qs::kTileLowBits) - 1;
+    uint64_t bits = low;
+    int slots = 0;
+    if (order.empty()) {  // a circuit without operations still writes |0...0>
+        out.emplace_back();
+        for (int q = 0; q < qs::kTileLowBits; ++q) out.back().bits.push_back(q);
+    }
+    for (const auto &w : order)
+        for (int b : w.blocks) {
+            uint64_t need = low;
+            for (int j = 0; j < blocks[size_t(b)].k; ++j) need |= uint64_t(1) << blocks[size_t(b)].q[j];
+            const int cost = qs::tile_mat_slots(blocks[size_t(b)].k);
+            if (out.empty() || __builtin_popcountll(bits | need) > qs::kBatchTileBits ||
+                slots + cost > qs::tile_mat_budget(qs::kBatchTileBits)) {
+                out.emplace_back();
+                bits = 0;
+                slots = 0;
+            }
+            bits |= need;
+            slots += cost;
+            out.back().blocks.push_back(b);
+            out.back().bits.clear();
+            for (int q = 0; q < 64; ++q)
+                if ((bits >> q) & 1) out.back().bits.push_back(q);
+        }
+    return out;
+}
+
 // Fusion, sweep grouping and default block matrices of one circuit for the
 // batched launch (every channel at its most likely pick), with what the
 // device needs to redo a block for other picks: the channel table and, for
@@ -3014,8 +3048,9 @@ qs_status plan_batched_circuit(const CircuitModel &m, const std::vector<const cd
         sw.push_back(std::move(one));
     } else {
         static const int no_budget[6] = {0, 0, 0, 0, 0, 0};
-        sw = qs::group_sweeps_best(n, blocks, qs::kBatchTileBits, 6, 1 << 30, 1 << 30, no_budget,
-                                   plan_restarts(n, n_traj), kGroupSeed);
+        const auto order = qs::group_sweeps_best(n, blocks, qs::kBatchOrderBits, qs::kBatchOrderLowBits, 1 << 30,
+                                                 1 << 30, no_budget, plan_restarts(n, n_traj), kGroupSeed);
+        sw = cut_sweeps(order, blocks);
     }
     std::vector<char> has_channel(blocks.size(), 0);
     for (const ChannelInfo &c : m.channels) has_channel[size_t(op_block[size_t(c.op)])] = 1;
@@ -3026,9 +3061,7 @@ qs_status plan_batched_circuit(const CircuitModel &m, const std::vector<const cd
         std::memset(&S, 0, sizeof(S));
         int local[64];
         for (int q = 0; q < 64; ++q) local[q] = q;
-        if (resident) {
-            S.tb = n;
-        } else {
+        if (!resident) {
             std::vector<char> in(n, 0);
             for (int q : w.bits) in[q] = 1;
             int cnt = int(w.bits.size());
@@ -3037,9 +3070,6 @@ qs_status plan_batched_circuit(const CircuitModel &m, const std::vector<const cd
                     in[q] = 1;
                     ++cnt;
                 }
-            if (cnt > qs::kBatchLdsQubits)  // the tile must fit the LDS state area
-                return fail(QS_ERR_NOT_SUPPORTED, "block too wide for a tile");
-            S.tb = cnt;
             int i = 0;
             for (int q = 0; q < n; ++q)
                 if (in[q]) {
@@ -3048,6 +3078,7 @@ qs_status plan_batched_circuit(const CircuitModel &m, const std::vector<const cd
                     ++i;
                 }
         }
+        int lofs = 0;
         S.g0 = int(e.gates.size());
         for (int b : w.blocks) {
             const qs::Block &B = blocks[b];
@@ -3055,6 +3086,17 @@ qs_status plan_batched_circuit(const CircuitModel &m, const std::vector<const cd
             std::memset(&G, 0, sizeof(G));
             G.k = B.k;
             for (int j = 0; j < B.k; ++j) G.lt[j] = local[B.q[j]];
+            if (!resident) {
+                qs::BatchTileGate T;
+                std::memset(&T, 0, sizeof(T));
+                T.k = B.k;
+                for (int j = 0; j < B.k; ++j) T.lt[j] = G.lt[j];
+                T.lofs = lofs;
+                lofs += qs::tile_mat_slots(B.k);
+                qs::batch_gate_tables(T);
+                e.tile_gates.push_back(T);
+                e.k5 |= B.k == 5;
+            }
             qs::fused_matrix(B.k, B.q, B.ops, m.ops, default_mats, tmp.data());
             const int D = 1 << B.k;
             G.mat = int(e.pool.size());
@@ -3132,6 +3174,68 @@ bool pinned_host(const void *p) {
         return false;
     }
     return a.type == hipMemoryTypeHost;
+}
+
+// Jobs [first, first + count) of the larger circuits run their sweeps
+// together; sweep s is one launch over the first active[s] of the wave's
+// parts (its jobs are sorted by sweep count).
+struct BatchWave {
+    int first = 0, count = 0;
+    size_t part0 = 0;
+    std::vector<int> active;
+};
+
+// States of a wave (1 GiB at most): every launch ends with a partly filled
+// round of workgroups, so few large waves beat cache-sized ones (64 circuits
+// of 12..18 qubits x 16 trajectories: 9.0 ms a batch with 128 MiB waves, 8.6
+// with 256 MiB, 8.2 with all 570 MiB in one).
+constexpr size_t kWaveAmps = size_t(1) << 27;
+constexpr size_t kWavePatched = size_t(1) << 25;  // float2 of rebuilt matrices
+
+void plan_waves(std::vector<qs::BatchJob> &jobs, const std::vector<qs::BatchCircuit> &circs,
+                const std::vector<BatchPlanCircuit> &plans, int64_t resident_jobs, size_t patched0,
+                std::vector<BatchWave> &waves, std::vector<qs::BatchPart> &parts, size_t &slot_amps,
+                size_t &wide_patched, size_t &n_mptr) {
+    size_t j = size_t(resident_jobs);
+    while (j < jobs.size()) {
+        BatchWave w;
+        w.first = int(j);
+        w.part0 = parts.size();
+        size_t amps = 0, patched = 0, mp = 0;
+        for (; j < jobs.size(); ++j) {
+            qs::BatchJob &J = jobs[j];
+            const qs::BatchCircuit &C = circs[size_t(J.circuit)];
+            const size_t need = size_t(1) << C.n;
+            const size_t pat = C.nch > 0 ? (size_t(C.pool_len) + 63) & ~size_t(63) : 0;
+            if (w.count > 0 && (amps + need > kWaveAmps || patched + pat > kWavePatched)) break;
+            J.slot = int64_t(amps);
+            J.mine = int64_t(patched0 + patched);
+            J.mptr = int64_t(mp);
+            amps += need;
+            patched += pat;
+            mp += size_t(C.n_gates);
+            ++w.count;
+        }
+        // two tiles per workgroup share the staging of the sweep's matrices
+        // once that leaves four rounds of workgroups (two per CU); more than
+        // two make the launch's last round longer than they save (the same
+        // batch: 8.95 ms at eight tiles, 8.15 at four, 7.81 at two)
+        const size_t tiles = amps >> qs::kBatchTileBits;
+        const int per = tiles >= 4096 ? 2 : 1;
+        for (int i = 0; i < w.count; ++i) {
+            const qs::BatchJob &J = jobs[size_t(w.first + i)];
+            const int nt = 1 << (circs[size_t(J.circuit)].n - qs::kBatchTileBits);
+            for (int t = 0; t < nt; t += per)
+                parts.push_back(qs::BatchPart{w.first + i, t, std::min(per, nt - t)});
+            const size_t steps = plans[size_t(J.circuit)].plan->sweeps.size();
+            w.active.resize(std::max(w.active.size(), steps), 0);
+            for (size_t s = 0; s < steps; ++s) w.active[s] = int(parts.size() - w.part0);
+        }
+        slot_amps = std::max(slot_amps, amps);
+        wide_patched = std::max(wide_patched, patched);
+        n_mptr = std::max(n_mptr, mp);
+        waves.push_back(std::move(w));
+    }
 }
 
 qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_batch_params *bp,
@@ -3231,8 +3335,8 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
         if (pieces[it].status != QS_OK) return fail(pieces[it].status, pieces[it].error);
 
     // ---- the launch's tables: each circuit's pieces with shifted offsets
-    size_t n_sweeps = 0, n_gates = 0, n_pool = 0, n_chans = 0, n_pbar = 0, n_members = 0, n_fmats = 0, n_ro = 0;
-    int max_tiled_n = 0;
+    size_t n_sweeps = 0, n_gates = 0, n_tgates = 0, n_pool = 0, n_chans = 0, n_pbar = 0, n_members = 0, n_fmats = 0, n_ro = 0;
+    bool wide_k5 = false;
     int64_t max_pool = 0, total_jobs = 0, total_samples = 0, total_choices = 0;
     for (int it = 0; it < n_items; ++it) {
         const BatchPlanEntry &E = *plans[it].plan;
@@ -3241,6 +3345,7 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
         C.s1 = int(n_sweeps + E.sweeps.size());
         C.g0 = int(n_gates);
         C.n_gates = int(E.gates.size());
+        C.tg0 = int(n_tgates);
         C.ch0 = int(n_chans);
         C.nch = int(E.chans.size());
         C.pool0 = int(n_pool);
@@ -3248,14 +3353,15 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
         if (C.readout >= 0) C.readout = int(n_ro);
         n_sweeps += E.sweeps.size();
         n_gates += E.gates.size();
+        n_tgates += E.tile_gates.size();
         n_pool += E.pool.size();
         n_chans += E.chans.size();
         n_pbar += E.pbar.size();
         n_members += E.members.size();
         n_fmats += E.fmats.size();
         n_ro += pieces[it].readout.size();
-        if (!plans[it].resident) max_tiled_n = std::max(max_tiled_n, C.n);
-        if (!E.chans.empty()) max_pool = std::max<int64_t>(max_pool, int64_t(E.pool.size()));
+        wide_k5 |= E.k5;
+        if (plans[it].resident && !E.chans.empty()) max_pool = std::max<int64_t>(max_pool, int64_t(E.pool.size()));
         total_jobs += items[it].n_traj;
         total_samples += items[it].n_traj * int64_t(items[it].n_samples);
         if (items[it].kraus_choices) total_choices += items[it].n_traj * int64_t(E.chans.size());
@@ -3263,7 +3369,8 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
     if (n_pool > (size_t(1) << 30) || n_fmats > (size_t(1) << 30) || n_gates > (size_t(1) << 30))
         return fail(QS_ERR_OUT_OF_MEMORY, "batched program too large");
 
-    // ---- jobs (largest first, so the persistent workgroups finish together)
+    // ---- jobs: the resident ones first, largest first (the persistent workgroups
+    // finish together), then the larger ones by sweep count
     std::vector<qs::BatchJob> jobs;
     jobs.reserve(size_t(total_jobs));
     std::vector<double> cost;
@@ -3296,11 +3403,27 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
     {
         std::vector<size_t> order(jobs.size());
         for (size_t j = 0; j < order.size(); ++j) order[j] = j;
-        std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) { return cost[a] > cost[b]; });
+        auto wide_sweeps = [&](size_t j) {
+            const size_t it = size_t(jobs[j].circuit);
+            return plans[it].resident ? size_t(0) : plans[it].plan->sweeps.size();
+        };
+        std::stable_sort(order.begin(), order.end(), [&](size_t a, size_t b) {
+            const size_t sa = wide_sweeps(a), sb = wide_sweeps(b);
+            if ((sa == 0) != (sb == 0)) return sa == 0;
+            return sa != sb ? sa > sb : cost[a] > cost[b];
+        });
         std::vector<qs::BatchJob> sorted(jobs.size());
         for (size_t j = 0; j < order.size(); ++j) sorted[j] = jobs[order[j]];
         jobs.swap(sorted);
     }
+    std::vector<BatchWave> waves;
+    std::vector<qs::BatchPart> parts;
+    const size_t patched_stride = (size_t(max_pool) + 63) & ~size_t(63);
+    const int grid = qs::batched_grid();
+    const size_t resident_patched =
+        resident_jobs > 0 ? std::max<size_t>(patched_stride, 64) * size_t(grid) : 0;
+    size_t slot_amps = 0, wide_patched = 0, n_mptr = 0;
+    plan_waves(jobs, circs, plans, resident_jobs, resident_patched, waves, parts, slot_amps, wide_patched, n_mptr);
     r->jobs = int64_t(jobs.size());
     r->resident_jobs = resident_jobs;
     r->gate_blocks = blocks_applied;
@@ -3324,13 +3447,15 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
     const size_t b_fmat = align(sizeof(double2) * std::max<size_t>(n_fmats, 1));
     const size_t b_out = align(sizeof(uint64_t) * size_t(std::max<int64_t>(total_samples, 1)));
     const size_t b_choice = align(size_t(std::max<int64_t>(total_choices, 1)));
-    const size_t prog_bytes = b_circ + b_sweep + b_gate + b_job + b_pool + b_ro + b_chan + b_pbar + b_mem + b_fmat;
+    const size_t b_tgate = align(sizeof(qs::BatchTileGate) * n_tgates);
+    const size_t b_part = align(sizeof(qs::BatchPart) * parts.size());
+    const size_t prog_bytes =
+        b_circ + b_sweep + b_gate + b_job + b_pool + b_ro + b_chan + b_pbar + b_mem + b_fmat + b_tgate + b_part;
     const size_t total = prog_bytes + b_out + b_choice;
-    const int grid = qs::batched_grid();
-    const size_t slot_amps = max_tiled_n > 0 ? size_t(1) << max_tiled_n : 0;
-    const size_t b_slots = sizeof(float2) * slot_amps * size_t(grid);
-    const size_t patched_stride = (size_t(max_pool) + 63) & ~size_t(63);
-    const size_t b_patched = sizeof(float2) * std::max<size_t>(patched_stride, 64) * size_t(grid);
+    const size_t b_slots = sizeof(float2) * slot_amps;
+    const size_t b_mptr = sizeof(float2 *) * n_mptr;
+    const size_t b_pmat = align(sizeof(float2) * (resident_patched + wide_patched));
+    const size_t b_patched = b_pmat + b_mptr;
     BatchBuffers &BB = batch_buffers();
     std::lock_guard<std::mutex> hold(BB.lock);
     hipError_t e = hipSuccess;
@@ -3368,27 +3493,27 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
     // the program, written straight into the pinned staging
     size_t o_circ = 0, o_sweep = o_circ + b_circ, o_gate = o_sweep + b_sweep, o_job = o_gate + b_gate,
            o_pool = o_job + b_job, o_ro = o_pool + b_pool, o_chan = o_ro + b_ro, o_pbar = o_chan + b_chan,
-           o_mem = o_pbar + b_pbar, o_fmat = o_mem + b_mem, o_out = o_fmat + b_fmat, o_choice = o_out + b_out;
+           o_mem = o_pbar + b_pbar, o_fmat = o_mem + b_mem, o_tgate = o_fmat + b_fmat, o_part = o_tgate + b_tgate, o_out = o_part + b_part,
+           o_choice = o_out + b_out;
     std::memcpy(hostp + o_circ, circs.data(), sizeof(qs::BatchCircuit) * circs.size());
     std::memcpy(hostp + o_job, jobs.data(), sizeof(qs::BatchJob) * jobs.size());
+    if (!parts.empty()) std::memcpy(hostp + o_part, parts.data(), sizeof(qs::BatchPart) * parts.size());
     {
         auto *sw = reinterpret_cast<qs::BatchSweep *>(hostp + o_sweep);
         auto *gt = reinterpret_cast<qs::BatchGate *>(hostp + o_gate);
+        auto *tg = reinterpret_cast<qs::BatchTileGate *>(hostp + o_tgate);
         auto *pl = reinterpret_cast<float2 *>(hostp + o_pool);
         auto *ro = reinterpret_cast<double *>(hostp + o_ro);
         auto *chn = reinterpret_cast<qs::BatchChannel *>(hostp + o_chan);
         auto *pb = reinterpret_cast<double *>(hostp + o_pbar);
         auto *mem = reinterpret_cast<qs::BatchMember *>(hostp + o_mem);
         auto *fm = reinterpret_cast<double2 *>(hostp + o_fmat);
-        size_t gs = 0, ps = 0, bs = 0, ms = 0, fs = 0;
+        size_t ps = 0, bs = 0, ms = 0, fs = 0;
         for (int it = 0; it < n_items; ++it) {
             const BatchPlanEntry &E = *plans[it].plan;
-            const int gshift = int(gs), pshift = int(ps), bshift = int(bs), mshift = int(ms), fshift = int(fs);
-            for (qs::BatchSweep S : E.sweeps) {
-                S.g0 += gshift;
-                S.g1 += gshift;
-                *sw++ = S;
-            }
+            const int pshift = int(ps), bshift = int(bs), mshift = int(ms), fshift = int(fs);
+            sw = std::copy(E.sweeps.begin(), E.sweeps.end(), sw);
+            tg = std::copy(E.tile_gates.begin(), E.tile_gates.end(), tg);
             for (qs::BatchGate G : E.gates) {
                 G.mat += pshift;
                 G.m0 += mshift;
@@ -3410,7 +3535,6 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
             if (circs[it].readout >= 0)
                 std::memcpy(ro + circs[it].readout, pieces[it].readout.data(),
                             sizeof(double) * pieces[it].readout.size());
-            gs += E.gates.size();
             ps += E.pool.size();
             bs += E.pbar.size();
             ms += E.members.size();
@@ -3431,6 +3555,7 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
         A.circs = reinterpret_cast<const qs::BatchCircuit *>(dbuf + o_circ);
         A.sweeps = reinterpret_cast<const qs::BatchSweep *>(dbuf + o_sweep);
         A.gates = reinterpret_cast<const qs::BatchGate *>(dbuf + o_gate);
+        A.tile_gates = reinterpret_cast<const qs::BatchTileGate *>(dbuf + o_tgate);
         A.jobs = reinterpret_cast<const qs::BatchJob *>(dbuf + o_job);
         A.mats = reinterpret_cast<const float2 *>(dbuf + o_pool);
         A.readout = reinterpret_cast<const double *>(dbuf + o_ro);
@@ -3442,16 +3567,27 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
         A.patched_stride = int64_t(patched_stride);
         A.choices = reinterpret_cast<int8_t *>(dbuf + o_choice);
         A.slots = b_slots ? BB.slots : nullptr;
-        A.slot_amps = int64_t(slot_amps);
+        A.mptr = reinterpret_cast<const float2 **>(reinterpret_cast<char *>(BB.patched) + b_pmat);
         A.out = reinterpret_cast<uint64_t *>(dbuf + o_out);
-        A.n_jobs = int(jobs.size());
+        A.n_jobs = int(resident_jobs);
+        const auto *dparts = reinterpret_cast<const qs::BatchPart *>(dbuf + o_part);
         const bool timing = (bp->flags & QS_TRAJ_TIME_KERNELS) != 0;
         if (timing) {
             if ((e = hipEventCreate(&ev0)) != hipSuccess) break;
             if ((e = hipEventCreate(&ev1)) != hipSuccess) break;
             if ((e = hipEventRecord(ev0, st)) != hipSuccess) break;
         }
-        if ((e = qs::launch_batched(A, std::min<int64_t>(grid, int64_t(jobs.size())), st)) != hipSuccess) break;
+        for (const BatchWave &w : waves) {
+            if ((e = qs::launch_batch_prepare(A, w.first, w.count, st)) != hipSuccess) break;
+            for (size_t s = 0; s < w.active.size() && e == hipSuccess; ++s)
+                e = qs::launch_batch_sweep(A, dparts + w.part0, w.active[s], int(s), wide_k5, st);
+            if (e != hipSuccess) break;
+            if ((e = qs::launch_batch_sample(A, w.first, w.count, st)) != hipSuccess) break;
+        }
+        if (e != hipSuccess) break;
+        if (resident_jobs > 0 &&
+            (e = qs::launch_batched(A, int(std::min<int64_t>(grid, resident_jobs)), st)) != hipSuccess)
+            break;
         if (timing && (e = hipEventRecord(ev1, st)) != hipSuccess) break;
         // samples come straight into a caller's buffer that is pinned host
         // memory (one transfer, no staging copy) when the item has many;

@@ -210,3 +210,39 @@ def test_batched_samples_into_pinned_and_pageable_buffers(qs, monkeypatch):
         assert np.array_equal(x["samples"], y["samples"])
         assert np.array_equal(x["samples"], z["samples"])
         assert np.array_equal(x["choices"], y["choices"])
+
+
+@pytest.mark.parametrize("n,depth,f,ntraj", [(14, 0, 3, 2), (14, 1, 1, 3), (14, 6, 4, 2), (15, 5, 5, 2), (17, 3, 2, 2)])
+def test_batched_sweeps_widths_and_edges(qs, orc, n, depth, f, ntraj):
+    """The tile sweeps of circuits above 13 qubits at the edges of what a
+    sweep holds: no operation at all, one-qubit blocks only, 4- and 5-qubit
+    blocks (one per sweep fits the staged matrices), a mix of widths."""
+    c = W.generic_grid_circuit(n, depth, p_dep=0.05, seed=31) if depth else W.Circuit(n, [], "empty")
+    w = TrajectoryWorkload("edge", c, n_traj=ntraj, seed=11, circuit_id=3, n_samples=12)
+    res, _ = qs.qs_run_batched([w], max_fuse=f)
+    m = orc.Marshalled(c)
+    for t in range(ntraj):
+        ref = orc.run_trajectory(c, t, seed=11, circ=3, n_samples=12, marshalled=m)
+        _, tie = compare_choices(res[0]["choices"][t], ref)
+        assert tie == 0
+        mism = np.nonzero(res[0]["samples"][t] != ref["samples"])[0]
+        assert np.all(ref["sample_margins"][mism] < SAMPLE_TIE), (t, mism)
+
+
+def test_batched_waves_agree_with_short_ranges(qs):
+    """More 18-qubit states than one wave holds (512): the trajectories of
+    both waves equal the same ones run a few at a time, where a workgroup
+    takes one tile instead of two."""
+    c = W.generic_grid_circuit(18, 2, p_dep=0.02, seed=5)
+
+    def run(offset, count):
+        w = TrajectoryWorkload("w", c, n_traj=count, seed=9, circuit_id=1, n_samples=4)
+        w.traj_offset = offset
+        res, _ = qs.qs_run_batched([w], max_fuse=3)
+        return res[0]
+
+    full = run(0, 515)
+    for first in (0, 509):
+        part = run(first, 6)
+        assert np.array_equal(full["choices"][first:first + 6], part["choices"])
+        assert np.array_equal(full["samples"][first:first + 6], part["samples"])
