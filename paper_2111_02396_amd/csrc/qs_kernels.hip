@@ -1448,15 +1448,20 @@ __global__ __launch_bounds__(kBlock) void norm_partials(const float2 *__restrict
     block_sum_write<1>(acc, partials + blockIdx.x);
 }
 
+// R = sum v v^dag is Hermitian, so only its upper triangle is summed (D real
+// and D (D - 1) / 2 complex entries: 16 accumulators instead of 32 for two
+// qubits, half the FP64 work) and the record is completed from it.  HBM-bound
+// (two qubits, 26 qubits: 107 us with the full matrix, 94 with the triangle;
+// the one-qubit pass takes 87).
 template <int K, typename Idx>
 __global__ __launch_bounds__(kBlock) void rdm_partials(const float2 *__restrict__ amp, Idx groups,
                                                        TargetArgs ta,
                                                        double *__restrict__ partials) {
     constexpr int D = 1 << K;
-    constexpr int W = 2 * D * D;
-    double acc[W];
+    constexpr int T = D * D;  // packed: diagonal entries, then (re, im) of j < l in row order
+    double acc[T];
 #pragma unroll
-    for (int w = 0; w < W; ++w) acc[w] = 0.0;
+    for (int w = 0; w < T; ++w) acc[w] = 0.0;
     const Idx stride = Idx(gridDim.x) * Idx(kBlock);
     for (Idx g = Idx(blockIdx.x) * Idx(kBlock) + Idx(threadIdx.x); g < groups; g += stride) {
         const Idx base = spread_index<K, Idx>(g, ta.t);
@@ -1468,16 +1473,33 @@ __global__ __launch_bounds__(kBlock) void rdm_partials(const float2 *__restrict_
             vi[j] = v.y;
         }
         // R[j][l] += v_j conj(v_l)
+        int w = D;
 #pragma unroll
-        for (int j = 0; j < D; ++j)
+        for (int j = 0; j < D; ++j) {
+            acc[j] = fma(vr[j], vr[j], fma(vi[j], vi[j], acc[j]));
 #pragma unroll
-            for (int l = 0; l < D; ++l) {
-                acc[2 * (j * D + l)] = fma(vr[j], vr[l], fma(vi[j], vi[l], acc[2 * (j * D + l)]));
-                acc[2 * (j * D + l) + 1] =
-                    fma(vi[j], vr[l], fma(-vr[j], vi[l], acc[2 * (j * D + l) + 1]));
+            for (int l = j + 1; l < D; ++l, w += 2) {
+                acc[w] = fma(vr[j], vr[l], fma(vi[j], vi[l], acc[w]));
+                acc[w + 1] = fma(vi[j], vr[l], fma(-vr[j], vi[l], acc[w + 1]));
             }
+        }
     }
-    block_sum_write<W>(acc, partials + size_t(blockIdx.x) * W);
+    __shared__ double sum[T];
+    block_sum_write<T>(acc, sum);
+    if (threadIdx.x == 0) {  // the work-item that wrote `sum`
+        double *rec = partials + size_t(blockIdx.x) * (2 * D * D);
+        int w = D;
+        for (int j = 0; j < D; ++j) {
+            rec[2 * (j * D + j)] = sum[j];
+            rec[2 * (j * D + j) + 1] = 0.0;
+            for (int l = j + 1; l < D; ++l, w += 2) {
+                rec[2 * (j * D + l)] = sum[w];
+                rec[2 * (j * D + l) + 1] = sum[w + 1];
+                rec[2 * (l * D + j)] = sum[w];
+                rec[2 * (l * D + j) + 1] = -sum[w + 1];
+            }
+        }
+    }
 }
 
 template <int K, typename Idx>
@@ -1509,66 +1531,104 @@ __global__ __launch_bounds__(kBlock) void apply_copy_norm(const float2 *__restri
 }
 
 // Per-qubit weights (see launch_zweights).  Workgroup w owns the contiguous
-// chunk [w 2^c, (w + 1) 2^c); work-item t reads x = chunk + 256 i + t, so
-// bits 0..7 of x come from t, bits 8..c-1 from the iteration i (uniform) and
-// the rest from the chunk (uniform per workgroup).  A work-item keeps its
-// total and one sum per iteration bit; the record's entries follow from
-// those (bit q < 8: the work-item's total if its bit q is set).
-constexpr int kZIterBits = 16;
+// chunk [w 2^c, (w + 1) 2^c).  HBM-bound: a work-item adds fewer than two FP64
+// sums per amplitude where one conditional sum per qubit took ten (26 qubits:
+// 412 us before, 93 now, 5.8 TB/s).
+//
+// Chunks of 2^12 and more: in step o of 2^(c - 12), work-item t reads the
+// eight pairs x = chunk + 4096 o + 512 r + 2 t + {0, 1} as 16-byte loads, so
+// bit 0 of x is the pair's half, bits 1..8 come from t, 9..11 from r and the
+// rest from o and the chunk (uniform).  The eight pairs are summed as a tree
+// whose inner nodes give the bit 9..11 sums; the step's total joins the sum
+// of every bit set in o.
+constexpr int kZStepBits = 12;
+constexpr int kZOuterBits = 12;  // o has c - 12 bits
+constexpr int kZSums = 1 + kZStepBits + kZOuterBits;
 template <typename Idx>
 __global__ __launch_bounds__(kBlock) void zweight_partials(const float2 *__restrict__ amp, int n, int c,
                                                            double *__restrict__ partials) {
     const int t = threadIdx.x;
-    const int ibits = c > 8 ? c - 8 : 0;
+    const int obits = c - kZStepBits;
     const Idx chunk = Idx(blockIdx.x) << c;
-    const Idx iters = Idx(1) << ibits;
-    const int active = c >= 8 || t < (1 << c);
-    double tot = 0.0;
-    double per_bit[kZIterBits];
+    // s[0]: total; s[1 + q]: the chunk's sum over bit q set, q < c
+    double s[kZSums];
 #pragma unroll
-    for (int j = 0; j < kZIterBits; ++j) per_bit[j] = 0.0;
-    if (active) {
-        for (Idx i = 0; i < iters; ++i) {
-            const float2 v = amp[chunk + (i << 8) + Idx(t)];
-            const double p = fma(double(v.x), double(v.x), double(v.y) * double(v.y));
-            tot += p;
+    for (int w = 0; w < kZSums; ++w) s[w] = 0.0;
+    for (uint32_t o = 0; o < (uint32_t(1) << obits); ++o) {
+        const float4 *p4 = reinterpret_cast<const float4 *>(amp + chunk + (Idx(o) << kZStepBits)) + t;
+        float4 v[8];
 #pragma unroll
-            for (int j = 0; j < kZIterBits; ++j)
-                if (j < ibits && ((i >> j) & 1)) per_bit[j] += p;
+        for (int r = 0; r < 8; ++r) v[r] = p4[r * kBlock];
+        double p[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const double lo = fma(double(v[r].x), double(v[r].x), double(v[r].y) * double(v[r].y));
+            const double hi = fma(double(v[r].z), double(v[r].z), double(v[r].w) * double(v[r].w));
+            s[1] += hi;
+            p[r] = lo + hi;
+        }
+        const double a0 = p[0] + p[1], a1 = p[2] + p[3], a2 = p[4] + p[5], a3 = p[6] + p[7];
+        const double b1 = a2 + a3;
+        const double all = (a0 + a1) + b1;
+        s[10] += (p[1] + p[3]) + (p[5] + p[7]);
+        s[11] += a1 + a3;
+        s[12] += b1;
+        s[0] += all;
+#pragma unroll
+        for (int j = 0; j < kZOuterBits; ++j)
+            if (j < obits && ((o >> j) & 1)) s[1 + kZStepBits + j] += all;
+    }
+#pragma unroll
+    for (int q = 1; q < 9; ++q) s[1 + q] = ((t >> (q - 1)) & 1) ? s[0] : 0.0;
+    __shared__ double sum[kZSums];
+    block_sum_write<kZSums>(s, sum);
+    if (t == 0) {  // the work-item that wrote `sum`
+        double *rec = partials + size_t(blockIdx.x) * kZRecord;
+        rec[0] = sum[0];
+        for (int q = 0; q < kZRecord - 1; ++q) {
+            double x = 0.0;
+            if (q < c) x = sum[1 + q];
+            else if (q < n) x = ((chunk >> q) & 1) ? sum[0] : 0.0;
+            rec[1 + q] = x;
         }
     }
-    double vals[kZRecord];
-    vals[0] = tot;
-#pragma unroll
-    for (int q = 0; q < kZRecord - 1; ++q) {
-        double x = 0.0;
-        if (q < n) {
-            if (q < 8) x = ((t >> q) & 1) ? tot : 0.0;
-            else if (q < 8 + ibits) x = per_bit[q - 8];
-            else x = ((chunk >> q) & 1) ? tot : 0.0;
-        }
-        vals[1 + q] = x;
-    }
-    block_sum_write<kZRecord>(vals, partials + size_t(blockIdx.x) * kZRecord);
 }
 
-// Sum `count` records of `width` doubles in a fixed order (one workgroup).
+// States below 2^12 amplitudes: one workgroup, work-item t takes x = t, t +
+// 256, ...
+__global__ __launch_bounds__(kBlock) void zweight_small(const float2 *__restrict__ amp, int n,
+                                                        double *__restrict__ out) {
+    double vals[1 + kZStepBits];
+#pragma unroll
+    for (int w = 0; w <= kZStepBits; ++w) vals[w] = 0.0;
+    for (int x = threadIdx.x; x < (1 << n); x += kBlock) {
+        const float2 v = amp[x];
+        const double p = fma(double(v.x), double(v.x), double(v.y) * double(v.y));
+        vals[0] += p;
+#pragma unroll
+        for (int q = 0; q < kZStepBits; ++q) vals[1 + q] += ((x >> q) & 1) ? p : 0.0;
+    }
+    block_sum_write<1 + kZStepBits>(vals, out);
+    for (int q = 1 + kZStepBits + int(threadIdx.x); q < kZRecord; q += kBlock) out[q] = 0.0;
+}
+
+// Sum `count` records of `width` doubles in a fixed order: workgroup w sums
+// entry w (one workgroup walking the entries took 2 us for each: 105 us for
+// 2048 Z-weight records, now 5).
 __global__ __launch_bounds__(kBlock) void reduce_records(const double *__restrict__ partials,
                                                          int count, int width,
                                                          double *__restrict__ out) {
     __shared__ double red[kBlock];
-    for (int w = 0; w < width; ++w) {
-        double s = 0.0;
-        for (int i = threadIdx.x; i < count; i += kBlock) s += partials[size_t(i) * width + w];
-        red[threadIdx.x] = s;
-        __syncthreads();
-        for (int h = kBlock / 2; h >= 1; h >>= 1) {
-            if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) out[w] = red[0];
+    const int w = blockIdx.x;
+    double s = 0.0;
+    for (int i = threadIdx.x; i < count; i += kBlock) s += partials[size_t(i) * width + w];
+    red[threadIdx.x] = s;
+    __syncthreads();
+    for (int h = kBlock / 2; h >= 1; h >>= 1) {
+        if (threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
         __syncthreads();
     }
+    if (threadIdx.x == 0) out[w] = red[0];
 }
 
 // ---------------------------------------------------------------- sampling
@@ -2193,7 +2253,7 @@ hipError_t launch_reduce_records(const double *partials, int count, int width, d
                                  hipStream_t st) {
     if (count < 1 || count > kMaxReduceBlocks || width < 1 || width > kMaxReduceWidth)
         return hipErrorInvalidValue;
-    reduce_records<<<1, kBlock, 0, st>>>(partials, count, width, out_dev);
+    reduce_records<<<unsigned(width), kBlock, 0, st>>>(partials, count, width, out_dev);
     return hipGetLastError();
 }
 
@@ -2210,14 +2270,18 @@ hipError_t launch_norm(const float2 *amp, int n, double *partials, double *out_d
 }
 
 hipError_t launch_zweights(const float2 *amp, int n, double *partials, double *out_dev, hipStream_t st) {
-    if (n < 1 || n > kZRecord - 1 || n - 8 > 11 + kZIterBits) return hipErrorInvalidValue;
-    // chunks of at least 256 amplitudes, at most kMaxReduceBlocks of them
-    const int lb = n - 8 < 11 ? (n - 8 > 0 ? n - 8 : 0) : 11;
-    const int c = n - lb;
+    if (n < 1 || n > kZRecord - 1) return hipErrorInvalidValue;
+    if (n < kZStepBits) {
+        zweight_small<<<1, kBlock, 0, st>>>(amp, n, out_dev);
+        return hipGetLastError();
+    }
+    // at most 1024 chunks (four workgroups per CU, 32 KiB of loads in flight each)
+    const int lb = n - kZStepBits < 10 ? n - kZStepBits : 10;
+    const int c = n - lb;  // 12..24
     const unsigned nb = 1u << lb;
     if (n <= 31) zweight_partials<uint32_t><<<nb, kBlock, 0, st>>>(amp, n, c, partials);
     else zweight_partials<uint64_t><<<nb, kBlock, 0, st>>>(amp, n, c, partials);
-    reduce_records<<<1, kBlock, 0, st>>>(partials, int(nb), kZRecord, out_dev);
+    reduce_records<<<kZRecord, kBlock, 0, st>>>(partials, int(nb), kZRecord, out_dev);
     return hipGetLastError();
 }
 
@@ -2237,7 +2301,7 @@ hipError_t launch_rdm(const float2 *amp, int n, int k, const int *t_sorted, doub
     } else {
         return hipErrorInvalidValue;
     }
-    reduce_records<<<1, kBlock, 0, st>>>(partials, nb, width, out_dev);
+    reduce_records<<<unsigned(width), kBlock, 0, st>>>(partials, nb, width, out_dev);
     return hipGetLastError();
 }
 
@@ -2254,7 +2318,7 @@ hipError_t launch_apply_copy_norm(const float2 *in, float2 *out, int n, const Ga
     } else {
         return hipErrorInvalidValue;
     }
-    reduce_records<<<1, kBlock, 0, st>>>(partials, nb, 2, out_dev);
+    reduce_records<<<2, kBlock, 0, st>>>(partials, nb, 2, out_dev);
     return hipGetLastError();
 }
 

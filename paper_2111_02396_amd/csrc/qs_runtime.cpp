@@ -60,7 +60,8 @@ struct qs_state_s {
     float2 *scratch = nullptr;  // second state for the conventional method
     double *red_partials = nullptr;
     double *red_out = nullptr;
-    double *red_host = nullptr;  // pinned
+    double *red_host = nullptr;  // pinned; a reduction whose result the host reads
+    double *red_host_dev = nullptr;  // ... ends in it directly, with no copy behind it
     double *samp_sums = nullptr;
     double *samp_incl = nullptr;
     double *samp_norm = nullptr;
@@ -245,6 +246,7 @@ qs_status ensure_reduce(qs_state s) {
     QS_HIP(s, hipMalloc(&s->red_partials, sizeof(double) * qs::kMaxReduceBlocks * qs::kMaxReduceWidth));
     QS_HIP(s, hipMalloc(&s->red_out, sizeof(double) * qs::kMaxReduceWidth));
     QS_HIP(s, hipHostMalloc(&s->red_host, sizeof(double) * qs::kMaxReduceWidth, hipHostMallocDefault));
+    QS_HIP(s, hipHostGetDevicePointer(reinterpret_cast<void **>(&s->red_host_dev), s->red_host, 0));
     return QS_OK;
 }
 
@@ -284,8 +286,7 @@ qs_status ensure_scratch(qs_state s) {
 // Sum of |psi|^2 over the current buffer; synchronises.
 qs_status device_norm(qs_state s, double *out) {
     QS_CHECK(ensure_reduce(s));
-    QS_HIP(s, qs::launch_norm(s->amp, s->n, s->red_partials, s->red_out, s->st));
-    QS_HIP(s, hipMemcpyAsync(s->red_host, s->red_out, sizeof(double), hipMemcpyDeviceToHost, s->st));
+    QS_HIP(s, qs::launch_norm(s->amp, s->n, s->red_partials, s->red_host_dev, s->st));
     QS_HIP(s, hipStreamSynchronize(s->st));
     *out = s->red_host[0];
     return QS_OK;
@@ -295,9 +296,7 @@ qs_status device_norm(qs_state s, double *out) {
 // R[j][l] = (red_host[2(jD+l)], red_host[2(jD+l)+1]).
 qs_status device_rdm(qs_state s, int k, const int *ts) {
     QS_CHECK(ensure_reduce(s));
-    QS_HIP(s, qs::launch_rdm(s->amp, s->n, k, ts, s->red_partials, s->red_out, s->st));
-    const int width = 2 << (2 * k);
-    QS_HIP(s, hipMemcpyAsync(s->red_host, s->red_out, sizeof(double) * width, hipMemcpyDeviceToHost, s->st));
+    QS_HIP(s, qs::launch_rdm(s->amp, s->n, k, ts, s->red_partials, s->red_host_dev, s->st));
     QS_HIP(s, hipStreamSynchronize(s->st));
     return QS_OK;
 }
@@ -778,9 +777,7 @@ qs_status qs_expectation_z(qs_state s, double *z_out) {
     if (!z_out) return fail(QS_ERR_INVALID_ARGUMENT, "null output");
     QS_CHECK(flush_pending(s));
     QS_CHECK(ensure_reduce(s));
-    QS_HIP(s, qs::launch_zweights(s->amp, s->n, s->red_partials, s->red_out, s->st));
-    QS_HIP(s, hipMemcpyAsync(s->red_host, s->red_out, sizeof(double) * (1 + s->n),
-                             hipMemcpyDeviceToHost, s->st));
+    QS_HIP(s, qs::launch_zweights(s->amp, s->n, s->red_partials, s->red_host_dev, s->st));
     QS_HIP(s, hipStreamSynchronize(s->st));
     return z_from_record(s->n, s->red_host, z_out);
 }

@@ -143,3 +143,24 @@ def test_driver_z_expectations_grid24_last_state(qs, orc):
     assert np.all(np.abs(z) <= 1.0 + 1e-12)
     ref = orc.z_expectations(got["state"].astype(np.complex128))
     assert np.max(np.abs(z[-1] - ref)) < 1e-12
+
+
+@pytest.mark.parametrize("n", [11, 12, 13, 22, 23])
+def test_reductions_at_the_edges_of_their_chunks(qs, n):
+    """<Z_q> and a two-qubit observable against numpy in 64 bits around 2^12
+    amplitudes (one workgroup, one step) and 2^22 (the most chunks)."""
+    rng = np.random.default_rng(n)
+    psi = random_state(n, rng)
+    w = psi.astype(np.complex128)
+    N = np.vdot(w, w).real
+    m = W.random_matrix(2, rng)
+    m = m + m.conj().T
+    rows = w.reshape(2, -1, 2).transpose(2, 0, 1).reshape(4, -1)  # row 2 (bit 0) + (bit n - 1)
+    with qs.State(n) as st:
+        qs.qs_load_state_from_host(st.h, psi)
+        z = qs.qs_expectation_z(st.h)
+        o = qs.qs_expectation(st.h, (n - 1, 0), m)
+    for q in range(n):
+        x = (np.abs(w) ** 2).reshape(-1, 2, 1 << q).sum(axis=(0, 2))
+        assert abs(z[q] - (x[0] - x[1]) / N) < 1e-12, q
+    assert abs(o - np.vdot(rows, m @ rows).real / N) < 1e-12 * np.abs(m).max()
