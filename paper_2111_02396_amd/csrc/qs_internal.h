@@ -266,10 +266,11 @@ int reduce_blocks_for(int n, int k);
 
 // Sampling: block sums, a single-workgroup scan, then one thread per sample.
 // sums / incl: device doubles [2^(n - B)] with B = min(n, kSampleBlockBits).
+// norm_host (optional): pinned host memory that gets the norm too.
 hipError_t launch_sample(const float2 *amp, int n, double *sums, double *incl,
                          uint64_t seed, uint32_t traj, uint32_t circ, int n_samples,
                          const ReadoutDesc &ro, uint64_t *out_dev, double *norm_dev,
-                         hipStream_t st);
+                         hipStream_t st, double *norm_host = nullptr);
 
 // Allocation-free sampling (qs_sample_measurements_noalloc): one fixed
 // device array per GPU holds the block sums, their prefix, the norm and the

@@ -1725,7 +1725,8 @@ __device__ __forceinline__ double workgroup_exclusive_scan(double x, double *wav
 __device__ __forceinline__ int scan_slot(int i) { return i + i / kScanPer; }
 
 __global__ __launch_bounds__(kScanThreads) void sample_scan_tiles(const double *__restrict__ sums,
-                                                                  int64_t nb, double *__restrict__ incl) {
+                                                                  int64_t nb, double *__restrict__ incl,
+                                                                  double *norm, double *norm_host) {
     __shared__ double tile[kScanTile + kScanTile / kScanPer];
     __shared__ double wave_tot[kScanThreads / 64];
     const int t = threadIdx.x;
@@ -1756,6 +1757,10 @@ __global__ __launch_bounds__(kScanThreads) void sample_scan_tiles(const double *
         const int i = j * kScanThreads + t;
         if (i < len) incl[base + i] = tile[scan_slot(i)];
     }
+    if (norm && t == 0) {  // the only tile: its last prefix is the norm
+        *norm = tile[scan_slot(len - 1)];
+        if (norm_host) *norm_host = tile[scan_slot(len - 1)];
+    }
 }
 
 // Tile totals (each tile's last prefix) added one after another: offsets[t]
@@ -1766,7 +1771,8 @@ constexpr int kScanMaxTiles = 2048;  // 2^(kMaxQubits - kSampleBlockBits) / kSca
 __global__ __launch_bounds__(kScanThreads) void sample_scan_offsets(const double *__restrict__ incl,
                                                                     int64_t nb, int n_tiles,
                                                                     double *__restrict__ offsets,
-                                                                    double *__restrict__ norm) {
+                                                                    double *__restrict__ norm,
+                                                                    double *norm_host) {
     __shared__ double tot[kScanMaxTiles];
     for (int t = threadIdx.x; t < n_tiles; t += kScanThreads) {
         const int64_t end = int64_t(t + 1) * kScanTile;
@@ -1787,6 +1793,7 @@ __global__ __launch_bounds__(kScanThreads) void sample_scan_offsets(const double
                 }
         }
         *norm = run;
+        if (norm_host) *norm_host = run;
     }
 }
 
@@ -1907,17 +1914,19 @@ __global__ __launch_bounds__(kBlock) void sample_draw(const float2 *__restrict__
         }
         x = uint64_t(first) + uint64_t(pick);
     }
-    if (lane == 0) {
-        if (ro.enabled) {
-            for (int q = 0; q < n; ++q) {
-                const int bit = int((x >> q) & 1u);
-                const double u = philox_uniform(seed, uint32_t(uint64_t(s) * uint64_t(n) + uint64_t(q)),
-                                                traj, circ, kStreamReadout);
-                if (u < (bit ? ro.e1[q] : ro.e0[q])) x ^= uint64_t(1) << q;
-            }
+    // readout: lane q draws for qubit q (28 draws in a row on one lane took
+    // 330 of the kernel's 470 us for 10^5 samples of 28 qubits)
+    if (ro.enabled) {
+        bool flip = false;
+        if (lane < n) {
+            const int bit = int((x >> lane) & 1u);
+            const double u = philox_uniform(seed, uint32_t(uint64_t(s) * uint64_t(n) + uint64_t(lane)),
+                                            traj, circ, kStreamReadout);
+            flip = u < (bit ? ro.e1[lane] : ro.e0[lane]);
         }
-        out[s] = x;
+        x ^= uint64_t(__ballot(flip));
     }
+    if (lane == 0) out[s] = x;
 }
 
 // ---------------------------------------------------------------- helpers
@@ -2357,7 +2366,7 @@ hipError_t noalloc_scratch(int device, double **out) {
 
 hipError_t launch_sample(const float2 *amp, int n, double *sums, double *incl, uint64_t seed,
                          uint32_t traj, uint32_t circ, int n_samples, const ReadoutDesc &ro,
-                         uint64_t *out_dev, double *norm_dev, hipStream_t st) {
+                         uint64_t *out_dev, double *norm_dev, hipStream_t st, double *norm_host) {
     const int B = n < kSampleBlockBits ? n : kSampleBlockBits;
     const int64_t nb = int64_t(1) << (n - B);
     const int64_t n_tiles = (nb + kScanTile - 1) / kScanTile;
@@ -2367,11 +2376,14 @@ hipError_t launch_sample(const float2 *amp, int n, double *sums, double *incl, u
         sample_block_sums<uint32_t><<<sum_grid, kBlock, 0, st>>>(amp, B, nb, sums);
     else
         sample_block_sums<uint64_t><<<sum_grid, kBlock, 0, st>>>(amp, B, nb, sums);
-    sample_scan_tiles<<<unsigned(n_tiles), kScanThreads, 0, st>>>(sums, nb, incl);
-    // the block sums have been read: their first n_tiles slots take the offsets
-    sample_scan_offsets<<<1, kScanThreads, 0, st>>>(incl, nb, int(n_tiles), sums, norm_dev);
-    if (n_tiles > 1)
+    // one tile (up to 23 qubits) needs no offsets
+    sample_scan_tiles<<<unsigned(n_tiles), kScanThreads, 0, st>>>(sums, nb, incl, n_tiles == 1 ? norm_dev : nullptr,
+                                                                  norm_host);
+    if (n_tiles > 1) {
+        // the block sums have been read: their first n_tiles slots take the offsets
+        sample_scan_offsets<<<1, kScanThreads, 0, st>>>(incl, nb, int(n_tiles), sums, norm_dev, norm_host);
         sample_scan_add<<<unsigned((nb - kScanTile + kBlock - 1) / kBlock), kBlock, 0, st>>>(incl, nb, sums);
+    }
     if (n_samples > 0) {
         const unsigned grid = unsigned((n_samples + kBlock / 64 - 1) / (kBlock / 64));
         if (B == 10 && n <= 31)

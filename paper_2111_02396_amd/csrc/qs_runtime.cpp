@@ -42,6 +42,11 @@ constexpr double kRenormLogThreshold = -46.0;  // ~1e-20 on the norm squared
 // records in the state's reduction buffer (past the norm pass's records).
 constexpr size_t kRdmRecordOffset = size_t(qs::kMaxReduceBlocks);
 
+// qs_sample_measurements draws up to this many samples straight into pinned
+// memory; beyond that one copy at the end is cheaper than 8-byte writes over
+// the host link.
+constexpr int kPinnedSamples = 4096;
+
 struct PendingOp {
     int k;
     int t[5];
@@ -67,6 +72,8 @@ struct qs_state_s {
     double *samp_norm = nullptr;
     uint64_t *samp_out = nullptr;
     size_t samp_cap = 0;
+    uint64_t *samp_host = nullptr;  // pinned, kPinnedSamples; its device address
+    uint64_t *samp_host_dev = nullptr;
     double *z_dev = nullptr;  // per-trajectory Z-weight records of the driver
     size_t z_cap = 0;         // records
     // matrix staging: two halves of a pinned host buffer mirrored on the
@@ -595,6 +602,7 @@ qs_status qs_destroy_state(qs_state s) {
     if (s->samp_incl) (void)hipFree(s->samp_incl);
     if (s->samp_norm) (void)hipFree(s->samp_norm);
     if (s->samp_out) (void)hipFree(s->samp_out);
+    if (s->samp_host) (void)hipHostFree(s->samp_host);
     if (s->z_dev) (void)hipFree(s->z_dev);
     if (s->arena_dev) {
         (void)hipFree(s->arena_dev);
@@ -854,13 +862,20 @@ qs_status qs_sample_measurements(qs_state s, uint64_t seed, uint32_t traj, int n
     QS_CHECK(flush_pending(s));
     QS_CHECK(ensure_sampling(s, size_t(std::max(n_samples, 1))));
     QS_CHECK(ensure_reduce(s));
-    QS_HIP(s, qs::launch_sample(s->amp, s->n, s->samp_sums, s->samp_incl, seed, traj, 0, n_samples,
-                                ro, s->samp_out, s->samp_norm, s->st));
-    QS_HIP(s, hipMemcpyAsync(s->red_host, s->samp_norm, sizeof(double), hipMemcpyDeviceToHost, s->st));
+    if (!s->samp_host) {
+        QS_HIP(s, hipHostMalloc(&s->samp_host, sizeof(uint64_t) * kPinnedSamples, hipHostMallocDefault));
+        QS_HIP(s, hipHostGetDevicePointer(reinterpret_cast<void **>(&s->samp_host_dev), s->samp_host, 0));
+    }
+    // few samples are drawn straight into pinned memory; the norm always is
+    const bool direct = n_samples <= kPinnedSamples;
+    QS_HIP(s, qs::launch_sample(s->amp, s->n, s->samp_sums, s->samp_incl, seed, traj, 0, n_samples, ro,
+                                direct ? s->samp_host_dev : s->samp_out, s->samp_norm, s->st, s->red_host_dev));
     QS_HIP(s, hipStreamSynchronize(s->st));
     const double N = s->red_host[0];
     if (!(N > 0.0) || !std::isfinite(N)) return fail(QS_ERR_ZERO_NORM, "state has zero norm");
-    if (n_samples > 0)
+    if (direct && n_samples > 0)
+        std::memcpy(bitstrings_out, s->samp_host, sizeof(uint64_t) * size_t(n_samples));
+    else if (n_samples > 0)
         QS_HIP(s, hipMemcpy(bitstrings_out, s->samp_out, sizeof(uint64_t) * n_samples, hipMemcpyDeviceToHost));
     return QS_OK;
 }
