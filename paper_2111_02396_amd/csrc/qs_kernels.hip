@@ -1856,16 +1856,32 @@ __global__ __launch_bounds__(kBlock) void sample_draw(const float2 *__restrict__
         const int per = PER > 0 ? PER : (len >= 64 ? len / 64 : 1);
         const int lanes = len >= 64 ? 64 : len;
         double part = 0.0;
-        float4 keep[PER > 0 ? PER / 2 : 1];
+        float2 keep[PER > 0 ? PER : 1];
         if constexpr (PER > 0) {
-            const float4 *p4 = reinterpret_cast<const float4 *>(amp + first + Idx(lane * PER));
+            // the block is read in whole lines and turned in LDS so that each
+            // lane gets its run of PER consecutive amplitudes; one pad slot
+            // per run keeps the runs on distinct banks.  Read straight from
+            // memory, each load touched 64 lines (10^5 samples: 202 us at 28
+            // qubits, now 184; a 20-qubit state, in cache: the whole call
+            // 185 us, now 164).
+            __shared__ float2 turn[kBlock / 64][64 * (PER + 1)];
+            float2 *mine = turn[threadIdx.x >> 6];
+            const float4 *p4 = reinterpret_cast<const float4 *>(amp + first);
+            float4 in[PER / 2];
 #pragma unroll
-            for (int i = 0; i < PER / 2; ++i) keep[i] = p4[i];
+            for (int i = 0; i < PER / 2; ++i) in[i] = p4[i * 64 + lane];
 #pragma unroll
             for (int i = 0; i < PER / 2; ++i) {
-                part = fma(double(keep[i].x), double(keep[i].x), fma(double(keep[i].y), double(keep[i].y), part));
-                part = fma(double(keep[i].z), double(keep[i].z), fma(double(keep[i].w), double(keep[i].w), part));
+                const int a = 2 * (i * 64 + lane);
+                mine[a + a / PER] = make_float2(in[i].x, in[i].y);
+                mine[a + a / PER + 1] = make_float2(in[i].z, in[i].w);
             }
+            __builtin_amdgcn_wave_barrier();  // a wavefront's LDS accesses keep their order
+#pragma unroll
+            for (int i = 0; i < PER; ++i) keep[i] = mine[lane * (PER + 1) + i];
+#pragma unroll
+            for (int i = 0; i < PER; ++i)
+                part = fma(double(keep[i].x), double(keep[i].x), fma(double(keep[i].y), double(keep[i].y), part));
         } else if (lane < lanes) {
             part = chunk_weight(amp, first + Idx(lane * per), per);
         }
@@ -1882,19 +1898,13 @@ __global__ __launch_bounds__(kBlock) void sample_draw(const float2 *__restrict__
                 if constexpr (PER > 0) {
                     bool found = false;
 #pragma unroll
-                    for (int i = 0; i < PER / 2; ++i) {
-                        const double r0 = fma(double(keep[i].x), double(keep[i].x),
-                                              fma(double(keep[i].y), double(keep[i].y), run));
-                        const double r1 = fma(double(keep[i].z), double(keep[i].z),
-                                              fma(double(keep[i].w), double(keep[i].w), r0));
-                        if (!found && target < r0) {
-                            idx = L * PER + 2 * i;
-                            found = true;
-                        } else if (!found && target < r1) {
-                            idx = L * PER + 2 * i + 1;
+                    for (int i = 0; i < PER; ++i) {
+                        run = fma(double(keep[i].x), double(keep[i].x),
+                                  fma(double(keep[i].y), double(keep[i].y), run));
+                        if (!found && target < run) {
+                            idx = L * PER + i;
                             found = true;
                         }
-                        run = r1;
                     }
                 } else if (per >= 2) {
                     const float4 *p4 = reinterpret_cast<const float4 *>(amp + first + Idx(L * per));
