@@ -93,6 +93,12 @@ struct TileArgs {
     TileGate g[kMaxTileGates];
 };
 
+// The tile launch of a single gate of at most four qubits.
+struct TileOneArgs {
+    int pos[kMaxTileBits];
+    TileGate g;
+};
+
 // ---- batched persistent launch -------------------------------------------
 // Device program of many small circuits.  A circuit whose state fits in LDS
 // (n <= kBatchLdsQubits) runs one trajectory per workgroup iteration, the
@@ -223,8 +229,9 @@ hipError_t launch_scale(float2 *amp, int n, float s, hipStream_t st);
 hipError_t launch_copy_state(float2 *dst, const float2 *src, int n, hipStream_t st);
 
 // Algorithm 1 for one fused gate.  mat_dev: device copy of g.m
-// ((2^k)^2 complex64, ascending-target order).  Gates with a target below 6
-// go through the tiled path, the others through the direct path.
+// ((2^k)^2 complex64, ascending-target order), or null for a gate of at most
+// kMaxArgGate qubits, whose matrix then travels with the launch.
+constexpr int kMaxArgGate = 4;
 hipError_t launch_apply_gate(float2 *amp, int n, const GateDesc &g, const float2 *mat_dev,
                              hipStream_t st);
 

@@ -13,6 +13,7 @@
 //    work-item per sample with Philox draws.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cstring>
 #include <mutex>
 
@@ -69,19 +70,32 @@ __device__ __forceinline__ float2 cmac(float2 acc, float2 a, float2 b) {
 
 // ---------------------------------------------------------------- gates
 
-// Direct path (every target >= 6): one 2^K-amplitude group per work-item;
-// the low six index bits are lane bits, so each load instruction of a
-// wavefront reads 64 consecutive amplitudes (512 B).  A work-item issues its
-// group's loads before the workgroup stages the matrix.  K <= 2 matrices are
-// read with wave-uniform addresses straight from memory (scalar loads);
-// larger ones are staged once per workgroup in LDS and read as broadcasts.
+// A gate's matrix as the first kernel argument, read through the kernel
+// argument segment: a program that applies gates one by one then needs no
+// copy of the matrix before each launch (a copy kernel of 2 us and the gaps
+// around it, for a gate of 9 us on 22 qubits).  A null device pointer selects
+// it.
+template <int K>
+struct MatArg {
+    alignas(16) float2 m[1 << (2 * K)];
+};
+__device__ __forceinline__ const float2 *gate_matrix(const float2 *dev) {
+    return dev ? dev : (const float2 *)(__builtin_amdgcn_kernarg_segment_ptr());
+}
+
+// Direct path on VALU: one 2^K-amplitude group per work-item.  A work-item
+// issues its group's loads before the workgroup stages the matrix.  K <= 2
+// matrices are read with wave-uniform addresses straight from memory (scalar
+// loads); larger ones are staged once per workgroup in LDS and read as
+// broadcasts (states too small for the matrix units, and 5-qubit gates of
+// fewer than 16 groups).
 template <int K, typename Idx>
-__global__ __launch_bounds__(kBlock) void apply_direct(float2 *__restrict__ amp, Idx groups,
-                                                       const float2 *__restrict__ mat,
-                                                       TargetArgs ta) {
+__global__ __launch_bounds__(kBlock) void apply_direct(MatArg<(K <= 4 ? K : 0)>, float2 *__restrict__ amp,
+                                                       Idx groups, const float2 *mat_dev, TargetArgs ta) {
     constexpr int D = 1 << K;
     constexpr bool kLds = K >= 3;
     __shared__ float2 sm[kLds ? D * D : 1];
+    const float2 *mat = gate_matrix(mat_dev);
     const Idx stride = Idx(gridDim.x) * Idx(kBlock);
     Idx g = Idx(blockIdx.x) * Idx(kBlock) + Idx(threadIdx.x);
     float2 v[D];
@@ -115,6 +129,137 @@ __global__ __launch_bounds__(kBlock) void apply_direct(float2 *__restrict__ amp,
         const Idx nb = spread_index<K, Idx>(g, ta.t);
 #pragma unroll
         for (int j = 0; j < D; ++j) v[j] = amp[nb + local_offset<K, Idx>(j, ta.t)];
+    }
+}
+
+// K <= 2 with every target >= kPairTarget: two groups that differ in bit 0
+// per work-item, so each access is a 16-byte amplitude pair.
+template <int K, typename Idx>
+__global__ __launch_bounds__(kBlock) void apply_pairs(MatArg<K>, float2 *__restrict__ amp, Idx pair_groups,
+                                                      const float2 *mat_dev, TargetArgs ta) {
+    constexpr int D = 1 << K;
+    const float2 *mat = gate_matrix(mat_dev);
+    float2 um[D * D];
+#pragma unroll
+    for (int i = 0; i < D * D; ++i) um[i] = const_entry(mat, i);
+    const Idx stride = Idx(gridDim.x) * Idx(kBlock);
+    for (Idx g = Idx(blockIdx.x) * Idx(kBlock) + Idx(threadIdx.x); g < pair_groups; g += stride) {
+        const Idx base = spread_index<K, Idx>(g << 1, ta.t);
+        float4 v[D];
+#pragma unroll
+        for (int j = 0; j < D; ++j)
+            v[j] = *reinterpret_cast<const float4 *>(amp + base + local_offset<K, Idx>(j, ta.t));
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            float2 lo = make_float2(0.f, 0.f), hi = make_float2(0.f, 0.f);
+#pragma unroll
+            for (int l = 0; l < D; ++l) {
+                lo = cmac(lo, um[j * D + l], make_float2(v[l].x, v[l].y));
+                hi = cmac(hi, um[j * D + l], make_float2(v[l].z, v[l].w));
+            }
+            *reinterpret_cast<float4 *>(amp + base + local_offset<K, Idx>(j, ta.t)) =
+                make_float4(lo.x, lo.y, hi.x, hi.y);
+        }
+    }
+}
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// K = 3, 4, 5 with every target >= 4, on FP32 MFMA straight from memory: the
+// contraction of tile_gate_mfma3/4/5 (16 groups per wavefront batch, lane
+// (n, q) = (l % 16, l / 16) supplies and returns the same amplitudes of group
+// n), but with the batch's 16 groups differing in index bits 0..3, so that
+// every access of a wavefront is four whole 128-byte lines and no LDS is
+// needed.  All four real products are formed (re = A x - B y, im = B x + A y):
+// memory bounds the pass, so the shorter three-product form would save
+// nothing and rounds worse.  22 qubits, 64 MB moved, per gate: k = 3 12.1 ->
+// 11.4 us (5.9 TB/s), k = 4 14.6 -> 13.5, k = 5 27.3 -> 19.7 against the VALU
+// form above.  The next batch's loads are issued before this one's products.
+template <int K, typename Idx>
+__global__ __launch_bounds__(kBlock) void apply_direct_mfma(MatArg<(K <= 4 ? K : 0)>, float2 *__restrict__ amp,
+                                                            Idx batches, const float2 *mat_dev, TargetArgs ta) {
+    constexpr int D = 1 << K;
+    constexpr int V = D / 4;            // amplitudes per lane
+    constexpr int H = K == 5 ? 2 : 1;   // halves of 16 output rows (K = 3: the 16 real rows)
+    const float2 *u = gate_matrix(mat_dev);
+    const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
+    // lane's amplitudes: 2q + s (K = 3), 4q + s (K = 4), 16 (s / 4) + 4q + s % 4 (K = 5)
+    Idx off[V];
+#pragma unroll
+    for (int s = 0; s < V; ++s) {
+        const int j = K == 3 ? 2 * q + s : 16 * (s >> 2) + 4 * q + (s & 3);
+        Idx o = Idx(n);
+#pragma unroll
+        for (int b = 0; b < K; ++b) o |= Idx((j >> b) & 1) << ta.t[b];
+        off[s] = o;
+    }
+    const Idx waves = Idx(gridDim.x) * Idx(kBlock / 64);
+    Idx batch = Idx(blockIdx.x) * Idx(kBlock / 64) + Idx(__builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6));
+    if (batch >= batches) return;
+    const Idx first = spread_index<K, Idx>(batch << 4, ta.t);
+    float2 v[V];
+#pragma unroll
+    for (int s = 0; s < V; ++s) v[s] = amp[first + off[s]];
+    // A operands: row l % 16, contraction entry of lane quarter q in step s
+    float fa[H][K == 3 ? 4 : V], fb[H][K == 3 ? 1 : V];
+    if constexpr (K == 3) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const float2 e = u[(n >> 1) * 8 + 2 * q + (s >> 1)];
+            fa[0][s] = (n & 1) == 0 ? ((s & 1) == 0 ? e.x : -e.y) : ((s & 1) == 0 ? e.y : e.x);
+        }
+    } else {
+#pragma unroll
+        for (int h = 0; h < H; ++h)
+#pragma unroll
+            for (int s = 0; s < V; ++s) {
+                const float2 e = u[(16 * h + n) * D + 16 * (s >> 2) + 4 * q + (s & 3)];
+                fa[h][s] = e.x;
+                fb[h][s] = e.y;
+            }
+    }
+    Idx base = first;
+    for (;;) {
+        const Idx next = batch + waves;
+        const bool more = next < batches;
+        Idx nbase = base;
+        float2 w[V];
+        if (more) {
+            nbase = spread_index<K, Idx>(next << 4, ta.t);
+#pragma unroll
+            for (int s = 0; s < V; ++s) w[s] = amp[nbase + off[s]];
+        }
+        if constexpr (K == 3) {
+            f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[0][0], v[0].x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[0][1], v[0].y, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[0][2], v[1].x, acc, 0, 0, 0);
+            acc = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[0][3], v[1].y, acc, 0, 0, 0);
+            amp[base + off[0]] = make_float2(acc[0], acc[1]);
+            amp[base + off[1]] = make_float2(acc[2], acc[3]);
+        } else {
+            float ny[V];
+#pragma unroll
+            for (int s = 0; s < V; ++s) ny[s] = -v[s].y;
+#pragma unroll
+            for (int h = 0; h < H; ++h) {
+                f32x4 re = {0.f, 0.f, 0.f, 0.f}, im = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < V; ++s) {
+                    re = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[h][s], v[s].x, re, 0, 0, 0);
+                    im = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[h][s], v[s].x, im, 0, 0, 0);
+                    re = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[h][s], ny[s], re, 0, 0, 0);
+                    im = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[h][s], v[s].y, im, 0, 0, 0);
+                }
+#pragma unroll
+                for (int r = 0; r < 4; ++r) amp[base + off[4 * h + r]] = make_float2(re[r], im[r]);
+            }
+        }
+        if (!more) break;
+        batch = next;
+        base = nbase;
+#pragma unroll
+        for (int s = 0; s < V; ++s) v[s] = w[s];
     }
 }
 
@@ -306,9 +451,6 @@ __device__ __forceinline__ void tile_gate_small(float2 *__restrict__ sd, const f
     }
     __builtin_amdgcn_s_setprio(0);
 }
-
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // A fused k-qubit block is a dense contraction W = U V over the tile's
 // 2^(tb-k) index groups.  For k = 3, 4, 5 it runs on FP32 MFMA
@@ -805,6 +947,31 @@ __global__ __launch_bounds__(NT) void apply_tile(float2 *__restrict__ amp, Idx n
     __shared__ float2 sd[1 << TB];
     extern __shared__ float2 sm[];
     tile_sweep<TB, Idx, K5, NT, RK, false>(amp, Idx(blockIdx.x), Idx(gridDim.x), n_tiles, ArgSweep{a}, sd, sm);
+}
+
+// One gate of at most four qubits over tiles, its matrix among the kernel's
+// arguments when the caller has no device copy.
+struct OneGate {
+    const TileOneArgs &a;
+    __device__ __forceinline__ int pos(int b) const { return a.pos[b]; }
+    __device__ __forceinline__ int n_gates() const { return 1; }
+    __device__ __forceinline__ int init_zero() const { return 0; }
+    __device__ __forceinline__ int rdm_lt() const { return 0; }
+    __device__ __forceinline__ double *rdm_out() const { return nullptr; }
+    __device__ __forceinline__ int k(int) const { return a.g.k; }
+    __device__ __forceinline__ int lt(int, int b) const { return a.g.lt[b]; }
+    __device__ __forceinline__ int lofs(int) const { return 0; }
+    __device__ __forceinline__ int tab(int, int b) const { return a.g.tab[b]; }
+    __device__ __forceinline__ const float2 *mat(int) const { return gate_matrix(a.g.mat); }
+};
+
+template <int TB, typename Idx>
+__global__ __launch_bounds__(kBlock) void apply_tile_one(MatArg<4>, float2 *__restrict__ amp, Idx n_tiles,
+                                                         TileOneArgs a) {
+    __shared__ float2 sd[1 << TB];
+    __shared__ float2 sm[416];  // tile_mat_slots(4)
+    tile_sweep<TB, Idx, false, kBlock, false, false>(amp, Idx(blockIdx.x), Idx(gridDim.x), n_tiles, OneGate{a}, sd,
+                                                     sm);
 }
 
 // ---------------------------------------------------------------- branch selection
@@ -1957,24 +2124,6 @@ GateArgs<K> make_args(const GateDesc &g) {
     return a;
 }
 
-template <typename Idx>
-hipError_t apply_direct_idx(float2 *amp, int n, const GateDesc &g, const float2 *mat_dev,
-                            hipStream_t st) {
-    const Idx groups = Idx(1) << (n - g.k);
-    const unsigned grid = grid_for(uint64_t(groups));
-    TargetArgs ta;
-    for (int b = 0; b < kMaxGateQubits; ++b) ta.t[b] = b < g.k ? g.t[b] : 0;
-    switch (g.k) {
-        case 1: apply_direct<1, Idx><<<grid, kBlock, 0, st>>>(amp, groups, mat_dev, ta); break;
-        case 2: apply_direct<2, Idx><<<grid, kBlock, 0, st>>>(amp, groups, mat_dev, ta); break;
-        case 3: apply_direct<3, Idx><<<grid, kBlock, 0, st>>>(amp, groups, mat_dev, ta); break;
-        case 4: apply_direct<4, Idx><<<grid, kBlock, 0, st>>>(amp, groups, mat_dev, ta); break;
-        case 5: apply_direct<5, Idx><<<grid, kBlock, 0, st>>>(amp, groups, mat_dev, ta); break;
-        default: return hipErrorInvalidValue;
-    }
-    return hipGetLastError();
-}
-
 int device_cus() {
     // initialised once, thread-safely (several host threads may launch at once)
     static const int cus = [] {
@@ -2176,11 +2325,14 @@ hipError_t launch_scale(float2 *amp, int n, float s, hipStream_t st) {
     return hipGetLastError();
 }
 
-bool tile_for_gate(int n, const GateDesc &g, TileArgs &a) {
-    if (n < kTileMinQubits) return false;
-    bool low = false;
-    for (int b = 0; b < g.k; ++b) low |= g.t[b] < 6;
-    if (!low) return false;
+// Lowest target the kernels that work straight on memory take: from bit 3 on
+// a pair kernel's accesses are whole 64-byte pieces, and the MFMA kernel
+// needs bits 0..3 for its 16 groups.  Gates below that stage tiles in LDS.
+constexpr int kPairTarget = 3;
+constexpr int kMfmaTarget = 4;
+
+// Tile of a single gate: bits 0..5, its targets and the lowest others.
+void tile_for_gate(int n, const GateDesc &g, TileArgs &a) {
     bool in_tile[kMaxQubits] = {false};
     int cnt = 0;
     for (int q = 0; q < 6; ++q) { in_tile[q] = true; ++cnt; }
@@ -2208,19 +2360,99 @@ bool tile_for_gate(int n, const GateDesc &g, TileArgs &a) {
         while (a.pos[lp] != g.t[b]) ++lp;
         a.g[0].lt[b] = lp;  // ascending because g.t is ascending
     }
-    return true;
+}
+
+template <int K>
+MatArg<K> mat_arg(const GateDesc &g, const float2 *dev) {
+    MatArg<K> m;
+    if (!dev) std::memcpy(m.m, g.m, sizeof(m.m));
+    return m;
+}
+
+template <int TB, typename Idx>
+hipError_t tile_one(float2 *amp, int n, const TileArgs &t, const GateDesc &g, const float2 *dev, hipStream_t st) {
+    TileOneArgs a;
+    for (int b = 0; b < kMaxTileBits; ++b) a.pos[b] = t.pos[b];
+    a.g = t.g[0];
+    a.g.mat = dev;
+    switch (g.k) {
+        case 1: gate_tables<1, SwizzledTile>(a.g.lt, a.g.tab); break;
+        case 2: gate_tables<2, SwizzledTile>(a.g.lt, a.g.tab); break;
+        case 3: gate_tables<3, SwizzledTile>(a.g.lt, a.g.tab); break;
+        default: gate_tables<4, SwizzledTile>(a.g.lt, a.g.tab); break;
+    }
+    MatArg<4> m;
+    if (!dev) std::memcpy(m.m, g.m, sizeof(float2) << (2 * g.k));
+    const uint64_t n_tiles = uint64_t(1) << (n - TB);
+    // the workgroups the CUs hold at once (LDS, and eight 256-work-item groups of wavefronts)
+    const uint64_t per_cu = std::min<uint64_t>(8, (160u * 1024u) / (sizeof(float2) * ((1u << TB) + 416u)));
+    const uint64_t grid = std::min<uint64_t>(n_tiles, uint64_t(device_cus()) * per_cu);
+    apply_tile_one<TB, Idx><<<unsigned(grid), kBlock, 0, st>>>(m, amp, Idx(n_tiles), a);
+    return hipGetLastError();
+}
+
+template <int K, typename Idx>
+hipError_t gate_k(float2 *amp, int n, const GateDesc &g, const float2 *dev, hipStream_t st) {
+    constexpr int KA = K <= 4 ? K : 0;
+    TargetArgs ta;
+    for (int b = 0; b < kMaxGateQubits; ++b) ta.t[b] = b < K ? g.t[b] : 0;
+    const MatArg<KA> m = mat_arg<KA>(g, K <= 4 ? dev : g.m);
+    if constexpr (K <= 2) {
+        if (g.t[0] >= kPairTarget) {
+            const uint64_t pairs = uint64_t(1) << (n - K - 1);
+            apply_pairs<K, Idx><<<grid_for(pairs), kBlock, 0, st>>>(m, amp, Idx(pairs), dev, ta);
+            return hipGetLastError();
+        }
+    } else {
+        if (g.t[0] >= kMfmaTarget) {  // then n - K >= 4: sixteen groups
+            const uint64_t batches = uint64_t(1) << (n - K - 4);
+            // a few batches per wavefront: the A operands are loaded once for
+            // them (k = 5, 22 qubits: 22.3 us at 8 workgroups per CU, 21.2 at
+            // 4, 19.7 at 2, 20.8 at 1; k = 3 12.2, 11.4, 12.1, 15.6)
+            const uint64_t cap = uint64_t(device_cus()) * (K == 5 ? 2 : 4);
+            const uint64_t grid = std::min<uint64_t>((batches + 3) / 4, cap);
+            apply_direct_mfma<K, Idx><<<unsigned(grid), kBlock, 0, st>>>(m, amp, Idx(batches), dev, ta);
+            return hipGetLastError();
+        }
+    }
+    if (n >= kTileMinQubits) {
+        TileArgs t;
+        std::memset(&t, 0, sizeof(t));
+        tile_for_gate(n, g, t);
+        if constexpr (K == 5) {
+            t.g[0].mat = dev;
+            return launch_apply_tile(amp, n, t, st);
+        } else {
+            switch (t.tb) {  // 10 .. k + 8, and no wider than the state
+                case 10: return tile_one<10, Idx>(amp, n, t, g, dev, st);
+                case 11: return tile_one<11, Idx>(amp, n, t, g, dev, st);
+                case 12: return tile_one<12, Idx>(amp, n, t, g, dev, st);
+                default: return hipErrorInvalidValue;
+            }
+        }
+    }
+    const uint64_t groups = uint64_t(1) << (n - K);
+    apply_direct<K, Idx><<<grid_for(groups), kBlock, 0, st>>>(m, amp, Idx(groups), dev, ta);
+    return hipGetLastError();
+}
+
+template <typename Idx>
+hipError_t gate_idx(float2 *amp, int n, const GateDesc &g, const float2 *dev, hipStream_t st) {
+    switch (g.k) {
+        case 1: return gate_k<1, Idx>(amp, n, g, dev, st);
+        case 2: return gate_k<2, Idx>(amp, n, g, dev, st);
+        case 3: return gate_k<3, Idx>(amp, n, g, dev, st);
+        case 4: return gate_k<4, Idx>(amp, n, g, dev, st);
+        case 5: return gate_k<5, Idx>(amp, n, g, dev, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_apply_gate(float2 *amp, int n, const GateDesc &g, const float2 *mat_dev,
                              hipStream_t st) {
-    TileArgs a;
-    std::memset(&a, 0, sizeof(a));
-    if (tile_for_gate(n, g, a)) {
-        a.g[0].mat = mat_dev;
-        return launch_apply_tile(amp, n, a, st);
-    }
-    if (n <= 31) return apply_direct_idx<uint32_t>(amp, n, g, mat_dev, st);
-    return apply_direct_idx<uint64_t>(amp, n, g, mat_dev, st);
+    if (!mat_dev && g.k > kMaxArgGate) return hipErrorInvalidValue;
+    if (n <= 31) return gate_idx<uint32_t>(amp, n, g, mat_dev, st);
+    return gate_idx<uint64_t>(amp, n, g, mat_dev, st);
 }
 
 hipError_t launch_apply_tile(float2 *amp, int n, const TileArgs &a, hipStream_t st, int *grid_out) {

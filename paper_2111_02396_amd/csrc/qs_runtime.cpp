@@ -213,6 +213,10 @@ qs_status enqueue_desc(qs_state s, const qs::GateDesc &g) {
     const size_t dd = size_t(1) << (2 * g.k);
     float2 *h = nullptr;
     const float2 *d = nullptr;
+    if (g.k <= qs::kMaxArgGate) {
+        QS_HIP(s, qs::launch_apply_gate(s->amp, s->n, g, nullptr, s->st));
+        return QS_OK;
+    }
     QS_CHECK(arena_stage(s, dd, &h, &d));
     std::memcpy(h, g.m, sizeof(float2) * dd);
     QS_CHECK(arena_commit(s));

@@ -47,6 +47,29 @@ def test_apply_fused_gate_parity(qs, orc, k, n):
             assert err < AMP_TOL, (k, n, t, err)
 
 
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5])
+@pytest.mark.parametrize("n", [5, 7, 9, 10, 11, 12, 13])
+@pytest.mark.parametrize("low", [2, 3, 4])
+def test_apply_gate_kernel_edges(qs, orc, k, n, low):
+    """Lowest targets on both sides of where the pair kernel (3), the MFMA
+    kernel (4) and the tile kernel take over, in states of fewer index groups
+    than a wavefront or a workgroup holds, targets not in order."""
+    if low + k > n:
+        pytest.skip("more targets than bits from the lowest one up")
+    rng = np.random.default_rng(10000 * k + 100 * n + low)
+    psi0 = random_state(n, rng)
+    t = [low] + [int(x) for x in low + 1 + rng.permutation(n - low - 1)[:k - 1]]
+    t = [t[i] for i in rng.permutation(k)]
+    U = W.random_matrix(k, rng)
+    with qs.State(n) as st:
+        qs.qs_load_state_from_host(st.h, psi0)
+        qs.qs_apply_fused_gate(st.h, t, U)
+        got = qs.qs_copy_state_to_host(st.h)
+    ref = psi0.astype(np.complex128)
+    orc.apply_matrix(ref, t, U)
+    assert rel_l2(got, ref) < AMP_TOL, t
+
+
 def test_norm_parity_and_determinism(qs, orc):
     rng = np.random.default_rng(5)
     for n in (3, 12, 20, 23):
