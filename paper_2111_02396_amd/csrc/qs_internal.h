@@ -118,18 +118,21 @@ constexpr int kBatchMaxSamples = 4096;
 
 struct BatchGate {
     int k;
-    int lt[kMaxGateQubits];  // ascending; global bits (resident) or tile-local bits
     int mat;                 // float2 offset of the default matrix in the pool
     int m0, m1;              // the block's operations in the member table
 };
 
-// The same block as a tile sweep reads it (circuits of n > kBatchLdsQubits;
-// kept apart from BatchGate, which the resident kernel carries in registers).
+// The same block as the gate loops read it, packed: a gate's description is a
+// few scalar registers (unpacked ones of two blocks ahead spilled).  On at
+// most kBatchTileBits local bits every LDS byte offset fits 16 bits.
 struct BatchTileGate {
-    int k;
-    int lt[kMaxGateQubits];
-    int lofs;                // float2 offset in the staged matrices
-    int tab[kMaxTileBits];   // LDS byte offset per logical bit (batch_gate_tables)
+    uint32_t head;           // bits 0..2 k; bits 4 + 4 j .. the ascending lt[j] (index bits
+                             // of a resident state, else tile-local bits)
+    uint32_t tab2[kMaxTileBits / 2];  // LDS byte offset per logical bit, two per word
+    int lofs;                // sweeps: float2 offset in the staged matrices
+    __host__ __device__ int k() const { return int(head & 7u); }
+    __host__ __device__ int lt(int j) const { return int((head >> (4 + 4 * j)) & 15u); }
+    __host__ __device__ int tab(int b) const { return int((tab2[b >> 1] >> (16 * (b & 1))) & 0xffffu); }
 };
 
 struct BatchSweep {          // circuits of n > kBatchLdsQubits
@@ -192,7 +195,7 @@ struct BatchArgs {
     const BatchCircuit *circs;
     const BatchSweep *sweeps;
     const BatchGate *gates;
-    const BatchTileGate *tile_gates;  // those of the larger circuits
+    const BatchTileGate *tile_gates;
     const BatchJob *jobs;
     const float2 *mats;      // default block matrices
     const double *readout;
@@ -325,8 +328,8 @@ hipError_t launch_batch_sweep(const BatchArgs &a, const BatchPart *parts, int n_
                               hipStream_t st);
 hipError_t launch_batch_sample(const BatchArgs &a, int job0, int jobs, hipStream_t st);
 
-// Fills g.tab for the sweeps' tile layout.
-void batch_gate_tables(BatchTileGate &g);
+// A block of k ascending local bits lt in the gate loops' form.
+BatchTileGate batch_tile_gate(int k, const int *lt, int lofs);
 
 // Workgroups the batched launch uses (persistent grid size).
 int batched_grid();

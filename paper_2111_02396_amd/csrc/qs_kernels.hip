@@ -297,11 +297,6 @@ struct SwizzledTile {
     }
 };
 
-// Plain layout (the batched kernel's resident states and tiles).
-struct PlainTile {
-    __host__ __device__ __forceinline__ static int map(int x) { return x; }
-};
-
 // Address table of a K-qubit gate on a tile.  Logical bit b of an index in
 // the gate's frame is target b for b < K and, for b >= K, the (b - K)-th
 // non-target local bit in ascending order (the group-index bits).
@@ -309,8 +304,7 @@ struct PlainTile {
 // that bit contributes.  The layout map is linear over GF(2), so the byte
 // offset of any amplitude is the XOR of tab[] over its logical bits, and the
 // gate loops only XOR table entries.  lt must be ascending; entries beyond the
-// tile's width are unused.  Built on the host for the tile kernel's launches
-// and on the device by the batched kernel.
+// tile's width are unused.  Built on the host.
 template <int K, class L>
 __host__ __device__ inline void gate_tables(const int *lt, int *tab) {
 #pragma unroll
@@ -557,14 +551,12 @@ __device__ __forceinline__ void stage_frag5(float *__restrict__ frag, const floa
 // disjoint groups, so reading ahead of the writes is safe).  The batch index
 // b = wave + W it occupies the logical bits after the lane's group bits.
 template <class L, int NT = kBlock>
-__device__ __forceinline__ void tile_gate_mfma3(float2 *__restrict__ sd, const float *__restrict__ frag,
-                                                const int *tab, int tb) {
+__device__ __forceinline__ void tile_gate_mfma3(float2 *__restrict__ sd, f32x4 afr, int a0, const int *tab,
+                                                int tb) {
     constexpr int W = NT / 64;
     constexpr int LW = ilog2(W);
-    const int lane = threadIdx.x & 63, wave = wave_index();
-    const f32x4 afr = *reinterpret_cast<const f32x4 *>(frag + lane * 4);
-    const int a0 = reinterpret_cast<const int *>(frag + kFrag3)[lane];  // amplitude 2q
-    const int a1 = a0 ^ tab[0];                                         // amplitude 2q + 1
+    const int wave = wave_index();
+    const int a1 = a0 ^ tab[0];  // amplitude 2q + 1
     const int iters = (1 << (tb - 3 - 4)) / W;  // batches per wave: >= 1 needs tb >= 7 + log2 W
     const int uw = tab_xor<LW>(tab, 7, wave);
     int ub = uw;
@@ -589,14 +581,11 @@ __device__ __forceinline__ void tile_gate_mfma3(float2 *__restrict__ sd, const f
 }
 
 template <class L, int NT = kBlock>
-__device__ __forceinline__ void tile_gate_mfma4(float2 *__restrict__ sd, const float *__restrict__ frag,
+__device__ __forceinline__ void tile_gate_mfma4(float2 *__restrict__ sd, f32x4 fa, f32x4 fb, f32x4 fs, int base,
                                                 const int *tab, int tb) {
     constexpr int W = NT / 64;
     constexpr int LW = ilog2(W);
-    const int lane = threadIdx.x & 63, wave = wave_index();
-    const f32x4 *fp = reinterpret_cast<const f32x4 *>(frag + lane * 12);
-    const f32x4 fa = fp[0], fb = fp[1], fs = fp[2];
-    const int base = reinterpret_cast<const int *>(frag + kFrag4)[lane];
+    const int wave = wave_index();
     int a[4];  // amplitude 4q + s of the lane's group
 #pragma unroll
     for (int s = 0; s < 4; ++s) a[s] = base ^ tab_xor<2>(tab, 0, s);
@@ -629,6 +618,22 @@ __device__ __forceinline__ void tile_gate_mfma4(float2 *__restrict__ sd, const f
         for (int s = 0; s < 4; ++s) v[s] = w[s];
     }
     __builtin_amdgcn_s_setprio(0);
+}
+
+// The same from the fragments a sweep staged in LDS.
+template <class L, int NT>
+__device__ __forceinline__ void staged_gate_mfma3(float2 *__restrict__ sd, const float *__restrict__ frag,
+                                                  const int *tab, int tb) {
+    const int lane = threadIdx.x & 63;
+    tile_gate_mfma3<L, NT>(sd, *reinterpret_cast<const f32x4 *>(frag + lane * 4),
+                           reinterpret_cast<const int *>(frag + kFrag3)[lane], tab, tb);
+}
+template <class L, int NT>
+__device__ __forceinline__ void staged_gate_mfma4(float2 *__restrict__ sd, const float *__restrict__ frag,
+                                                  const int *tab, int tb) {
+    const int lane = threadIdx.x & 63;
+    const f32x4 *fp = reinterpret_cast<const f32x4 *>(frag + lane * 12);
+    tile_gate_mfma4<L, NT>(sd, fp[0], fp[1], fp[2], reinterpret_cast<const int *>(frag + kFrag4)[lane], tab, tb);
 }
 
 // The two output halves are formed one after the other from the same
@@ -828,11 +833,11 @@ __device__ __forceinline__ void tile_sweep(float2 *__restrict__ amp, Idx first, 
                 case 1: tile_gate_small<1, SwizzledTile, NT>(sd, a.mat(gi), lt, tab, TB); break;
                 case 2: tile_gate_small<2, SwizzledTile, NT>(sd, a.mat(gi), lt, tab, TB); break;
                 case 3:
-                    tile_gate_mfma3<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)),
+                    staged_gate_mfma3<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)),
                                                       tab, TB);
                     break;
                 case 4:
-                    tile_gate_mfma4<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)),
+                    staged_gate_mfma4<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)),
                                                       tab, TB);
                     break;
                 default:
@@ -1036,48 +1041,72 @@ __global__ __launch_bounds__(64) void select_branch(SelectArgs a) {
 
 // ---------------------------------------------------------------- batched
 
-// One fused block on amplitudes held in LDS (a whole resident state, or a
-// tile).  For k <= 4, `lm` is the block's matrix already copied to LDS; for
-// k = 5, `gm` is the global copy (two pointers, so that LDS reads compile
-// to LDS instructions rather than flat ones, which would wait for every
-// global load in flight).  Fragments for the MFMA gates are staged per
-// block.  `then` runs after the block's arithmetic and before the trailing
-// barrier, which lets the next block reuse the staging area.
+// A block on a state held in LDS: uniform values, in scalar registers.
+struct ResidentGate {
+    uint32_t head;
+    uint32_t tab2[kMaxTileBits / 2];  // as in BatchTileGate
+    const float2 *m;
+    int sel;  // >= 0: the matrix is the outcome of this selection, made just before the block
+    __device__ __forceinline__ int k() const { return int(head & 7u); }
+};
+
+// The lane part of an MFMA gate's addresses: XOR of tab[] over the lane's
+// group bits (logical bits nb..nb+3) and quarter bits (qb, qb+1).
+__device__ __forceinline__ int lane_offset(const int *tab, int nb, int qb) {
+    const int lane = threadIdx.x & 63;
+    int v = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) v ^= ((lane >> b) & 1) ? tab[nb + b] : 0;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) v ^= ((lane >> (4 + b)) & 1) ? tab[qb + b] : 0;
+    return v;
+}
+
+// One block on a resident state.  For k <= 4, `lm` is the block's matrix in
+// LDS, from which every lane forms its own MFMA operands (a 16- or 32-byte
+// read and a few VALU operations: staging them as fragments first took a
+// second barrier per block); for k = 5, `gm` is the global copy (two
+// pointers, so that LDS reads compile to LDS instructions rather than flat
+// ones, which would wait for every global load in flight).  `then` runs after
+// the block's arithmetic and before the closing barrier.
+// The MFMA paths need at least one 16-group batch per wavefront at 512
+// work-items (k = 3: 10 bits, k = 4: 11); the 256-work-item form keeps the
+// same rule, so a job's arithmetic does not depend on the form.
 template <int NT, class Then>
-__device__ __forceinline__ void batched_gate(float2 *__restrict__ sd, float *__restrict__ frag,
-                                             const BatchGate &g, const float2 *lm, const float2 *gm, int tb,
-                                             Then then) {
+__device__ __forceinline__ void resident_gate(float2 *__restrict__ sd, float2 *wide, const ResidentGate &g,
+                                              const float2 *lm, int tb, Then then) {
+    const int lane = threadIdx.x & 63;
+    const int k = g.k();
     int lt[kMaxGateQubits], tab[kMaxTileBits];
 #pragma unroll
-    for (int b = 0; b < kMaxGateQubits; ++b) lt[b] = g.lt[b];
-    // MFMA paths need at least one 16-group batch per wavefront at 512
-    // work-items (k = 3: 10 bits, k = 4: 11); the 256-work-item form keeps
-    // the same rule, so a job's arithmetic does not depend on the form
-    if (g.k == 1) {
-        gate_tables<1, PlainTile>(lt, tab);
-        tile_gate_small<1, PlainTile, NT, true>(sd, lm, lt, tab, tb);
-    } else if (g.k == 2) {
-        gate_tables<2, PlainTile>(lt, tab);
-        tile_gate_small<2, PlainTile, NT, true>(sd, lm, lt, tab, tb);
-    } else if (g.k == 3 && tb >= 10) {
-        gate_tables<3, PlainTile>(lt, tab);
-        stage_frag3<NT>(frag, lm, tab);
-        __syncthreads();
-        tile_gate_mfma3<PlainTile, NT>(sd, frag, tab, tb);
-    } else if (g.k == 4 && tb >= 11) {
-        gate_tables<4, PlainTile>(lt, tab);
-        stage_frag4<NT>(frag, lm, tab);
-        __syncthreads();
-        tile_gate_mfma4<PlainTile, NT>(sd, frag, tab, tb);
-    } else if (g.k == 3) {
-        tile_gate_valu<3, PlainTile, NT>(sd, lm, lt, tb);
-    } else if (g.k == 4) {
-        tile_gate_valu<4, PlainTile, NT>(sd, lm, lt, tb);
+    for (int j = 0; j < kMaxGateQubits; ++j) lt[j] = int((g.head >> (4 + 4 * j)) & 15u);
+#pragma unroll
+    for (int b = 0; b < kMaxTileBits; ++b) tab[b] = int((g.tab2[b >> 1] >> (16 * (b & 1))) & 0xffffu);
+    if (k == 1) {
+        tile_gate_small<1, SwizzledTile, NT, true>(sd, lm, lt, tab, tb);
+    } else if (k == 2) {
+        tile_gate_small<2, SwizzledTile, NT, true>(sd, lm, lt, tab, tb);
+    } else if (k == 3 && tb >= 10) {
+        // RealForm[l % 16][4 (l / 16) + s], s < 4: two entries of row (l % 16) / 2
+        const float4 e = *reinterpret_cast<const float4 *>(lm + ((lane & 15) >> 1) * 8 + 2 * (lane >> 4));
+        const bool im = lane & 1;
+        const f32x4 afr = {im ? e.y : e.x, im ? e.x : -e.y, im ? e.w : e.z, im ? e.z : -e.w};
+        tile_gate_mfma3<SwizzledTile, NT>(sd, afr, lane_offset(tab, 3, 1), tab, tb);
+    } else if (k == 4 && tb >= 11) {
+        const float4 *p = reinterpret_cast<const float4 *>(lm + (lane & 15) * 16 + 4 * (lane >> 4));
+        const float4 e = p[0], f = p[1];
+        const f32x4 fa = {e.x, e.z, f.x, f.z};
+        const f32x4 fb = {-(e.x + e.y), -(e.z + e.w), -(f.x + f.y), -(f.z + f.w)};
+        const f32x4 fs = {e.y - e.x, e.w - e.z, f.y - f.x, f.w - f.z};
+        tile_gate_mfma4<SwizzledTile, NT>(sd, fa, fb, fs, lane_offset(tab, 4, 2), tab, tb);
+    } else if (k == 3) {
+        tile_gate_valu<3, SwizzledTile, NT>(sd, lm, lt, tb);
+    } else if (k == 4) {
+        tile_gate_valu<4, SwizzledTile, NT>(sd, lm, lt, tb);
     } else {
-        float2 *mm = reinterpret_cast<float2 *>(frag);
-        for (int i = threadIdx.x; i < 1024; i += NT) mm[i] = gm[i];
+        for (int i = threadIdx.x; i < 1024; i += NT) wide[i] = g.m[i];
         __syncthreads();
-        tile_gate_valu<5, PlainTile, NT>(sd, mm, lt, tb);
+        tile_gate_valu<5, SwizzledTile, NT>(sd, wide, lt, tb);
     }
     then();
     __syncthreads();
@@ -1096,54 +1125,38 @@ __device__ __forceinline__ int draw_pick(const double *pb, int nk, double r) {
     return nk - 1;
 }
 
-// A block of a job: its descriptor and its matrix (the default one, or the
-// job's recomputed copy when one of the block's channels took another pick).
-struct BatchedRef {
-    BatchGate g;
-    const float2 *m;
-};
-
-__device__ __forceinline__ BatchedRef batched_ref(const BatchArgs &A, const uint32_t *mask,
-                                                  const float2 *mine, const BatchCircuit &C, int gi) {
-    BatchedRef r;
-    r.g = A.gates[gi];
-    const int rel = gi - C.g0;
-    const bool patched = (mask[rel >> 5] >> (rel & 31)) & 1u;
-    r.m = patched ? mine + (r.g.mat - C.pool0) : A.mats + r.g.mat;
-    return r;
+// This work-item's entry of a k <= 4 matrix that is in memory (at most 256
+// entries, one per work-item).
+__device__ __forceinline__ bool resident_holds(const ResidentGate &g) {
+    return g.k() <= 4 && g.sel < 0 && int(threadIdx.x) < (1 << (2 * g.k()));
 }
 
-// This work-item's entry of a k <= 4 matrix (at most 256 entries, one per
-// work-item).
-__device__ __forceinline__ bool batched_holds(const BatchedRef &r) {
-    return r.g.k <= 4 && int(threadIdx.x) < (1 << (2 * r.g.k));
-}
-
-// Blocks [g0, g1) on the amplitudes in `sd`, software-pipelined so that no
+// `count` blocks on the amplitudes in `sd`, software-pipelined so that no
 // global-memory latency sits between two blocks: while block i runs, the
 // matrix of block i + 1 travels into registers (and lands in the other half
 // of the double-buffered LDS copy `raw` after block i's arithmetic) and the
 // descriptor of block i + 2 is loaded.  Workgroup barriers on gfx950 do not
 // wait for outstanding global loads, so both overlap the block's work.
-template <int NT>
-__device__ __forceinline__ void batched_blocks(const BatchArgs &A, const uint32_t *mask, const float2 *mine,
-                               const BatchCircuit &C, int g0, int g1, float2 *__restrict__ sd,
-                               float *__restrict__ frag, float2 *raw, int tb) {
-    if (g0 >= g1) return;
-    BatchedRef cur = batched_ref(A, mask, mine, C, g0);
-    if (batched_holds(cur)) raw[threadIdx.x] = cur.m[threadIdx.x];
-    BatchedRef nxt = cur;
-    if (g0 + 1 < g1) nxt = batched_ref(A, mask, mine, C, g0 + 1);
+// select(sel, dst) runs a selection that writes its block's matrix to dst.
+template <int NT, class Src, class Select>
+__device__ __forceinline__ void resident_blocks(const Src &src, int count, float2 *__restrict__ sd, float2 *wide,
+                                                float2 *raw, int tb, Select select) {
+    if (count <= 0) return;
+    ResidentGate cur = src.gate(0);
+    if (resident_holds(cur)) raw[threadIdx.x] = cur.m[threadIdx.x];
+    ResidentGate nxt = cur;
+    if (count > 1) nxt = src.gate(1);
     __syncthreads();
     int buf = 0;
-    for (int gi = g0; gi < g1; ++gi) {
-        const bool put1 = gi + 1 < g1 && batched_holds(nxt);
+    for (int gi = 0; gi < count; ++gi) {
+        if (cur.sel >= 0) select(cur.sel, raw + 256 * buf);
+        const bool put1 = gi + 1 < count && resident_holds(nxt);
         float2 e1 = make_float2(0.f, 0.f);
         if (put1) e1 = nxt.m[threadIdx.x];
-        BatchedRef after = nxt;
-        if (gi + 2 < g1) after = batched_ref(A, mask, mine, C, gi + 2);
+        ResidentGate after = nxt;
+        if (gi + 2 < count) after = src.gate(gi + 2);
         float2 *next_raw = raw + 256 * (buf ^ 1);
-        batched_gate<NT>(sd, frag, cur.g, raw + 256 * buf, cur.m, tb, [&] {
+        resident_gate<NT>(sd, wide, cur, raw + 256 * buf, tb, [&] {
             if (put1) next_raw[threadIdx.x] = e1;
         });
         cur = nxt;
@@ -1151,6 +1164,27 @@ __device__ __forceinline__ void batched_blocks(const BatchArgs &A, const uint32_
         buf ^= 1;
     }
 }
+
+// The blocks of a batched job: the circuit's descriptors, each with its
+// default matrix or the job's rebuilt copy.
+struct BatchBlocks {
+    const __attribute__((address_space(4))) BatchTileGate *g;
+    const __attribute__((address_space(4))) BatchGate *b;
+    const uint32_t *mask;
+    const float2 *mats, *mine;
+    int pool0;
+    __device__ __forceinline__ ResidentGate gate(int gi) const {
+        ResidentGate r;
+        r.head = g[gi].head;
+#pragma unroll
+        for (int j = 0; j < kMaxTileBits / 2; ++j) r.tab2[j] = g[gi].tab2[j];
+        const int mat = b[gi].mat;
+        const uint32_t word = __builtin_amdgcn_readfirstlane(mask[gi >> 5]);
+        r.m = ((word >> (gi & 31)) & 1u) ? mine + (mat - pool0) : mats + mat;
+        r.sel = -1;
+        return r;
+    }
+};
 
 // One operation (k qubits; block position of its bit b in bits 3b..3b+2 of
 // `lpp`) on a column of a fused block's matrix, as the host's fusion does
@@ -1323,15 +1357,15 @@ __device__ __forceinline__ void draw_and_patch(const BatchArgs &A, const BatchJo
     __syncthreads();
 }
 
-// Samples of a job's final state at `p` (2^n amplitudes): inverse CDF over
+// Samples of a job's final state, amp(i) its amplitudes: inverse CDF over
 // 256 contiguous chunks whose FP64 sums are scanned in a fixed order; readout
 // flips as in sample_draw.  PIECE amplitudes are loaded at a time (16 for a
 // state in global memory, so that a work-item's 128-byte line is one burst of
 // independent loads; the order of the additions is the same for any PIECE,
 // which divides the chunk length).  `part` is 256 doubles of LDS.
-template <int NT, int PIECE>
+template <int NT, int PIECE, class Amp>
 __device__ __forceinline__ void batched_sample(const BatchArgs &A, const BatchJob &J, const BatchCircuit &C,
-                                               const float2 *p, double *part) {
+                                               Amp amp, double *part) {
     const int n = C.n;
     const int dim = 1 << n;
     // chunk c = amplitudes [c*L, (c+1)*L), L = dim / 256 (>= 1), the same 256
@@ -1343,7 +1377,7 @@ __device__ __forceinline__ void batched_sample(const BatchArgs &A, const BatchJo
         for (int i = 0; i < L; i += PIECE) {
             float2 v[PIECE];
 #pragma unroll
-            for (int j = 0; j < PIECE; ++j) v[j] = p[threadIdx.x * L + i + j];
+            for (int j = 0; j < PIECE; ++j) v[j] = amp(int(threadIdx.x) * L + i + j);
 #pragma unroll
             for (int j = 0; j < PIECE; ++j)
                 acc = fma(double(v[j].x), double(v[j].x), fma(double(v[j].y), double(v[j].y), acc));
@@ -1409,7 +1443,7 @@ __device__ __forceinline__ void batched_sample(const BatchArgs &A, const BatchJo
             for (int i = 0; i < L; i += PIECE) {
                 float2 v[PIECE];
 #pragma unroll
-                for (int j = 0; j < PIECE; ++j) v[j] = p[lo * L + i + j];
+                for (int j = 0; j < PIECE; ++j) v[j] = amp(lo * L + i + j);
                 int found = -1;
 #pragma unroll
                 for (int j = 0; j < PIECE; ++j) {
@@ -1450,7 +1484,7 @@ template <int NT>
 __global__ __launch_bounds__(NT) void run_batched(BatchArgs A) {
     extern __shared__ float2 smem[];
     float2 *sd = smem;                                                   // 2^13 amplitudes
-    float *frag = reinterpret_cast<float *>(smem + (1 << kBatchLdsQubits));  // 2048 floats
+    float2 *wide = smem + (1 << kBatchLdsQubits);                        // a 5-qubit block's matrix
     float2 *raw = smem + (1 << kBatchLdsQubits) + 1024;                  // 2 x 256 entries
     __shared__ double part[kBlock];
     float2 *mine = A.patched + size_t(blockIdx.x) * size_t(A.patched_stride);
@@ -1462,8 +1496,15 @@ __global__ __launch_bounds__(NT) void run_batched(BatchArgs A) {
         draw_and_patch<NT>(A, J, C, mask, reinterpret_cast<double2 *>(sd), reinterpret_cast<double2 *>(raw), mine);
         for (int i = threadIdx.x; i < dim; i += NT) sd[i] = make_float2(i == 0 ? 1.f : 0.f, 0.f);
         __syncthreads();
-        batched_blocks<NT>(A, mask, mine, C, C.g0, C.g0 + C.n_gates, sd, frag, raw, C.n);
-        batched_sample<NT, 1>(A, J, C, sd, part);
+        BatchBlocks src;
+        src.g = (const __attribute__((address_space(4))) BatchTileGate *)(A.tile_gates) + C.tg0;
+        src.b = (const __attribute__((address_space(4))) BatchGate *)(A.gates) + C.g0;
+        src.mask = mask;
+        src.mats = A.mats;
+        src.mine = mine;
+        src.pool0 = C.pool0;
+        resident_blocks<NT>(src, C.n_gates, sd, wide, raw, C.n, [](int, float2 *) {});
+        batched_sample<NT, 1>(A, J, C, [&](int i) { return sd[SwizzledTile::map(i)]; }, part);
         __syncthreads();
     }
 }
@@ -1508,10 +1549,10 @@ struct JobSweep {
     __device__ __forceinline__ int init_zero() const { return zero; }
     __device__ __forceinline__ int rdm_lt() const { return 0; }
     __device__ __forceinline__ double *rdm_out() const { return nullptr; }
-    __device__ __forceinline__ int k(int gi) const { return g[gi].k; }
-    __device__ __forceinline__ int lt(int gi, int b) const { return g[gi].lt[b]; }
+    __device__ __forceinline__ int k(int gi) const { return int(g[gi].head & 7u); }
+    __device__ __forceinline__ int lt(int gi, int b) const { return int((g[gi].head >> (4 + 4 * b)) & 15u); }
     __device__ __forceinline__ int lofs(int gi) const { return g[gi].lofs; }
-    __device__ __forceinline__ int tab(int gi, int b) const { return g[gi].tab[b]; }
+    __device__ __forceinline__ int tab(int gi, int b) const { return int((g[gi].tab2[b >> 1] >> (16 * (b & 1))) & 0xffffu); }
     __device__ __forceinline__ const float2 *mat(int gi) const { return reinterpret_cast<const float2 *>(m[gi]); }
 };
 
@@ -1541,7 +1582,8 @@ __global__ __launch_bounds__(kBlock) void batch_sample(BatchArgs A, int job0) {
     __shared__ double part[kBlock];
     const BatchJob J = A.jobs[job0 + int(blockIdx.x)];
     const BatchCircuit C = A.circs[J.circuit];
-    batched_sample<kBlock, 16>(A, J, C, A.slots + J.slot, part);
+    const float2 *p = A.slots + J.slot;
+    batched_sample<kBlock, 16>(A, J, C, [p](int i) { return p[i]; }, part);
 }
 
 // ---------------------------------------------------------------- utility
@@ -2275,14 +2317,23 @@ hipError_t launch_batch_sample(const BatchArgs &a, int job0, int jobs, hipStream
     return hipGetLastError();
 }
 
-void batch_gate_tables(BatchTileGate &g) {
-    switch (g.k) {
-        case 1: gate_tables<1, SwizzledTile>(g.lt, g.tab); break;
-        case 2: gate_tables<2, SwizzledTile>(g.lt, g.tab); break;
-        case 3: gate_tables<3, SwizzledTile>(g.lt, g.tab); break;
-        case 4: gate_tables<4, SwizzledTile>(g.lt, g.tab); break;
-        default: gate_tables<5, SwizzledTile>(g.lt, g.tab); break;
+BatchTileGate batch_tile_gate(int k, const int *lt, int lofs) {
+    int tab[kMaxTileBits];
+    switch (k) {
+        case 1: gate_tables<1, SwizzledTile>(lt, tab); break;
+        case 2: gate_tables<2, SwizzledTile>(lt, tab); break;
+        case 3: gate_tables<3, SwizzledTile>(lt, tab); break;
+        case 4: gate_tables<4, SwizzledTile>(lt, tab); break;
+        default: gate_tables<5, SwizzledTile>(lt, tab); break;
     }
+    BatchTileGate g;
+    g.head = uint32_t(k);
+    for (int j = 0; j < k; ++j) g.head |= uint32_t(lt[j]) << (4 + 4 * j);
+    // entries past the 13 local bits are never used
+    for (int b = 0; b < kMaxTileBits; b += 2)
+        g.tab2[b >> 1] = (uint32_t(tab[b]) & 0xffffu) | (uint32_t(tab[b + 1]) << 16);
+    g.lofs = lofs;
+    return g;
 }
 
 int reduce_blocks_for(int n, int k) {

@@ -2866,7 +2866,7 @@ struct BatchPlanKey {
 struct BatchPlanEntry {
     std::vector<qs::BatchSweep> sweeps;     // gate ranges local to the circuit
     std::vector<qs::BatchGate> gates;       // mat: offset into pool; m0, m1: into members
-    std::vector<qs::BatchTileGate> tile_gates;  // the larger circuits' blocks, as sweeps read them
+    std::vector<qs::BatchTileGate> tile_gates;  // the blocks with their LDS address tables
     std::vector<float2> pool;               // the default matrices of the blocks
     std::vector<qs::BatchChannel> chans;    // pbar: into pbar; unit: into fmats
     std::vector<double> pbar;
@@ -3101,18 +3101,12 @@ qs_status plan_batched_circuit(const CircuitModel &m, const std::vector<const cd
             qs::BatchGate G;
             std::memset(&G, 0, sizeof(G));
             G.k = B.k;
-            for (int j = 0; j < B.k; ++j) G.lt[j] = local[B.q[j]];
-            if (!resident) {
-                qs::BatchTileGate T;
-                std::memset(&T, 0, sizeof(T));
-                T.k = B.k;
-                for (int j = 0; j < B.k; ++j) T.lt[j] = G.lt[j];
-                T.lofs = lofs;
-                lofs += qs::tile_mat_slots(B.k);
-                qs::batch_gate_tables(T);
-                e.tile_gates.push_back(T);
-                e.k5 |= B.k == 5;
-            }
+
+            int lt[qs::kMaxGateQubits];
+            for (int j = 0; j < B.k; ++j) lt[j] = local[B.q[j]];
+            e.tile_gates.push_back(qs::batch_tile_gate(B.k, lt, lofs));
+            lofs += qs::tile_mat_slots(B.k);
+            e.k5 |= !resident && B.k == 5;
             qs::fused_matrix(B.k, B.q, B.ops, m.ops, default_mats, tmp.data());
             const int D = 1 << B.k;
             G.mat = int(e.pool.size());
