@@ -212,6 +212,48 @@ struct BatchArgs {
     int n_jobs;              // resident jobs (the first ones)
 };
 
+// ---- trajectories side by side -------------------------------------------
+// Programs of several trajectories of one circuit, planned by the host (which
+// knows every pick but those of inner-product channels), run by one launch
+// each (resident states) or one launch per step over all of them.
+struct TrajGate {
+    BatchTileGate g;
+    int sel;                 // resident: >= 0, a selection to make before the block
+    const float2 *m;
+};
+// Flag in a resident block's head: its matrix is the last selection's outcome.
+constexpr uint32_t kSelectedGate = 1u << 31;
+
+// A channel that needs inner products (see SelectArgs).
+struct TrajSelect {
+    const double *excess, *pbar, *cand;
+    float2 *dst;             // sweeps: where the block's matrix goes
+    const double *records;   // sweeps: the workgroup records of its reduced density matrix
+    int *choice, *err;
+    double resid;
+    int nk, k, Db, n_records;
+    int t[kMaxChannelQubits];  // ascending
+};
+
+struct TrajJob {             // resident
+    int g0, n_gates;
+    float2 *out;             // the final state's place, or null
+};
+
+struct TrajResidentArgs {
+    const TrajJob *jobs;
+    const TrajGate *gates;
+    const TrajSelect *sels;
+    int n;
+};
+
+struct TrajSweep {           // n > kBatchLdsQubits: one trajectory's sweep of a step
+    float2 *amp;
+    double *rdm_out;         // or null
+    int pos[kMaxTileBits];
+    int g0, n_gates, init_zero, rdm_lt;
+};
+
 // Blocks per batched circuit: the job's patched-block flags are one bit each
 // in a 2 KiB LDS array.
 constexpr int kBatchMaxBlocks = 16384;
@@ -327,6 +369,14 @@ hipError_t launch_batch_prepare(const BatchArgs &a, int job0, int jobs, hipStrea
 hipError_t launch_batch_sweep(const BatchArgs &a, const BatchPart *parts, int n_parts, int step, bool k5,
                               hipStream_t st);
 hipError_t launch_batch_sample(const BatchArgs &a, int job0, int jobs, hipStream_t st);
+
+// Trajectories of resident states, one workgroup each.
+hipError_t launch_traj_resident(const TrajResidentArgs &a, int jobs, hipStream_t st);
+// One step of trajectories of n > kBatchLdsQubits qubits: `count` sweeps over
+// all their tiles (traj_sweep_records workgroups each), then its selections.
+int traj_sweep_records(int n);
+hipError_t launch_traj_sweep(const TrajSweep *sweeps, const TrajGate *gates, int n, int count, hipStream_t st);
+hipError_t launch_traj_select(const TrajSelect *sels, int count, hipStream_t st);
 
 // A block of k ascending local bits lt in the gate loops' form.
 BatchTileGate batch_tile_gate(int k, const int *lt, int lofs);

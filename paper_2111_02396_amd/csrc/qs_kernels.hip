@@ -855,7 +855,7 @@ __device__ __forceinline__ void tile_sweep(float2 *__restrict__ amp, Idx first, 
             const float2 lo = sd[tid_l + (r << (NB + 1))], hi = sd[(tid_l ^ 1) + (r << (NB + 1))];
             o[r] = make_float4(lo.x, lo.y, hi.x, hi.y);
         }
-        if constexpr (RK) {
+        if (RK && a.rdm_out()) {
             // the work-item's amplitudes are local indices 2 tid + e + 2 NT r,
             // read again from LDS (a rolled loop keeps the registers of the
             // common sweep); the partner across the qubit's bit pc sits at
@@ -887,7 +887,7 @@ __device__ __forceinline__ void tile_sweep(float2 *__restrict__ amp, Idx first, 
     for (tile += step; tile < last; tile += step) run_tile(tile, true);
 #pragma unroll
     for (int r = 0; r < R; ++r) *reinterpret_cast<float4 *>(amp + prev_base + off_r[r]) = o[r];
-    if constexpr (RK) {
+    if (RK && a.rdm_out()) {
         // wavefront sums by a fixed shuffle tree, then the wavefronts in order
         // through LDS (the tile is no longer needed once every wavefront has
         // read its last tile out)
@@ -981,56 +981,56 @@ __global__ __launch_bounds__(kBlock) void apply_tile_one(MatArg<4>, float2 *__re
 
 // ---------------------------------------------------------------- branch selection
 
+// Steps 13-20 of Algorithm 2 on one work-item: the pick and the factor
+// 1/sqrt(p N) from R (`rdm`, D x D complex128).
+__device__ __forceinline__ void pick_branch(const double *rdm, int D, const double *excess, const double *pbar,
+                                            int nk, double resid, int *err, int *pick, double *scale) {
+    double N = 0.0;
+    for (int j = 0; j < D; ++j) N += rdm[2 * (j * D + j)];
+    auto weight = [&](int i) {
+        const double *M = excess + size_t(i) * D * D * 2;
+        double tr = 0.0;  // Re sum_jl M[j][l] R[l][j]
+        for (int j = 0; j < D; ++j)
+            for (int l = 0; l < D; ++l) {
+                const double mr = M[2 * (j * D + l)], mi = M[2 * (j * D + l) + 1];
+                const double rr = rdm[2 * (l * D + j)], ri = rdm[2 * (l * D + j) + 1];
+                tr += mr * rr - mi * ri;
+            }
+        return tr / N;
+    };
+    double r = resid;
+    int chosen = -1, last_pos = -1;
+    double e_chosen = 0.0;
+    for (int i = 0; i < nk; ++i) {
+        const double e = weight(i);
+        if (e > 0.0) last_pos = i;
+        if (r < e) {
+            chosen = i;
+            e_chosen = e;
+            break;
+        }
+        r -= e;
+    }
+    if (chosen < 0) {
+        chosen = last_pos >= 0 ? last_pos : nk - 1;
+        e_chosen = weight(chosen);
+    }
+    const double p = pbar[chosen] + e_chosen;
+    if (!(N > 0.0) || !(p > 0.0) || !(N < INFINITY)) {
+        *err = 1;
+        *scale = 0.0;
+    } else {
+        *scale = 1.0 / sqrt(p * N);
+    }
+    *pick = chosen;
+}
+
 __global__ __launch_bounds__(64) void select_branch(SelectArgs a) {
     __shared__ double scale;
     __shared__ int pick;
     if (threadIdx.x == 0) {
-        const int D = a.D;
-        double N = 0.0;
-        for (int j = 0; j < D; ++j) N += a.rdm[2 * (j * D + j)];
-        double r = a.resid;
-        int chosen = -1, last_pos = -1;
-        double e_chosen = 0.0;
-        for (int i = 0; i < a.nk; ++i) {
-            const double *M = a.excess + size_t(i) * D * D * 2;
-            double tr = 0.0;  // Re sum_jl M[j][l] R[l][j]
-            for (int j = 0; j < D; ++j)
-                for (int l = 0; l < D; ++l) {
-                    const double mr = M[2 * (j * D + l)], mi = M[2 * (j * D + l) + 1];
-                    const double rr = a.rdm[2 * (l * D + j)], ri = a.rdm[2 * (l * D + j) + 1];
-                    tr += mr * rr - mi * ri;
-                }
-            const double e = tr / N;
-            if (e > 0.0) last_pos = i;
-            if (r < e) {
-                chosen = i;
-                e_chosen = e;
-                break;
-            }
-            r -= e;
-        }
-        if (chosen < 0) {
-            chosen = last_pos >= 0 ? last_pos : a.nk - 1;
-            // e of the fallback pick
-            const double *M = a.excess + size_t(chosen) * D * D * 2;
-            double tr = 0.0;
-            for (int j = 0; j < D; ++j)
-                for (int l = 0; l < D; ++l) {
-                    const double mr = M[2 * (j * D + l)], mi = M[2 * (j * D + l) + 1];
-                    const double rr = a.rdm[2 * (l * D + j)], ri = a.rdm[2 * (l * D + j) + 1];
-                    tr += mr * rr - mi * ri;
-                }
-            e_chosen = tr / N;
-        }
-        const double p = a.pbar[chosen] + e_chosen;
-        if (!(N > 0.0) || !(p > 0.0) || !(N < INFINITY)) {
-            *a.err = 1;
-            scale = 0.0;
-        } else {
-            scale = 1.0 / sqrt(p * N);
-        }
-        pick = chosen;
-        *a.choice = chosen;
+        pick_branch(a.rdm, a.D, a.excess, a.pbar, a.nk, a.resid, a.err, &pick, &scale);
+        *a.choice = pick;
     }
     __syncthreads();
     const int dd = a.Db * a.Db;
@@ -1046,8 +1046,10 @@ struct ResidentGate {
     uint32_t head;
     uint32_t tab2[kMaxTileBits / 2];  // as in BatchTileGate
     const float2 *m;
-    int sel;  // >= 0: the matrix is the outcome of this selection, made just before the block
+    int sel;  // >= 0: a selection to make before the block
     __device__ __forceinline__ int k() const { return int(head & 7u); }
+    // the matrix is the outcome of the last selection made
+    __device__ __forceinline__ bool selected() const { return head & kSelectedGate; }
 };
 
 // The lane part of an MFMA gate's addresses: XOR of tab[] over the lane's
@@ -1069,10 +1071,10 @@ __device__ __forceinline__ int lane_offset(const int *tab, int nb, int qb) {
 // pointers, so that LDS reads compile to LDS instructions rather than flat
 // ones, which would wait for every global load in flight).  `then` runs after
 // the block's arithmetic and before the closing barrier.
-// The MFMA paths need at least one 16-group batch per wavefront at 512
-// work-items (k = 3: 10 bits, k = 4: 11); the 256-work-item form keeps the
-// same rule, so a job's arithmetic does not depend on the form.
-template <int NT, class Then>
+// The MFMA paths need at least one 16-group batch per wavefront: M3 and M4 are
+// the fewest bits they run at for k = 3 and 4 (10 and 11 at 512 work-items, 9
+// and 10 at 256).
+template <int NT, int M3, int M4, class Then>
 __device__ __forceinline__ void resident_gate(float2 *__restrict__ sd, float2 *wide, const ResidentGate &g,
                                               const float2 *lm, int tb, Then then) {
     const int lane = threadIdx.x & 63;
@@ -1086,13 +1088,13 @@ __device__ __forceinline__ void resident_gate(float2 *__restrict__ sd, float2 *w
         tile_gate_small<1, SwizzledTile, NT, true>(sd, lm, lt, tab, tb);
     } else if (k == 2) {
         tile_gate_small<2, SwizzledTile, NT, true>(sd, lm, lt, tab, tb);
-    } else if (k == 3 && tb >= 10) {
+    } else if (k == 3 && tb >= M3) {
         // RealForm[l % 16][4 (l / 16) + s], s < 4: two entries of row (l % 16) / 2
         const float4 e = *reinterpret_cast<const float4 *>(lm + ((lane & 15) >> 1) * 8 + 2 * (lane >> 4));
         const bool im = lane & 1;
         const f32x4 afr = {im ? e.y : e.x, im ? e.x : -e.y, im ? e.w : e.z, im ? e.z : -e.w};
         tile_gate_mfma3<SwizzledTile, NT>(sd, afr, lane_offset(tab, 3, 1), tab, tb);
-    } else if (k == 4 && tb >= 11) {
+    } else if (k == 4 && tb >= M4) {
         const float4 *p = reinterpret_cast<const float4 *>(lm + (lane & 15) * 16 + 4 * (lane >> 4));
         const float4 e = p[0], f = p[1];
         const f32x4 fa = {e.x, e.z, f.x, f.z};
@@ -1128,7 +1130,7 @@ __device__ __forceinline__ int draw_pick(const double *pb, int nk, double r) {
 // This work-item's entry of a k <= 4 matrix that is in memory (at most 256
 // entries, one per work-item).
 __device__ __forceinline__ bool resident_holds(const ResidentGate &g) {
-    return g.k() <= 4 && g.sel < 0 && int(threadIdx.x) < (1 << (2 * g.k()));
+    return g.k() <= 4 && !g.selected() && int(threadIdx.x) < (1 << (2 * g.k()));
 }
 
 // `count` blocks on the amplitudes in `sd`, software-pipelined so that no
@@ -1137,10 +1139,12 @@ __device__ __forceinline__ bool resident_holds(const ResidentGate &g) {
 // of the double-buffered LDS copy `raw` after block i's arithmetic) and the
 // descriptor of block i + 2 is loaded.  Workgroup barriers on gfx950 do not
 // wait for outstanding global loads, so both overlap the block's work.
-// select(sel, dst) runs a selection that writes its block's matrix to dst.
-template <int NT, class Src, class Select>
+// select(sel, dst) makes a selection on the state as it stands between two
+// blocks and writes the matrix of a later block to dst (`chosen`; at most one
+// is pending).
+template <int NT, int M3, int M4, class Src, class Select>
 __device__ __forceinline__ void resident_blocks(const Src &src, int count, float2 *__restrict__ sd, float2 *wide,
-                                                float2 *raw, int tb, Select select) {
+                                                float2 *raw, float2 *chosen, int tb, Select select) {
     if (count <= 0) return;
     ResidentGate cur = src.gate(0);
     if (resident_holds(cur)) raw[threadIdx.x] = cur.m[threadIdx.x];
@@ -1149,14 +1153,14 @@ __device__ __forceinline__ void resident_blocks(const Src &src, int count, float
     __syncthreads();
     int buf = 0;
     for (int gi = 0; gi < count; ++gi) {
-        if (cur.sel >= 0) select(cur.sel, raw + 256 * buf);
+        if (cur.sel >= 0) select(cur.sel, chosen);
         const bool put1 = gi + 1 < count && resident_holds(nxt);
         float2 e1 = make_float2(0.f, 0.f);
         if (put1) e1 = nxt.m[threadIdx.x];
         ResidentGate after = nxt;
         if (gi + 2 < count) after = src.gate(gi + 2);
         float2 *next_raw = raw + 256 * (buf ^ 1);
-        resident_gate<NT>(sd, wide, cur, raw + 256 * buf, tb, [&] {
+        resident_gate<NT, M3, M4>(sd, wide, cur, cur.selected() ? chosen : raw + 256 * buf, tb, [&] {
             if (put1) next_raw[threadIdx.x] = e1;
         });
         cur = nxt;
@@ -1503,7 +1507,9 @@ __global__ __launch_bounds__(NT) void run_batched(BatchArgs A) {
         src.mats = A.mats;
         src.mine = mine;
         src.pool0 = C.pool0;
-        resident_blocks<NT>(src, C.n_gates, sd, wide, raw, C.n, [](int, float2 *) {});
+        // the same MFMA rule at either group size: a job's arithmetic does not
+        // depend on the launch it runs in
+        resident_blocks<NT, 10, 11>(src, C.n_gates, sd, wide, raw, raw, C.n, [](int, float2 *) {});
         batched_sample<NT, 1>(A, J, C, [&](int i) { return sd[SwizzledTile::map(i)]; }, part);
         __syncthreads();
     }
@@ -1584,6 +1590,190 @@ __global__ __launch_bounds__(kBlock) void batch_sample(BatchArgs A, int job0) {
     const BatchCircuit C = A.circs[J.circuit];
     const float2 *p = A.slots + J.slot;
     batched_sample<kBlock, 16>(A, J, C, [p](int i) { return p[i]; }, part);
+}
+
+// ---------------------------------------------------------------- trajectories side by side
+
+// A resident trajectory's blocks.
+struct TrajBlocks {
+    const __attribute__((address_space(4))) TrajGate *g;
+    __device__ __forceinline__ ResidentGate gate(int gi) const {
+        ResidentGate r;
+        r.head = g[gi].g.head;
+#pragma unroll
+        for (int j = 0; j < kMaxTileBits / 2; ++j) r.tab2[j] = g[gi].g.tab2[j];
+        r.m = (const float2 *)(g[gi].m);
+        r.sel = g[gi].sel;
+        return r;
+    }
+};
+
+// R of K ascending qubits of a resident state, summed over the workgroup in a
+// fixed order into red[0 .. 2 D D) (LDS; ends with a barrier).
+template <int K, int NT>
+__device__ __forceinline__ void resident_rdm(const float2 *sd, int n, const int *t, double *red) {
+    constexpr int D = 1 << K;
+    constexpr int T = D * D;  // as in rdm_partials
+    double acc[T];
+#pragma unroll
+    for (int w = 0; w < T; ++w) acc[w] = 0.0;
+    for (int g = threadIdx.x; g < (1 << (n - K)); g += NT) {
+        const int base = spread_index<K, int>(g, t);
+        double vr[D], vi[D];
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            const float2 v = sd[SwizzledTile::map(base | local_offset<K, int>(j, t))];
+            vr[j] = v.x;
+            vi[j] = v.y;
+        }
+        int w = D;
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            acc[j] = fma(vr[j], vr[j], fma(vi[j], vi[j], acc[j]));
+#pragma unroll
+            for (int l = j + 1; l < D; ++l, w += 2) {
+                acc[w] = fma(vr[j], vr[l], fma(vi[j], vi[l], acc[w]));
+                acc[w + 1] = fma(vi[j], vr[l], fma(-vr[j], vi[l], acc[w + 1]));
+            }
+        }
+    }
+#pragma unroll
+    for (int w = 0; w < T; ++w) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) acc[w] += __shfl_xor(acc[w], off, 64);
+    }
+    double *part = red + 32;  // [wavefront][T]
+    if ((threadIdx.x & 63) == 0) {
+#pragma unroll
+        for (int w = 0; w < T; ++w) part[(threadIdx.x >> 6) * T + w] = acc[w];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double sum[T];
+#pragma unroll
+        for (int w = 0; w < T; ++w) {
+            double x = 0.0;
+            for (int i = 0; i < NT / 64; ++i) x += part[i * T + w];
+            sum[w] = x;
+        }
+        int w = D;
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            red[2 * (j * D + j)] = sum[j];
+            red[2 * (j * D + j) + 1] = 0.0;
+#pragma unroll
+            for (int l = j + 1; l < D; ++l, w += 2) {
+                red[2 * (j * D + l)] = sum[w];
+                red[2 * (j * D + l) + 1] = sum[w + 1];
+                red[2 * (l * D + j)] = sum[w];
+                red[2 * (l * D + j) + 1] = -sum[w + 1];
+            }
+        }
+    }
+}
+
+// One trajectory per workgroup, its state in LDS from |0...0> to the end: the
+// blocks in launch order, each selection where its channel stands in the
+// circuit (between the blocks of the operations before it and after it).  Bound by the chain of blocks on one CU (LDS round trip,
+// barrier, a few MFMAs each: about 1 us), so a call's trajectories run side
+// by side on as many CUs.
+template <int NT, int M3, int M4>
+__global__ __launch_bounds__(NT) void run_resident(TrajResidentArgs A) {
+    extern __shared__ float2 smem[];
+    float2 *sd = smem;                    // 2^n amplitudes
+    float2 *wide = smem + (1 << A.n);     // a 5-qubit block's matrix
+    float2 *raw = wide + 1024;            // 2 x 256 entries
+    float2 *chosen = raw + 512;           // a selection's matrix
+    __shared__ double red[32 + 16 * (NT / 64)];
+    __shared__ double scale;
+    __shared__ int pick;
+    const TrajJob J = A.jobs[blockIdx.x];
+    for (int i = threadIdx.x; i < (1 << A.n); i += NT) sd[i] = make_float2(i == 0 ? 1.f : 0.f, 0.f);
+    __syncthreads();
+    TrajBlocks src;
+    src.g = (const __attribute__((address_space(4))) TrajGate *)(A.gates) + J.g0;
+    resident_blocks<NT, M3, M4>(src, J.n_gates, sd, wide, raw, chosen, A.n, [&](int sel, float2 *dst) {
+        const TrajSelect S = A.sels[sel];
+        if (S.k == 1) resident_rdm<1, NT>(sd, A.n, S.t, red);
+        else resident_rdm<2, NT>(sd, A.n, S.t, red);
+        if (threadIdx.x == 0) {  // the work-item that wrote `red`
+            pick_branch(red, 1 << S.k, S.excess, S.pbar, S.nk, S.resid, S.err, &pick, &scale);
+            *S.choice = pick;
+        }
+        __syncthreads();
+        const int dd = S.Db * S.Db;  // at most 256
+        const double *c = S.cand + size_t(pick) * dd * 2;
+        if (int(threadIdx.x) < dd)
+            dst[threadIdx.x] =
+                make_float2(float(c[2 * threadIdx.x] * scale), float(c[2 * threadIdx.x + 1] * scale));
+        __syncthreads();
+    });
+    if (J.out)
+        for (int i = threadIdx.x; i < (1 << A.n); i += NT) J.out[i] = sd[SwizzledTile::map(i)];
+}
+
+// A sweep of one trajectory, in device tables.
+struct TrajSweepSrc {
+    const __attribute__((address_space(4))) TrajSweep *s;
+    const __attribute__((address_space(4))) TrajGate *g;  // the sweep's first gate
+    __device__ __forceinline__ int pos(int b) const { return s->pos[b]; }
+    __device__ __forceinline__ int n_gates() const { return s->n_gates; }
+    __device__ __forceinline__ int init_zero() const { return s->init_zero; }
+    __device__ __forceinline__ int rdm_lt() const { return s->rdm_lt; }
+    __device__ __forceinline__ double *rdm_out() const { return (double *)(s->rdm_out); }
+    __device__ __forceinline__ int k(int gi) const { return int(g[gi].g.head & 7u); }
+    __device__ __forceinline__ int lt(int gi, int b) const { return int((g[gi].g.head >> (4 + 4 * b)) & 15u); }
+    __device__ __forceinline__ int lofs(int gi) const { return g[gi].g.lofs; }
+    __device__ __forceinline__ int tab(int gi, int b) const {
+        return int((g[gi].g.tab2[b >> 1] >> (16 * (b & 1))) & 0xffffu);
+    }
+    __device__ __forceinline__ const float2 *mat(int gi) const { return (const float2 *)(g[gi].m); }
+};
+
+// Step of several trajectories: workgroup (x, y) takes tile x of sweep y.
+// One trajectory of 14..21 qubits has 2 to 256 tiles for 512 workgroup slots
+// and a sweep of it takes 12 to 20 us whatever its size, so the sweeps of
+// several trajectories share a launch.
+__global__ __launch_bounds__(kBatchWideThreads) void traj_sweep(const TrajSweep *sweeps, const TrajGate *gates,
+                                                                uint32_t n_tiles) {
+    __shared__ float2 sd[1 << kBatchTileBits];
+    extern __shared__ float2 sm[];
+    TrajSweepSrc src;
+    src.s = (const __attribute__((address_space(4))) TrajSweep *)(sweeps) + blockIdx.y;
+    src.g = (const __attribute__((address_space(4))) TrajGate *)(gates) + src.s->g0;
+    tile_sweep<kBatchTileBits, uint32_t, false, kBatchWideThreads, true, true>(
+        (float2 *)(src.s->amp), blockIdx.x, gridDim.x, n_tiles, src, sd, sm);
+}
+
+// A step's selections, one wavefront each: the sweep's workgroup records are
+// summed in a fixed order, then as select_branch.
+__global__ __launch_bounds__(64) void traj_select(const TrajSelect *sels) {
+    __shared__ double red[8];
+    __shared__ double scale;
+    __shared__ int pick;
+    const TrajSelect S = sels[blockIdx.x];
+    double acc[8];
+#pragma unroll
+    for (int w = 0; w < 8; ++w) acc[w] = 0.0;
+    for (int i = threadIdx.x; i < S.n_records; i += 64) {
+#pragma unroll
+        for (int w = 0; w < 8; ++w) acc[w] += S.records[size_t(i) * 8 + w];
+    }
+#pragma unroll
+    for (int w = 0; w < 8; ++w) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) acc[w] += __shfl_xor(acc[w], off, 64);
+        if (threadIdx.x == 0) red[w] = acc[w];
+    }
+    if (threadIdx.x == 0) {
+        pick_branch(red, 2, S.excess, S.pbar, S.nk, S.resid, S.err, &pick, &scale);
+        *S.choice = pick;
+    }
+    __syncthreads();
+    const int dd = S.Db * S.Db;
+    const double *c = S.cand + size_t(pick) * dd * 2;
+    for (int i = threadIdx.x; i < dd; i += 64)
+        S.dst[i] = make_float2(float(c[2 * i] * scale), float(c[2 * i + 1] * scale));
 }
 
 // ---------------------------------------------------------------- utility
@@ -2314,6 +2504,41 @@ hipError_t launch_batch_sweep(const BatchArgs &a, const BatchPart *parts, int n_
 hipError_t launch_batch_sample(const BatchArgs &a, int job0, int jobs, hipStream_t st) {
     if (jobs < 1) return hipErrorInvalidValue;
     batch_sample<<<unsigned(jobs), kBlock, 0, st>>>(a, job0);
+    return hipGetLastError();
+}
+
+hipError_t launch_traj_resident(const TrajResidentArgs &a, int jobs, hipStream_t st) {
+    if (a.n < 1 || a.n > kBatchLdsQubits || jobs < 1) return hipErrorInvalidValue;
+    const size_t most = sizeof(float2) * ((size_t(1) << kBatchLdsQubits) + 1792);
+    static const hipError_t attr256 = hipFuncSetAttribute(reinterpret_cast<const void *>(&run_resident<256, 9, 10>),
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, int(most));
+    static const hipError_t attr512 = hipFuncSetAttribute(reinterpret_cast<const void *>(&run_resident<512, 10, 11>),
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, int(most));
+    if (attr256 != hipSuccess) return attr256;
+    if (attr512 != hipSuccess) return attr512;
+    const size_t lds = sizeof(float2) * ((size_t(1) << a.n) + 1792);
+    // below 11 qubits eight wavefronts have no 16-group batch of a 4-qubit block each
+    if (a.n <= 10) run_resident<256, 9, 10><<<unsigned(jobs), 256, lds, st>>>(a);
+    else run_resident<512, 10, 11><<<unsigned(jobs), 512, lds, st>>>(a);
+    return hipGetLastError();
+}
+
+int traj_sweep_records(int n) { return 1 << (n - kBatchTileBits); }
+
+hipError_t launch_traj_sweep(const TrajSweep *sweeps, const TrajGate *gates, int n, int count, hipStream_t st) {
+    const size_t lds = sizeof(float2) * size_t(tile_mat_budget(kBatchTileBits));
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&traj_sweep),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (attr != hipSuccess) return attr;
+    if (n <= kBatchTileBits || n > 31 || count < 1 || count > 65535) return hipErrorInvalidValue;
+    const unsigned tiles = 1u << (n - kBatchTileBits);
+    traj_sweep<<<dim3(tiles, unsigned(count)), kBatchWideThreads, lds, st>>>(sweeps, gates, tiles);
+    return hipGetLastError();
+}
+
+hipError_t launch_traj_select(const TrajSelect *sels, int count, hipStream_t st) {
+    if (count < 1) return hipErrorInvalidValue;
+    traj_select<<<unsigned(count), 64, 0, st>>>(sels);
     return hipGetLastError();
 }
 

@@ -88,6 +88,8 @@ struct qs_state_s {
     std::vector<PendingOp> pending;
     bool poisoned = false;
     // trajectory-driver buffers kept across calls (allocated on first use)
+    float2 *side_buf = nullptr;      // states beside this one, and sweep records
+    size_t side_cap = 0;             // bytes
     int *sel_choice_dev = nullptr;   // device-side picks [kChoiceCap] + error flag
     int *sel_choice_host = nullptr;  // pinned mirror
     double *sel_rdm = nullptr;       // the pending channel's reduced density matrix
@@ -613,6 +615,7 @@ qs_status qs_destroy_state(qs_state s) {
         (void)hipHostFree(s->arena_host);
         for (int i = 0; i < 2; ++i) (void)hipEventDestroy(s->arena_ev[i]);
     }
+    if (s->side_buf) (void)hipFree(s->side_buf);
     if (s->sel_choice_dev) (void)hipFree(s->sel_choice_dev);
     if (s->sel_choice_host) (void)hipHostFree(s->sel_choice_host);
     if (s->sel_rdm) (void)hipFree(s->sel_rdm);
@@ -1302,6 +1305,126 @@ void segment_insert(const SegKey &k, const std::vector<qs::Sweep> &sw) {
     g_seg_fifo.push_back(k);
 }
 
+// Host worker threads for the planners' parallel loops, started on
+// first use and kept: starting threads on every call cost more than the
+// per-trajectory draws they share.  One loop runs at a time; the calling
+// thread takes part in it.
+class HostPool {
+  public:
+    static HostPool &get() {
+        static HostPool *pool = new HostPool();  // never destroyed: workers may outlive statics
+        return *pool;
+    }
+    unsigned size() const { return unsigned(workers_.size()) + 1; }
+    // fn(lo, hi) over [0, n) in chunks of `chunk`, on at most `width` threads.
+    void run(size_t n, size_t chunk, unsigned width, const std::function<void(size_t, size_t)> &fn) {
+        if (n == 0) return;
+        chunk = std::max<size_t>(chunk, 1);
+        width = std::max(1u, std::min(width, size()));
+        if (width == 1 || n <= chunk) {
+            fn(0, n);
+            return;
+        }
+        std::lock_guard<std::mutex> one(run_mu_);
+        {
+            std::lock_guard<std::mutex> lock(mu_);
+            fn_ = &fn;
+            n_ = n;
+            chunk_ = chunk;
+            next_.store(0);
+            helpers_ = width - 1;
+            busy_ = 0;
+            ++generation_;
+        }
+        cv_.notify_all();
+        drain();
+        // helpers that have not started by now stay out of this loop
+        std::unique_lock<std::mutex> lock(mu_);
+        helpers_ = 0;
+        done_cv_.wait(lock, [&] { return busy_ == 0; });
+        fn_ = nullptr;
+    }
+
+  private:
+    HostPool() {
+        const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
+        const unsigned nw = std::min(15u, hw > 1 ? hw - 1 : 0u);
+        for (unsigned i = 0; i < nw; ++i) workers_.emplace_back([this] { loop(); });
+        for (auto &w : workers_) w.detach();
+    }
+    void drain() {
+        for (;;) {
+            const size_t lo = next_.fetch_add(chunk_);
+            if (lo >= n_) return;
+            (*fn_)(lo, std::min(n_, lo + chunk_));
+        }
+    }
+    void loop() {
+        uint64_t seen = 0;
+        for (;;) {
+            {
+                std::unique_lock<std::mutex> lock(mu_);
+                cv_.wait(lock, [&] { return generation_ != seen && helpers_ > 0; });
+                seen = generation_;
+                --helpers_;
+                ++busy_;
+            }
+            drain();
+            {
+                std::lock_guard<std::mutex> lock(mu_);
+                --busy_;
+            }
+            done_cv_.notify_all();
+        }
+    }
+    std::vector<std::thread> workers_;
+    std::mutex run_mu_, mu_;
+    std::condition_variable cv_, done_cv_;
+    const std::function<void(size_t, size_t)> *fn_ = nullptr;
+    size_t n_ = 0, chunk_ = 1;
+    std::atomic<size_t> next_{0};
+    unsigned helpers_ = 0, busy_ = 0;
+    uint64_t generation_ = 0;
+};
+
+// A trajectory's program for the launches that run several side by side: the
+// blocks in launch order, cut into sweeps (n > kBatchLdsQubits) and with a
+// selection per inner-product channel.  Offsets are float2 in `mats`.
+struct TrajPlan {
+    struct Gate {
+        int k = 0;
+        int t[5] = {};                  // ascending index bits
+        const float2 *dev = nullptr;    // default matrix, else `off`
+        size_t off = 0;
+        int sel = -1;                   // the matrix is this selection's outcome
+        int before = -1;                // a selection made in front of this block
+    };
+    struct Cut {
+        int pos[qs::kMaxTileBits] = {};
+        int g0 = 0, g1 = 0;
+        int sel = -1, rdm_q = -1;       // the selection after this sweep, and its qubit
+    };
+    struct Select {
+        int channel = 0;
+        double resid = 0.0;
+        size_t cand = 0;                // nk x Db x Db complex128
+        size_t dst = 0;                 // Db x Db float2 (sweeps)
+        int Db = 0;
+    };
+    bool ok = false;                    // false: the one-by-one path runs it
+    int sweeps = 0;                     // sweeps with gates, as the one-by-one path counts them
+    std::vector<Gate> gates;
+    std::vector<Cut> cuts;
+    std::vector<Select> sels;
+    std::vector<float2> mats;
+};
+
+// Side by side, trajectories of n > kBatchLdsQubits share sweep launches of up
+// to this many 2^13-amplitude tiles (64 MiB of states; 512 workgroups are
+// resident at once).  From 22 qubits on one trajectory fills the GPU.
+constexpr int kSideTiles = 1024;
+constexpr int kSideMaxQubits = 21;
+
 struct Runner {
     qs_state s;
     const CircuitModel &m;
@@ -1336,7 +1459,7 @@ struct Runner {
         const TileLayout *L;
         std::vector<std::array<int, 3>> members;  // block, first op index, end op index
     };
-    std::deque<TileLayout> seg_layouts;
+    std::deque<TileLayout> run_layouts;  // those of run_delayed's segments
     // naive mode: gate blocks per inter-channel segment
     std::vector<std::vector<BlockDesc>> naive_segments;
     std::vector<cd> tmp;
@@ -1616,7 +1739,7 @@ struct Runner {
         pending_reset = true;
         log_norm_bound = 0.0;
         std::vector<SegSweep> seg;
-        segment_sweeps(0, int(m.ops.size()), true, seg);
+        segment_sweeps(0, int(m.ops.size()), true, run_layouts, seg);
         std::vector<Unit> units;
         for (const SegSweep &ss : seg) {
             Unit u{ss.L, {}};
@@ -1664,7 +1787,8 @@ struct Runner {
     // restricted to the segment, regrouped into sweeps of their own (reusing
     // the whole-circuit sweeps would launch every sweep that straddles the
     // split twice: ~6 extra sweeps per split on a 24-qubit grid).
-    void segment_sweeps(int seg_start, int seg_end, bool whole_plan, std::vector<SegSweep> &out) {
+    void segment_sweeps(int seg_start, int seg_end, bool whole_plan, std::deque<TileLayout> &seg_layouts,
+                        std::vector<SegSweep> &out) const {
         out.clear();
         if (whole_plan) {
             for (size_t u = 0; u < sweeps.size(); ++u) {
@@ -1961,7 +2085,7 @@ struct Runner {
         graph_failed = true;
         if (!s->st) return QS_OK;  // replays on the null stream are left out
         std::vector<SegSweep> seg;
-        segment_sweeps(0, int(m.ops.size()), true, seg);
+        segment_sweeps(0, int(m.ops.size()), true, run_layouts, seg);
         std::vector<Unit> units;
         for (const SegSweep &ss : seg) {
             if (!ss.L->tiled) return QS_OK;  // only tile sweeps are captured
@@ -2120,6 +2244,514 @@ struct Runner {
         return QS_OK;
     }
 
+    // Candidate i = (the block's later operations, fused once) x K_i on the
+    // channel's qubits: the block begins with the channel, so each candidate
+    // costs 2 Db^2 Dc multiply-adds instead of a fusion of its own.
+    void fill_candidates(const ChannelInfo &ci, int kb, const int *q, const std::vector<int> &later,
+                         const std::vector<const cd *> &mats, std::vector<cd> &work, double *out) const {
+        const int Dc = 1 << ci.k, Db = 1 << kb;
+        work.resize(size_t(Db) * Db);  // fused_matrix writes Db x Db entries
+        qs::fused_matrix(kb, q, later, m.ops, mats, work.data());
+        int cpos[2] = {0, 0};
+        int cmask = 0;
+        for (int j = 0; j < ci.k; ++j) {
+            cpos[j] = int(std::find(q, q + kb, ci.t[j]) - q);
+            cmask |= 1 << cpos[j];
+        }
+        auto spread = [&](int jx) {
+            int x = 0;
+            for (int j = 0; j < ci.k; ++j)
+                if ((jx >> j) & 1) x |= 1 << cpos[j];
+            return x;
+        };
+        for (int i = 0; i < ci.nk; ++i) {
+            const cd *K = ci.kraus + size_t(i) * Dc * Dc;
+            double *o = out + 2 * size_t(i) * Db * Db;
+            for (int c = 0; c < Db; ++c) {
+                int jc = 0;
+                for (int j = 0; j < ci.k; ++j) jc |= ((c >> cpos[j]) & 1) << j;
+                const int base = c & ~cmask;
+                for (int r = 0; r < Db; ++r) {
+                    cd acc = 0.0;
+                    for (int jx = 0; jx < Dc; ++jx)
+                        acc += work[size_t(r) * Db + (base | spread(jx))] * K[jx * Dc + jc];
+                    o[2 * (size_t(r) * Db + c)] = acc.real();
+                    o[2 * (size_t(r) * Db + c) + 1] = acc.imag();
+                }
+            }
+        }
+    }
+
+    // ---- trajectories side by side
+
+    bool resident() const { return m.n <= qs::kBatchLdsQubits; }
+
+    // Whether the call's trajectories may run side by side: the delayed
+    // scheme without kernel timing or graph replay, the default tile width,
+    // samples and Z records that fit their device buffers at once, and, for
+    // sweeps, one-qubit inner-product channels and blocks of at most four
+    // qubits (what the sweep that forms a reduced density matrix takes).
+    bool side_by_side() const {
+        if (p.mode != QS_KRAUS_DELAYED || timing || graph_wanted || tuning || p.n_traj < 1) return false;
+        if (p.tile_bits != 0 && p.tile_bits != qs::kDefaultTileBits) return false;
+        if (p.n_traj * int64_t(std::max(p.n_samples, 0)) > int64_t(s->samp_cap) && p.n_samples > 0) return false;
+        if (res.z_expect && p.n_traj > int64_t(s->z_cap)) return false;
+        if (resident()) return true;
+        if (m.n > kSideMaxQubits || p.n_traj < 2) return false;
+        for (const ChannelInfo &c : m.channels)
+            if (!c.mixture && c.k != 1) return false;
+        for (const qs::Block &b : blocks)
+            if (b.k > 4) return false;
+        return true;
+    }
+
+    // Program of one trajectory (any host thread): as run_delayed, without
+    // launching anything.  A trajectory whose norm bound would call for a
+    // renormalisation in between is left to run_delayed.
+    void plan_trajectory(int64_t rel, uint32_t traj, TrajPlan &P) const {
+        P = TrajPlan();
+        const int nch = int(m.channels.size());
+        const int n_ops = int(m.ops.size());
+        std::vector<int> pick(nch, -1), slow;  // slow: channel indices
+        std::vector<double> resid(nch, 0.0);
+        std::vector<const cd *> mats = default_mats;
+        std::vector<char> dirty(blocks.size(), 0);
+        for (int c = 0; c < nch; ++c) {
+            const ChannelInfo &ci = m.channels[c];
+            const double r = qs::philox_uniform(p.seed, channel_draw_index(uint32_t(c)), traj, p.circuit_id,
+                                                qs::kStreamChannel);
+            pick[c] = select_fast(ci, r, &resid[c]);
+            if (pick[c] < 0) {
+                slow.push_back(c);
+            } else if (pick[c] != ci.default_pick) {
+                mats[ci.op] = fast_pick_matrix(ci, pick[c]);
+                dirty[op_block[ci.op]] = 1;
+            }
+        }
+        int8_t *choices = res.kraus_choices ? res.kraus_choices + rel * nch : nullptr;
+        int8_t *paths = res.kraus_paths ? res.kraus_paths + rel * nch : nullptr;
+        for (int c = 0; c < nch; ++c) {
+            if (choices) choices[c] = int8_t(pick[c]);
+            if (paths) paths[c] = pick[c] < 0 ? 1 : 0;
+        }
+        if (res.n_slow) res.n_slow[rel] = int32_t(slow.size());
+
+        std::vector<SegSweep> seg;
+        std::deque<TileLayout> store;
+        std::vector<int> sub, later;
+        std::vector<cd> work;
+        BlockDesc bd;
+        double norm_bound = 0.0;
+        int seg_start = 0, pending = -1;  // pending: the selection whose block is to come
+        int unmade = -1;                  // the selection the next block follows
+        auto push = [&](TrajPlan::Gate &g) {
+            g.before = unmade;
+            unmade = -1;
+            P.gates.push_back(g);
+        };
+        auto reserve = [&](size_t f2) {
+            const size_t at = P.mats.size();
+            P.mats.resize(at + ((f2 + 3) & ~size_t(3)));
+            return at;
+        };
+        for (size_t si = 0;; ++si) {
+            const int seg_end = si < slow.size() ? m.channels[slow[si]].op : n_ops;
+            // the one-by-one path's order of the blocks (a resident state too:
+            // the same trajectory rounds alike whichever way it runs)
+            segment_sweeps(seg_start, seg_end, slow.empty(), store, seg);
+            for (const SegSweep &ss : seg) {
+                const size_t g0 = P.gates.size();
+                double lb = 0.0;
+                for (const auto &mem : ss.members) {
+                    const int b = mem[0];
+                    const auto &ops = blocks[b].ops;
+                    const bool whole = mem[1] == 0 && mem[2] == int(ops.size());
+                    TrajPlan::Gate g;
+                    if (whole && !dirty[b]) {
+                        if (block_desc[b].identity) continue;
+                        g.k = block_desc[b].g.k;
+                        for (int j = 0; j < 5; ++j) g.t[j] = block_desc[b].g.t[j];
+                        g.dev = block_desc[b].dev;
+                        lb += block_desc[b].log_bound;
+                        push(g);
+                        continue;
+                    }
+                    sub.assign(ops.begin() + mem[1], ops.begin() + mem[2]);
+                    if (pending >= 0 && m.channels[P.sels[pending].channel].op == sub[0]) {
+                        TrajPlan::Select &S = P.sels[pending];
+                        const ChannelInfo &ci = m.channels[S.channel];
+                        int q[5] = {};
+                        const int kb = qs::union_qubits(sub, m.ops, q);
+                        if (kb > 4) return;
+                        S.Db = 1 << kb;
+                        later.assign(sub.begin() + 1, sub.end());
+                        S.cand = reserve(size_t(ci.nk) * S.Db * S.Db * 2);
+                        fill_candidates(ci, kb, q, later, mats, work, reinterpret_cast<double *>(&P.mats[S.cand]));
+                        mats[ci.op] = ci.kraus + size_t(ci.nk - 1) * (size_t(1) << (2 * ci.k));
+                        if (!resident()) S.dst = reserve(size_t(S.Db) * S.Db);
+                        g.k = kb;
+                        for (int j = 0; j < 5; ++j) g.t[j] = j < kb ? q[j] : 0;
+                        g.sel = pending;
+                        pending = -1;
+                        push(g);
+                        continue;
+                    }
+                    build_block(m, sub, mats, work, bd);
+                    if (bd.identity) continue;
+                    for (int o : sub) {
+                        const int c = m.channel_of_op[o];
+                        lb += c < 0 ? m.gate_log_bound[o] : (pick[c] >= 0 ? m.channels[c].log_pbar[pick[c]] : 0.0);
+                    }
+                    g.k = bd.g.k;
+                    for (int j = 0; j < 5; ++j) g.t[j] = bd.g.t[j];
+                    const size_t dd = size_t(1) << (2 * g.k);
+                    g.off = reserve(dd);
+                    std::memcpy(&P.mats[g.off], bd.g.m, sizeof(float2) * dd);
+                    push(g);
+                }
+                norm_bound += lb;
+                if (norm_bound < kRenormLogThreshold) return;
+                if (P.gates.size() == g0) continue;
+                ++P.sweeps;
+                if (resident()) continue;
+                TrajPlan::Cut c;
+                c.g0 = int(g0);
+                c.g1 = int(P.gates.size());
+                set_tile(P, c, -1);
+                P.cuts.push_back(c);
+            }
+            if (si == slow.size()) break;
+            // the channel at seg_end: its qubit in the last sweep's tile, or in
+            // a sweep without gates that only forms the density matrix
+            TrajPlan::Select S;
+            S.channel = slow[si];
+            S.resid = resid[slow[si]];
+            pending = unmade = int(P.sels.size());
+            P.sels.push_back(S);
+            if (!resident()) {
+                const int q = m.channels[S.channel].t[0];
+                if (P.cuts.empty() || P.cuts.back().sel >= 0 || !set_tile(P, P.cuts.back(), q)) {
+                    TrajPlan::Cut c;
+                    c.g0 = c.g1 = int(P.gates.size());
+                    set_tile(P, c, q);
+                    P.cuts.push_back(c);
+                }
+                P.cuts.back().sel = pending;
+                P.cuts.back().rdm_q = q;
+            }
+            dirty[op_block[seg_end]] = 1;
+            norm_bound = 0.0;  // renormalised by the folded 1/sqrt(p N)
+            seg_start = seg_end;
+        }
+        if (!resident() && P.cuts.empty()) {  // no operation left: a sweep that writes |0...0>
+            TrajPlan::Cut c;
+            set_tile(P, c, -1);
+            P.cuts.push_back(c);
+        }
+        P.ok = true;
+    }
+
+    // The tile of a side-by-side sweep: its gates' bits, then `extra` (>= 0),
+    // then the lowest others.  Returns whether it holds `extra`.
+    bool set_tile(const TrajPlan &P, TrajPlan::Cut &c, int extra) const {
+        std::array<char, qs::kMaxQubits> in{};
+        int cnt = 0;
+        auto take = [&](int q) {
+            if (cnt < qs::kBatchTileBits && !in[size_t(q)]) {
+                in[size_t(q)] = 1;
+                ++cnt;
+            }
+        };
+        for (int q = 0; q < qs::kTileLowBits; ++q) take(q);
+        for (int g = c.g0; g < c.g1; ++g)
+            for (int j = 0; j < P.gates[size_t(g)].k; ++j) take(P.gates[size_t(g)].t[j]);
+        if (extra >= 0) take(extra);
+        for (int q = 0; q < m.n; ++q) take(q);
+        int i = 0;
+        for (int q = 0; q < m.n; ++q)
+            if (in[size_t(q)]) c.pos[i++] = q;
+        return extra < 0 || in[size_t(extra)];
+    }
+
+    // Workspace of the side-by-side sweeps: the states beside the caller's
+    // and the workgroup records; false when there is no room for it.
+    bool ensure_side(int slots, bool all_states) {
+        const size_t dim = size_t(1) << m.n;
+        const size_t states = (all_states ? size_t(slots) : size_t(slots) - 1) * dim * sizeof(float2);
+        const size_t rec = resident() ? 0 : size_t(slots) * size_t(qs::traj_sweep_records(m.n)) * 8 * sizeof(double);
+        if (states + rec <= s->side_cap) return true;
+        if (s->side_buf) {
+            if (hipStreamSynchronize(s->st) != hipSuccess) return false;
+            (void)hipFree(s->side_buf);
+        }
+        s->side_buf = nullptr;
+        s->side_cap = 0;
+        if (hipMalloc(&s->side_buf, states + rec) != hipSuccess) {
+            (void)hipGetLastError();
+            s->side_buf = nullptr;
+            return false;
+        }
+        s->side_cap = states + rec;
+        return true;
+    }
+
+    // What a finished trajectory leaves: samples and a Z record in their
+    // places in the call's buffers.
+    qs_status finish_side(int64_t rel, float2 *amp) {
+        const uint32_t traj = uint32_t(p.traj_offset + rel);
+        if (p.n_samples > 0) {
+            QS_HIP(s, qs::launch_sample(amp, s->n, s->samp_sums, s->samp_incl, p.seed, traj, p.circuit_id,
+                                        p.n_samples, ro, s->samp_out + rel * p.n_samples, s->samp_norm, s->st));
+            res.sweeps += 1;
+        }
+        if (res.z_expect) {
+            QS_HIP(s, qs::launch_zweights(amp, s->n, s->red_partials, s->z_dev + size_t(rel) * qs::kZRecord, s->st));
+            res.sweeps += 1;
+        }
+        return QS_OK;
+    }
+
+    static size_t f2_of(size_t bytes) { return (bytes + 255) / 256 * 32; }
+
+    size_t program_f2(const TrajPlan &P) const {
+        return f2_of(P.mats.size() * sizeof(float2)) + f2_of(P.gates.size() * sizeof(qs::TrajGate)) +
+               f2_of(P.cuts.size() * sizeof(qs::TrajSweep)) + f2_of(P.sels.size() * sizeof(qs::TrajSelect)) +
+               f2_of(sizeof(qs::TrajJob)) + 64;
+    }
+
+    // Launches trajectories [first, first + plans.size()) of the call from
+    // their programs, staged in the arena with one copy.
+    qs_status launch_side(int64_t first, const TrajPlan *plans, const std::vector<int> &which, int slots) {
+        const size_t n_traj = which.size();
+        size_t mats = 0, n_gates = 0, n_cuts = 0, n_sels = 0;
+        for (int w : which) {
+            mats += plans[w].mats.size();
+            n_gates += plans[w].gates.size();
+            n_cuts += plans[w].cuts.size();
+            n_sels += plans[w].sels.size();
+        }
+        if (choice_owner.size() + n_sels > size_t(kChoiceCap)) QS_CHECK(drain_choices());
+        const size_t f_gate = f2_of(n_gates * sizeof(qs::TrajGate)), f_sel = f2_of(n_sels * sizeof(qs::TrajSelect)),
+                     f_cut = f2_of(n_cuts * sizeof(qs::TrajSweep)), f_job = f2_of(n_traj * sizeof(qs::TrajJob));
+        float2 *h = nullptr;
+        const float2 *d = nullptr;
+        QS_CHECK(arena_stage(s, f2_of(mats * sizeof(float2)) + f_gate + f_sel + f_cut + f_job, &h, &d));
+        const size_t o_gate = f2_of(mats * sizeof(float2)), o_sel = o_gate + f_gate, o_cut = o_sel + f_sel,
+                     o_job = o_cut + f_cut;
+        auto *gates = reinterpret_cast<qs::TrajGate *>(h + o_gate);
+        auto *sels = reinterpret_cast<qs::TrajSelect *>(h + o_sel);
+        auto *cuts = reinterpret_cast<qs::TrajSweep *>(h + o_cut);
+        auto *jobs = reinterpret_cast<qs::TrajJob *>(h + o_job);
+        const bool keep = p.n_samples > 0 || res.z_expect;
+        const size_t dim = size_t(1) << m.n;
+        const int64_t last = p.n_traj - 1;
+        // matrices, gates and selections trajectory by trajectory
+        std::vector<size_t> mat0(n_traj), gate0(n_traj), sel0(n_traj);
+        size_t mo = 0, go = 0, so = 0;
+        for (size_t i = 0; i < n_traj; ++i) {
+            const TrajPlan &P = plans[which[i]];
+            res.sweeps += P.sweeps;
+            res.gate_sweeps += P.sweeps;
+            if (P.sweeps > 0) res.zero_start_sweeps++;
+            mat0[i] = mo;
+            gate0[i] = go;
+            sel0[i] = so;
+            if (!P.mats.empty()) std::memcpy(h + mo, P.mats.data(), sizeof(float2) * P.mats.size());
+            mo += P.mats.size();
+            so += P.sels.size();
+            auto emit = [&](const TrajPlan::Gate &g, const int *pos, int &lofs) {
+                int lt[qs::kMaxGateQubits];
+                for (int j = 0; j < g.k; ++j)
+                    lt[j] = pos ? int(std::find(pos, pos + qs::kBatchTileBits, g.t[j]) - pos) : g.t[j];
+                qs::TrajGate &G = gates[go++];
+                G.g = qs::batch_tile_gate(g.k, lt, lofs);
+                lofs += qs::tile_mat_slots(g.k);
+                if (g.sel >= 0) G.g.head |= qs::kSelectedGate;
+                G.sel = g.before >= 0 ? int(sel0[i]) + g.before : -1;
+                G.m = g.dev ? g.dev : d + mat0[i] + (g.sel >= 0 ? P.sels[size_t(g.sel)].dst : g.off);
+                res.gate_k_launches[g.k]++;
+            };
+            if (resident()) {
+                int lofs = 0;
+                for (const auto &g : P.gates) emit(g, nullptr, lofs);
+            } else {
+                for (const auto &c : P.cuts) {
+                    int lofs = 0;
+                    for (int g = c.g0; g < c.g1; ++g) emit(P.gates[size_t(g)], c.pos, lofs);
+                }
+            }
+        }
+        auto fill_select = [&](qs::TrajSelect &D, size_t i, size_t si, const double *records) {
+            const TrajPlan &P = plans[which[i]];
+            const TrajPlan::Select &S = P.sels[si];
+            const ChannelInfo &ci = m.channels[S.channel];
+            D.excess = chan_excess[S.channel];
+            D.pbar = chan_pbar[S.channel];
+            D.cand = reinterpret_cast<const double *>(d + mat0[i] + S.cand);
+            D.dst = const_cast<float2 *>(d + mat0[i] + S.dst);
+            D.records = records;
+            D.choice = dev_choice + choice_owner.size();
+            D.err = dev_choice + kChoiceCap;
+            D.resid = S.resid;
+            D.nk = ci.nk;
+            D.k = ci.k;
+            D.Db = S.Db;
+            D.n_records = resident() ? 0 : qs::traj_sweep_records(m.n);
+            for (int j = 0; j < 2; ++j) D.t[j] = j < ci.k ? ci.ts[j] : 0;
+            choice_owner.emplace_back(first + which[i], S.channel);
+        };
+        float2 *side = s->side_buf;
+        if (resident()) {
+            for (size_t i = 0; i < n_traj; ++i) {
+                const TrajPlan &P = plans[which[i]];
+                const bool is_last = first + which[i] == last;
+                jobs[i].g0 = int(gate0[i]);
+                jobs[i].n_gates = int(P.gates.size());
+                jobs[i].out = is_last ? s->amp : (keep ? side + size_t(i) * dim : nullptr);
+                for (size_t si = 0; si < P.sels.size(); ++si) fill_select(sels[sel0[i] + si], i, si, nullptr);
+            }
+            QS_CHECK(arena_commit(s));
+            qs::TrajResidentArgs A;
+            A.jobs = reinterpret_cast<const qs::TrajJob *>(d + o_job);
+            A.gates = reinterpret_cast<const qs::TrajGate *>(d + o_gate);
+            A.sels = reinterpret_cast<const qs::TrajSelect *>(d + o_sel);
+            A.n = m.n;
+            QS_HIP(s, qs::launch_traj_resident(A, int(n_traj), s->st));
+            if (keep)
+                for (size_t i = 0; i < n_traj; ++i)
+                    QS_CHECK(finish_side(first + which[i], first + which[i] == last ? s->amp : side + i * dim));
+            return QS_OK;
+        }
+        // each state runs a queue of trajectories; the call's last one ends
+        // the queue of the caller's state (state 0)
+        std::vector<std::vector<size_t>> queue(static_cast<size_t>(slots));
+        {
+            std::vector<size_t> load(size_t(slots), 0);
+            size_t n_free = n_traj;
+            const bool has_last = first + which[n_traj - 1] == last;
+            if (has_last) {
+                --n_free;
+                load[0] = plans[which[n_free]].cuts.size();
+            }
+            for (size_t i = 0; i < n_free; ++i) {
+                const size_t q = size_t(std::min_element(load.begin(), load.end()) - load.begin());
+                load[q] += plans[which[i]].cuts.size();
+                queue[q].push_back(i);
+            }
+            if (has_last) queue[0].push_back(n_free);
+        }
+        const size_t rec_len = size_t(qs::traj_sweep_records(m.n)) * 8;
+        double *records = reinterpret_cast<double *>(side + size_t(slots - 1) * dim);
+        struct Step {
+            size_t c0, c1, s0, s1;
+            std::vector<std::pair<size_t, size_t>> ends;  // (trajectory, state)
+        };
+        std::vector<Step> steps;
+        std::vector<size_t> qi(size_t(slots), 0), ci(size_t(slots), 0);
+        size_t co = 0;
+        so = 0;
+        for (;;) {
+            Step st{co, co, so, so, {}};
+            for (size_t q = 0; q < size_t(slots); ++q) {
+                if (qi[q] >= queue[q].size()) continue;
+                const size_t i = queue[q][qi[q]];
+                const TrajPlan &P = plans[which[i]];
+                const TrajPlan::Cut &c = P.cuts[ci[q]];
+                qs::TrajSweep &D = cuts[co++];
+                D.amp = q == 0 ? s->amp : side + (q - 1) * dim;
+                D.rdm_out = c.sel >= 0 ? records + q * rec_len : nullptr;
+                for (int b = 0; b < qs::kMaxTileBits; ++b) D.pos[b] = c.pos[b];
+                D.g0 = int(gate0[i]) + c.g0;
+                D.n_gates = c.g1 - c.g0;
+                D.init_zero = ci[q] == 0 ? 1 : 0;
+                D.rdm_lt = c.sel >= 0 ? int(std::find(c.pos, c.pos + qs::kBatchTileBits, c.rdm_q) - c.pos) : 0;
+                if (c.sel >= 0) fill_select(sels[so++], i, size_t(c.sel), records + q * rec_len);
+                if (++ci[q] == P.cuts.size()) {
+                    st.ends.emplace_back(i, q);
+                    ci[q] = 0;
+                    ++qi[q];
+                }
+            }
+            if (co == st.c0) break;
+            st.c1 = co;
+            st.s1 = so;
+            steps.push_back(std::move(st));
+        }
+        QS_CHECK(arena_commit(s));
+        const auto *dcuts = reinterpret_cast<const qs::TrajSweep *>(d + o_cut);
+        const auto *dgates = reinterpret_cast<const qs::TrajGate *>(d + o_gate);
+        const auto *dsels = reinterpret_cast<const qs::TrajSelect *>(d + o_sel);
+        for (const Step &st : steps) {
+            QS_HIP(s, qs::launch_traj_sweep(dcuts + st.c0, dgates, m.n, int(st.c1 - st.c0), s->st));
+            if (st.s1 > st.s0) QS_HIP(s, qs::launch_traj_select(dsels + st.s0, int(st.s1 - st.s0), s->st));
+            for (const auto &e : st.ends) {
+                QS_CHECK(finish_side(first + which[e.first], e.second == 0 ? s->amp : side + (e.second - 1) * dim));
+            }
+        }
+        return QS_OK;
+    }
+
+    // The call's trajectories side by side; *done stays false when there is
+    // no room for the workspace.
+    qs_status run_side_by_side(bool *done) {
+        const bool keep = p.n_samples > 0 || res.z_expect;
+        const int slots =
+            resident() ? 256
+                       : int(std::min<int64_t>(std::max(kSideTiles >> (m.n - qs::kBatchTileBits), 2),
+                                               std::min<int64_t>(p.n_traj, 64)));
+        if (resident() ? keep && !ensure_side(int(std::min<int64_t>(slots, p.n_traj)), true)
+                       : !ensure_side(slots, false))
+            return QS_OK;
+        *done = true;
+        QS_CHECK(restore_home(s));
+        const int64_t chunk = resident() ? 256 : std::max<int64_t>(4 * slots, 32);
+        std::vector<TrajPlan> plans;
+        std::vector<int> which;
+        for (int64_t first = 0; first < p.n_traj; first += chunk) {
+            const int64_t count = std::min<int64_t>(chunk, p.n_traj - first);
+            plans.resize(size_t(count));
+            HostPool::get().run(size_t(count), 1, 16u, [&](size_t lo, size_t hi) {
+                for (size_t i = lo; i < hi; ++i)
+                    plan_trajectory(first + int64_t(i), uint32_t(p.traj_offset + first + int64_t(i)), plans[i]);
+            });
+            // the ones left to the one-by-one path, in the caller's state; the
+            // call's last trajectory stays last there
+            auto alone = [&](int64_t i) -> qs_status {
+                QS_CHECK(run_delayed(first + i, uint32_t(p.traj_offset + first + i)));
+                QS_CHECK(settle_reset());
+                return finish_side(first + i, s->amp);
+            };
+            auto fits = [&](int64_t i) { return plans[size_t(i)].ok && program_f2(plans[size_t(i)]) <= kArenaHalf / 2; };
+            for (int64_t i = 0; i < count; ++i)
+                if (!fits(i) && first + i != p.n_traj - 1) QS_CHECK(alone(i));
+            which.clear();
+            size_t f2 = 0;
+            for (int64_t i = 0; i < count; ++i) {
+                if (!fits(i)) continue;
+                const size_t need = program_f2(plans[size_t(i)]);
+                if (!which.empty() && f2 + need > kArenaHalf) {
+                    QS_CHECK(launch_side(first, plans.data(), which, slots));
+                    which.clear();
+                    f2 = 0;
+                }
+                which.push_back(int(i));
+                f2 += need;
+            }
+            if (!which.empty()) QS_CHECK(launch_side(first, plans.data(), which, slots));
+            if (first + count == p.n_traj && !fits(count - 1)) QS_CHECK(alone(count - 1));
+        }
+        pending_reset = false;
+        if (p.n_samples > 0) {
+            sample_first_traj = 0;
+            sample_fill = p.n_traj * p.n_samples;
+        }
+        if (res.z_expect) {
+            z_first_traj = 0;
+            z_fill = p.n_traj;
+        }
+        return QS_OK;
+    }
+
     qs_status run_delayed(int64_t rel, uint32_t traj) {
         const int nch = int(m.channels.size());
         // steps 1-11 of Algorithm 2 for every channel: state-independent
@@ -2170,12 +2802,12 @@ struct Runner {
         std::deque<BlockDesc> dyn;
         std::vector<Unit> units;
         std::vector<SegSweep> seg;
-        seg_layouts.clear();
+        run_layouts.clear();
         for (;;) {
             const int seg_end = slow_idx < int(slow_ops.size()) ? slow_ops[slow_idx] : n_ops;
             dyn.clear();
             units.clear();
-            segment_sweeps(seg_start, seg_end, slow_ops.empty(), seg);
+            segment_sweeps(seg_start, seg_end, slow_ops.empty(), run_layouts, seg);
             for (const SegSweep &ss : seg) {
                 Unit unit{ss.L, {}};
                 for (const auto &mem : ss.members) {
@@ -2208,41 +2840,8 @@ struct Runner {
                         const float2 *dc = nullptr;
                         QS_CHECK(arena_stage(s, cand_f2, &hc, &dc));
                         double *hcd = reinterpret_cast<double *>(hc);
-                        // candidate i = (the block's later operations, fused
-                        // once) x K_i on the channel's qubits: the block begins
-                        // with the channel, so each candidate costs 2 Db^2 Dc
-                        // multiply-adds instead of a fusion of its own
-                        tmp.resize(size_t(Db) * Db);  // fused_matrix writes Db x Db entries
                         rest_ops.assign(sub.begin() + 1, sub.end());
-                        qs::fused_matrix(kb, q, rest_ops, m.ops, mats, tmp.data());
-                        int cpos[2] = {0, 0};
-                        int cmask = 0;
-                        for (int j = 0; j < ci.k; ++j) {
-                            cpos[j] = int(std::find(q, q + kb, ci.t[j]) - q);
-                            cmask |= 1 << cpos[j];
-                        }
-                        auto spread = [&](int jx) {
-                            int x = 0;
-                            for (int j = 0; j < ci.k; ++j)
-                                if ((jx >> j) & 1) x |= 1 << cpos[j];
-                            return x;
-                        };
-                        for (int i = 0; i < ci.nk; ++i) {
-                            const cd *K = ci.kraus + size_t(i) * Dc * Dc;
-                            double *out = hcd + 2 * size_t(i) * Db * Db;
-                            for (int c = 0; c < Db; ++c) {
-                                int jc = 0;
-                                for (int j = 0; j < ci.k; ++j) jc |= ((c >> cpos[j]) & 1) << j;
-                                const int base = c & ~cmask;
-                                for (int r = 0; r < Db; ++r) {
-                                    cd acc = 0.0;
-                                    for (int jx = 0; jx < Dc; ++jx)
-                                        acc += tmp[size_t(r) * Db + (base | spread(jx))] * K[jx * Dc + jc];
-                                    out[2 * (size_t(r) * Db + c)] = acc.real();
-                                    out[2 * (size_t(r) * Db + c) + 1] = acc.imag();
-                                }
-                            }
-                        }
+                        fill_candidates(ci, kb, q, rest_ops, mats, tmp, hcd);
                         mats[sel.op] = ci.kraus + size_t(ci.nk - 1) * Dc * Dc;
                         bd.g.k = kb;
                         for (int b2 = 0; b2 < 5; ++b2) bd.g.t[b2] = b2 < kb ? q[b2] : 0;
@@ -2394,7 +2993,9 @@ struct Runner {
         graph_wanted = p.mode == QS_KRAUS_DELAYED && (p.flags & QS_TRAJ_GRAPH) &&
                        !(p.flags & QS_TRAJ_NO_GRAPH) && !tuning &&
                        m.n <= kGraphMaxQubits && p.n_traj >= 2;
-        for (int64_t rel = 0; rel < p.n_traj; ++rel) {
+        bool side = false;
+        if (delayed && side_by_side()) QS_CHECK(run_side_by_side(&side));
+        for (int64_t rel = side ? p.n_traj : 0; rel < p.n_traj; ++rel) {
             const uint32_t traj = uint32_t(p.traj_offset + rel);
             if (delayed) QS_CHECK(run_delayed(rel, traj));
             else QS_CHECK(run_naive(rel, traj));
@@ -2931,88 +3532,6 @@ BatchBuffers &batch_buffers() {
 void to_float2(int D, const cd *m, float2 *out) {
     for (int i = 0; i < D * D; ++i) out[i] = make_float2(float(m[i].real()), float(m[i].imag()));
 }
-
-// Host worker threads for the batched planner's parallel loops, started on
-// first use and kept: starting threads on every call cost more than the
-// per-trajectory draws they share.  One loop runs at a time; the calling
-// thread takes part in it.
-class HostPool {
-  public:
-    static HostPool &get() {
-        static HostPool *pool = new HostPool();  // never destroyed: workers may outlive statics
-        return *pool;
-    }
-    unsigned size() const { return unsigned(workers_.size()) + 1; }
-    // fn(lo, hi) over [0, n) in chunks of `chunk`, on at most `width` threads.
-    void run(size_t n, size_t chunk, unsigned width, const std::function<void(size_t, size_t)> &fn) {
-        if (n == 0) return;
-        chunk = std::max<size_t>(chunk, 1);
-        width = std::max(1u, std::min(width, size()));
-        if (width == 1 || n <= chunk) {
-            fn(0, n);
-            return;
-        }
-        std::lock_guard<std::mutex> one(run_mu_);
-        {
-            std::lock_guard<std::mutex> lock(mu_);
-            fn_ = &fn;
-            n_ = n;
-            chunk_ = chunk;
-            next_.store(0);
-            helpers_ = width - 1;
-            busy_ = 0;
-            ++generation_;
-        }
-        cv_.notify_all();
-        drain();
-        // helpers that have not started by now stay out of this loop
-        std::unique_lock<std::mutex> lock(mu_);
-        helpers_ = 0;
-        done_cv_.wait(lock, [&] { return busy_ == 0; });
-        fn_ = nullptr;
-    }
-
-  private:
-    HostPool() {
-        const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
-        const unsigned nw = std::min(15u, hw > 1 ? hw - 1 : 0u);
-        for (unsigned i = 0; i < nw; ++i) workers_.emplace_back([this] { loop(); });
-        for (auto &w : workers_) w.detach();
-    }
-    void drain() {
-        for (;;) {
-            const size_t lo = next_.fetch_add(chunk_);
-            if (lo >= n_) return;
-            (*fn_)(lo, std::min(n_, lo + chunk_));
-        }
-    }
-    void loop() {
-        uint64_t seen = 0;
-        for (;;) {
-            {
-                std::unique_lock<std::mutex> lock(mu_);
-                cv_.wait(lock, [&] { return generation_ != seen && helpers_ > 0; });
-                seen = generation_;
-                --helpers_;
-                ++busy_;
-            }
-            drain();
-            {
-                std::lock_guard<std::mutex> lock(mu_);
-                --busy_;
-            }
-            done_cv_.notify_all();
-        }
-    }
-    std::vector<std::thread> workers_;
-    std::mutex run_mu_, mu_;
-    std::condition_variable cv_, done_cv_;
-    const std::function<void(size_t, size_t)> *fn_ = nullptr;
-    size_t n_ = 0, chunk_ = 1;
-    std::atomic<size_t> next_{0};
-    unsigned helpers_ = 0, busy_ = 0;
-    uint64_t generation_ = 0;
-};
 
 // The blocks in the order of `order`, cut into runs whose qubits fit a tile
 // and whose staged matrices fit its budget.

@@ -1,0 +1,72 @@
+"""Trajectories run side by side (resident states up to 13 qubits, shared
+sweep launches from 14) against the same trajectories one by one, which the
+driver does when it times its kernels."""
+
+import torch  # noqa: F401  (imported at collection: the first import can be slow)
+
+import numpy as np
+import pytest
+
+import workloads as W
+from gpu_helpers import AMP_TOL, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+def _circuit(n, depth, two_qubit):
+    """A noisy grid with mixtures and inner-product channels; with
+    `two_qubit`, damping on pairs as one two-qubit channel, too."""
+    c = W.generic_grid_circuit(n, depth, p_dep=0.02, gamma=0.01, seed=40 + n)
+    if not two_qubit:
+        return c
+    k = W.amplitude_damp(0.02)
+    pair = [np.kron(a, b) for a in k for b in k]
+    ops = []
+    for i, op in enumerate(c.ops):
+        ops.append(op)
+        if op.kind == W.GATE and len(op.qubits) == 2 and i % 3 == 0:
+            ops.append(W.Op(W.CHANNEL, tuple(reversed(op.qubits)), pair, op.moment, "pair_damp"))
+    return W.Circuit(n, ops, "pairs")
+
+
+@pytest.mark.parametrize("n,depth,f,two_qubit,n_traj,states", [
+    (1, 6, 4, False, 90, 1), (2, 8, 2, True, 60, 1), (5, 8, 5, True, 20, 2), (9, 8, 4, True, 11, 1),
+    (10, 10, 4, False, 12, 1), (11, 8, 3, True, 7, 1), (13, 6, 4, True, 300, 1), (13, 6, 5, False, 3, 2),
+    (14, 8, 4, False, 70, 1), (14, 6, 4, True, 4, 1), (15, 6, 5, False, 3, 1), (16, 6, 1, False, 9, 3),
+    (19, 5, 4, False, 20, 1), (21, 4, 3, False, 6, 1)])
+def test_side_by_side_equals_one_by_one(qs, n, depth, f, two_qubit, n_traj, states):
+    c = _circuit(n, depth, two_qubit)
+    e0, e1 = W.readout_arrays(n, 0.01, 0.02)
+    kw = dict(seed=5, traj_offset=3, circuit_id=2, max_fuse=f, n_samples=7, p0to1=e0, p1to0=e1, return_state=True,
+              z_expect=True)
+    handles = [qs.State(n) for _ in range(states)]
+    try:
+        hs = [h.h for h in handles]
+        got = qs.qs_run_trajectories(hs if states > 1 else hs[0], c, n_traj, **kw)
+        ref = qs.qs_run_trajectories(hs[0], c, n_traj, time_kernels=True, **kw)
+    finally:
+        for h in handles:
+            h.close()
+    assert ref["n_slow"].sum() > 0
+    for key in ("choices", "paths", "n_slow"):
+        assert np.array_equal(got[key], ref[key]), key
+    # from 10 qubits on both run the same blocks in the same order on the same
+    # units; below, the one-by-one path multiplies in another order
+    assert np.abs(got["z_expect"] - ref["z_expect"]).max() < 2 * AMP_TOL
+    assert rel_l2(got["state"], ref["state"]) < AMP_TOL
+    if n >= 10:
+        assert np.array_equal(got["samples"], ref["samples"])
+        assert got["gate_sweeps"] == ref["gate_sweeps"]
+
+
+def test_range_split_keeps_results(qs):
+    """The same range in one call, in pieces and one by one through
+    traj_offset; a 14-qubit piece of one trajectory takes the other path."""
+    for n in (8, 14):
+        c = _circuit(n, 6, False)
+        with qs.State(n) as st:
+            whole = qs.qs_run_trajectories(st.h, c, 9, seed=1, max_fuse=4, return_state=True)
+            for first, count in ((0, 4), (4, 4), (8, 1)):
+                part = qs.qs_run_trajectories(st.h, c, count, seed=1, max_fuse=4, traj_offset=first, return_state=True)
+                assert np.array_equal(part["choices"], whole["choices"][first:first + count])
+        assert np.array_equal(part["state"], whole["state"])
