@@ -137,7 +137,7 @@ struct BatchTileGate {
 
 struct BatchSweep {          // circuits of n > kBatchLdsQubits
     int pos[kMaxTileBits];   // the tile's kBatchTileBits index bits
-    int g0, g1;              // block range, relative to the circuit's first
+    int g0, g1;              // block range
 };
 
 // A workgroup's share of a sweep launch: `tiles` tiles of one job.
@@ -145,16 +145,27 @@ struct BatchPart {
     int job, tile0, tiles;
 };
 
+struct BatchGate;
+struct BatchTileGate;
+struct BatchChannel;
+struct BatchMember;
+
+// A circuit of the batch: its tables on the device (those of its plan; every
+// offset inside them is the circuit's own) and what the call asks of it.
 struct BatchCircuit {
+    const BatchSweep *sweeps;
+    const BatchGate *gates;
+    const BatchTileGate *tile_gates;
+    const float2 *mats;      // default block matrices
+    const BatchChannel *chans;
+    const double *pbar;
+    const BatchMember *members;
+    const double2 *fmats;    // FP64 gate and channel matrices for the members
     int n;
     int resident;
-    int s0, s1;              // sweep range
+    int n_gates, nch;
     int n_samples;
     int readout;             // offset of 2n doubles (e0[], e1[]) in the readout pool, or -1
-    int g0, n_gates;         // the circuit's blocks (absolute first, count)
-    int tg0;                 // its first entry in tile_gates
-    int ch0, nch;            // the circuit's channels in the channel table
-    int pool0, pool_len;     // float2 range of the circuit's default matrices in the pool
 };
 
 // A channel of a batched circuit (Algorithm 2's fast path for mixtures of
@@ -164,7 +175,7 @@ struct BatchChannel {
     int32_t nk;              // Kraus operators
     int32_t default_pick;    // the pick folded into the default block matrices
     int32_t pbar;            // offset of the nk probabilities in the pbar pool
-    int32_t gate;            // block holding the channel, relative to the circuit's first
+    int32_t gate;            // block holding the channel
     int32_t unit;            // double2 offset of K_i / sqrt(pbar_i), i < nk, in the FP64 pool
     uint32_t identity;       // bit i: K_i is a multiple of I (left out of the fused product)
 };
@@ -193,16 +204,8 @@ struct BatchJob {
 
 struct BatchArgs {
     const BatchCircuit *circs;
-    const BatchSweep *sweeps;
-    const BatchGate *gates;
-    const BatchTileGate *tile_gates;
     const BatchJob *jobs;
-    const float2 *mats;      // default block matrices
     const double *readout;
-    const BatchChannel *chans;
-    const double *pbar;
-    const BatchMember *members;
-    const double2 *fmats;    // FP64 gate and channel matrices for the members
     float2 *patched;         // matrices of the blocks a job's picks change
     int64_t patched_stride;  // float2 entries per workgroup of run_batched
     const float2 **mptr;     // per job of a wave: its blocks' matrices

@@ -1176,7 +1176,6 @@ struct BatchBlocks {
     const __attribute__((address_space(4))) BatchGate *b;
     const uint32_t *mask;
     const float2 *mats, *mine;
-    int pool0;
     __device__ __forceinline__ ResidentGate gate(int gi) const {
         ResidentGate r;
         r.head = g[gi].head;
@@ -1184,7 +1183,7 @@ struct BatchBlocks {
         for (int j = 0; j < kMaxTileBits / 2; ++j) r.tab2[j] = g[gi].tab2[j];
         const int mat = b[gi].mat;
         const uint32_t word = __builtin_amdgcn_readfirstlane(mask[gi >> 5]);
-        r.m = ((word >> (gi & 31)) & 1u) ? mine + (mat - pool0) : mats + mat;
+        r.m = ((word >> (gi & 31)) & 1u) ? mine + mat : mats + mat;
         r.sel = -1;
         return r;
     }
@@ -1277,7 +1276,7 @@ __device__ __forceinline__ void fuse_member_wide(double2 *col, double2 *old, int
 // (the same Philox call as the draw pass).
 __device__ __forceinline__ void fuse_patched(const BatchArgs &A, const BatchJob &J, const BatchCircuit &C,
                                              int rel, double2 *ws, double2 *ush, float2 *mine) {
-    const BatchGate g = A.gates[C.g0 + rel];
+    const BatchGate g = C.gates[rel];
     const int D = 1 << g.k;
     const int per_pass = D <= 16 ? D : 16;
     const int lane = int(threadIdx.x) & 63;
@@ -1289,17 +1288,17 @@ __device__ __forceinline__ void fuse_patched(const BatchArgs &A, const BatchJob 
         if (on)
             for (int r = 0; r < D; ++r) col[r] = make_double2(r == c ? 1.0 : 0.0, 0.0);
         for (int mi = g.m0; mi < g.m1; ++mi) {
-            const BatchMember M = A.members[mi];
+            const BatchMember M = C.members[mi];
             const double2 *U;
             if (M.src >= 0) {
-                U = A.fmats + M.src;
+                U = C.fmats + M.src;
             } else {
                 const int ci = -M.src - 1;
-                const BatchChannel ch = A.chans[C.ch0 + ci];
-                const int pick = draw_pick(A.pbar + ch.pbar, ch.nk,
+                const BatchChannel ch = C.chans[ci];
+                const int pick = draw_pick(C.pbar + ch.pbar, ch.nk,
                                            philox_uniform(J.seed, uint32_t(ci), J.traj, J.circ_id, kStreamChannel));
                 if ((ch.identity >> pick) & 1u) continue;
-                U = A.fmats + ch.unit + pick * (1 << (2 * M.k));
+                U = C.fmats + ch.unit + pick * (1 << (2 * M.k));
             }
             int lpp = 0;
 #pragma unroll
@@ -1321,7 +1320,7 @@ __device__ __forceinline__ void fuse_patched(const BatchArgs &A, const BatchJob 
             }
         }
         if (on) {
-            float2 *dst = mine + (g.mat - C.pool0);
+            float2 *dst = mine + g.mat;
             for (int r = 0; r < D; ++r) dst[r * D + c] = make_float2(float(col[r].x), float(col[r].y));
         }
     }
@@ -1340,8 +1339,8 @@ __device__ __forceinline__ void draw_and_patch(const BatchArgs &A, const BatchJo
     for (int w = threadIdx.x; w < words; w += NT) mask[w] = 0u;
     __syncthreads();
     for (int c = threadIdx.x; c < C.nch; c += NT) {
-        const BatchChannel ch = A.chans[C.ch0 + c];
-        const int pick = draw_pick(A.pbar + ch.pbar, ch.nk,
+        const BatchChannel ch = C.chans[c];
+        const int pick = draw_pick(C.pbar + ch.pbar, ch.nk,
                                    philox_uniform(J.seed, uint32_t(c), J.traj, J.circ_id, kStreamChannel));
         if (J.choices >= 0) A.choices[J.choices + c] = int8_t(pick);
         if (pick != ch.default_pick) atomicOr(&mask[ch.gate >> 5], 1u << (ch.gate & 31));
@@ -1501,12 +1500,11 @@ __global__ __launch_bounds__(NT) void run_batched(BatchArgs A) {
         for (int i = threadIdx.x; i < dim; i += NT) sd[i] = make_float2(i == 0 ? 1.f : 0.f, 0.f);
         __syncthreads();
         BatchBlocks src;
-        src.g = (const __attribute__((address_space(4))) BatchTileGate *)(A.tile_gates) + C.tg0;
-        src.b = (const __attribute__((address_space(4))) BatchGate *)(A.gates) + C.g0;
+        src.g = (const __attribute__((address_space(4))) BatchTileGate *)(C.tile_gates);
+        src.b = (const __attribute__((address_space(4))) BatchGate *)(C.gates);
         src.mask = mask;
-        src.mats = A.mats;
+        src.mats = C.mats;
         src.mine = mine;
-        src.pool0 = C.pool0;
         // the same MFMA rule at either group size: a job's arithmetic does not
         // depend on the launch it runs in
         resident_blocks<NT, 10, 11>(src, C.n_gates, sd, wide, raw, raw, C.n, [](int, float2 *) {});
@@ -1537,9 +1535,9 @@ __global__ __launch_bounds__(kBlock) void batch_prepare(BatchArgs A, int job0) {
     double2 *ws = reinterpret_cast<double2 *>(smem);
     draw_and_patch<kBlock>(A, J, C, mask, ws, ws + 4 * 1024, mine);
     for (int gi = threadIdx.x; gi < C.n_gates; gi += kBlock) {
-        const int mat = A.gates[C.g0 + gi].mat;
+        const int mat = C.gates[gi].mat;
         const bool patched = (mask[gi >> 5] >> (gi & 31)) & 1u;
-        A.mptr[J.mptr + gi] = patched ? mine + (mat - C.pool0) : A.mats + mat;
+        A.mptr[J.mptr + gi] = patched ? mine + mat : C.mats + mat;
     }
 }
 
@@ -1576,8 +1574,8 @@ __global__ __launch_bounds__(kBatchWideThreads) void batch_sweep(BatchArgs A, co
     const Jobs J = (Jobs)(A.jobs) + P->job;
     const Circs C = (Circs)(A.circs) + J->circuit;
     JobSweep src;
-    src.s = (Sweeps)(A.sweeps) + C->s0 + step;
-    src.g = (Gates)(A.tile_gates) + C->tg0 + src.s->g0;
+    src.s = (Sweeps)(C->sweeps) + step;
+    src.g = (Gates)(C->tile_gates) + src.s->g0;
     src.m = (Words)(A.mptr) + J->mptr + src.s->g0;
     src.zero = step == 0 ? 1 : 0;
     tile_sweep<kBatchTileBits, uint32_t, K5, kBatchWideThreads, false, true>(

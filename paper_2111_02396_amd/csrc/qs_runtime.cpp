@@ -98,6 +98,7 @@ struct qs_state_s {
     uint64_t static_tag = 0;         // cached plan whose matrices static_buf holds (0: none)
     double *chan_dev = nullptr;      // channels' excess matrices and bounds
     size_t chan_cap = 0;             // doubles
+    uint64_t chan_tag = 0;           // cached model and mode whose channels chan_dev holds (0: none)
 };
 
 namespace {
@@ -993,7 +994,8 @@ struct BlockDesc {
     qs::GateDesc g;
     bool identity = false;
     double log_bound = 0.0;
-    const float2 *dev = nullptr;  // device copy of g.m
+    const float2 *dev = nullptr;  // device copy of g.m, or null:
+    size_t static_off = 0;        // a plan's block, at this offset of the call's static matrices
 };
 
 // Stage a block's matrix in the arena (committed later, before its launch).
@@ -1109,11 +1111,51 @@ struct PlanKey {
     }
 };
 
+struct TileLayout {
+    bool tiled = false;
+    int tb = 0;
+    int pos[qs::kMaxTileBits] = {};
+    int8_t local[qs::kMaxQubits] = {};
+
+    // Tile layout of a sweep: its qubits plus the lowest others up to the tile
+    // width (at least 10 bits, and k + 8 for its widest block).
+    static TileLayout of(int n, const qs::Sweep &sw, const std::vector<qs::Block> &bl) {
+        TileLayout L;
+        const auto &bits = sw.bits;
+        if (bits.empty() || int(bits.size()) > qs::kMaxTileBits) return L;
+        int maxk = 1;
+        for (int b : sw.blocks) maxk = std::max(maxk, bl[b].k);
+        int tb = std::max<int>(int(bits.size()), std::min(qs::kMaxTileBits, std::max(10, maxk + 8)));
+        tb = std::min(tb, n);
+        std::vector<char> in(n, 0);
+        for (int q : bits) in[q] = 1;
+        int cnt = int(bits.size());
+        for (int q = 0; q < n && cnt < tb; ++q)
+            if (!in[q]) {
+                in[q] = 1;
+                ++cnt;
+            }
+        L.tb = tb;
+        int i = 0;
+        for (int q = 0; q < qs::kMaxQubits; ++q) L.local[q] = -1;
+        for (int q = 0; q < n; ++q)
+            if (in[q]) {
+                L.pos[i] = q;
+                L.local[q] = int8_t(i);
+                ++i;
+            }
+        L.tiled = true;
+        return L;
+    }
+};
+
 struct PlanEntry {
     std::vector<qs::Block> blocks;
     std::vector<int> op_block;
-    std::vector<BlockDesc> block_desc;  // device copies not set
+    std::vector<BlockDesc> block_desc;  // device copies not set, static offsets are
     std::vector<qs::Sweep> sweeps;
+    std::vector<TileLayout> layouts;
+    size_t static_len = 0;              // float2 of the blocks' matrices
 };
 
 constexpr size_t kPlanCacheEntries = 32;
@@ -1145,6 +1187,16 @@ uint64_t circuit_hash(const qs_circuit *c) {
     auto mix = [&h](const void *p, size_t len) {
         const unsigned char *b = static_cast<const unsigned char *>(p);
         size_t i = 0;
+        // four chains, so that the multiplications overlap
+        uint64_t lane[4] = {h, h ^ 0x9ddfea08eb382d69ull, h ^ 0xc2b2ae3d27d4eb4full, h ^ 0x165667b19e3779f9ull};
+        for (; i + 32 <= len; i += 32)
+            for (int j = 0; j < 4; ++j) {
+                uint64_t w;
+                std::memcpy(&w, b + i + 8 * j, 8);
+                lane[j] = (lane[j] ^ w) * 0xff51afd7ed558ccdull;
+                lane[j] ^= lane[j] >> 32;
+            }
+        for (int j = 0; j < 4; ++j) h = (h ^ lane[j]) * 0x9fb21c651e98df25ull, h ^= h >> 32;
         for (; i + 8 <= len; i += 8) {
             uint64_t w;
             std::memcpy(&w, b + i, 8);
@@ -1199,15 +1251,17 @@ qs_status circuit_model(const qs_circuit *c, std::shared_ptr<const ModelEntry> *
     if (!c || !c->ops || c->n_ops < 0 || !c->mat_pool || c->pool_len < 0)
         return fail(QS_ERR_INVALID_ARGUMENT, "bad circuit");
     const uint64_t h = circuit_hash(c);
+    std::vector<std::shared_ptr<const ModelEntry>> alike;
     {
         std::lock_guard<std::mutex> lock(g_model_mu);
         auto range = g_model_cache.equal_range(h);
-        for (auto it = range.first; it != range.second; ++it)
-            if (same_circuit(*it->second, c)) {
-                *out = it->second;
-                return QS_OK;
-            }
+        for (auto it = range.first; it != range.second; ++it) alike.push_back(it->second);
     }
+    for (auto &a : alike)  // compared outside the lock: a batch looks its circuits up on many threads
+        if (same_circuit(*a, c)) {
+            *out = std::move(a);
+            return QS_OK;
+        }
     auto e = std::make_shared<ModelEntry>();
     e->hash = h;
     e->n = c->n_qubits;
@@ -1430,24 +1484,19 @@ struct Runner {
     const CircuitModel &m;
     const qs_traj_params &p;
     qs_traj_result &res;
-    int max_fuse;
-    uint64_t chash = 0;   // model id of the call's circuit (0: do not cache the plan)
-    bool tuning = false;  // an autotuner trial: default plan only, no channel uploads
-    // delayed mode: default plan
+    const int max_fuse;
+    const uint64_t chash;  // model id of the call's circuit (0: do not cache the plan)
+    bool tuning = false;   // an autotuner trial: default plan only, no channel uploads
+    // delayed mode: default plan, shared with the cache
     std::vector<const cd *> default_mats;
-    std::vector<double> default_log;
-    std::vector<qs::Block> blocks;
-    std::vector<int> op_block;
-    std::vector<BlockDesc> block_desc;
+    std::vector<cd> tmp;
+    const std::shared_ptr<const PlanEntry> plan;
+    const std::vector<qs::Block> &blocks;
+    const std::vector<int> &op_block;
+    const std::vector<BlockDesc> &block_desc;
     // tile sweeps over the default plan: the sweep order is the launch order
-    struct TileLayout {
-        bool tiled = false;
-        int tb = 0;
-        int pos[qs::kMaxTileBits] = {};
-        int8_t local[qs::kMaxQubits] = {};
-    };
-    std::vector<qs::Sweep> sweeps;
-    std::vector<TileLayout> layouts;
+    const std::vector<qs::Sweep> &sweeps;
+    const std::vector<TileLayout> &layouts;
     struct Unit {
         const TileLayout *L;
         std::vector<const BlockDesc *> items;
@@ -1462,7 +1511,6 @@ struct Runner {
     std::deque<TileLayout> run_layouts;  // those of run_delayed's segments
     // naive mode: gate blocks per inter-channel segment
     std::vector<std::vector<BlockDesc>> naive_segments;
-    std::vector<cd> tmp;
     std::vector<int> rest_ops;  // a slow block's operations after its channel
     std::deque<std::vector<cd>> slow_mats;
     qs::ReadoutDesc ro;
@@ -1476,7 +1524,9 @@ struct Runner {
     // matrices and bounds, the picks written by the select kernel, an error flag
     double *chan_buf = nullptr;
     std::vector<const double *> chan_excess, chan_pbar;
-    int *dev_choice = nullptr;      // [kChoiceCap] picks, then [kChoiceCap] = error flag
+    int *dev_error = nullptr;       // error flag, followed by
+    int *dev_choice = nullptr;      // [kChoiceCap] picks
+    bool selecting = false;         // a selection has been launched
     int *host_choice = nullptr;     // pinned mirror
     double *sel_rdm = nullptr;      // R of the pending channel; a renormalisation
                                     // launched before the select cannot overwrite it
@@ -1536,41 +1586,53 @@ struct Runner {
         size_t total = 0;
         for (const auto &c : m.channels)
             if (!c.mixture) total += c.excess_sorted.size() * 2 + c.pbar.size();
+        if (total == 0) return QS_OK;  // no channel can need inner products
         if (!s->sel_choice_dev) {
             QS_HIP(s, hipMalloc(&s->sel_choice_dev, sizeof(int) * (kChoiceCap + 1)));
             QS_HIP(s, hipMalloc(&s->sel_rdm, sizeof(double) * qs::kMaxReduceWidth));
             QS_HIP(s, hipHostMalloc(&s->sel_choice_host, sizeof(int) * (kChoiceCap + 1),
                                     hipHostMallocDefault));
         }
-        dev_choice = s->sel_choice_dev;
+        dev_error = s->sel_choice_dev;
+        dev_choice = s->sel_choice_dev + 1;
         host_choice = s->sel_choice_host;
         sel_rdm = s->sel_rdm;
-        QS_HIP(s, hipMemsetAsync(dev_choice + kChoiceCap, 0, sizeof(int), s->st));
-        if (total == 0) return QS_OK;
-        std::vector<double> host(total);
+        // a cached model's channels are fixed by its id and the mode: the
+        // state keeps their tables from one call to the next
+        const uint64_t tag = chash ? (chash << 2) | uint64_t(p.mode & 3) : 0;
+        const bool have = tag != 0 && tag == s->chan_tag && total <= s->chan_cap;
+        std::vector<double> host(have ? 0 : total);
         std::vector<size_t> at(nch, 0);
         size_t pos = 0;
         for (size_t c = 0; c < nch; ++c) {
             const auto &ci = m.channels[c];
             if (ci.mixture) continue;
             at[c] = pos;
+            if (have) {
+                pos += 2 * ci.excess_sorted.size() + ci.pbar.size();
+                continue;
+            }
             for (const cd &z : ci.excess_sorted) {
                 host[pos++] = z.real();
                 host[pos++] = z.imag();
             }
             for (double pb : ci.pbar) host[pos++] = pb;
         }
-        if (total > s->chan_cap) {
-            if (s->chan_dev) QS_HIP(s, hipFree(s->chan_dev));
-            s->chan_dev = nullptr;
-            s->chan_cap = 0;
-            QS_HIP(s, hipMalloc(&s->chan_dev, sizeof(double) * total));
-            s->chan_cap = total;
+        if (!have) {
+            s->chan_tag = 0;
+            if (total > s->chan_cap) {
+                if (s->chan_dev) QS_HIP(s, hipFree(s->chan_dev));
+                s->chan_dev = nullptr;
+                s->chan_cap = 0;
+                QS_HIP(s, hipMalloc(&s->chan_dev, sizeof(double) * total));
+                s->chan_cap = total;
+            }
+            QS_HIP(s, hipMemcpyAsync(s->chan_dev, host.data(), sizeof(double) * total, hipMemcpyHostToDevice,
+                                     s->st));
+            QS_HIP(s, hipStreamSynchronize(s->st));  // `host` is pageable and ends with this call
+            s->chan_tag = tag;
         }
         chan_buf = s->chan_dev;
-        QS_HIP(s, hipMemcpyAsync(chan_buf, host.data(), sizeof(double) * total, hipMemcpyHostToDevice,
-                                 s->st));
-        QS_HIP(s, hipStreamSynchronize(s->st));  // `host` is pageable and ends with this call
         for (size_t c = 0; c < nch; ++c) {
             const auto &ci = m.channels[c];
             if (ci.mixture) continue;
@@ -1580,53 +1642,36 @@ struct Runner {
         return QS_OK;
     }
 
-    // Copy the picks made on the device back into the result array.
+    // Clears the error flag before the call's first selection.
+    qs_status open_selections() {
+        if (selecting) return QS_OK;
+        selecting = true;
+        QS_HIP(s, hipMemsetAsync(dev_error, 0, sizeof(int), s->st));
+        return QS_OK;
+    }
+
+    // Copy the error flag and the picks made on the device back.
     qs_status drain_choices() {
-        // the picks made so far and the error flag
-        if (!choice_owner.empty())
-            QS_HIP(s, hipMemcpyAsync(host_choice, dev_choice, sizeof(int) * choice_owner.size(),
-                                     hipMemcpyDeviceToHost, s->st));
-        QS_HIP(s, hipMemcpyAsync(host_choice + kChoiceCap, dev_choice + kChoiceCap, sizeof(int),
+        if (!selecting) return QS_OK;
+        QS_HIP(s, hipMemcpyAsync(host_choice, dev_error, sizeof(int) * (1 + choice_owner.size()),
                                  hipMemcpyDeviceToHost, s->st));
         QS_HIP(s, hipStreamSynchronize(s->st));
         const int nch = int(m.channels.size());
         if (res.kraus_choices)
             for (size_t i = 0; i < choice_owner.size(); ++i)
                 res.kraus_choices[choice_owner[i].first * nch + choice_owner[i].second] =
-                    int8_t(host_choice[i]);
+                    int8_t(host_choice[1 + i]);
         choice_owner.clear();
-        if (host_choice[kChoiceCap] != 0)
+        if (host_choice[0] != 0)
             return fail(QS_ERR_ZERO_NORM, "a channel needing inner products met a zero norm or weight");
         return QS_OK;
     }
 
-    // Upload the matrices of `descs` to one device buffer and point at it.
-    // Uploads the matrices of `descs` to the state's static buffer, unless
-    // it already holds those of the cached plan `tag` (0: always upload).
-    qs_status upload_static(std::vector<BlockDesc *> &descs, uint64_t tag = 0) {
-        size_t total = 0;
-        for (auto *d : descs)
-            if (!d->identity) total += size_t(1) << (2 * d->g.k);
-        if (total == 0) return QS_OK;
-        if (tag != 0 && tag == s->static_tag && total <= s->static_cap) {
-            static_mats = s->static_buf;
-            size_t pos = 0;
-            for (auto *d : descs) {
-                if (d->identity) continue;
-                d->dev = static_mats + pos;
-                pos += size_t(1) << (2 * d->g.k);
-            }
-            return QS_OK;
-        }
+    // Uploads `host` to the state's static buffer, which then holds the
+    // matrices of the cached plan `tag` (0: of none).
+    qs_status upload_static(const std::vector<float2> &host, uint64_t tag) {
+        const size_t total = host.size();
         s->static_tag = 0;
-        std::vector<float2> host(total);
-        size_t pos = 0;
-        for (auto *d : descs) {
-            if (d->identity) continue;
-            const size_t dd = size_t(1) << (2 * d->g.k);
-            std::memcpy(host.data() + pos, d->g.m, sizeof(float2) * dd);
-            pos += dd;
-        }
         if (total > s->static_cap) {
             QS_HIP(s, hipStreamSynchronize(s->st));  // an earlier call's kernels may still read it
             if (s->static_buf) QS_HIP(s, hipFree(s->static_buf));
@@ -1640,12 +1685,6 @@ struct Runner {
                                  s->st));
         QS_HIP(s, hipStreamSynchronize(s->st));  // `host` is pageable and ends with this call
         s->static_tag = tag;
-        pos = 0;
-        for (auto *d : descs) {
-            if (d->identity) continue;
-            d->dev = static_mats + pos;
-            pos += size_t(1) << (2 * d->g.k);
-        }
         return QS_OK;
     }
     int64_t sample_fill = 0;        // samples buffered on the device
@@ -1654,83 +1693,86 @@ struct Runner {
     int64_t z_first_traj = 0;
     std::vector<double> z_host;
 
-    Runner(qs_state s_, const CircuitModel &m_, const qs_traj_params &p_, qs_traj_result &r_,
+    Runner(qs_state s_, const CircuitModel &m_, const qs_traj_params &p_, qs_traj_result &r_, uint64_t chash_,
            hipEvent_t ref = nullptr, std::vector<std::pair<double, double>> *intervals = nullptr)
-        : s(s_), m(m_), p(p_), res(r_) {
-        max_fuse = p.max_fuse > 0 ? p.max_fuse : kDefaultFuse;
+        : s(s_), m(m_), p(p_), res(r_), max_fuse(p_.max_fuse > 0 ? p_.max_fuse : kDefaultFuse), chash(chash_),
+          plan(default_plan()), blocks(plan->blocks), op_block(plan->op_block), block_desc(plan->block_desc),
+          sweeps(plan->sweeps), layouts(plan->layouts) {
         timer.ref = ref;
         timer.intervals = intervals;
     }
 
-    qs_status plan_delayed() {
+    int plan_tile_bits() const { return p.tile_bits == 0 ? qs::kDefaultTileBits : p.tile_bits; }
+
+    // The call's default plan, from the cache or made now (delayed modes;
+    // also fills default_mats).
+    std::shared_ptr<const PlanEntry> default_plan() {
+        if (p.mode == QS_KRAUS_NAIVE) return std::make_shared<PlanEntry>();
         const int n_ops = int(m.ops.size());
         default_mats.assign(n_ops, nullptr);
-        default_log.assign(n_ops, 0.0);
         for (int o = 0; o < n_ops; ++o) {
             if (m.kind[o] == QS_OP_GATE) {
                 default_mats[o] = m.gate_mat[o];
-                default_log[o] = m.gate_log_bound[o];
             } else {
                 const ChannelInfo &c = m.channels[m.channel_of_op[o]];
                 default_mats[o] = fast_pick_matrix(c, c.default_pick);
-                default_log[o] = c.log_pbar[c.default_pick];
             }
         }
-        const PlanKey key{chash, m.n, p.mode, max_fuse, p.tile_bits == 0 ? qs::kDefaultTileBits : p.tile_bits};
+        const PlanKey key{chash, m.n, p.mode, max_fuse, plan_tile_bits()};
         std::shared_ptr<const PlanEntry> cached;
         if (chash) plan_lookup(key, &cached);
-        if (cached) {
-            blocks = cached->blocks;
-            op_block = cached->op_block;
-            block_desc = cached->block_desc;
-            sweeps = cached->sweeps;
-        } else {
-            blocks = qs::fuse_greedy(m.n, m.ops, max_fuse, &op_block);
-            block_desc.resize(blocks.size());
-            for (size_t b = 0; b < blocks.size(); ++b) {
-                build_block(m, blocks[b].ops, default_mats, tmp, block_desc[b]);
-                double lb = 0.0;
-                for (int o : blocks[b].ops) lb += default_log[o];
-                block_desc[b].log_bound = lb;
+        if (cached) return cached;
+        auto e = std::make_shared<PlanEntry>();
+        e->blocks = qs::fuse_greedy(m.n, m.ops, max_fuse, &e->op_block);
+        e->block_desc.resize(e->blocks.size());
+        for (size_t b = 0; b < e->blocks.size(); ++b) {
+            BlockDesc &d = e->block_desc[b];
+            build_block(m, e->blocks[b].ops, default_mats, tmp, d);
+            for (int o : e->blocks[b].ops) {
+                const int c = m.channel_of_op[o];
+                d.log_bound += c < 0 ? m.gate_log_bound[o] : m.channels[c].log_pbar[m.channels[c].default_pick];
             }
-            plan_sweeps();
-            if (chash) {
-                auto e = std::make_shared<PlanEntry>();
-                e->blocks = blocks;
-                e->op_block = op_block;
-                e->block_desc = block_desc;
-                e->sweeps = sweeps;
-                plan_insert(key, std::move(e));
+            if (d.identity) continue;
+            d.static_off = e->static_len;
+            e->static_len += size_t(1) << (2 * d.g.k);
+        }
+        const int T = plan_tile_bits();
+        if (T >= 10 && m.n >= qs::kTileMinQubits) {
+            e->sweeps = qs::group_sweeps_best(m.n, e->blocks, std::min(T, m.n), qs::kTileLowBits, qs::kMaxTileGates,
+                                              qs::tile_mat_budget(std::min(T, m.n)), tile_slots(),
+                                              plan_restarts(m.n, p.n_traj), kGroupSeed);
+        } else {
+            for (size_t b = 0; b < e->blocks.size(); ++b) {
+                qs::Sweep sw;
+                sw.blocks.push_back(int(b));
+                e->sweeps.push_back(std::move(sw));
             }
         }
-        layouts.resize(sweeps.size());
-        for (size_t u = 0; u < sweeps.size(); ++u) layouts[u] = make_layout(sweeps[u], blocks);
-        std::vector<BlockDesc *> all;
-        for (auto &d : block_desc) all.push_back(&d);
+        e->layouts.resize(e->sweeps.size());
+        for (size_t u = 0; u < e->sweeps.size(); ++u) e->layouts[u] = TileLayout::of(m.n, e->sweeps[u], e->blocks);
+        if (chash) plan_insert(key, e);
+        return e;
+    }
+
+    // Device copies of the plan's matrices and the channels' tables.
+    qs_status plan_delayed() {
         if (!tuning) QS_CHECK(upload_channels());
         // a plan from the cache is fixed by its key: the state keeps its
         // matrices from one call to the next
         const uint64_t tag = chash ? (chash << 16) | (uint64_t(p.mode & 3) << 12) |
-                                         (uint64_t(max_fuse) << 8) | uint64_t(key.tb)
+                                         (uint64_t(max_fuse) << 8) | uint64_t(plan_tile_bits())
                                    : 0;
-        return upload_static(all, tag);
+        if (plan->static_len == 0 || (tag != 0 && tag == s->static_tag && plan->static_len <= s->static_cap)) {
+            static_mats = s->static_buf;
+            return QS_OK;
+        }
+        std::vector<float2> host(plan->static_len);
+        for (const BlockDesc &d : block_desc)
+            if (!d.identity) std::memcpy(host.data() + d.static_off, d.g.m, sizeof(float2) << (2 * d.g.k));
+        return upload_static(host, tag);
     }
 
-    void plan_sweeps() {
-        const int T = p.tile_bits == 0 ? qs::kDefaultTileBits : p.tile_bits;
-        sweeps.clear();
-        if (T >= 10 && m.n >= qs::kTileMinQubits) {
-            sweeps = qs::group_sweeps_best(m.n, blocks, std::min(T, m.n), qs::kTileLowBits,
-                                           qs::kMaxTileGates, qs::tile_mat_budget(std::min(T, m.n)),
-                                           tile_slots(), plan_restarts(m.n, p.n_traj), kGroupSeed);
-        } else {
-            for (size_t b = 0; b < blocks.size(); ++b) {
-                qs::Sweep sw;
-                sw.blocks.push_back(int(b));
-                sweeps.push_back(std::move(sw));
-            }
-        }
-    }
+    const float2 *mat_of(const BlockDesc &d) const { return d.dev ? d.dev : static_mats + d.static_off; }
 
     // The default plan once from |0...0> (every channel at its most likely
     // pick, no inner products): the autotuner's trial.
@@ -1749,37 +1791,6 @@ struct Runner {
         }
         QS_CHECK(flush_units(units));
         return settle_reset();
-    }
-
-    // Tile layout of a sweep: its qubits plus the lowest others up to the tile
-    // width (at least 10 bits, and k + 8 for its widest block).
-    TileLayout make_layout(const qs::Sweep &sw, const std::vector<qs::Block> &bl) const {
-        TileLayout L;
-        const auto &bits = sw.bits;
-        if (bits.empty() || int(bits.size()) > qs::kMaxTileBits) return L;
-        int maxk = 1;
-        for (int b : sw.blocks) maxk = std::max(maxk, bl[b].k);
-        int tb = std::max<int>(int(bits.size()), std::min(qs::kMaxTileBits, std::max(10, maxk + 8)));
-        tb = std::min(tb, m.n);
-        std::vector<char> in(m.n, 0);
-        for (int q : bits) in[q] = 1;
-        int cnt = int(bits.size());
-        for (int q = 0; q < m.n && cnt < tb; ++q)
-            if (!in[q]) {
-                in[q] = 1;
-                ++cnt;
-            }
-        L.tb = tb;
-        int i = 0;
-        for (int q = 0; q < qs::kMaxQubits; ++q) L.local[q] = -1;
-        for (int q = 0; q < m.n; ++q)
-            if (in[q]) {
-                L.pos[i] = q;
-                L.local[q] = int8_t(i);
-                ++i;
-            }
-        L.tiled = true;
-        return L;
     }
 
     // The sweeps of the segment [seg_start, seg_end): the call's plan when the
@@ -1839,9 +1850,9 @@ struct Runner {
                 int(w.bits.size()) < qs::kMaxTileBits) {
                 qs::Sweep w2 = w;
                 w2.bits.insert(std::upper_bound(w2.bits.begin(), w2.bits.end(), rq), rq);
-                seg_layouts.push_back(make_layout(w2, rb));
+                seg_layouts.push_back(TileLayout::of(m.n, w2, rb));
             } else {
-                seg_layouts.push_back(make_layout(w, rb));
+                seg_layouts.push_back(TileLayout::of(m.n, w, rb));
             }
             SegSweep ss{&seg_layouts.back(), {}};
             for (int b : w.blocks) ss.members.push_back(orig[b]);
@@ -1900,7 +1911,7 @@ struct Runner {
             g.k = d->g.k;
             for (int b = 0; b < d->g.k; ++b) g.lt[b] = L.local[d->g.t[b]];
             g.lofs = lofs;
-            g.mat = d->dev;
+            g.mat = mat_of(*d);
             lofs += qs::tile_mat_slots(d->g.k);
             lb += d->log_bound;
             res.gate_k_launches[d->g.k]++;
@@ -1974,10 +1985,14 @@ struct Runner {
             else close();
         }
         close();  // the tail after the last channel
-        std::vector<BlockDesc *> all;
+        std::vector<float2> host;
         for (auto &segv : naive_segments)
-            for (auto &d : segv) all.push_back(&d);
-        return upload_static(all);
+            for (auto &d : segv) {
+                if (d.identity) continue;
+                d.static_off = host.size();
+                host.insert(host.end(), d.g.m, d.g.m + (size_t(1) << (2 * d.g.k)));
+            }
+        return host.empty() ? QS_OK : upload_static(host, 0);
     }
 
     qs_status launch_block(const BlockDesc &d) {
@@ -1994,7 +2009,7 @@ struct Runner {
         }
         if (d.identity) return QS_OK;
         if (timing) QS_CHECK(timer.open(s));
-        QS_HIP(s, qs::launch_apply_gate(s->amp, s->n, d.g, d.dev, s->st));
+        QS_HIP(s, qs::launch_apply_gate(s->amp, s->n, d.g, mat_of(d), s->st));
         if (timing) {
             timer.launched();
             QS_CHECK(timer.close(s));
@@ -2371,7 +2386,7 @@ struct Runner {
                         if (block_desc[b].identity) continue;
                         g.k = block_desc[b].g.k;
                         for (int j = 0; j < 5; ++j) g.t[j] = block_desc[b].g.t[j];
-                        g.dev = block_desc[b].dev;
+                        g.dev = mat_of(block_desc[b]);
                         lb += block_desc[b].log_bound;
                         push(g);
                         continue;
@@ -2531,6 +2546,7 @@ struct Runner {
             n_sels += plans[w].sels.size();
         }
         if (choice_owner.size() + n_sels > size_t(kChoiceCap)) QS_CHECK(drain_choices());
+        if (n_sels > 0) QS_CHECK(open_selections());
         const size_t f_gate = f2_of(n_gates * sizeof(qs::TrajGate)), f_sel = f2_of(n_sels * sizeof(qs::TrajSelect)),
                      f_cut = f2_of(n_cuts * sizeof(qs::TrajSweep)), f_job = f2_of(n_traj * sizeof(qs::TrajJob));
         float2 *h = nullptr;
@@ -2591,7 +2607,7 @@ struct Runner {
             D.dst = const_cast<float2 *>(d + mat0[i] + S.dst);
             D.records = records;
             D.choice = dev_choice + choice_owner.size();
-            D.err = dev_choice + kChoiceCap;
+            D.err = dev_error;
             D.resid = S.resid;
             D.nk = ci.nk;
             D.k = ci.k;
@@ -2861,7 +2877,8 @@ struct Runner {
                         A.cand = reinterpret_cast<const double *>(dc);
                         A.dst = const_cast<float2 *>(bd.dev);
                         A.choice = dev_choice + choice_owner.size();
-                        A.err = dev_choice + kChoiceCap;
+                        A.err = dev_error;
+                        QS_CHECK(open_selections());
                         A.resid = sel.resid;
                         A.nk = ci.nk;
                         A.D = Dc;
@@ -3005,7 +3022,7 @@ struct Runner {
         }
         QS_CHECK(flush_samples());
         QS_CHECK(flush_z());
-        if (delayed && dev_choice) QS_CHECK(drain_choices());
+        if (delayed) QS_CHECK(drain_choices());
         if (timing) {
             QS_CHECK(timer.finish(s));
             res.gate_kernel_ms = timer.total_ms;
@@ -3125,19 +3142,16 @@ qs_status resolve_widths(qs_state s, const CircuitModel &m, uint64_t chash, cons
             if (by_traj) {
                 q.n_traj = 1;
                 q.traj_offset = p.traj_offset + nt < (int64_t(1) << 32) ? p.traj_offset + nt : p.traj_offset;
-                Runner warm(s, m, q, dummy);
-                warm.chash = chash;
+                Runner warm(s, m, q, dummy, chash);
                 QS_CHECK(warm.run());
                 q.n_traj = nt;
                 q.traj_offset = p.traj_offset;
-                Runner trial(s, m, q, dummy);
-                trial.chash = chash;
+                Runner trial(s, m, q, dummy, chash);
                 const auto ta = std::chrono::steady_clock::now();
                 QS_CHECK(trial.run());  // ends with a stream synchronisation
                 t = 1e3 * std::chrono::duration<double>(std::chrono::steady_clock::now() - ta).count();
             } else {
-                Runner trial(s, m, q, dummy);
-                trial.chash = chash;
+                Runner trial(s, m, q, dummy, chash);
                 trial.tuning = true;
                 QS_CHECK(trial.plan_delayed());
                 for (int r = 0; r < reps; ++r) {
@@ -3223,8 +3237,7 @@ qs_status run_trajectories_impl(qs_state s, const qs_circuit *c, const qs_traj_p
     r->max_fuse_used = q.max_fuse;
     r->tile_bits_used = tile_bits_reported(m.n, q.tile_bits);
     r->tune_ms = tms;
-    Runner run(s, m, q, *r, ref, intervals);
-    run.chash = chash;
+    Runner run(s, m, q, *r, chash, ref, intervals);
     const qs_status st = run.run();
     r->host_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     return st;
@@ -3516,6 +3529,48 @@ struct BatchBuffers {
     size_t patched_cap = 0;  // bytes
     char *host = nullptr;    // pinned staging for the program
     size_t host_cap = 0;
+    // the plans' tables on the device, one after another; a plan in the map
+    // finds its own in place.  Full, the area starts over (kBatchTableBytes
+    // at most, unless one batch needs more).
+    char *tables = nullptr;
+    size_t tables_cap = 0, tables_used = 0;
+    std::map<std::shared_ptr<const BatchPlanEntry>, size_t> tables_at;
+};
+constexpr size_t kBatchTableBytes = size_t(64) << 20;
+
+// Where a plan's tables lie within its piece of the device area.
+struct BatchTableLayout {
+    size_t sweeps, gates, tile_gates, mats, chans, pbar, members, fmats, bytes;
+    explicit BatchTableLayout(const BatchPlanEntry &E) {
+        size_t at = 0;
+        auto take = [&at](size_t len) {
+            const size_t here = at;
+            at += (len + 255) & ~size_t(255);
+            return here;
+        };
+        sweeps = take(sizeof(qs::BatchSweep) * E.sweeps.size());
+        gates = take(sizeof(qs::BatchGate) * E.gates.size());
+        tile_gates = take(sizeof(qs::BatchTileGate) * E.tile_gates.size());
+        mats = take(sizeof(float2) * E.pool.size());
+        chans = take(sizeof(qs::BatchChannel) * E.chans.size());
+        pbar = take(sizeof(double) * E.pbar.size());
+        members = take(sizeof(qs::BatchMember) * E.members.size());
+        fmats = take(sizeof(double2) * E.fmats.size());
+        bytes = at + 256;  // descriptors are read two blocks ahead
+    }
+    void write(const BatchPlanEntry &E, char *to) const {
+        auto put = [to](size_t at, const auto &v) {
+            if (!v.empty()) std::memcpy(to + at, v.data(), sizeof(v[0]) * v.size());
+        };
+        put(sweeps, E.sweeps);
+        put(gates, E.gates);
+        put(tile_gates, E.tile_gates);
+        put(mats, E.pool);
+        put(chans, E.chans);
+        put(pbar, E.pbar);
+        put(members, E.members);
+        put(fmats, E.fmats);
+    }
 };
 
 BatchBuffers &batch_buffers() {
@@ -3735,7 +3790,8 @@ void plan_waves(std::vector<qs::BatchJob> &jobs, const std::vector<qs::BatchCirc
             qs::BatchJob &J = jobs[j];
             const qs::BatchCircuit &C = circs[size_t(J.circuit)];
             const size_t need = size_t(1) << C.n;
-            const size_t pat = C.nch > 0 ? (size_t(C.pool_len) + 63) & ~size_t(63) : 0;
+            const size_t pat =
+                C.nch > 0 ? (plans[size_t(J.circuit)].plan->pool.size() + 63) & ~size_t(63) : 0;
             if (w.count > 0 && (amps + need > kWaveAmps || patched + pat > kWavePatched)) break;
             J.slot = int64_t(amps);
             J.mine = int64_t(patched0 + patched);
@@ -3863,31 +3919,16 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
     for (int it = 0; it < n_items; ++it)
         if (pieces[it].status != QS_OK) return fail(pieces[it].status, pieces[it].error);
 
-    // ---- the launch's tables: each circuit's pieces with shifted offsets
-    size_t n_sweeps = 0, n_gates = 0, n_tgates = 0, n_pool = 0, n_chans = 0, n_pbar = 0, n_members = 0, n_fmats = 0, n_ro = 0;
+    // ---- what the call's circuits add up to
+    size_t n_ro = 0;
     bool wide_k5 = false;
     int64_t max_pool = 0, total_jobs = 0, total_samples = 0, total_choices = 0;
     for (int it = 0; it < n_items; ++it) {
         const BatchPlanEntry &E = *plans[it].plan;
         qs::BatchCircuit &C = circs[it];
-        C.s0 = int(n_sweeps);
-        C.s1 = int(n_sweeps + E.sweeps.size());
-        C.g0 = int(n_gates);
         C.n_gates = int(E.gates.size());
-        C.tg0 = int(n_tgates);
-        C.ch0 = int(n_chans);
         C.nch = int(E.chans.size());
-        C.pool0 = int(n_pool);
-        C.pool_len = int(E.pool.size());
         if (C.readout >= 0) C.readout = int(n_ro);
-        n_sweeps += E.sweeps.size();
-        n_gates += E.gates.size();
-        n_tgates += E.tile_gates.size();
-        n_pool += E.pool.size();
-        n_chans += E.chans.size();
-        n_pbar += E.pbar.size();
-        n_members += E.members.size();
-        n_fmats += E.fmats.size();
         n_ro += pieces[it].readout.size();
         wide_k5 |= E.k5;
         if (plans[it].resident && !E.chans.empty()) max_pool = std::max<int64_t>(max_pool, int64_t(E.pool.size()));
@@ -3895,8 +3936,6 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
         total_samples += items[it].n_traj * int64_t(items[it].n_samples);
         if (items[it].kraus_choices) total_choices += items[it].n_traj * int64_t(E.chans.size());
     }
-    if (n_pool > (size_t(1) << 30) || n_fmats > (size_t(1) << 30) || n_gates > (size_t(1) << 30))
-        return fail(QS_ERR_OUT_OF_MEMORY, "batched program too large");
 
     // ---- jobs: the resident ones first, largest first (the persistent workgroups
     // finish together), then the larger ones by sweep count
@@ -3965,21 +4004,13 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
     // ---- device buffers (one program allocation, one upload)
     auto align = [](size_t x) { return (x + 255) & ~size_t(255); };
     const size_t b_circ = align(sizeof(qs::BatchCircuit) * circs.size());
-    const size_t b_sweep = align(sizeof(qs::BatchSweep) * std::max<size_t>(n_sweeps, 1));
-    const size_t b_gate = align(sizeof(qs::BatchGate) * std::max<size_t>(n_gates, 1));
     const size_t b_job = align(sizeof(qs::BatchJob) * jobs.size());
-    const size_t b_pool = align(sizeof(float2) * std::max<size_t>(n_pool, 1));
     const size_t b_ro = align(sizeof(double) * std::max<size_t>(n_ro, 1));
-    const size_t b_chan = align(sizeof(qs::BatchChannel) * std::max<size_t>(n_chans, 1));
-    const size_t b_pbar = align(sizeof(double) * std::max<size_t>(n_pbar, 1));
-    const size_t b_mem = align(sizeof(qs::BatchMember) * std::max<size_t>(n_members, 1));
-    const size_t b_fmat = align(sizeof(double2) * std::max<size_t>(n_fmats, 1));
     const size_t b_out = align(sizeof(uint64_t) * size_t(std::max<int64_t>(total_samples, 1)));
     const size_t b_choice = align(size_t(std::max<int64_t>(total_choices, 1)));
-    const size_t b_tgate = align(sizeof(qs::BatchTileGate) * n_tgates);
     const size_t b_part = align(sizeof(qs::BatchPart) * parts.size());
-    const size_t prog_bytes =
-        b_circ + b_sweep + b_gate + b_job + b_pool + b_ro + b_chan + b_pbar + b_mem + b_fmat + b_tgate + b_part;
+    // the call's own part, then its outputs; the circuits' tables apart
+    const size_t prog_bytes = b_circ + b_job + b_ro + b_part;
     const size_t total = prog_bytes + b_out + b_choice;
     const size_t b_slots = sizeof(float2) * slot_amps;
     const size_t b_mptr = sizeof(float2 *) * n_mptr;
@@ -4004,72 +4035,84 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
         *cap = need;
         return QS_OK;
     };
-    QS_CHECK(grow_dev(reinterpret_cast<void **>(&BB.prog), &BB.prog_cap, total, "program buffers"));
+    QS_CHECK(grow_dev(reinterpret_cast<void **>(&BB.prog), &BB.prog_cap, b_out + b_choice, "output buffers"));
     QS_CHECK(grow_dev(reinterpret_cast<void **>(&BB.slots), &BB.slots_cap, b_slots, "state slots"));
     QS_CHECK(grow_dev(reinterpret_cast<void **>(&BB.patched), &BB.patched_cap, b_patched, "patched matrices"));
-    if (total > BB.host_cap) {
+    // the plans whose tables are not on the device yet
+    std::vector<std::pair<const BatchPlanEntry *, size_t>> fresh;  // and where they go
+    size_t fresh_bytes = 0, fresh_at = 0;
+    auto miss = [&](bool all) {
+        fresh.clear();
+        fresh_bytes = 0;
+        fresh_at = BB.tables_used;
+        std::map<std::shared_ptr<const BatchPlanEntry>, size_t> add;
+        for (int it = 0; it < n_items; ++it) {
+            const auto &P = plans[it].plan;
+            if ((!all && BB.tables_at.count(P)) || add.count(P)) continue;
+            add[P] = fresh_at + fresh_bytes;
+            fresh.emplace_back(P.get(), fresh_bytes);
+            fresh_bytes += BatchTableLayout(*P).bytes;
+        }
+        return add;
+    };
+    auto added = miss(false);
+    // (the call's own part is staged behind them, in the same copy)
+    if (fresh_at + fresh_bytes + prog_bytes > BB.tables_cap) {
+        // start over, in a larger area while it may grow (no launch reads the
+        // old one: every call ends with its stream idle)
+        BB.tables_at.clear();
+        BB.tables_used = 0;
+        added = miss(true);
+        const size_t need = fresh_bytes + prog_bytes;
+        if (need > BB.tables_cap || BB.tables_cap < kBatchTableBytes)
+            QS_CHECK(grow_dev(reinterpret_cast<void **>(&BB.tables), &BB.tables_cap,
+                              std::max(need, std::min(kBatchTableBytes, std::max(2 * BB.tables_cap, 4 * need))),
+                              "circuit tables"));
+    }
+    for (int it = 0; it < n_items; ++it) {
+        const auto &P = plans[it].plan;
+        const auto in = added.find(P);
+        const char *base = BB.tables + (in != added.end() ? in->second : BB.tables_at[P]);
+        const BatchTableLayout L(*P);
+        qs::BatchCircuit &C = circs[it];
+        C.sweeps = reinterpret_cast<const qs::BatchSweep *>(base + L.sweeps);
+        C.gates = reinterpret_cast<const qs::BatchGate *>(base + L.gates);
+        C.tile_gates = reinterpret_cast<const qs::BatchTileGate *>(base + L.tile_gates);
+        C.mats = reinterpret_cast<const float2 *>(base + L.mats);
+        C.chans = reinterpret_cast<const qs::BatchChannel *>(base + L.chans);
+        C.pbar = reinterpret_cast<const double *>(base + L.pbar);
+        C.members = reinterpret_cast<const qs::BatchMember *>(base + L.members);
+        C.fmats = reinterpret_cast<const double2 *>(base + L.fmats);
+    }
+    const size_t host_bytes = total + fresh_bytes;
+    if (host_bytes > BB.host_cap) {
         if (BB.host) (void)hipHostFree(BB.host);
         BB.host = nullptr;
         BB.host_cap = 0;
-        if (hipHostMalloc(reinterpret_cast<void **>(&BB.host), total, hipHostMallocDefault) != hipSuccess) {
+        if (hipHostMalloc(reinterpret_cast<void **>(&BB.host), host_bytes, hipHostMallocDefault) != hipSuccess) {
             (void)hipGetLastError();
             return fail(QS_ERR_OUT_OF_MEMORY, "allocating pinned staging failed");
         }
-        BB.host_cap = total;
+        BB.host_cap = host_bytes;
     }
-    char *dbuf = BB.prog;
-    char *hostp = BB.host;
+    char *fresh_host = BB.host;
+    char *hostp = BB.host + fresh_bytes;
+    char *dbuf = BB.tables + fresh_at + fresh_bytes;
+    char *dout = BB.prog, *hout = hostp + prog_bytes;
     // the program, written straight into the pinned staging
-    size_t o_circ = 0, o_sweep = o_circ + b_circ, o_gate = o_sweep + b_sweep, o_job = o_gate + b_gate,
-           o_pool = o_job + b_job, o_ro = o_pool + b_pool, o_chan = o_ro + b_ro, o_pbar = o_chan + b_chan,
-           o_mem = o_pbar + b_pbar, o_fmat = o_mem + b_mem, o_tgate = o_fmat + b_fmat, o_part = o_tgate + b_tgate, o_out = o_part + b_part,
-           o_choice = o_out + b_out;
+    const size_t o_circ = 0, o_job = o_circ + b_circ, o_ro = o_job + b_job, o_part = o_ro + b_ro,
+                 o_out = 0, o_choice = o_out + b_out;
     std::memcpy(hostp + o_circ, circs.data(), sizeof(qs::BatchCircuit) * circs.size());
     std::memcpy(hostp + o_job, jobs.data(), sizeof(qs::BatchJob) * jobs.size());
     if (!parts.empty()) std::memcpy(hostp + o_part, parts.data(), sizeof(qs::BatchPart) * parts.size());
-    {
-        auto *sw = reinterpret_cast<qs::BatchSweep *>(hostp + o_sweep);
-        auto *gt = reinterpret_cast<qs::BatchGate *>(hostp + o_gate);
-        auto *tg = reinterpret_cast<qs::BatchTileGate *>(hostp + o_tgate);
-        auto *pl = reinterpret_cast<float2 *>(hostp + o_pool);
-        auto *ro = reinterpret_cast<double *>(hostp + o_ro);
-        auto *chn = reinterpret_cast<qs::BatchChannel *>(hostp + o_chan);
-        auto *pb = reinterpret_cast<double *>(hostp + o_pbar);
-        auto *mem = reinterpret_cast<qs::BatchMember *>(hostp + o_mem);
-        auto *fm = reinterpret_cast<double2 *>(hostp + o_fmat);
-        size_t ps = 0, bs = 0, ms = 0, fs = 0;
-        for (int it = 0; it < n_items; ++it) {
-            const BatchPlanEntry &E = *plans[it].plan;
-            const int pshift = int(ps), bshift = int(bs), mshift = int(ms), fshift = int(fs);
-            sw = std::copy(E.sweeps.begin(), E.sweeps.end(), sw);
-            tg = std::copy(E.tile_gates.begin(), E.tile_gates.end(), tg);
-            for (qs::BatchGate G : E.gates) {
-                G.mat += pshift;
-                G.m0 += mshift;
-                G.m1 += mshift;
-                *gt++ = G;
-            }
-            for (qs::BatchChannel c : E.chans) {
-                c.pbar += bshift;
-                c.unit += fshift;
-                *chn++ = c;
-            }
-            for (qs::BatchMember M : E.members) {
-                if (M.src >= 0) M.src += fshift;
-                *mem++ = M;
-            }
-            if (!E.pool.empty()) std::memcpy(pl + ps, E.pool.data(), sizeof(float2) * E.pool.size());
-            if (!E.pbar.empty()) std::memcpy(pb + bs, E.pbar.data(), sizeof(double) * E.pbar.size());
-            if (!E.fmats.empty()) std::memcpy(fm + fs, E.fmats.data(), sizeof(double2) * E.fmats.size());
-            if (circs[it].readout >= 0)
-                std::memcpy(ro + circs[it].readout, pieces[it].readout.data(),
-                            sizeof(double) * pieces[it].readout.size());
-            ps += E.pool.size();
-            bs += E.pbar.size();
-            ms += E.members.size();
-            fs += E.fmats.size();
-        }
-    }
+    for (int it = 0; it < n_items; ++it)
+        if (circs[it].readout >= 0)
+            std::memcpy(reinterpret_cast<double *>(hostp + o_ro) + circs[it].readout, pieces[it].readout.data(),
+                        sizeof(double) * pieces[it].readout.size());
+    HostPool::get().run(fresh.size(), 4, 16u, [&](size_t lo, size_t hi) {
+        for (size_t i = lo; i < hi; ++i)
+            BatchTableLayout(*fresh[i].first).write(*fresh[i].first, fresh_host + fresh[i].second);
+    });
     const auto t_plan = std::chrono::steady_clock::now();
     r->plan_seconds = std::chrono::duration<double>(t_plan - t0).count();
     std::vector<char> direct(size_t(n_items), 0);
@@ -4079,25 +4122,19 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
     qs_status status = QS_OK;
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     do {
-        if ((e = hipMemcpyAsync(dbuf, hostp, prog_bytes, hipMemcpyHostToDevice, st)) != hipSuccess) break;
+        if ((e = hipMemcpyAsync(BB.tables + fresh_at, fresh_host, fresh_bytes + prog_bytes, hipMemcpyHostToDevice,
+                                st)) != hipSuccess)
+            break;
         qs::BatchArgs A;
         A.circs = reinterpret_cast<const qs::BatchCircuit *>(dbuf + o_circ);
-        A.sweeps = reinterpret_cast<const qs::BatchSweep *>(dbuf + o_sweep);
-        A.gates = reinterpret_cast<const qs::BatchGate *>(dbuf + o_gate);
-        A.tile_gates = reinterpret_cast<const qs::BatchTileGate *>(dbuf + o_tgate);
         A.jobs = reinterpret_cast<const qs::BatchJob *>(dbuf + o_job);
-        A.mats = reinterpret_cast<const float2 *>(dbuf + o_pool);
         A.readout = reinterpret_cast<const double *>(dbuf + o_ro);
-        A.chans = reinterpret_cast<const qs::BatchChannel *>(dbuf + o_chan);
-        A.pbar = reinterpret_cast<const double *>(dbuf + o_pbar);
-        A.members = reinterpret_cast<const qs::BatchMember *>(dbuf + o_mem);
-        A.fmats = reinterpret_cast<const double2 *>(dbuf + o_fmat);
         A.patched = BB.patched;
         A.patched_stride = int64_t(patched_stride);
-        A.choices = reinterpret_cast<int8_t *>(dbuf + o_choice);
+        A.choices = reinterpret_cast<int8_t *>(dout + o_choice);
         A.slots = b_slots ? BB.slots : nullptr;
         A.mptr = reinterpret_cast<const float2 **>(reinterpret_cast<char *>(BB.patched) + b_pmat);
-        A.out = reinterpret_cast<uint64_t *>(dbuf + o_out);
+        A.out = reinterpret_cast<uint64_t *>(dout + o_out);
         A.n_jobs = int(resident_jobs);
         const auto *dparts = reinterpret_cast<const qs::BatchPart *>(dbuf + o_part);
         const bool timing = (bp->flags & QS_TRAJ_TIME_KERNELS) != 0;
@@ -4128,7 +4165,7 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
             for (int it = 0; it < n_items && e == hipSuccess; ++it) {
                 const int64_t cnt = items[it].n_traj * int64_t(items[it].n_samples);
                 if (cnt > 0 && direct[size_t(it)])
-                    e = hipMemcpyAsync(items[it].bitstrings, dbuf + o_out + sizeof(uint64_t) * size_t(ob),
+                    e = hipMemcpyAsync(items[it].bitstrings, dout + o_out + sizeof(uint64_t) * size_t(ob),
                                        sizeof(uint64_t) * size_t(cnt), hipMemcpyDeviceToHost, st);
                 else if (cnt > 0)
                     staged = true;
@@ -4137,14 +4174,16 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
             if (e != hipSuccess) break;
         }
         if (staged &&
-            (e = hipMemcpyAsync(hostp + o_out, dbuf + o_out, sizeof(uint64_t) * size_t(total_samples),
+            (e = hipMemcpyAsync(hout + o_out, dout + o_out, sizeof(uint64_t) * size_t(total_samples),
                                 hipMemcpyDeviceToHost, st)) != hipSuccess)
             break;
         if (total_choices > 0 &&
-            (e = hipMemcpyAsync(hostp + o_choice, dbuf + o_choice, size_t(total_choices), hipMemcpyDeviceToHost,
+            (e = hipMemcpyAsync(hout + o_choice, dout + o_choice, size_t(total_choices), hipMemcpyDeviceToHost,
                                 st)) != hipSuccess)
             break;
         if ((e = hipStreamSynchronize(st)) != hipSuccess) break;
+        BB.tables_at.insert(added.begin(), added.end());
+        BB.tables_used += fresh_bytes;
         if (timing) {
             float ms = 0.f;
             if ((e = hipEventElapsedTime(&ms, ev0, ev1)) != hipSuccess) break;
@@ -4158,8 +4197,8 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
     if (ev1) (void)hipEventDestroy(ev1);
     if (status != QS_OK) return status;
     {
-        const uint64_t *out = reinterpret_cast<const uint64_t *>(hostp + o_out);
-        const int8_t *chs = reinterpret_cast<const int8_t *>(hostp + o_choice);
+        const uint64_t *out = reinterpret_cast<const uint64_t *>(hout + o_out);
+        const int8_t *chs = reinterpret_cast<const int8_t *>(hout + o_choice);
         int64_t ob = 0, cb = 0;
         for (int it = 0; it < n_items; ++it) {
             const int64_t cnt = items[it].n_traj * int64_t(items[it].n_samples);
