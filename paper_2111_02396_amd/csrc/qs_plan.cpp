@@ -488,70 +488,76 @@ std::vector<Sweep> group_sweeps_best(int n_qubits, const std::vector<Block> &blo
         z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
         return size_t((z ^ (z >> 31)) % m);
     };
-    std::vector<int> npred, ready, cands;
-    std::vector<char> in(n_qubits, 0);
+    // qubit sets as bit masks; a restart's sweeps in flat arrays, made into
+    // Sweeps only when it is the best so far
+    std::vector<uint64_t> mask(nb, 0), bits;
+    std::vector<int> slots(nb), npred, ready, cands(nb), order(nb), starts;
+    std::vector<int> ready0;
+    for (int b = 0; b < nb; ++b) {
+        for (int j = 0; j < blocks[b].k; ++j) mask[b] |= uint64_t(1) << blocks[b].q[j];
+        slots[b] = slot_per_k[blocks[b].k];
+        if (npred0[b] == 0) ready0.push_back(b);
+    }
+    const uint64_t low_mask = (uint64_t(1) << low) - 1;
     for (int r = 0; r < restarts; ++r) {
         npred = npred0;
-        ready.clear();
-        for (int b = 0; b < nb; ++b)
-            if (npred[b] == 0) ready.push_back(b);
-        std::vector<Sweep> cur;
+        ready = ready0;
+        starts.clear();
+        bits.clear();
         int done = 0;
         bool ok = true;
         while (done < nb) {
-            if (cur.size() + 1 >= best.size()) {  // cannot end with fewer sweeps
+            if (starts.size() + 1 >= best.size()) {  // cannot end with fewer sweeps
                 ok = false;
                 break;
             }
-            std::fill(in.begin(), in.end(), 0);
-            int nbits = 0, mats = 0;
-            for (int q = 0; q < low; ++q) {
-                in[q] = 1;
-                ++nbits;
-            }
-            Sweep sw;
+            uint64_t in = low_mask;
+            int nbits = low, mats = 0;
+            const int start = done;
             for (;;) {
-                if (int(sw.blocks.size()) >= max_blocks) break;
+                if (done - start >= max_blocks) break;
                 // the sweep's first block: any ready block that fits; later
                 // ones: the least qubit growth, ties drawn at random
-                cands.clear();
-                int least = 1 << 30;
-                for (int i = 0; i < int(ready.size()); ++i) {
-                    const Block &B = blocks[ready[i]];
-                    int g = 0;
-                    for (int j = 0; j < B.k; ++j) g += in[B.q[j]] ? 0 : 1;
-                    if (nbits + g > max_bits || mats + slot_per_k[B.k] > mat_budget) continue;
-                    const int key = sw.blocks.empty() ? 0 : g;
+                int n_cands = 0, least = 1 << 30;
+                const int n_ready = int(ready.size());
+                for (int i = 0; i < n_ready; ++i) {
+                    const int b = ready[i];
+                    const int g = __builtin_popcountll(mask[b] & ~in);
+                    if (nbits + g > max_bits || mats + slots[b] > mat_budget) continue;
+                    const int key = done == start ? 0 : g;
+                    if (key > least) continue;
                     if (key < least) {
                         least = key;
-                        cands.clear();
+                        n_cands = 0;
                     }
-                    if (key == least) cands.push_back(i);
+                    cands[n_cands++] = i;
                 }
-                if (cands.empty()) break;
-                const int pos = cands[draw(cands.size())];
+                if (n_cands == 0) break;
+                const int pos = cands[draw(size_t(n_cands))];
                 const int b = ready[pos];
                 ready.erase(ready.begin() + pos);
-                sw.blocks.push_back(b);
-                ++done;
-                mats += slot_per_k[blocks[b].k];
-                for (int j = 0; j < blocks[b].k; ++j)
-                    if (!in[blocks[b].q[j]]) {
-                        in[blocks[b].q[j]] = 1;
-                        ++nbits;
-                    }
+                order[done++] = b;
+                mats += slots[b];
+                in |= mask[b];
+                nbits = __builtin_popcountll(in);
                 for (int s2 : succ[b])
                     if (--npred[s2] == 0) ready.push_back(s2);
             }
-            if (sw.blocks.empty()) {
+            if (done == start) {
                 ok = false;
                 break;
             }
-            for (int q = 0; q < n_qubits; ++q)
-                if (in[q]) sw.bits.push_back(q);
-            cur.push_back(std::move(sw));
+            starts.push_back(start);
+            bits.push_back(in);
         }
-        if (ok && cur.size() < best.size()) best = std::move(cur);
+        if (!ok || starts.size() >= best.size()) continue;
+        best.assign(starts.size(), Sweep());
+        for (size_t u = 0; u < starts.size(); ++u) {
+            const int end = u + 1 < starts.size() ? starts[u + 1] : nb;
+            best[u].blocks.assign(order.begin() + starts[u], order.begin() + end);
+            for (int q = 0; q < n_qubits; ++q)
+                if ((bits[u] >> q) & 1) best[u].bits.push_back(q);
+        }
     }
     return best;
 }
