@@ -45,11 +45,17 @@ COUNTER_SUMMARY = os.path.join(ROOT, "profiles", "apply_tile_grid24_counters.md"
 
 # Flops per amplitude of a fused k-qubit block: the algorithmic count of a
 # complex 2^k x 2^k mat-vec (Section 3.1), and what the kernels issue: k = 3
-# on MFMA in the real form, k = 4 and 5 on MFMA with three real products
-# instead of four, k = 1 and 2 on VALU.
+# on FP32 MFMA in the real form, k = 5 with three real products instead of
+# four, k = 4 on BF16 MFMA with both operands split in three (six products of
+# the 32 x 32 real form; seven VALU instructions per amplitude split it) from
+# 14 qubits on and as k = 5 below; k = 1 and 2 on VALU.
 ALG_FLOPS = {k: 8 << k for k in range(1, 6)}
 MFMA_FLOPS = {3: 64, 4: 96, 5: 192}
+BF16_MFMA_PEAK_TFLOPS = 2500.0
+BF16_SPLIT_FLOPS = 768
+SPLIT_MIN_QUBITS = 14
 VALU_FLOPS = {1: 16, 2: 32}
+SPLIT_VALU_FLOPS = 14  # the issue slots of seven instructions, two flops each
 
 
 def kernel_source_digest() -> str:
@@ -113,10 +119,12 @@ def sweep_roofline(n, ms, launches, zero_start, k_hist):
     alg_bytes = 2 * state_bytes * launches - state_bytes * zero_start
     bytes_per_launch = alg_bytes / launches
     alg_flops = sum(k_hist[k] * ALG_FLOPS[k] for k in range(1, 6)) * amps
-    mfma_flops = sum(k_hist[k] * MFMA_FLOPS.get(k, 0) for k in range(1, 6)) * amps
-    valu_flops = sum(k_hist[k] * VALU_FLOPS.get(k, 0) for k in range(1, 6)) * amps
+    split = k_hist[4] * amps if n >= SPLIT_MIN_QUBITS else 0.0  # amplitudes of split 4-qubit blocks
+    mfma_flops = sum(k_hist[k] * MFMA_FLOPS.get(k, 0) for k in range(1, 6)) * amps - split * MFMA_FLOPS[4]
+    bf16_flops = split * BF16_SPLIT_FLOPS
+    valu_flops = sum(k_hist[k] * VALU_FLOPS.get(k, 0) for k in range(1, 6)) * amps + split * SPLIT_VALU_FLOPS
     hbm_us = bytes_per_launch / (HBM_PEAK_GBPS * 1e3)
-    mfma_us = mfma_flops / launches / (FP32_MFMA_PEAK_TFLOPS * 1e6)
+    mfma_us = (mfma_flops / FP32_MFMA_PEAK_TFLOPS + bf16_flops / BF16_MFMA_PEAK_TFLOPS) / launches / 1e6
     valu_us = valu_flops / launches / (FP32_VALU_PEAK_TFLOPS * 1e6)
     gbps = alg_bytes / sec / 1e9 if sec > 0 else 0.0
     return {
@@ -126,17 +134,18 @@ def sweep_roofline(n, ms, launches, zero_start, k_hist):
         "hbm": {"achieved": gbps, "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": gbps / HBM_PEAK_GBPS,
                 "algorithmic_bytes_per_launch": bytes_per_launch, "floor_us_per_launch": hbm_us},
         "compute": {
-            "mfma_issued_tflops": mfma_flops / sec / 1e12 if sec > 0 else 0.0,
-            "mfma_issued_frac": (mfma_flops / sec / 1e12) / FP32_MFMA_PEAK_TFLOPS if sec > 0 else 0.0,
+            "mfma_issued_tflops": (mfma_flops + bf16_flops) / sec / 1e12 if sec > 0 else 0.0,
+            "mfma_issued_frac": mfma_us * launches / 1e6 / sec if sec > 0 else 0.0,
             "algorithmic_tflops": alg_flops / sec / 1e12 if sec > 0 else 0.0,
             "algorithmic_frac_of_fp32_mfma_peak":
                 (alg_flops / sec / 1e12) / FP32_MFMA_PEAK_TFLOPS if sec > 0 else 0.0,
             "mfma_floor_us_per_launch": mfma_us,
             "valu_floor_us_per_launch": valu_us,
             "floor_us_per_launch": mfma_us + valu_us,
-            "basis": ("issued flops per amplitude: k=3 64 (real form), k=4 96 and k=5 192 "
-                      "(three real products) on FP32 MFMA at 157.3 TFLOP/s; k=1 16 and k=2 32 "
-                      "on FP32 VALU at 78.65 TFLOP/s (no packed FP32)"),
+            "basis": ("issued flops per amplitude: k=3 64 (real form) and k=5 192 (three real products) "
+                      "on FP32 MFMA at 157.3 TFLOP/s; k=4 768 (six products of operands split in three) "
+                      "on BF16 MFMA at 2500 TFLOP/s and 14 on VALU for the split from 14 qubits on, 96 on "
+                      "FP32 MFMA below; k=1 16 and k=2 32 on FP32 VALU at 78.65 TFLOP/s (no packed FP32)"),
         },
         "bound": "hbm" if hbm_us >= mfma_us + valu_us else "mfma",
     }

@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
 
 #include "qs_internal.h"
 #include "qs_philox.h"
@@ -636,6 +637,156 @@ __device__ __forceinline__ void staged_gate_mfma4(float2 *__restrict__ sd, const
     tile_gate_mfma4<L, NT>(sd, fp[0], fp[1], fp[2], reinterpret_cast<const int *>(frag + kFrag4)[lane], tab, tb);
 }
 
+// ---- k = 4 on BF16 MFMA with FP32 operands split in three
+// x = h + m + l with h, m, l BF16 (8 significant bits each, rounded to
+// nearest), exactly for every FP32 x away from the exponent's lower end.  Of
+// the nine products of a split operand pair the three below 2^-26 of the
+// largest are left out; the other six are exact in FP32 and are accumulated
+// in FP32 from the smallest up, 32 terms per instruction.  Against the FP32
+// form above: 192 matrix cycles per batch of 16 groups instead of 384, plus
+// 28 VALU instructions for the split, which can issue beside BF16 products
+// (beside FP32 ones none did): a block on 2^24 amplitudes takes 11.4 us
+// instead of 14, a 24-qubit sweep of four 65 instead of 75, a 28-qubit one
+// 1.03 ms instead of 1.11.  The result is nearer the 64-bit one: relative L2
+// error of noisy 15- to 30-qubit trajectories 0.4 to 0.9e-6 instead of 0.75
+// to 1.2e-6 (one rounding per 32 terms and product instead of one per 4, and
+// no sums of real and imaginary parts).  3-qubit blocks stay on FP32: split,
+// they measured no faster (their products are a third of the split's cost).
+// Used for the sweeps of states above kBatchLdsQubits qubits, whichever
+// launch runs them; resident states and the batched launch keep the FP32
+// form, in which their results are pinned.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+struct Split3 {
+    unsigned int h, m, l;  // two BF16 values each: low half from the first argument
+};
+__device__ __forceinline__ bf16x2 pack_bf16(float a, float b) {
+    const bf16x2 p = {(__bf16)a, (__bf16)b};  // round to nearest even
+    return p;
+}
+// Seven instructions for two values: the remainder x - h comes from a
+// two-term BF16 dot product with (-1, 0) or (0, -1), which needs no unpacking
+// (both terms and the result are exact).  The two constants are made opaque:
+// as inline constants both assemble to -1.0, which the instruction reads as
+// the second one.
+__device__ __forceinline__ bf16x2 opaque_bf16(unsigned int bits) {
+    asm("" : "+s"(bits));
+    return __builtin_bit_cast(bf16x2, bits);
+}
+__device__ __forceinline__ Split3 split3(float a, float b) {
+    const bf16x2 lo = opaque_bf16(0x0000bf80u), hi = opaque_bf16(0xbf800000u);
+    const bf16x2 h = pack_bf16(a, b);
+    a = __builtin_amdgcn_fdot2_f32_bf16(h, lo, a, false);
+    b = __builtin_amdgcn_fdot2_f32_bf16(h, hi, b, false);
+    const bf16x2 m = pack_bf16(a, b);
+    a = __builtin_amdgcn_fdot2_f32_bf16(m, lo, a, false);
+    b = __builtin_amdgcn_fdot2_f32_bf16(m, hi, b, false);
+    const bf16x2 l = pack_bf16(a, b);
+    return Split3{__builtin_bit_cast(unsigned int, h), __builtin_bit_cast(unsigned int, m),
+                  __builtin_bit_cast(unsigned int, l)};
+}
+__device__ __forceinline__ f32x4 mfma_bf16(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
+                                                   0, 0, 0);
+}
+
+// Issue priority of a split gate: products before splitting, so that the
+// matrix unit is fed while other wavefronts' VALU work fills the cycles in
+// between, and within each the wavefronts that have more batches to do (see
+// prio_for_remaining).
+__device__ __forceinline__ void prio_split(int remaining, bool products) {
+    if (products) {
+        if (remaining >= 3) __builtin_amdgcn_s_setprio(3);
+        else __builtin_amdgcn_s_setprio(2);
+    } else {
+        if (remaining >= 3) __builtin_amdgcn_s_setprio(1);
+        else __builtin_amdgcn_s_setprio(0);
+    }
+}
+
+// Fragments: for U[l % 16][4 (l / 16) + s] = a + ib, s < 4, the pair (a, -b)
+// split: dword 12 lane + 4 part + s, part 0 (h), 1 (m), 2 (l).  Lane table as
+// for k = 4.
+template <int NT = kBlock>
+__device__ __forceinline__ void stage_split4(unsigned int *__restrict__ frag, const float2 *__restrict__ u,
+                                             const int *tab) {
+    for (int i = threadIdx.x; i < 64 * 4; i += NT) {
+        const int lane = i >> 2, s = i & 3;
+        const float2 e = u[(lane & 15) * 16 + 4 * (lane >> 4) + s];
+        const Split3 f = split3(e.x, -e.y);
+        frag[12 * lane + s] = f.h;
+        frag[12 * lane + 4 + s] = f.m;
+        frag[12 * lane + 8 + s] = f.l;
+    }
+    stage_lane_table<NT>(reinterpret_cast<int *>(frag + kFrag4), tab, 4, 2);
+}
+
+// Lane (n, q) supplies amplitudes 4 q + s of group n as (x, y) pairs in the
+// contraction and gets amplitudes 4 q + r back, as in tile_gate_mfma4.  The
+// real part contracts with (a, -b), the imaginary one with (b, a), which is
+// the same dword with its halves swapped and the low one negated.
+template <class L, int NT>
+__device__ __forceinline__ void tile_gate_split4(float2 *__restrict__ sd, const float *__restrict__ frag,
+                                                 const int *tab, int tb) {
+    constexpr int W = NT / 64;
+    constexpr int LW = ilog2(W);
+    const int lane = threadIdx.x & 63, wave = wave_index();
+    const u32x4 *fp = reinterpret_cast<const u32x4 *>(frag + lane * 12);
+    u32x4 F[3], G[3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        F[p] = fp[p];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) G[p][s] = __builtin_amdgcn_alignbit(F[p][s], F[p][s], 16) ^ 0x8000u;
+    }
+    const int base = reinterpret_cast<const int *>(frag + kFrag4)[lane];
+    int a[4];  // amplitude 4q + s of the lane's group
+#pragma unroll
+    for (int s = 0; s < 4; ++s) a[s] = base ^ tab_xor<2>(tab, 0, s);
+    const int iters = (1 << (tb - 4 - 4)) / W;  // batches per wave: >= 1 needs tb >= 8 + log2 W
+    const int uw = tab_xor<LW>(tab, 8, wave);
+    int ub = uw;
+    float2 v[4];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) v[s] = lds_get(sd, a[s] ^ ub);
+    for (int it = 0; it < iters; ++it) {
+        prio_split(iters - it, false);
+        const int itn = it + 1 < iters ? it + 1 : it;
+        const int ubn = uw ^ tab_xor<kMaxTileBits - 8 - LW>(tab, 8 + LW, itn);
+        u32x4 E[3];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const Split3 e = split3(v[s].x, v[s].y);
+            E[0][s] = e.h;
+            E[1][s] = e.m;
+            E[2][s] = e.l;
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) v[s] = lds_get(sd, a[s] ^ ubn);
+        prio_split(iters - it, true);
+        f32x4 re = {0.f, 0.f, 0.f, 0.f}, im = {0.f, 0.f, 0.f, 0.f};
+        re = mfma_bf16(F[2], E[0], re);
+        im = mfma_bf16(G[2], E[0], im);
+        re = mfma_bf16(F[0], E[2], re);
+        im = mfma_bf16(G[0], E[2], im);
+        re = mfma_bf16(F[1], E[1], re);
+        im = mfma_bf16(G[1], E[1], im);
+        re = mfma_bf16(F[1], E[0], re);
+        im = mfma_bf16(G[1], E[0], im);
+        re = mfma_bf16(F[0], E[1], re);
+        im = mfma_bf16(G[0], E[1], im);
+        re = mfma_bf16(F[0], E[0], re);
+        im = mfma_bf16(G[0], E[0], im);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) lds_put2(sd, a[r] ^ ub, re[r], im[r]);
+        ub = ubn;
+    }
+    __builtin_amdgcn_s_setprio(0);
+}
+
 // The two output halves are formed one after the other from the same
 // inputs in registers.
 template <class L, int NT = kBlock>
@@ -713,7 +864,7 @@ __device__ __forceinline__ void tile_gate_mfma5(float2 *__restrict__ sd, const f
 // first + step, ... below last are this workgroup's.
 // K5V: 5-qubit blocks take the VALU path at any tile width (the batched
 // launch, whose resident states do).
-template <int TB, typename Idx, bool K5, int NT, bool RK, bool K5V, class Src>
+template <int TB, typename Idx, bool K5, int NT, bool RK, bool K5V, bool SP, class Src>
 __device__ __forceinline__ void tile_sweep(float2 *__restrict__ amp, Idx first, Idx step, Idx last, const Src &a,
                                            float2 *__restrict__ sd, float2 *__restrict__ sm) {
     constexpr int NB = ilog2(NT);
@@ -770,7 +921,8 @@ __device__ __forceinline__ void tile_sweep(float2 *__restrict__ amp, Idx first, 
 #pragma unroll
         for (int b = 0; b < kMaxTileBits; ++b) gtab[b] = a.tab(gi, b);
         if (k == 4) {
-            stage_frag4<NT>(reinterpret_cast<float *>(dst), src, gtab);
+            if constexpr (SP) stage_split4<NT>(reinterpret_cast<unsigned int *>(dst), src, gtab);
+            else stage_frag4<NT>(reinterpret_cast<float *>(dst), src, gtab);
         } else if (k == 3) {
             stage_frag3<NT>(reinterpret_cast<float *>(dst), src, gtab);
         } else if (k == 5) {
@@ -837,7 +989,11 @@ __device__ __forceinline__ void tile_sweep(float2 *__restrict__ amp, Idx first, 
                                                       tab, TB);
                     break;
                 case 4:
-                    staged_gate_mfma4<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)),
+if constexpr (SP)
+                        tile_gate_split4<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)), tab,
+                                                           TB);
+                    else
+                        staged_gate_mfma4<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)),
                                                       tab, TB);
                     break;
                 default:
@@ -944,14 +1100,14 @@ struct ArgSweep {
     __device__ __forceinline__ const float2 *mat(int gi) const { return a.g[gi].mat; }
 };
 
-template <int TB, typename Idx, bool K5, int NT, bool RK>
+template <int TB, typename Idx, bool K5, int NT, bool RK, bool SP>
 __global__ __launch_bounds__(NT) void apply_tile(float2 *__restrict__ amp, Idx n_tiles, TileArgs a) {
     // The tile is a static array (its LDS address is a link-time constant
     // that folds into the LDS instructions' offsets); the launch's matrices
     // follow it in dynamic LDS.
     __shared__ float2 sd[1 << TB];
     extern __shared__ float2 sm[];
-    tile_sweep<TB, Idx, K5, NT, RK, false>(amp, Idx(blockIdx.x), Idx(gridDim.x), n_tiles, ArgSweep{a}, sd, sm);
+    tile_sweep<TB, Idx, K5, NT, RK, false, SP>(amp, Idx(blockIdx.x), Idx(gridDim.x), n_tiles, ArgSweep{a}, sd, sm);
 }
 
 // One gate of at most four qubits over tiles, its matrix among the kernel's
@@ -975,7 +1131,7 @@ __global__ __launch_bounds__(kBlock) void apply_tile_one(MatArg<4>, float2 *__re
                                                          TileOneArgs a) {
     __shared__ float2 sd[1 << TB];
     __shared__ float2 sm[416];  // tile_mat_slots(4)
-    tile_sweep<TB, Idx, false, kBlock, false, false>(amp, Idx(blockIdx.x), Idx(gridDim.x), n_tiles, OneGate{a}, sd,
+    tile_sweep<TB, Idx, false, kBlock, false, false, false>(amp, Idx(blockIdx.x), Idx(gridDim.x), n_tiles, OneGate{a}, sd,
                                                      sm);
 }
 
@@ -1578,7 +1734,7 @@ __global__ __launch_bounds__(kBatchWideThreads) void batch_sweep(BatchArgs A, co
     src.g = (Gates)(C->tile_gates) + src.s->g0;
     src.m = (Words)(A.mptr) + J->mptr + src.s->g0;
     src.zero = step == 0 ? 1 : 0;
-    tile_sweep<kBatchTileBits, uint32_t, K5, kBatchWideThreads, false, true>(
+    tile_sweep<kBatchTileBits, uint32_t, K5, kBatchWideThreads, false, true, false>(
         A.slots + J->slot, uint32_t(P->tile0), 1u, uint32_t(P->tile0 + P->tiles), src, sd, sm);
 }
 
@@ -1739,7 +1895,7 @@ __global__ __launch_bounds__(kBatchWideThreads) void traj_sweep(const TrajSweep 
     TrajSweepSrc src;
     src.s = (const __attribute__((address_space(4))) TrajSweep *)(sweeps) + blockIdx.y;
     src.g = (const __attribute__((address_space(4))) TrajGate *)(gates) + src.s->g0;
-    tile_sweep<kBatchTileBits, uint32_t, false, kBatchWideThreads, true, true>(
+    tile_sweep<kBatchTileBits, uint32_t, false, kBatchWideThreads, true, true, true>(
         (float2 *)(src.s->amp), blockIdx.x, gridDim.x, n_tiles, src, sd, sm);
 }
 
@@ -2369,10 +2525,10 @@ int device_cus() {
 // Once per instantiation, thread-safely: allow the matrix region, and read
 // how many workgroups per CU registers and waves allow (with no matrices the
 // LDS is not what limits the count); a negative value is an error.
-template <int TB, typename Idx, bool K5, int NT, bool RK>
+template <int TB, typename Idx, bool K5, int NT, bool RK, bool SP>
 int tile_reg_limit() {
     static const int reg_limit = [] {
-        const void *fn = reinterpret_cast<const void *>(&apply_tile<TB, Idx, K5, NT, RK>);
+        const void *fn = reinterpret_cast<const void *>(&apply_tile<TB, Idx, K5, NT, RK, SP>);
         if (hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 int(sizeof(float2) * kTileMatBudget)) != hipSuccess)
             return -1;
@@ -2385,13 +2541,13 @@ int tile_reg_limit() {
 
 // launch = false only sets the instantiation up (no stream work), so that a
 // later launch under stream capture makes no attribute or occupancy calls.
-template <int TB, typename Idx, bool K5, int NT, bool RK>
+template <int TB, typename Idx, bool K5, int NT, bool RK, bool SP>
 hipError_t tile_launch(float2 *amp, int n, const TileArgs &a, hipStream_t st, bool launch,
                        int *grid_out) {
     // static tile + dynamic matrices
     const size_t dyn = sizeof(float2) * size_t(a.mat_total);
     const size_t lds = sizeof(float2) * (size_t(1) << TB) + dyn;
-    const int reg_limit = tile_reg_limit<TB, Idx, K5, NT, RK>();
+    const int reg_limit = tile_reg_limit<TB, Idx, K5, NT, RK, SP>();
     if (reg_limit < 0) return hipErrorInvalidDeviceFunction;
     const int cus = device_cus();
     if (!launch) return hipSuccess;
@@ -2404,7 +2560,7 @@ hipError_t tile_launch(float2 *amp, int n, const TileArgs &a, hipStream_t st, bo
     if (grid > uint64_t(n_tiles)) grid = uint64_t(n_tiles);
     if (RK && grid > uint64_t(kMaxReduceBlocks)) return hipErrorInvalidValue;  // record space
     if (grid_out) *grid_out = int(grid);
-    apply_tile<TB, Idx, K5, NT, RK><<<unsigned(grid), NT, dyn, st>>>(amp, n_tiles, a);
+    apply_tile<TB, Idx, K5, NT, RK, SP><<<unsigned(grid), NT, dyn, st>>>(amp, n_tiles, a);
     return hipGetLastError();
 }
 
@@ -2419,12 +2575,17 @@ hipError_t tile_launch_k(float2 *amp, int n, const TileArgs &a, hipStream_t st, 
     // more workgroups and do better with 256 (measured on the 24-qubit noisy
     // grid).
     constexpr int NT = TB >= 14 ? 1024 : (TB >= 13 ? 512 : kBlock);
-    if (a.rdm_out) {
-        if (k5) return hipErrorInvalidValue;
-        return tile_launch<TB, Idx, false, NT, true>(amp, n, a, st, launch, grid_out);
-    }
-    return k5 ? tile_launch<TB, Idx, true, NT, false>(amp, n, a, st, launch, grid_out)
-              : tile_launch<TB, Idx, false, NT, false>(amp, n, a, st, launch, grid_out);
+    auto go = [&](auto split) {
+        constexpr bool SP = decltype(split)::value;
+        if (a.rdm_out) {
+            if (k5) return hipErrorInvalidValue;
+            return tile_launch<TB, Idx, false, NT, true, SP>(amp, n, a, st, launch, grid_out);
+        }
+        return k5 ? tile_launch<TB, Idx, true, NT, false, SP>(amp, n, a, st, launch, grid_out)
+                  : tile_launch<TB, Idx, false, NT, false, SP>(amp, n, a, st, launch, grid_out);
+    };
+    if (n > kBatchLdsQubits) return go(std::true_type());
+    return go(std::false_type());
 }
 
 template <typename Idx>

@@ -70,6 +70,22 @@ def test_apply_gate_kernel_edges(qs, orc, k, n, low):
     assert rel_l2(got, ref) < AMP_TOL, t
 
 
+@pytest.mark.parametrize("tile_bits", [10, 11, 12, 13, 14])
+@pytest.mark.parametrize("n", [13, 14, 17])
+def test_four_qubit_blocks_by_tile_width(qs, orc, n, tile_bits):
+    """Dense 4-qubit blocks through the driver at every tile width, on both
+    sides of 14 qubits, where the sweeps change to split operands.  A block's
+    products and sums of 16 complex terms keep about 2^-23 of relative
+    accuracy each way, so 24 of them stay below 24 * 2^-22."""
+    rng = np.random.default_rng(100 * n + tile_bits)
+    ops = [W.Op(W.GATE, tuple(int(x) for x in rng.choice(n, size=4, replace=False)), [W.random_unitary(4, rng)], i, "u")
+           for i in range(24)]
+    c = W.Circuit(n, ops, "dense4")
+    with qs.State(n) as st:
+        got = qs.qs_run_trajectories(st.h, c, 1, max_fuse=4, tile_bits=tile_bits, return_state=True)["state"]
+    assert rel_l2(got, orc.simulate(c)) < 24 * 2.0 ** -22
+
+
 def test_norm_parity_and_determinism(qs, orc):
     rng = np.random.default_rng(5)
     for n in (3, 12, 20, 23):
