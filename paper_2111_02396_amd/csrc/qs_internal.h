@@ -376,8 +376,9 @@ hipError_t launch_batch_sample(const BatchArgs &a, int job0, int jobs, hipStream
 // Trajectories of resident states, one workgroup each.
 hipError_t launch_traj_resident(const TrajResidentArgs &a, int jobs, hipStream_t st);
 // One step of trajectories of n > kBatchLdsQubits qubits: `count` sweeps over
-// all their tiles (traj_sweep_records workgroups each), then its selections.
-int traj_sweep_records(int n);
+// all their tiles (traj_sweep_groups workgroups each, at most one per tile,
+// with a density-matrix record of each), then its selections.
+int traj_sweep_groups(int n, int count);
 hipError_t launch_traj_sweep(const TrajSweep *sweeps, const TrajGate *gates, int n, int count, hipStream_t st);
 hipError_t launch_traj_select(const TrajSelect *sels, int count, hipStream_t st);
 

@@ -1884,18 +1884,19 @@ struct TrajSweepSrc {
     __device__ __forceinline__ const float2 *mat(int gi) const { return (const float2 *)(g[gi].m); }
 };
 
-// Step of several trajectories: workgroup (x, y) takes tile x of sweep y.
-// One trajectory of 14..21 qubits has 2 to 256 tiles for 512 workgroup slots
-// and a sweep of it takes 12 to 20 us whatever its size, so the sweeps of
-// several trajectories share a launch.
-__global__ __launch_bounds__(kBatchWideThreads) void traj_sweep(const TrajSweep *sweeps, const TrajGate *gates,
-                                                                uint32_t n_tiles) {
+// Step of several trajectories: workgroup (x, y) takes tiles x, x + gridDim.x,
+// ... of sweep y.  One trajectory of 14..21 qubits has 2 to 256 tiles for 512
+// workgroup slots and a sweep of it takes 12 to 20 us whatever its size, so
+// the sweeps of several trajectories share a launch.
+template <int NT>
+__global__ __launch_bounds__(NT, 4) void traj_sweep(const TrajSweep *sweeps, const TrajGate *gates,
+                                                    uint32_t n_tiles) {
     __shared__ float2 sd[1 << kBatchTileBits];
     extern __shared__ float2 sm[];
     TrajSweepSrc src;
     src.s = (const __attribute__((address_space(4))) TrajSweep *)(sweeps) + blockIdx.y;
     src.g = (const __attribute__((address_space(4))) TrajGate *)(gates) + src.s->g0;
-    tile_sweep<kBatchTileBits, uint32_t, false, kBatchWideThreads, true, true, true>(
+    tile_sweep<kBatchTileBits, uint32_t, false, NT, true, true, true>(
         (float2 *)(src.s->amp), blockIdx.x, gridDim.x, n_tiles, src, sd, sm);
 }
 
@@ -2682,16 +2683,31 @@ hipError_t launch_traj_resident(const TrajResidentArgs &a, int jobs, hipStream_t
     return hipGetLastError();
 }
 
-int traj_sweep_records(int n) { return 1 << (n - kBatchTileBits); }
+// With no more tiles than CUs, a tile's workgroup has 16 wavefronts: alone on
+// its CU, eight leave two per SIMD (one 20-qubit trajectory, 128 tiles: 19 us
+// a launch with 512 work-items, 17.3 with 1024).  From twice the 512
+// resident workgroups on, each takes several tiles, so that the next tile's
+// loads run under this one's gates and the matrices are staged once for them
+// (20 trajectories of 21 qubits: 3.32 ms with a tile each, 2.81 like this).
+int traj_sweep_groups(int n, int count) {
+    int groups = 1 << (n - kBatchTileBits);
+    while (groups > 1 && int64_t(groups) * count >= 4 * int64_t(device_cus())) groups /= 2;
+    return groups;
+}
 
 hipError_t launch_traj_sweep(const TrajSweep *sweeps, const TrajGate *gates, int n, int count, hipStream_t st) {
     const size_t lds = sizeof(float2) * size_t(tile_mat_budget(kBatchTileBits));
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&traj_sweep),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
-    if (attr != hipSuccess) return attr;
+    static const hipError_t attr512 = hipFuncSetAttribute(reinterpret_cast<const void *>(&traj_sweep<512>),
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    static const hipError_t attr1024 = hipFuncSetAttribute(reinterpret_cast<const void *>(&traj_sweep<1024>),
+                                                           hipFuncAttributeMaxDynamicSharedMemorySize, int(lds));
+    if (attr512 != hipSuccess) return attr512;
+    if (attr1024 != hipSuccess) return attr1024;
     if (n <= kBatchTileBits || n > 31 || count < 1 || count > 65535) return hipErrorInvalidValue;
     const unsigned tiles = 1u << (n - kBatchTileBits);
-    traj_sweep<<<dim3(tiles, unsigned(count)), kBatchWideThreads, lds, st>>>(sweeps, gates, tiles);
+    const dim3 grid(unsigned(traj_sweep_groups(n, count)), unsigned(count));
+    if (int64_t(tiles) * count <= device_cus()) traj_sweep<1024><<<grid, 1024, lds, st>>>(sweeps, gates, tiles);
+    else traj_sweep<512><<<grid, 512, lds, st>>>(sweeps, gates, tiles);
     return hipGetLastError();
 }
 

@@ -2493,7 +2493,7 @@ struct Runner {
     bool ensure_side(int slots, bool all_states) {
         const size_t dim = size_t(1) << m.n;
         const size_t states = (all_states ? size_t(slots) : size_t(slots) - 1) * dim * sizeof(float2);
-        const size_t rec = resident() ? 0 : size_t(slots) * size_t(qs::traj_sweep_records(m.n)) * 8 * sizeof(double);
+        const size_t rec = resident() ? 0 : size_t(slots) * (size_t(1) << (m.n - qs::kBatchTileBits)) * 8 * sizeof(double);
         if (states + rec <= s->side_cap) return true;
         if (s->side_buf) {
             if (hipStreamSynchronize(s->st) != hipSuccess) return false;
@@ -2612,7 +2612,7 @@ struct Runner {
             D.nk = ci.nk;
             D.k = ci.k;
             D.Db = S.Db;
-            D.n_records = resident() ? 0 : qs::traj_sweep_records(m.n);
+            D.n_records = 0;  // set with the step's workgroup count
             for (int j = 0; j < 2; ++j) D.t[j] = j < ci.k ? ci.ts[j] : 0;
             choice_owner.emplace_back(first + which[i], S.channel);
         };
@@ -2656,7 +2656,7 @@ struct Runner {
             }
             if (has_last) queue[0].push_back(n_free);
         }
-        const size_t rec_len = size_t(qs::traj_sweep_records(m.n)) * 8;
+        const size_t rec_len = (size_t(1) << (m.n - qs::kBatchTileBits)) * 8;
         double *records = reinterpret_cast<double *>(side + size_t(slots - 1) * dim);
         struct Step {
             size_t c0, c1, s0, s1;
@@ -2691,6 +2691,8 @@ struct Runner {
             if (co == st.c0) break;
             st.c1 = co;
             st.s1 = so;
+            for (size_t i = st.s0; i < st.s1; ++i)
+                sels[i].n_records = qs::traj_sweep_groups(m.n, int(st.c1 - st.c0));
             steps.push_back(std::move(st));
         }
         QS_CHECK(arena_commit(s));
