@@ -551,7 +551,7 @@ __device__ __forceinline__ void stage_frag5(float *__restrict__ frag, const floa
 // this one's MFMAs, so the LDS latency hides behind them (batches touch
 // disjoint groups, so reading ahead of the writes is safe).  The batch index
 // b = wave + W it occupies the logical bits after the lane's group bits.
-template <class L, int NT = kBlock>
+template <class L, int NT = kBlock, bool PAIR = false>
 __device__ __forceinline__ void tile_gate_mfma3(float2 *__restrict__ sd, f32x4 afr, int a0, const int *tab,
                                                 int tb) {
     constexpr int W = NT / 64;
@@ -560,6 +560,46 @@ __device__ __forceinline__ void tile_gate_mfma3(float2 *__restrict__ sd, f32x4 a
     const int a1 = a0 ^ tab[0];  // amplitude 2q + 1
     const int iters = (1 << (tb - 3 - 4)) / W;  // batches per wave: >= 1 needs tb >= 7 + log2 W
     const int uw = tab_xor<LW>(tab, 7, wave);
+    if constexpr (PAIR) {
+        // two batches at a time: with two wavefronts per SIMD the chain of
+        // four dependent products per batch is what a block waits for (with
+        // the parallel member look-up of fuse_patched: 100 trajectories of the
+        // 12-qubit chain 134 -> 120 us, 300 of 13 qubits 382 -> 341 a call)
+        if (iters >= 2) {
+            auto part = [&](int it) { return uw ^ tab_xor<kMaxTileBits - 7 - LW>(tab, 7 + LW, it); };
+            int u0 = part(0), u1 = part(1);
+            float2 p0 = lds_get(sd, a0 ^ u0), p1 = lds_get(sd, a1 ^ u0);
+            float2 q0 = lds_get(sd, a0 ^ u1), q1 = lds_get(sd, a1 ^ u1);
+            for (int it = 0; it < iters; it += 2) {
+                prio_for_remaining(iters - it);
+                const int nx = it + 2 < iters ? it + 2 : it;
+                const int n0 = part(nx), n1 = part(nx + 1);
+                const float2 r0 = lds_get(sd, a0 ^ n0), r1 = lds_get(sd, a1 ^ n0);
+                const float2 s0 = lds_get(sd, a0 ^ n1), s1 = lds_get(sd, a1 ^ n1);
+                f32x4 x = {0.f, 0.f, 0.f, 0.f}, y = {0.f, 0.f, 0.f, 0.f};
+                x = __builtin_amdgcn_mfma_f32_16x16x4f32(afr[0], p0.x, x, 0, 0, 0);
+                y = __builtin_amdgcn_mfma_f32_16x16x4f32(afr[0], q0.x, y, 0, 0, 0);
+                x = __builtin_amdgcn_mfma_f32_16x16x4f32(afr[1], p0.y, x, 0, 0, 0);
+                y = __builtin_amdgcn_mfma_f32_16x16x4f32(afr[1], q0.y, y, 0, 0, 0);
+                x = __builtin_amdgcn_mfma_f32_16x16x4f32(afr[2], p1.x, x, 0, 0, 0);
+                y = __builtin_amdgcn_mfma_f32_16x16x4f32(afr[2], q1.x, y, 0, 0, 0);
+                x = __builtin_amdgcn_mfma_f32_16x16x4f32(afr[3], p1.y, x, 0, 0, 0);
+                y = __builtin_amdgcn_mfma_f32_16x16x4f32(afr[3], q1.y, y, 0, 0, 0);
+                lds_put(sd, a0 ^ u0, make_float2(x[0], x[1]));
+                lds_put(sd, a1 ^ u0, make_float2(x[2], x[3]));
+                lds_put(sd, a0 ^ u1, make_float2(y[0], y[1]));
+                lds_put(sd, a1 ^ u1, make_float2(y[2], y[3]));
+                u0 = n0;
+                u1 = n1;
+                p0 = r0;
+                p1 = r1;
+                q0 = s0;
+                q1 = s1;
+            }
+            __builtin_amdgcn_s_setprio(0);
+            return;
+        }
+    }
     int ub = uw;
     float2 v0 = lds_get(sd, a0 ^ ub), v1 = lds_get(sd, a1 ^ ub);
     for (int it = 0; it < iters; ++it) {
@@ -1249,7 +1289,7 @@ __device__ __forceinline__ void resident_gate(float2 *__restrict__ sd, float2 *w
         const float4 e = *reinterpret_cast<const float4 *>(lm + ((lane & 15) >> 1) * 8 + 2 * (lane >> 4));
         const bool im = lane & 1;
         const f32x4 afr = {im ? e.y : e.x, im ? e.x : -e.y, im ? e.w : e.z, im ? e.z : -e.w};
-        tile_gate_mfma3<SwizzledTile, NT>(sd, afr, lane_offset(tab, 3, 1), tab, tb);
+        tile_gate_mfma3<SwizzledTile, NT, true>(sd, afr, lane_offset(tab, 3, 1), tab, tb);
     } else if (k == 4 && tb >= M4) {
         const float4 *p = reinterpret_cast<const float4 *>(lm + (lane & 15) * 16 + 4 * (lane >> 4));
         const float4 e = p[0], f = p[1];
@@ -1430,7 +1470,7 @@ __device__ __forceinline__ void fuse_member_wide(double2 *col, double2 *old, int
 // qubits are staged in `ush`, 64 complex128), and writes it as complex64
 // to the job's copy of the block's matrix.  Channel picks are drawn again
 // (the same Philox call as the draw pass).
-__device__ __forceinline__ void fuse_patched(const BatchArgs &A, const BatchJob &J, const BatchCircuit &C,
+__device__ void fuse_patched(const BatchArgs &A, const BatchJob &J, const BatchCircuit &C,
                                              int rel, double2 *ws, double2 *ush, float2 *mine) {
     const BatchGate g = C.gates[rel];
     const int D = 1 << g.k;
@@ -1443,36 +1483,54 @@ __device__ __forceinline__ void fuse_patched(const BatchArgs &A, const BatchJob 
         const int c = c0 + lane;
         if (on)
             for (int r = 0; r < D; ++r) col[r] = make_double2(r == c ? 1.0 : 0.0, 0.0);
-        for (int mi = g.m0; mi < g.m1; ++mi) {
-            const BatchMember M = C.members[mi];
-            const double2 *U;
-            if (M.src >= 0) {
-                U = C.fmats + M.src;
-            } else {
-                const int ci = -M.src - 1;
-                const BatchChannel ch = C.chans[ci];
-                const int pick = draw_pick(C.pbar + ch.pbar, ch.nk,
-                                           philox_uniform(J.seed, uint32_t(ci), J.traj, J.circ_id, kStreamChannel));
-                if ((ch.identity >> pick) & 1u) continue;
-                U = C.fmats + ch.unit + pick * (1 << (2 * M.k));
-            }
-            int lpp = 0;
-#pragma unroll
-            for (int b = 0; b < kMaxGateQubits; ++b) lpp |= (M.lp[b] & 7) << (3 * b);
-            if (M.k <= 3) {
-                // the wavefront's lanes run in lockstep: the previous
-                // operator's reads precede these writes, and these writes
-                // precede the reads below
-                __builtin_amdgcn_wave_barrier();
-                if (lane < (1 << (2 * M.k))) ush[lane] = U[lane];
-                __builtin_amdgcn_wave_barrier();
-                if (on) {
-                    if (M.k == 1) fuse_member_small<1>(col, D, lpp, ush);
-                    else if (M.k == 2) fuse_member_small<2>(col, D, lpp, ush);
-                    else fuse_member_small<3>(col, D, lpp, ush);
+        for (int m0 = g.m0; m0 < g.m1; m0 += 64) {
+            // lane i resolves member m0 + i: width (0: an identity pick, left
+            // out), positions, and where its operator lies.  One by one, each
+            // member waited for four dependent loads and a draw (about 2 us).
+            const int count = g.m1 - m0 < 64 ? g.m1 - m0 : 64;
+            int mk = 0, mlpp = 0, moff = 0;
+            if (lane < count) {
+                const BatchMember M = C.members[m0 + lane];
+                mk = M.k;
+                moff = M.src;
+                if (M.src < 0) {
+                    const int ci = -M.src - 1;
+                    const BatchChannel ch = C.chans[ci];
+                    const int pick = draw_pick(C.pbar + ch.pbar, ch.nk,
+                                               philox_uniform(J.seed, uint32_t(ci), J.traj, J.circ_id,
+                                                              kStreamChannel));
+                    moff = ch.unit + pick * (1 << (2 * M.k));
+                    if ((ch.identity >> pick) & 1u) mk = 0;
                 }
-            } else if (on) {
-                fuse_member_wide(col, old, D, M.k, lpp, U);
+#pragma unroll
+                for (int b = 0; b < kMaxGateQubits; ++b) mlpp |= (M.lp[b] & 7) << (3 * b);
+            }
+            // operators of up to three qubits travel one member ahead
+            auto fetch = [&](int i) {
+                const int k = __builtin_amdgcn_readlane(mk, i);
+                const double2 *U = C.fmats + __builtin_amdgcn_readlane(moff, i);
+                return k >= 1 && k <= 3 && lane < (1 << (2 * k)) ? U[lane] : make_double2(0.0, 0.0);
+            };
+            double2 u = fetch(0);
+            for (int i = 0; i < count; ++i) {
+                const int k = __builtin_amdgcn_readlane(mk, i), lpp = __builtin_amdgcn_readlane(mlpp, i);
+                const double2 u_next = i + 1 < count ? fetch(i + 1) : u;
+                if (k >= 1 && k <= 3) {
+                    // the wavefront's lanes run in lockstep: the previous
+                    // operator's reads precede these writes, and these writes
+                    // precede the reads below
+                    __builtin_amdgcn_wave_barrier();
+                    if (lane < (1 << (2 * k))) ush[lane] = u;
+                    __builtin_amdgcn_wave_barrier();
+                    if (on) {
+                        if (k == 1) fuse_member_small<1>(col, D, lpp, ush);
+                        else if (k == 2) fuse_member_small<2>(col, D, lpp, ush);
+                        else fuse_member_small<3>(col, D, lpp, ush);
+                    }
+                } else if (k > 3 && on) {
+                    fuse_member_wide(col, old, D, k, lpp, C.fmats + __builtin_amdgcn_readlane(moff, i));
+                }
+                u = u_next;
             }
         }
         if (on) {
@@ -1505,12 +1563,13 @@ __device__ __forceinline__ void draw_and_patch(const BatchArgs &A, const BatchJo
     const int wave = int(threadIdx.x) >> 6;
     double2 *ws = ws4 + wave * 1024;
     double2 *ush = ush4 + wave * 64;
-    for (int w = wave; wave < 4 && w < words; w += 4) {
+    // the flagged blocks in turn to the four wavefronts, wherever they lie
+    for (int w = 0, turn = 0; wave < 4 && w < words; ++w) {
         uint32_t bits = __builtin_amdgcn_readfirstlane(mask[w]);
         while (bits) {
             const int b = __builtin_ctz(bits);
             bits &= bits - 1u;
-            fuse_patched(A, J, C, 32 * w + b, ws, ush, mine);
+            if ((turn++ & 3) == wave) fuse_patched(A, J, C, 32 * w + b, ws, ush, mine);
         }
     }
     __syncthreads();
