@@ -398,7 +398,7 @@ def sub_grid28(qs, W, torch, steps=3, max_fuse=4):
 
 def sub_batched(qs, W, torch, steps=2):
     """4096 trajectories = 256 circuits x 16, n ~ U{12..18}, depth ~ U{10..40},
-    depolarizing 1e-3, one persistent launch (fusion width autotuned); the same
+    depolarizing 1e-3, one batched call (fusion width autotuned); the same
     work one trajectory per qs_run_trajectories call on every 16th circuit."""
     items = W.batched_workload()
     n_traj = sum(w.n_traj for w in items)

@@ -328,7 +328,7 @@ qs_status qs_run_trajectories(qs_state s, const qs_circuit *c, const qs_traj_par
 qs_status qs_run_trajectories_concurrent(qs_state *states, int n_states, const qs_circuit *c,
                                          const qs_traj_params *p, qs_traj_result *r);
 
-/* ---- batched persistent launch ------------------------------------------ */
+/* ---- batched launch ------------------------------------------------------- */
 
 /* One circuit of a batched launch and where its results go. */
 typedef struct {
@@ -363,26 +363,26 @@ typedef struct {
     int64_t gate_blocks;       /* fused blocks applied, summed over trajectories */
     double host_seconds;       /* wall time of the call */
     double plan_seconds;       /* host planning (draws, patched blocks, packing) */
-    double kernel_ms;          /* QS_TRAJ_TIME_KERNELS: the persistent launch */
+    double kernel_ms;          /* QS_TRAJ_TIME_KERNELS: the call's kernels, from the first
+                                  to the last */
     int32_t max_fuse_used;     /* the fusion width the launch ran with */
     int32_t pad;
     double tune_ms;            /* wall time spent autotuning in this call (0 if cached/fixed) */
 } qs_batch_result;
 
-/* Many small noisy circuits in ONE persistent kernel launch (Section 3.5's
- * trajectories, run side by side).  Every trajectory's draws are resolved
- * from the Kraus bounds on the host (mixtures only), each circuit is fused
- * once (Section 3.2) and a trajectory carries only the blocks whose picks
- * differ from the circuit's most likely ones.  On the device each
- * workgroup takes trajectories in turn: a state of n <= 13 qubits lives in
- * LDS for the whole trajectory; a larger one streams 2^12-amplitude tiles
- * of a per-workgroup slot in device memory, one pass per tile sweep.  The
- * workgroup then samples with readout flips exactly as
- * qs_sample_measurements does (same Philox streams, circuit id from the
+/* Many small noisy circuits in one call (Section 3.5's trajectories, run
+ * side by side).  Each circuit is fused once (Section 3.2, on the host); the
+ * device draws every trajectory's channels and rebuilds the blocks whose
+ * picks differ from the circuit's most likely ones.  A state of n <= 13
+ * qubits lives in LDS for its whole trajectory, one workgroup of a
+ * persistent launch each.  Larger ones (n = 14..18) have a state each in
+ * device memory, up to 1 GiB of states at a time, and run as one launch per
+ * tile sweep over all of them.  Samples are drawn with readout flips exactly
+ * as qs_sample_measurements does (same Philox streams, circuit id from the
  * item).  Results are written to each item's host arrays.
  * Only mixtures of unitaries are taken: for them Algorithm 2 never needs an
  * inner product (the bounds sum to one), so every trajectory's program is
- * fixed before the launch and the workgroups never wait on a reduction.  A
+ * fixed by its draws and no kernel waits on a reduction.  A
  * channel with rank-deficient or non-normal Kraus operators (amplitude or
  * phase damping) needs the state-dependent second loop of Algorithm 2;
  * circuits with such channels go through qs_run_trajectories (the serving

@@ -430,7 +430,7 @@ class PreparedBatch:
 
 def qs_run_batched(workloads, max_fuse: int = 0, hip_stream: Optional[int] = None,
                    time_kernels: bool = False, record_choices: bool = True, copy: bool = True):
-    """Run workloads (or a PreparedBatch) in one persistent launch; returns
+    """Run workloads (or a PreparedBatch) in one batched call; returns
     per-workload {"samples", "choices"} and launch statistics.  With
     copy=False the arrays are views of a PreparedBatch's own buffers, valid
     until its next call."""

@@ -99,7 +99,7 @@ struct TileOneArgs {
     TileGate g;
 };
 
-// ---- batched persistent launch -------------------------------------------
+// ---- batched launches ----------------------------------------------------
 // Device program of many small circuits.  A circuit whose state fits in LDS
 // (n <= kBatchLdsQubits) runs one trajectory per workgroup iteration, the
 // state in LDS throughout; larger ones run as tile sweeps over all jobs of a

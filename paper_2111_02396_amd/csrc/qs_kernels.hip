@@ -1,16 +1,17 @@
 // gfx950 kernels for the state-vector hot path.
 //
-//  * gate application (Section 3.1, Algorithm 1), k <= 5: a direct path
-//    for gates whose targets are all >= 6 (one index group per work-item,
-//    64-amplitude rows per wavefront load) and a tiled path that stages
-//    2^tb-amplitude tiles in LDS for gates touching bits 0..5 and for
-//    several gates per sweep; fused matrices always sit in LDS and are read
-//    with wave-uniform (broadcast) addresses;
+//  * gate application (Section 3.1, Algorithm 1), k <= 5: single gates whose
+//    targets lie high enough straight from memory (amplitude pairs on VALU
+//    for k <= 2, MFMA for k >= 3), and a tiled path that stages
+//    2^tb-amplitude tiles in LDS for low targets and for several gates per
+//    sweep, of one state or of many trajectories' states in one launch;
+//  * small circuits (n <= 13) with the state in LDS from the first gate to
+//    the last sample;
 //  * FP64 reductions (norm, two-qubit reduced density matrix, the
 //    conventional method's trial norm) with a fixed grid and a fixed
 //    butterfly/tree order, so results are bit-identical run to run;
-//  * measurement sampling: FP64 block sums, one-workgroup scan, one
-//    work-item per sample with Philox draws.
+//  * measurement sampling: FP64 block sums, a tiled scan, one wavefront per
+//    sample with Philox draws.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

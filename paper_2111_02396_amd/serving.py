@@ -7,8 +7,8 @@ runs on one of two lanes:
 
 * the batch lane takes every admitted request with at most 18 qubits whose
   channels are all mixtures of unitaries and packs whatever is waiting into
-  one persistent launch (``qs_run_batched``); requests that arrive while a
-  launch runs join the next one;
+  one ``qs_run_batched`` call; requests that arrive while a call runs join
+  the next one;
 * the slot lane runs larger requests (or any other noise) with
   ``qs_run_trajectories``, each on its own stream and state, several at
   once, so their work overlaps on the device.
@@ -40,8 +40,8 @@ def footprint_bytes(n: int) -> int:
 def batchable(circuit) -> bool:
     """At most 18 qubits and every channel a mixture of unitaries (each
     K_i^dag K_i a multiple of I, as qs_kraus_bounds reports): Algorithm 2
-    then picks every Kraus operator from the bounds, which the persistent
-    launch requires."""
+    then picks every Kraus operator from the bounds, which the batched
+    call requires."""
     if circuit.n > BATCH_MAX_QUBITS:
         return False
     seen = {}
