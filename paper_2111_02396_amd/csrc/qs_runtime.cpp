@@ -1478,6 +1478,9 @@ struct TrajPlan {
 // resident at once).  From 22 qubits on one trajectory fills the GPU.
 constexpr int kSideTiles = 1024;
 constexpr int kSideMaxQubits = 21;
+// Samples and Z records a call holds on the device at once.
+constexpr int64_t kSampleRecords = int64_t(1) << 22;
+constexpr int64_t kZRecords = 4096;
 
 struct Runner {
     qs_state s;
@@ -2996,12 +2999,12 @@ struct Runner {
         QS_CHECK(fill_readout(m.n, p.p0to1, p.p1to0, ro));
         if (p.n_samples > 0) {
             const int64_t total = p.n_traj * int64_t(p.n_samples);
-            const int64_t cap = std::max<int64_t>(p.n_samples, std::min<int64_t>(total, int64_t(1) << 22));
+            const int64_t cap = std::max<int64_t>(p.n_samples, std::min<int64_t>(total, kSampleRecords));
             QS_CHECK(ensure_sampling(s, size_t(cap)));
         }
         QS_CHECK(ensure_reduce(s));
         if (res.z_expect && p.n_traj > 0)
-            QS_CHECK(ensure_zrecords(s, size_t(std::min<int64_t>(p.n_traj, 4096))));
+            QS_CHECK(ensure_zrecords(s, size_t(std::min<int64_t>(p.n_traj, kZRecords))));
         timing = (p.flags & QS_TRAJ_TIME_KERNELS) != 0;
         if (timing) QS_CHECK(timer.init(s, 256));
         // the in-place conventional mode runs on the delayed machinery (its
@@ -3052,16 +3055,42 @@ namespace {
 // times one pass of it from |0...0> on the state's own stream, keeping the
 // fastest; where the channels' bounds predict two or more inner-product
 // channels per trajectory, it times the call's first trajectories instead,
-// host planning included.  The choice is cached per (circuit, size, mode)
-// for the life of the process, so later calls, and the chunks of a
+// host planning included.  The choice is cached per (circuit, size, mode,
+// whether the call can run side by side) for the life of the process, so later calls, and the chunks of a
 // concurrent call, run the same plan.
 struct TuneKey {
     uint64_t hash;
     int n, mode, f_req, tb_req;
+    bool side;
     bool operator<(const TuneKey &o) const {
-        return std::tie(hash, n, mode, f_req, tb_req) < std::tie(o.hash, o.n, o.mode, o.f_req, o.tb_req);
+        return std::tie(hash, n, mode, f_req, tb_req, side) <
+               std::tie(o.hash, o.n, o.mode, o.f_req, o.tb_req, o.side);
     }
 };
+
+// Whether a call of 13 to 21 qubits runs side by side if its widths let it
+// (Runner::side_by_side: 13-bit tiles, and blocks of at most four qubits in
+// shared sweeps).  The tuner offers such a call no other widths: its trials
+// time one state's passes, which on these sizes are as fast or faster on
+// 12-bit tiles (one trajectory of 14 qubits 135 against 156 us, of 20 qubits
+// equal), and with that width the call would run its trajectories one by one:
+// 200 trajectories of the grid at depth 20, 12-bit tiles one by one against
+// 13-bit side by side: 13 qubits 11.2k against 53k trajectories/s, 14 qubits
+// 9.6k against 49k, 16 qubits 7.4k against 35k, 18 qubits 6.3k against 24k,
+// 20 qubits 4.2k against 10k.  A single trajectory, and a call that times its
+// kernels or replays a graph, is tuned over all widths as one state's passes.
+bool side_call(const CircuitModel &m, const qs_traj_params &p, bool z_records) {
+    if (p.mode != QS_KRAUS_DELAYED || (p.tile_bits != 0 && p.tile_bits != qs::kDefaultTileBits)) return false;
+    if (p.flags & QS_TRAJ_TIME_KERNELS) return false;
+    if ((p.flags & QS_TRAJ_GRAPH) && !(p.flags & QS_TRAJ_NO_GRAPH)) return false;
+    if (m.n < qs::kBatchLdsQubits || m.n > kSideMaxQubits || p.n_traj < 2) return false;
+    if (p.n_samples > 0 && p.n_traj > kSampleRecords / p.n_samples) return false;
+    if (z_records && p.n_traj > kZRecords) return false;
+    if (m.n == qs::kBatchLdsQubits) return true;
+    for (const ChannelInfo &c : m.channels)
+        if (!c.mixture && c.k != 1) return false;
+    return true;
+}
 constexpr double kTuneMargin = 0.03;  // a candidate must beat the default widths by 3 %
 // From this many expected inner-product channels per trajectory on, the
 // trials are whole trajectories timed on the host clock (the host's
@@ -3091,7 +3120,7 @@ std::map<TuneKey, std::pair<int, int>> g_tune_cache;
 // The widths a call runs with (tiles: 1 = none).  Tunes when max_fuse is 0
 // in the delayed mode; otherwise max_fuse (0: 4) and tile_bits (0: 13).
 qs_status resolve_widths(qs_state s, const CircuitModel &m, uint64_t chash, const qs_traj_params &p,
-                         int *f_out, int *tb_out, double *tune_ms) {
+                         bool z_records, int *f_out, int *tb_out, double *tune_ms) {
     *tune_ms = 0.0;
     *f_out = p.max_fuse > 0 ? p.max_fuse : kDefaultFuse;
     *tb_out = p.tile_bits == 0 ? qs::kDefaultTileBits : p.tile_bits;
@@ -3099,12 +3128,15 @@ qs_status resolve_widths(qs_state s, const CircuitModel &m, uint64_t chash, cons
                        (p.tile_bits >= 10 && p.tile_bits <= qs::kMaxTileBits);
     if (p.max_fuse != 0 || p.mode != QS_KRAUS_DELAYED || p.n_traj <= 0 || !tb_ok || m.n != s->n)
         return QS_OK;
-    const std::vector<int> fs = m.n < 16 ? std::vector<int>{2, 3, 4, 5} : std::vector<int>{3, 4, 5};
+    const bool side = side_call(m, p, z_records);
+    std::vector<int> fs = m.n < 16 ? std::vector<int>{2, 3, 4, 5} : std::vector<int>{3, 4, 5};
+    if (side && m.n > qs::kBatchLdsQubits) fs.pop_back();
     std::vector<int> tbs;
     if (p.tile_bits != 0) tbs = {p.tile_bits};
+    else if (side) tbs = {qs::kDefaultTileBits};
     else if (m.n > 12) tbs = {12, 13, 14};  // smaller states fit one tile of any of these widths
     else tbs = {qs::kDefaultTileBits};
-    const TuneKey key{chash, m.n, p.mode, p.max_fuse, p.tile_bits};
+    const TuneKey key{chash, m.n, p.mode, p.max_fuse, p.tile_bits, side};
     std::lock_guard<std::mutex> lock(g_tune_mu);
     auto it = g_tune_cache.find(key);
     if (it != g_tune_cache.end()) {
@@ -3235,7 +3267,7 @@ qs_status run_trajectories_impl(qs_state s, const qs_circuit *c, const qs_traj_p
     const uint64_t chash = me->id;
     qs_traj_params q = *p;
     double tms = 0.0;
-    QS_CHECK(resolve_widths(s, m, chash, *p, &q.max_fuse, &q.tile_bits, &tms));
+    QS_CHECK(resolve_widths(s, m, chash, *p, r->z_expect != nullptr, &q.max_fuse, &q.tile_bits, &tms));
     r->max_fuse_used = q.max_fuse;
     r->tile_bits_used = tile_bits_reported(m.n, q.tile_bits);
     r->tune_ms = tms;
@@ -3303,7 +3335,7 @@ qs_status qs_run_trajectories_concurrent(qs_state *states, int n_states, const q
         }
         const CircuitModel &m = p->mode == QS_KRAUS_CONVENTIONAL_INPLACE ? conv : me->model;
         QS_CHECK(flush_pending(states[0]));
-        QS_CHECK(resolve_widths(states[0], m, me->id, *p, &pr.max_fuse, &pr.tile_bits, &tms));
+        QS_CHECK(resolve_widths(states[0], m, me->id, *p, r->z_expect != nullptr, &pr.max_fuse, &pr.tile_bits, &tms));
     }
     // contiguous chunks, the first (n_traj mod n_states) one trajectory longer
     std::vector<qs_traj_params> sp(n_states, pr);

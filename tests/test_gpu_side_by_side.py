@@ -70,3 +70,29 @@ def test_range_split_keeps_results(qs):
                 part = qs.qs_run_trajectories(st.h, c, count, seed=1, max_fuse=4, traj_offset=first, return_state=True)
                 assert np.array_equal(part["choices"], whole["choices"][first:first + count])
         assert np.array_equal(part["state"], whole["state"])
+
+
+@pytest.mark.parametrize("n,n_traj,states", [(13, 2, 1), (13, 9, 2), (14, 2, 1), (14, 3, 2), (16, 5, 1),
+                                             (21, 2, 1), (21, 3, 2)])
+def test_tuned_calls_keep_the_widths_that_run_side_by_side(qs, n, n_traj, states):
+    """With both widths left to the tuner, a call that can run side by side is
+    tuned over the fusion width alone (at most four qubits from 14 qubits on),
+    and equals the one-by-one run with the same widths."""
+    c = _circuit(n, 5, False)
+    kw = dict(seed=6, traj_offset=1, n_samples=9, return_state=True)
+    handles = [qs.State(n) for _ in range(states)]
+    try:
+        hs = [h.h for h in handles]
+        got = qs.qs_run_trajectories(hs if states > 1 else hs[0], c, n_traj, max_fuse=0, **kw)
+        f, tb = got["max_fuse_used"], got["tile_bits_used"]
+        again = qs.qs_run_trajectories(hs[0], c, n_traj, max_fuse=0, **kw)
+        ref = qs.qs_run_trajectories(hs[0], c, n_traj, max_fuse=f, tile_bits=tb, time_kernels=True, **kw)
+    finally:
+        for h in handles:
+            h.close()
+    assert tb == 13 and (n == 13 or f <= 4)
+    assert again["tune_ms"] == 0.0
+    for key in ("choices", "paths", "samples"):
+        assert np.array_equal(got[key], ref[key]), key
+        assert np.array_equal(got[key], again[key]), key
+    assert rel_l2(got["state"], ref["state"]) < AMP_TOL
