@@ -23,6 +23,7 @@
 #include "qs_internal.h"
 #include "qs_philox.h"
 #include "qs_plan.h"
+#include "qs_pool.h"
 
 using qs::cd;
 
@@ -1359,88 +1360,6 @@ void segment_insert(const SegKey &k, const std::vector<qs::Sweep> &sw) {
     g_seg_fifo.push_back(k);
 }
 
-// Host worker threads for the planners' parallel loops, started on
-// first use and kept: starting threads on every call cost more than the
-// per-trajectory draws they share.  One loop runs at a time; the calling
-// thread takes part in it.
-class HostPool {
-  public:
-    static HostPool &get() {
-        static HostPool *pool = new HostPool();  // never destroyed: workers may outlive statics
-        return *pool;
-    }
-    unsigned size() const { return unsigned(workers_.size()) + 1; }
-    // fn(lo, hi) over [0, n) in chunks of `chunk`, on at most `width` threads.
-    void run(size_t n, size_t chunk, unsigned width, const std::function<void(size_t, size_t)> &fn) {
-        if (n == 0) return;
-        chunk = std::max<size_t>(chunk, 1);
-        width = std::max(1u, std::min(width, size()));
-        if (width == 1 || n <= chunk) {
-            fn(0, n);
-            return;
-        }
-        std::lock_guard<std::mutex> one(run_mu_);
-        {
-            std::lock_guard<std::mutex> lock(mu_);
-            fn_ = &fn;
-            n_ = n;
-            chunk_ = chunk;
-            next_.store(0);
-            helpers_ = width - 1;
-            busy_ = 0;
-            ++generation_;
-        }
-        cv_.notify_all();
-        drain();
-        // helpers that have not started by now stay out of this loop
-        std::unique_lock<std::mutex> lock(mu_);
-        helpers_ = 0;
-        done_cv_.wait(lock, [&] { return busy_ == 0; });
-        fn_ = nullptr;
-    }
-
-  private:
-    HostPool() {
-        const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
-        const unsigned nw = std::min(15u, hw > 1 ? hw - 1 : 0u);
-        for (unsigned i = 0; i < nw; ++i) workers_.emplace_back([this] { loop(); });
-        for (auto &w : workers_) w.detach();
-    }
-    void drain() {
-        for (;;) {
-            const size_t lo = next_.fetch_add(chunk_);
-            if (lo >= n_) return;
-            (*fn_)(lo, std::min(n_, lo + chunk_));
-        }
-    }
-    void loop() {
-        uint64_t seen = 0;
-        for (;;) {
-            {
-                std::unique_lock<std::mutex> lock(mu_);
-                cv_.wait(lock, [&] { return generation_ != seen && helpers_ > 0; });
-                seen = generation_;
-                --helpers_;
-                ++busy_;
-            }
-            drain();
-            {
-                std::lock_guard<std::mutex> lock(mu_);
-                --busy_;
-            }
-            done_cv_.notify_all();
-        }
-    }
-    std::vector<std::thread> workers_;
-    std::mutex run_mu_, mu_;
-    std::condition_variable cv_, done_cv_;
-    const std::function<void(size_t, size_t)> *fn_ = nullptr;
-    size_t n_ = 0, chunk_ = 1;
-    std::atomic<size_t> next_{0};
-    unsigned helpers_ = 0, busy_ = 0;
-    uint64_t generation_ = 0;
-};
-
 // A trajectory's program for the launches that run several side by side: the
 // blocks in launch order, cut into sweeps (n > kBatchLdsQubits) and with a
 // selection per inner-product channel.  Offsets are float2 in `mats`.
@@ -1481,6 +1400,21 @@ constexpr int kSideMaxQubits = 21;
 // Samples and Z records a call holds on the device at once.
 constexpr int64_t kSampleRecords = int64_t(1) << 22;
 constexpr int64_t kZRecords = 4096;
+
+// Expected channels per trajectory that need inner products: for each
+// channel that is not a mixture of unitaries, the chance that the draw lands
+// past the sum of its bounds (Algorithm 2 resolves every other draw from the
+// bounds alone).
+double expected_slow_paths(const CircuitModel &m) {
+    double e = 0.0;
+    for (const ChannelInfo &c : m.channels) {
+        if (c.mixture) continue;
+        double sum = 0.0;
+        for (double x : c.pbar) sum += x;
+        e += std::max(0.0, 1.0 - sum);
+    }
+    return e;
+}
 
 struct Runner {
     qs_state s;
@@ -2731,7 +2665,12 @@ struct Runner {
         for (int64_t first = 0; first < p.n_traj; first += chunk) {
             const int64_t count = std::min<int64_t>(chunk, p.n_traj - first);
             plans.resize(size_t(count));
-            HostPool::get().run(size_t(count), 1, 16u, [&](size_t lo, size_t hi) {
+            // a thread for about 40 us of planning (1000 operations; a channel that
+            // needs inner products weighs as 500): less is done before a helper
+            // is awake
+            const double load = double(count) * (double(m.ops.size()) + 500.0 * expected_slow_paths(m));
+            const unsigned threads = unsigned(std::min(16.0, 1.0 + load / 1000.0));
+            qs::HostPool::get().run(size_t(count), 1, threads, [&](size_t lo, size_t hi) {
                 for (size_t i = lo; i < hi; ++i)
                     plan_trajectory(first + int64_t(i), uint32_t(p.traj_offset + first + int64_t(i)), plans[i]);
             });
@@ -3100,20 +3039,6 @@ constexpr double kTuneSlowPaths = 2.0;
 constexpr double kTuneTrajMargin = 0.05;
 constexpr int64_t kTuneTrajectories = 4;
 
-// Expected channels per trajectory that need inner products: for each
-// channel that is not a mixture of unitaries, the chance that the draw lands
-// past the sum of its bounds (Algorithm 2 resolves every other draw from the
-// bounds alone).
-double expected_slow_paths(const CircuitModel &m) {
-    double e = 0.0;
-    for (const ChannelInfo &c : m.channels) {
-        if (c.mixture) continue;
-        double sum = 0.0;
-        for (double x : c.pbar) sum += x;
-        e += std::max(0.0, 1.0 - sum);
-    }
-    return e;
-}
 std::mutex g_tune_mu;  // one tuning at a time: concurrent trials would disturb each other's timings
 std::map<TuneKey, std::pair<int, int>> g_tune_cache;
 
@@ -3947,7 +3872,7 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
             P.plan = std::move(e);
         }
     };
-    HostPool::get().run(size_t(n_items), 1, 16u, [&](size_t lo, size_t hi) {
+    qs::HostPool::get().run(size_t(n_items), 1, 16u, [&](size_t lo, size_t hi) {
         for (size_t it = lo; it < hi; ++it) plan_one(int(it));
     });
     for (int it = 0; it < n_items; ++it)
@@ -4143,7 +4068,7 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
         if (circs[it].readout >= 0)
             std::memcpy(reinterpret_cast<double *>(hostp + o_ro) + circs[it].readout, pieces[it].readout.data(),
                         sizeof(double) * pieces[it].readout.size());
-    HostPool::get().run(fresh.size(), 4, 16u, [&](size_t lo, size_t hi) {
+    qs::HostPool::get().run(fresh.size(), 4, 16u, [&](size_t lo, size_t hi) {
         for (size_t i = lo; i < hi; ++i)
             BatchTableLayout(*fresh[i].first).write(*fresh[i].first, fresh_host + fresh[i].second);
     });
