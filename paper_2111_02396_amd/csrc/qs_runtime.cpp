@@ -2248,13 +2248,40 @@ struct Runner {
         if (p.tile_bits != 0 && p.tile_bits != qs::kDefaultTileBits) return false;
         if (p.n_traj * int64_t(std::max(p.n_samples, 0)) > int64_t(s->samp_cap) && p.n_samples > 0) return false;
         if (res.z_expect && p.n_traj > int64_t(s->z_cap)) return false;
-        if (resident()) return true;
+        if (resident()) return resident_pays();
         if (m.n > kSideMaxQubits || p.n_traj < 2) return false;
         for (const ChannelInfo &c : m.channels)
             if (!c.mixture && c.k != 1) return false;
         for (const qs::Block &b : blocks)
             if (b.k > 4) return false;
         return true;
+    }
+
+    // Whether a call of resident states is faster side by side.  A few
+    // trajectories are not where a workgroup is the slower place for their
+    // blocks.  From three 5-qubit blocks on: they run on VALU there, but on
+    // MFMA one by one from 11 qubits on (noiseless at max_fuse 5, in us a call
+    // side by side and one by one: one of 11 / 12 / 13 qubits 343 / 355 / 396
+    // and 104 / 125 / 176, three 350 / 365 / 404 and 241 / 307 / 440, four of
+    // 11 354 and 309, thirty-two 401 / 416 / 458 and 2200 / 2894 / 4363), and
+    // below 10 qubits on more than one workgroup (one of 6 / 9 qubits 193 / 238
+    // and 145 / 184; of 10, on one either way, 256 and 280).  A 13-qubit state
+    // without inner-product channels fills a workgroup's tile either way, and
+    // small blocks cross it faster in sweeps (max_fuse 1 / 2 / 3 204 / 205 /
+    // 138 and 189 / 189 / 126; with 4-qubit blocks 110 and 120).
+    bool resident_pays() const {
+        size_t k5 = 0, k4 = 0, all = 0;
+        for (const BlockDesc &d : block_desc) {
+            if (d.identity) continue;
+            ++all;
+            k5 += d.g.k == 5;
+            k4 += d.g.k == 4;
+        }
+        if (k5 > 2 || 2 * k5 > all) return m.n == 10 || p.n_traj > (m.n < 10 ? 1 : m.n == 11 ? 4 : 3);
+        if (m.n < qs::kBatchLdsQubits || p.n_traj > 1 || k4 + k5 > 0) return true;
+        for (const ChannelInfo &c : m.channels)
+            if (!c.mixture) return true;
+        return false;
     }
 
     // Program of one trajectory (any host thread): as run_delayed, without

@@ -96,3 +96,19 @@ def test_tuned_calls_keep_the_widths_that_run_side_by_side(qs, n, n_traj, states
         assert np.array_equal(got[key], ref[key]), key
         assert np.array_equal(got[key], again[key]), key
     assert rel_l2(got["state"], ref["state"]) < AMP_TOL
+
+
+@pytest.mark.parametrize("n,n_traj,noise", [(11, 1, 0.0), (11, 4, 0.01), (12, 1, 0.01), (12, 3, 0.0), (13, 1, 0.0),
+                                            (13, 2, 0.01)])
+def test_few_trajectories_of_five_qubit_blocks_stay_on_the_matrix_units(qs, n, n_traj, noise):
+    """A workgroup per trajectory multiplies 5-qubit blocks on VALU, three
+    times as slow for a single one; such a call runs as the timed one does,
+    bit for bit."""
+    c = W.generic_grid_circuit(n, 12, p_dep=noise or None, gamma=noise or None, seed=n)
+    kw = dict(seed=4, max_fuse=5, n_samples=3, return_state=True)
+    with qs.State(n) as st:
+        got = qs.qs_run_trajectories(st.h, c, n_traj, **kw)
+        ref = qs.qs_run_trajectories(st.h, c, n_traj, time_kernels=True, **kw)
+    assert got["gate_k_launches"][5] > 0
+    for key in ("choices", "samples", "state"):
+        assert np.array_equal(got[key], ref[key]), key
