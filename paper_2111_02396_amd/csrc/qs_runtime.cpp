@@ -38,6 +38,10 @@ qs_status fail(qs_status st, const std::string &msg) {
 
 constexpr int kDefaultFuse = 4;
 constexpr size_t kArenaHalf = size_t(1) << 18;  // float2 per half of the staging ring (2 MiB)
+// The ring of a state that has only staged a few small trajectories at a time.
+// Device allocations below 2 MiB cost 1 us, larger ones 12 and as much again to
+// free, about a tenth of a request that makes a state for one small trajectory.
+constexpr size_t kArenaSmallHalf = size_t(1) << 16;
 constexpr double kRenormLogThreshold = -46.0;  // ~1e-20 on the norm squared
 // Where a sweep that forms a reduced density matrix writes its workgroup
 // records in the state's reduction buffer (past the norm pass's records).
@@ -81,6 +85,7 @@ struct qs_state_s {
     // device; a half is refilled only after its last copy has completed
     float2 *arena_dev = nullptr;
     float2 *arena_host = nullptr;
+    size_t arena_len = 0;        // float2 per half
     hipEvent_t arena_ev[2] = {};
     bool arena_live[2] = {false, false};
     int arena_half = 0;
@@ -164,20 +169,34 @@ void make_desc(int k, const int *t, const cd *m, qs::GateDesc &g) {
         g.m[i] = make_float2(float(sorted[i].real()), float(sorted[i].imag()));
 }
 
-qs_status ensure_arena(qs_state s) {
-    if (s->arena_dev) return QS_OK;
-    QS_HIP(s, hipMalloc(&s->arena_dev, sizeof(float2) * 2 * kArenaHalf));
-    QS_HIP(s, hipHostMalloc(&s->arena_host, sizeof(float2) * 2 * kArenaHalf, hipHostMallocDefault));
-    for (int i = 0; i < 2; ++i) QS_HIP(s, hipEventCreateWithFlags(&s->arena_ev[i], hipEventDisableTiming));
+// Makes the ring's halves hold `len` float2.  Only where nothing is staged
+// and no pending launch reads the ring.
+qs_status arena_reserve(qs_state s, size_t len) {
+    if (s->arena_len >= len) return QS_OK;
+    if (s->arena_dev) {
+        QS_HIP(s, hipStreamSynchronize(s->st));
+        QS_HIP(s, hipFree(s->arena_dev));
+        s->arena_dev = nullptr;
+        s->arena_len = 0;
+        QS_HIP(s, hipHostFree(s->arena_host));
+        s->arena_host = nullptr;
+    }
+    QS_HIP(s, hipMalloc(&s->arena_dev, sizeof(float2) * 2 * len));
+    QS_HIP(s, hipHostMalloc(&s->arena_host, sizeof(float2) * 2 * len, hipHostMallocDefault));
+    for (int i = 0; i < 2; ++i) {
+        if (!s->arena_ev[i]) QS_HIP(s, hipEventCreateWithFlags(&s->arena_ev[i], hipEventDisableTiming));
+        s->arena_live[i] = false;
+    }
     s->arena_half = 0;
     s->arena_head = s->arena_committed = 0;
+    s->arena_len = len;
     return QS_OK;
 }
 
 // Copy everything staged since the last commit to the device (one copy).
 qs_status arena_commit(qs_state s) {
     if (s->arena_head == s->arena_committed) return QS_OK;
-    const size_t base = size_t(s->arena_half) * kArenaHalf;
+    const size_t base = size_t(s->arena_half) * s->arena_len;
     QS_HIP(s, hipMemcpyAsync(s->arena_dev + base + s->arena_committed,
                              s->arena_host + base + s->arena_committed,
                              sizeof(float2) * (s->arena_head - s->arena_committed),
@@ -190,26 +209,26 @@ qs_status arena_commit(qs_state s) {
 
 // Whether `count` float2 fit in the current half without switching halves.
 bool arena_fits(qs_state s, size_t count) {
-    return s->arena_dev && s->arena_head + count <= kArenaHalf;
+    return s->arena_head + count <= s->arena_len;
 }
 
 // Reserve `count` float2 of staging; returns the host slot and device address.
 // A full half is committed and the other half reused once its copy is done.
 qs_status arena_stage(qs_state s, size_t count, float2 **host, const float2 **dev) {
-    QS_CHECK(ensure_arena(s));
-    if (count > kArenaHalf) return fail(QS_ERR_INVALID_ARGUMENT, "matrix staging request too large");
-    if (s->arena_head + count > kArenaHalf) {
+    if (!s->arena_dev) QS_CHECK(arena_reserve(s, kArenaHalf));
+    if (count > s->arena_len) return fail(QS_ERR_INVALID_ARGUMENT, "matrix staging request too large");
+    if (s->arena_head + count > s->arena_len) {
         QS_CHECK(arena_commit(s));
         s->arena_half ^= 1;
         if (s->arena_live[s->arena_half]) QS_HIP(s, hipEventSynchronize(s->arena_ev[s->arena_half]));
         s->arena_live[s->arena_half] = false;
         s->arena_head = s->arena_committed = 0;
     }
-    const size_t base = size_t(s->arena_half) * kArenaHalf + s->arena_head;
+    const size_t base = size_t(s->arena_half) * s->arena_len + s->arena_head;
     *host = s->arena_host + base;
     *dev = s->arena_dev + base;
     s->arena_head += (count + 31) & ~size_t(31);  // 256 B alignment
-    if (s->arena_head > kArenaHalf) s->arena_head = kArenaHalf;
+    if (s->arena_head > s->arena_len) s->arena_head = s->arena_len;
     return QS_OK;
 }
 
@@ -612,11 +631,10 @@ qs_status qs_destroy_state(qs_state s) {
     if (s->samp_out) (void)hipFree(s->samp_out);
     if (s->samp_host) (void)hipHostFree(s->samp_host);
     if (s->z_dev) (void)hipFree(s->z_dev);
-    if (s->arena_dev) {
-        (void)hipFree(s->arena_dev);
-        (void)hipHostFree(s->arena_host);
-        for (int i = 0; i < 2; ++i) (void)hipEventDestroy(s->arena_ev[i]);
-    }
+    if (s->arena_dev) (void)hipFree(s->arena_dev);
+    if (s->arena_host) (void)hipHostFree(s->arena_host);
+    for (int i = 0; i < 2; ++i)
+        if (s->arena_ev[i]) (void)hipEventDestroy(s->arena_ev[i]);
     if (s->side_buf) (void)hipFree(s->side_buf);
     if (s->sel_choice_dev) (void)hipFree(s->sel_choice_dev);
     if (s->sel_choice_host) (void)hipHostFree(s->sel_choice_host);
@@ -2515,7 +2533,9 @@ struct Runner {
                      f_cut = f2_of(n_cuts * sizeof(qs::TrajSweep)), f_job = f2_of(n_traj * sizeof(qs::TrajJob));
         float2 *h = nullptr;
         const float2 *d = nullptr;
-        QS_CHECK(arena_stage(s, f2_of(mats * sizeof(float2)) + f_gate + f_sel + f_cut + f_job, &h, &d));
+        const size_t need = f2_of(mats * sizeof(float2)) + f_gate + f_sel + f_cut + f_job;
+        QS_CHECK(arena_reserve(s, need <= kArenaSmallHalf / 2 ? kArenaSmallHalf : kArenaHalf));
+        QS_CHECK(arena_stage(s, need, &h, &d));
         const size_t o_gate = f2_of(mats * sizeof(float2)), o_sel = o_gate + f_gate, o_cut = o_sel + f_sel,
                      o_job = o_cut + f_cut;
         auto *gates = reinterpret_cast<qs::TrajGate *>(h + o_gate);
@@ -2681,7 +2701,8 @@ struct Runner {
             resident() ? 256
                        : int(std::min<int64_t>(std::max(kSideTiles >> (m.n - qs::kBatchTileBits), 2),
                                                std::min<int64_t>(p.n_traj, 64)));
-        if (resident() ? keep && !ensure_side(int(std::min<int64_t>(slots, p.n_traj)), true)
+        // (the call's last trajectory ends in the caller's state)
+        if (resident() ? keep && !ensure_side(int(std::min<int64_t>(slots, p.n_traj - 1)), true)
                        : !ensure_side(slots, false))
             return QS_OK;
         *done = true;
@@ -2704,6 +2725,7 @@ struct Runner {
             // the ones left to the one-by-one path, in the caller's state; the
             // call's last trajectory stays last there
             auto alone = [&](int64_t i) -> qs_status {
+                QS_CHECK(arena_reserve(s, kArenaHalf));
                 QS_CHECK(run_delayed(first + i, uint32_t(p.traj_offset + first + i)));
                 QS_CHECK(settle_reset());
                 return finish_side(first + i, s->amp);
@@ -2983,6 +3005,7 @@ struct Runner {
                        m.n <= kGraphMaxQubits && p.n_traj >= 2;
         bool side = false;
         if (delayed && side_by_side()) QS_CHECK(run_side_by_side(&side));
+        if (!side && s->arena_dev) QS_CHECK(arena_reserve(s, kArenaHalf));
         for (int64_t rel = side ? p.n_traj : 0; rel < p.n_traj; ++rel) {
             const uint32_t traj = uint32_t(p.traj_offset + rel);
             if (delayed) QS_CHECK(run_delayed(rel, traj));

@@ -112,3 +112,18 @@ def test_few_trajectories_of_five_qubit_blocks_stay_on_the_matrix_units(qs, n, n
     assert got["gate_k_launches"][5] > 0
     for key in ("choices", "samples", "state"):
         assert np.array_equal(got[key], ref[key]), key
+
+
+def test_staging_grows_with_the_calls(qs):
+    """One small trajectory, then many, then one by one on one handle: each
+    equals the call on a handle of its own."""
+    c = _circuit(9, 8, True)
+    calls = [(1, {}), (120, {}), (3, dict(time_kernels=True)), (2, {})]
+    kw = dict(seed=8, max_fuse=4, n_samples=5, return_state=True, z_expect=True)
+    with qs.State(9) as st:
+        for count, more in calls:
+            got = qs.qs_run_trajectories(st.h, c, count, **kw, **more)
+            with qs.State(9) as own:
+                ref = qs.qs_run_trajectories(own.h, c, count, **kw, **more)
+            for key in ("choices", "samples", "state", "z_expect"):
+                assert np.array_equal(got[key], ref[key]), (count, key)
