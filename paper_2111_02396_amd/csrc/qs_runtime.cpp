@@ -1441,6 +1441,10 @@ struct Runner {
     qs_traj_result &res;
     const int max_fuse;
     const uint64_t chash;  // model id of the call's circuit (0: do not cache the plan)
+    // trajectories of the whole call, of which a chunk of a concurrent call runs
+    // a part: what decides how results round goes by these, so that they do
+    // not depend on the number of states
+    const int64_t call_traj;
     bool tuning = false;   // an autotuner trial: default plan only, no channel uploads
     // delayed mode: default plan, shared with the cache
     std::vector<const cd *> default_mats;
@@ -1649,9 +1653,9 @@ struct Runner {
     std::vector<double> z_host;
 
     Runner(qs_state s_, const CircuitModel &m_, const qs_traj_params &p_, qs_traj_result &r_, uint64_t chash_,
-           hipEvent_t ref = nullptr, std::vector<std::pair<double, double>> *intervals = nullptr)
+           int64_t call_traj_, hipEvent_t ref = nullptr, std::vector<std::pair<double, double>> *intervals = nullptr)
         : s(s_), m(m_), p(p_), res(r_), max_fuse(p_.max_fuse > 0 ? p_.max_fuse : kDefaultFuse), chash(chash_),
-          plan(default_plan()), blocks(plan->blocks), op_block(plan->op_block), block_desc(plan->block_desc),
+          call_traj(call_traj_), plan(default_plan()), blocks(plan->blocks), op_block(plan->op_block), block_desc(plan->block_desc),
           sweeps(plan->sweeps), layouts(plan->layouts) {
         timer.ref = ref;
         timer.intervals = intervals;
@@ -2295,8 +2299,8 @@ struct Runner {
             k5 += d.g.k == 5;
             k4 += d.g.k == 4;
         }
-        if (k5 > 2 || 2 * k5 > all) return m.n == 10 || p.n_traj > (m.n < 10 ? 1 : m.n == 11 ? 4 : 3);
-        if (m.n < qs::kBatchLdsQubits || p.n_traj > 1 || k4 + k5 > 0) return true;
+        if (k5 > 2 || 2 * k5 > all) return m.n == 10 || call_traj > (m.n < 10 ? 1 : m.n == 11 ? 4 : 3);
+        if (m.n < qs::kBatchLdsQubits || call_traj > 1 || k4 + k5 > 0) return true;
         for (const ChannelInfo &c : m.channels)
             if (!c.mixture) return true;
         return false;
@@ -3151,16 +3155,16 @@ qs_status resolve_widths(qs_state s, const CircuitModel &m, uint64_t chash, cons
             if (by_traj) {
                 q.n_traj = 1;
                 q.traj_offset = p.traj_offset + nt < (int64_t(1) << 32) ? p.traj_offset + nt : p.traj_offset;
-                Runner warm(s, m, q, dummy, chash);
+                Runner warm(s, m, q, dummy, chash, p.n_traj);
                 QS_CHECK(warm.run());
                 q.n_traj = nt;
                 q.traj_offset = p.traj_offset;
-                Runner trial(s, m, q, dummy, chash);
+                Runner trial(s, m, q, dummy, chash, p.n_traj);
                 const auto ta = std::chrono::steady_clock::now();
                 QS_CHECK(trial.run());  // ends with a stream synchronisation
                 t = 1e3 * std::chrono::duration<double>(std::chrono::steady_clock::now() - ta).count();
             } else {
-                Runner trial(s, m, q, dummy, chash);
+                Runner trial(s, m, q, dummy, chash, p.n_traj);
                 trial.tuning = true;
                 QS_CHECK(trial.plan_delayed());
                 for (int r = 0; r < reps; ++r) {
@@ -3200,9 +3204,10 @@ int tile_bits_reported(int n, int tb) {
 }
 
 // qs_run_trajectories, optionally reporting every timed bracket of sweeps as
-// an interval after the completed event `ref`.
+// an interval after the completed event `ref`; `call_traj`: trajectories of
+// the concurrent call that these are a chunk of.
 qs_status run_trajectories_impl(qs_state s, const qs_circuit *c, const qs_traj_params *p,
-                                qs_traj_result *r, hipEvent_t ref,
+                                qs_traj_result *r, int64_t call_traj, hipEvent_t ref,
                                 std::vector<std::pair<double, double>> *intervals) {
     const auto t0 = std::chrono::steady_clock::now();
     QS_CHECK(check_handle(s));
@@ -3246,7 +3251,7 @@ qs_status run_trajectories_impl(qs_state s, const qs_circuit *c, const qs_traj_p
     r->max_fuse_used = q.max_fuse;
     r->tile_bits_used = tile_bits_reported(m.n, q.tile_bits);
     r->tune_ms = tms;
-    Runner run(s, m, q, *r, chash, ref, intervals);
+    Runner run(s, m, q, *r, chash, call_traj, ref, intervals);
     const qs_status st = run.run();
     r->host_seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     return st;
@@ -3275,7 +3280,7 @@ double union_length(std::vector<std::pair<double, double>> iv) {
 
 qs_status qs_run_trajectories(qs_state s, const qs_circuit *c, const qs_traj_params *p,
                               qs_traj_result *r) {
-    return run_trajectories_impl(s, c, p, r, nullptr, nullptr);
+    return run_trajectories_impl(s, c, p, r, p ? p->n_traj : 0, nullptr, nullptr);
 }
 
 qs_status qs_run_trajectories_concurrent(qs_state *states, int n_states, const qs_circuit *c,
@@ -3352,7 +3357,7 @@ qs_status qs_run_trajectories_concurrent(qs_state *states, int n_states, const q
             message[j] = "cannot select the state's device";
             return;
         }
-        status[j] = run_trajectories_impl(states[j], c, &sp[j], &sr[j], ref, timing ? &iv[j] : nullptr);
+        status[j] = run_trajectories_impl(states[j], c, &sp[j], &sr[j], p->n_traj, ref, timing ? &iv[j] : nullptr);
         if (status[j] != QS_OK) message[j] = g_last_error;
     };
     std::vector<std::thread> pool;

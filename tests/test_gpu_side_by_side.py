@@ -127,3 +127,21 @@ def test_staging_grows_with_the_calls(qs):
                 ref = qs.qs_run_trajectories(own.h, c, count, **kw, **more)
             for key in ("choices", "samples", "state", "z_expect"):
                 assert np.array_equal(got[key], ref[key]), (count, key)
+
+
+@pytest.mark.parametrize("n,f,n_traj,states", [(7, 5, 3, 3), (8, 5, 5, 4), (11, 5, 6, 3), (12, 5, 4, 2), (13, 5, 5, 4),
+                                               (13, 3, 2, 2), (14, 4, 3, 3), (16, 4, 5, 4)])
+def test_chunks_round_as_the_whole_call(qs, n, f, n_traj, states):
+    """A concurrent call's chunks take the path that one state would take for
+    the whole range, however few trajectories each has."""
+    c = W.generic_grid_circuit(n, 8, p_dep=0.01, gamma=0.002 if n > 13 else None, seed=n)
+    kw = dict(seed=11, max_fuse=f, n_samples=3, return_state=True, z_expect=True)
+    handles = [qs.State(n) for _ in range(states)]
+    try:
+        got = qs.qs_run_trajectories([h.h for h in handles], c, n_traj, **kw)
+        ref = qs.qs_run_trajectories(handles[0].h, c, n_traj, **kw)
+    finally:
+        for h in handles:
+            h.close()
+    for key in ("choices", "samples", "z_expect", "state"):
+        assert np.array_equal(got[key], ref[key]), key
