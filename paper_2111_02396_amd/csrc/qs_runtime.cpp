@@ -1434,6 +1434,35 @@ double expected_slow_paths(const CircuitModel &m) {
     return e;
 }
 
+// Whether the sweeps of a call of n_traj trajectories are replayed from a HIP
+// graph where they can be.
+constexpr int kGraphMaxQubits = 22;
+bool graph_call(const CircuitModel &m, const qs_traj_params &p, int64_t n_traj) {
+    return p.mode == QS_KRAUS_DELAYED && (p.flags & QS_TRAJ_GRAPH) && !(p.flags & QS_TRAJ_NO_GRAPH) &&
+           m.n <= kGraphMaxQubits && n_traj >= 2;
+}
+
+// Whether n_traj trajectories may run side by side at the default tile width:
+// the delayed scheme without kernel timing or graph replay, samples and Z
+// records of one flush.  Up to 13 qubits that is all; from 14 qubits on at
+// least two trajectories share sweeps, which take gates of at most four qubits
+// and inner-product channels of one (what the sweep that forms a reduced
+// density matrix takes).  The call alone decides, not what its state did
+// before: where the two ways round differently its results would change.
+bool side_call(const CircuitModel &m, const qs_traj_params &p, bool z_records, int64_t n_traj) {
+    if (p.mode != QS_KRAUS_DELAYED || n_traj < 1 || (p.flags & QS_TRAJ_TIME_KERNELS) || graph_call(m, p, n_traj))
+        return false;
+    if (n_traj > 1 && p.n_samples > 0 && n_traj > kSampleRecords / p.n_samples) return false;
+    if (z_records && n_traj > kZRecords) return false;
+    if (m.n <= qs::kBatchLdsQubits) return true;
+    if (m.n > kSideMaxQubits || n_traj < 2) return false;
+    for (const ChannelInfo &c : m.channels)
+        if (!c.mixture && c.k != 1) return false;
+    for (const qs::PlanOp &o : m.ops)
+        if (o.k > 4) return false;
+    return true;
+}
+
 struct Runner {
     qs_state s;
     const CircuitModel &m;
@@ -1521,7 +1550,6 @@ struct Runner {
     int gtab_half = 0;
     std::vector<char> gdirty_prev;         // blocks the previous replay patched
     static constexpr size_t kNoSlot = ~size_t(0);
-    static constexpr int kGraphMaxQubits = 22;
 
     ~Runner() {
         if (gtab_dev) (void)hipStreamSynchronize(s->st);
@@ -2260,23 +2288,19 @@ struct Runner {
 
     bool resident() const { return m.n <= qs::kBatchLdsQubits; }
 
-    // Whether the call's trajectories may run side by side: the delayed
-    // scheme without kernel timing or graph replay, the default tile width,
-    // samples and Z records that fit their device buffers at once, and, for
-    // sweeps, one-qubit inner-product channels and blocks of at most four
-    // qubits (what the sweep that forms a reduced density matrix takes).
+    // Whether the trajectories run side by side: on tiles of the default width,
+    // in blocks that shared sweeps take.  (From 14 qubits on both ways round
+    // alike, so each chunk of a concurrent call decides for itself.)
     bool side_by_side() const {
-        if (p.mode != QS_KRAUS_DELAYED || timing || graph_wanted || tuning || p.n_traj < 1) return false;
-        if (p.tile_bits != 0 && p.tile_bits != qs::kDefaultTileBits) return false;
-        if (p.n_traj * int64_t(std::max(p.n_samples, 0)) > int64_t(s->samp_cap) && p.n_samples > 0) return false;
-        if (res.z_expect && p.n_traj > int64_t(s->z_cap)) return false;
-        if (resident()) return resident_pays();
-        if (m.n > kSideMaxQubits || p.n_traj < 2) return false;
-        for (const ChannelInfo &c : m.channels)
-            if (!c.mixture && c.k != 1) return false;
-        for (const qs::Block &b : blocks)
-            if (b.k > 4) return false;
-        return true;
+        if (tuning || plan_tile_bits() != qs::kDefaultTileBits) return false;
+        const bool z = res.z_expect != nullptr;
+        if (resident()) return side_call(m, p, z, call_traj) && resident_pays();
+        return side_call(m, p, z, p.n_traj) && max_block() <= 4;
+    }
+    int max_block() const {
+        int k = 0;
+        for (const qs::Block &b : blocks) k = std::max(k, b.k);
+        return k;
     }
 
     // Whether a call of resident states is faster side by side.  A few
@@ -3004,9 +3028,7 @@ struct Runner {
         const bool delayed = p.mode != QS_KRAUS_NAIVE;
         if (delayed) QS_CHECK(plan_delayed());
         else QS_CHECK(plan_naive());
-        graph_wanted = p.mode == QS_KRAUS_DELAYED && (p.flags & QS_TRAJ_GRAPH) &&
-                       !(p.flags & QS_TRAJ_NO_GRAPH) && !tuning &&
-                       m.n <= kGraphMaxQubits && p.n_traj >= 2;
+        graph_wanted = !tuning && graph_call(m, p, p.n_traj);
         bool side = false;
         if (delayed && side_by_side()) QS_CHECK(run_side_by_side(&side));
         if (!side && s->arena_dev) QS_CHECK(arena_reserve(s, kArenaHalf));
@@ -3061,29 +3083,16 @@ struct TuneKey {
     }
 };
 
-// Whether a call of 13 to 21 qubits runs side by side if its widths let it
-// (Runner::side_by_side: 13-bit tiles, and blocks of at most four qubits in
-// shared sweeps).  The tuner offers such a call no other widths: its trials
-// time one state's passes, which on these sizes are as fast or faster on
-// 12-bit tiles (one trajectory of 14 qubits 135 against 156 us, of 20 qubits
-// equal), and with that width the call would run its trajectories one by one:
-// 200 trajectories of the grid at depth 20, 12-bit tiles one by one against
-// 13-bit side by side: 13 qubits 11.2k against 53k trajectories/s, 14 qubits
-// 9.6k against 49k, 16 qubits 7.4k against 35k, 18 qubits 6.3k against 24k,
-// 20 qubits 4.2k against 10k.  A single trajectory, and a call that times its
-// kernels or replays a graph, is tuned over all widths as one state's passes.
-bool side_call(const CircuitModel &m, const qs_traj_params &p, bool z_records) {
-    if (p.mode != QS_KRAUS_DELAYED || (p.tile_bits != 0 && p.tile_bits != qs::kDefaultTileBits)) return false;
-    if (p.flags & QS_TRAJ_TIME_KERNELS) return false;
-    if ((p.flags & QS_TRAJ_GRAPH) && !(p.flags & QS_TRAJ_NO_GRAPH)) return false;
-    if (m.n < qs::kBatchLdsQubits || m.n > kSideMaxQubits || p.n_traj < 2) return false;
-    if (p.n_samples > 0 && p.n_traj > kSampleRecords / p.n_samples) return false;
-    if (z_records && p.n_traj > kZRecords) return false;
-    if (m.n == qs::kBatchLdsQubits) return true;
-    for (const ChannelInfo &c : m.channels)
-        if (!c.mixture && c.k != 1) return false;
-    return true;
-}
+// A call of 13 to 21 qubits that can run side by side is offered no tile width
+// but the default: its trials time one state's passes, which on these sizes
+// are as fast or faster on 12-bit tiles (one trajectory of 14 qubits 135
+// against 156 us, of 20 qubits equal), and with that width it would run its
+// trajectories one by one: 200 trajectories of the grid at depth 20, 12-bit
+// tiles one by one against 13-bit side by side: 13 qubits 11.2k against 53k
+// trajectories/s, 14 qubits 9.6k against 49k, 16 qubits 7.4k against 35k, 18
+// qubits 6.3k against 24k, 20 qubits 4.2k against 10k.  A single trajectory,
+// and a call that times its kernels or replays a graph, is tuned over all
+// widths as one state's passes.
 constexpr double kTuneMargin = 0.03;  // a candidate must beat the default widths by 3 %
 // From this many expected inner-product channels per trajectory on, the
 // trials are whole trajectories timed on the host clock (the host's
@@ -3107,7 +3116,9 @@ qs_status resolve_widths(qs_state s, const CircuitModel &m, uint64_t chash, cons
                        (p.tile_bits >= 10 && p.tile_bits <= qs::kMaxTileBits);
     if (p.max_fuse != 0 || p.mode != QS_KRAUS_DELAYED || p.n_traj <= 0 || !tb_ok || m.n != s->n)
         return QS_OK;
-    const bool side = side_call(m, p, z_records);
+    const bool side = m.n >= qs::kBatchLdsQubits && p.n_traj >= 2 &&
+                      (p.tile_bits == 0 || p.tile_bits == qs::kDefaultTileBits) &&
+                      side_call(m, p, z_records, p.n_traj);
     std::vector<int> fs = m.n < 16 ? std::vector<int>{2, 3, 4, 5} : std::vector<int>{3, 4, 5};
     if (side && m.n > qs::kBatchLdsQubits) fs.pop_back();
     std::vector<int> tbs;

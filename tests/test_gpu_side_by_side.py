@@ -145,3 +145,20 @@ def test_chunks_round_as_the_whole_call(qs, n, f, n_traj, states):
             h.close()
     for key in ("choices", "samples", "z_expect", "state"):
         assert np.array_equal(got[key], ref[key]), key
+
+
+def test_path_does_not_depend_on_what_the_state_did_before(qs):
+    """More samples than a flush holds run one by one, also on a handle whose
+    sample buffer an earlier call made larger (5-qubit blocks of 11 qubits
+    round differently side by side)."""
+    c = W.generic_grid_circuit(11, 8, p_dep=0.02, seed=3)
+    kw = dict(seed=2, max_fuse=5, n_samples=900000, return_state=True, record_choices=False)
+    with qs.State(11) as st, qs.State(11) as used:
+        qs.qs_sample_measurements(used.h, 1, 0, 5000000)
+        a = qs.qs_run_trajectories(st.h, c, 5, **kw)
+        b = qs.qs_run_trajectories(used.h, c, 5, **kw)
+        side = qs.qs_run_trajectories(st.h, c, 5, **dict(kw, n_samples=0))
+    assert not np.array_equal(side["state"], a["state"])
+    assert np.array_equal(a["state"], b["state"])
+    assert np.array_equal(a["samples"], b["samples"])
+    assert rel_l2(side["state"], a["state"]) < AMP_TOL
