@@ -112,13 +112,15 @@ typedef struct {
                               channel at its most likely pick) on the device for each
                               candidate width (2..5 below 16 qubits, else 3..5) and keeps
                               the fastest, cached per circuit and state size for the life
-                              of the process (the conventional modes use 4); a call of two
-                              or more trajectories that can share launches (14..21 qubits)
-                              is tuned over widths up to 4 */
+                              of the process (the conventional modes use 4); a call that
+                              can run side by side (up to 13 qubits; two or more
+                              trajectories of 14..21) is timed over up to 32 of its
+                              trajectories instead, apart for 1, 2..7, 8..31 and more of
+                              them, and from 14 qubits on over widths up to 4 */
     int32_t tile_bits;     /* LDS tile sweeps: fused gates whose qubits fit a tile of this
                               many index bits (bits 0..3 always included) share one pass
                               over the state; 0 = library default (13), or, when max_fuse
-                              is 0, autotuned with it over 12..14 (13 where the call's
+                              is 0, autotuned with it over 12..14 (13 where two or more
                               trajectories can run side by side); 1 = off (one pass per
                               fused gate), otherwise 10..14 */
     int32_t n_samples;     /* measurement samples per trajectory (>= 0) */

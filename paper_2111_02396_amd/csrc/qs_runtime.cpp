@@ -1475,6 +1475,7 @@ struct Runner {
     // not depend on the number of states
     const int64_t call_traj;
     bool tuning = false;   // an autotuner trial: default plan only, no channel uploads
+    bool one_by_one = false;  // an autotuner trial of trajectories that the call runs so
     // delayed mode: default plan, shared with the cache
     std::vector<const cd *> default_mats;
     std::vector<cd> tmp;
@@ -2292,7 +2293,7 @@ struct Runner {
     // in blocks that shared sweeps take.  (From 14 qubits on both ways round
     // alike, so each chunk of a concurrent call decides for itself.)
     bool side_by_side() const {
-        if (tuning || plan_tile_bits() != qs::kDefaultTileBits) return false;
+        if (tuning || one_by_one || plan_tile_bits() != qs::kDefaultTileBits) return false;
         const bool z = res.z_expect != nullptr;
         if (resident()) return side_call(m, p, z, call_traj) && resident_pays();
         return side_call(m, p, z, p.n_traj) && max_block() <= 4;
@@ -3065,34 +3066,30 @@ namespace {
 // ---- autotuning of the fusion width and the tile width
 // Section 3.2: the best largest fused-gate size depends on the circuit and
 // the machine (larger on GPUs and for large circuits), and the choice is left
-// to trying values.  Here the driver tries them: for every candidate pair it
-// plans the circuit's default plan (each channel at its most likely pick) and
-// times one pass of it from |0...0> on the state's own stream, keeping the
-// fastest; where the channels' bounds predict two or more inner-product
-// channels per trajectory, it times the call's first trajectories instead,
-// host planning included.  The choice is cached per (circuit, size, mode,
-// whether the call can run side by side) for the life of the process, so later calls, and the chunks of a
-// concurrent call, run the same plan.
+// to trying values.  Here the driver tries them, on the path that the call
+// takes: for every candidate pair of widths it plans the circuit's default
+// plan (each channel at its most likely pick) and times one pass of it from
+// |0...0> on the state's own stream, keeping the fastest.  Where the channels'
+// bounds predict two or more inner-product channels per trajectory, and where
+// the call can run side by side, it times some of the call's trajectories
+// instead, host planning included.  The choice is cached per (circuit, size,
+// mode, kind of call) for the life of the process, so later calls, and the
+// chunks of a concurrent call, run the same plan.
+// Kinds of call: passes of one state; one trajectory of at most 13 qubits; 2 to
+// 7, 8 to 31, and more trajectories side by side (the launches of a few are
+// bound by their chain of blocks, those of many by planning and by the work:
+// 8 qubits without noise, 3 trajectories 83 us at max_fuse 2 and 138 at 4, 100
+// trajectories 408 and 270).
+enum TuneKind { kTuneOneByOne, kTuneResident, kTuneFew, kTuneSome, kTuneMany };
 struct TuneKey {
     uint64_t hash;
-    int n, mode, f_req, tb_req;
-    bool side;
+    int n, mode, f_req, tb_req, kind;
     bool operator<(const TuneKey &o) const {
-        return std::tie(hash, n, mode, f_req, tb_req, side) <
-               std::tie(o.hash, o.n, o.mode, o.f_req, o.tb_req, o.side);
+        return std::tie(hash, n, mode, f_req, tb_req, kind) <
+               std::tie(o.hash, o.n, o.mode, o.f_req, o.tb_req, o.kind);
     }
 };
 
-// A call of 13 to 21 qubits that can run side by side is offered no tile width
-// but the default: its trials time one state's passes, which on these sizes
-// are as fast or faster on 12-bit tiles (one trajectory of 14 qubits 135
-// against 156 us, of 20 qubits equal), and with that width it would run its
-// trajectories one by one: 200 trajectories of the grid at depth 20, 12-bit
-// tiles one by one against 13-bit side by side: 13 qubits 11.2k against 53k
-// trajectories/s, 14 qubits 9.6k against 49k, 16 qubits 7.4k against 35k, 18
-// qubits 6.3k against 24k, 20 qubits 4.2k against 10k.  A single trajectory,
-// and a call that times its kernels or replays a graph, is tuned over all
-// widths as one state's passes.
 constexpr double kTuneMargin = 0.03;  // a candidate must beat the default widths by 3 %
 // From this many expected inner-product channels per trajectory on, the
 // trials are whole trajectories timed on the host clock (the host's
@@ -3101,6 +3098,8 @@ constexpr double kTuneMargin = 0.03;  // a candidate must beat the default width
 constexpr double kTuneSlowPaths = 2.0;
 constexpr double kTuneTrajMargin = 0.05;
 constexpr int64_t kTuneTrajectories = 4;
+// Trials of calls that can run side by side: up to this many trajectories.
+constexpr int64_t kTuneSideTrajectories = 32;
 
 std::mutex g_tune_mu;  // one tuning at a time: concurrent trials would disturb each other's timings
 std::map<TuneKey, std::pair<int, int>> g_tune_cache;
@@ -3116,17 +3115,26 @@ qs_status resolve_widths(qs_state s, const CircuitModel &m, uint64_t chash, cons
                        (p.tile_bits >= 10 && p.tile_bits <= qs::kMaxTileBits);
     if (p.max_fuse != 0 || p.mode != QS_KRAUS_DELAYED || p.n_traj <= 0 || !tb_ok || m.n != s->n)
         return QS_OK;
-    const bool side = m.n >= qs::kBatchLdsQubits && p.n_traj >= 2 &&
-                      (p.tile_bits == 0 || p.tile_bits == qs::kDefaultTileBits) &&
+    const bool side = (p.tile_bits == 0 || p.tile_bits == qs::kDefaultTileBits) &&
                       side_call(m, p, z_records, p.n_traj);
+    const TuneKind kind = !side ? kTuneOneByOne
+                          : p.n_traj < 2 ? kTuneResident
+                          : p.n_traj < 8 ? kTuneFew
+                          : p.n_traj < kTuneSideTrajectories ? kTuneSome : kTuneMany;
+    const bool several = kind >= kTuneFew;
     std::vector<int> fs = m.n < 16 ? std::vector<int>{2, 3, 4, 5} : std::vector<int>{3, 4, 5};
-    if (side && m.n > qs::kBatchLdsQubits) fs.pop_back();
+    if (several && m.n > qs::kBatchLdsQubits) fs.pop_back();
+    // several trajectories run side by side on 13-bit tiles only, three to five
+    // times as fast as one by one on any (200 trajectories of the grid at depth
+    // 20, 12-bit tiles one by one against 13-bit side by side: 13 qubits 11.2k
+    // against 53k trajectories/s, 14 qubits 9.6k against 49k, 16 qubits 7.4k
+    // against 35k, 18 qubits 6.3k against 24k, 20 qubits 4.2k against 10k);
+    // smaller states fit one tile of any width
     std::vector<int> tbs;
     if (p.tile_bits != 0) tbs = {p.tile_bits};
-    else if (side) tbs = {qs::kDefaultTileBits};
-    else if (m.n > 12) tbs = {12, 13, 14};  // smaller states fit one tile of any of these widths
+    else if (!several && m.n > 12) tbs = {12, 13, 14};
     else tbs = {qs::kDefaultTileBits};
-    const TuneKey key{chash, m.n, p.mode, p.max_fuse, p.tile_bits, side};
+    const TuneKey key{chash, m.n, p.mode, p.max_fuse, p.tile_bits, kind};
     std::lock_guard<std::mutex> lock(g_tune_mu);
     auto it = g_tune_cache.find(key);
     if (it != g_tune_cache.end()) {
@@ -3145,12 +3153,14 @@ qs_status resolve_widths(qs_state s, const CircuitModel &m, uint64_t chash, cons
         }
     } guard{ev};
     const int reps = m.n >= 29 ? 1 : 2;  // the first of two also warms caches
-    // circuits whose trajectories often need inner products are timed over
-    // the call's first few trajectories (the same draws for every
-    // candidate), after one untimed trajectory that loads each candidate's
-    // plan and kernels
-    const bool by_traj = expected_slow_paths(m) >= kTuneSlowPaths;
-    const int64_t nt = std::min<int64_t>(kTuneTrajectories, p.n_traj);
+    // circuits whose trajectories often need inner products, and calls that can
+    // run side by side, are timed over the call's first few trajectories (the
+    // same draws for every candidate) after a run of others that loads each
+    // candidate's plan and kernels; side by side a call takes as little as
+    // 50 us, so the fastest of five counts (fewer where the candidate is out)
+    const bool by_traj = side || expected_slow_paths(m) >= kTuneSlowPaths;
+    const int64_t nt = std::min<int64_t>(side ? kTuneSideTrajectories : kTuneTrajectories, p.n_traj);
+    const int64_t warm_nt = side ? nt : 1;
     double best = 1e300, t_default = -1.0;
     for (int f : fs) {
         for (int tb : tbs) {
@@ -3164,16 +3174,20 @@ qs_status resolve_widths(qs_state s, const CircuitModel &m, uint64_t chash, cons
             std::memset(&dummy, 0, sizeof(dummy));
             double t = 1e300;
             if (by_traj) {
-                q.n_traj = 1;
-                q.traj_offset = p.traj_offset + nt < (int64_t(1) << 32) ? p.traj_offset + nt : p.traj_offset;
+                q.n_traj = warm_nt;
+                q.traj_offset = p.traj_offset + nt + warm_nt <= (int64_t(1) << 32) ? p.traj_offset + nt : p.traj_offset;
                 Runner warm(s, m, q, dummy, chash, p.n_traj);
+                warm.one_by_one = !side;
                 QS_CHECK(warm.run());
                 q.n_traj = nt;
                 q.traj_offset = p.traj_offset;
-                Runner trial(s, m, q, dummy, chash, p.n_traj);
-                const auto ta = std::chrono::steady_clock::now();
-                QS_CHECK(trial.run());  // ends with a stream synchronisation
-                t = 1e3 * std::chrono::duration<double>(std::chrono::steady_clock::now() - ta).count();
+                for (int r = 0; r < (side ? 5 : 1) && (r == 0 || t < 1.5 * best); ++r) {
+                    const auto ta = std::chrono::steady_clock::now();
+                    Runner trial(s, m, q, dummy, chash, p.n_traj);
+                    trial.one_by_one = !side;
+                    QS_CHECK(trial.run());  // ends with a stream synchronisation
+                    t = std::min(t, 1e3 * std::chrono::duration<double>(std::chrono::steady_clock::now() - ta).count());
+                }
             } else {
                 Runner trial(s, m, q, dummy, chash, p.n_traj);
                 trial.tuning = true;

@@ -162,3 +162,27 @@ def test_path_does_not_depend_on_what_the_state_did_before(qs):
     assert np.array_equal(a["state"], b["state"])
     assert np.array_equal(a["samples"], b["samples"])
     assert rel_l2(side["state"], a["state"]) < AMP_TOL
+
+
+def test_tuner_times_the_kind_of_call_it_tunes(qs):
+    """One trajectory in a workgroup, many side by side and timed passes of one
+    state have choices of their own; a circuit with a 5-qubit gate above 13
+    qubits always runs as passes of one state and shares theirs."""
+    c = W.generic_grid_circuit(9, 7, p_dep=0.01, gamma=0.003, seed=21)
+    with qs.State(9) as st:
+        def tune_ms(n_traj, **kw):
+            return qs.qs_run_trajectories(st.h, c, n_traj, seed=1, max_fuse=0, **kw)["tune_ms"]
+
+        assert tune_ms(1) > 0.0
+        assert tune_ms(40) > 0.0
+        assert tune_ms(3, time_kernels=True) > 0.0
+        assert [tune_ms(1), tune_ms(64), tune_ms(1, time_kernels=True)] == [0.0] * 3
+    ops = list(W.generic_grid_circuit(14, 4, p_dep=0.01, seed=22).ops)
+    wide = W.random_unitary(5, np.random.Generator(np.random.PCG64(2)))
+    ops.insert(20, W.Op(W.GATE, (1, 4, 7, 10, 13), [wide], ops[20].moment, "wide"))
+    c = W.Circuit(14, ops, "wide")
+    with qs.State(14) as st:
+        one = qs.qs_run_trajectories(st.h, c, 1, seed=1, max_fuse=0)
+        four = qs.qs_run_trajectories(st.h, c, 4, seed=1, max_fuse=0)
+    assert one["tune_ms"] > 0.0 and four["tune_ms"] == 0.0
+    assert (one["max_fuse_used"], one["tile_bits_used"]) == (four["max_fuse_used"], four["tile_bits_used"])
