@@ -1118,15 +1118,16 @@ struct KernelTimer {
 
 // ---- per-circuit plan cache
 // The default plan of a circuit (fusion into blocks, their matrices, the tile
-// sweep grouping) depends only on the circuit, the mode's channel bounds and
-// the widths, so calls that run the same circuit again (one state per call,
+// sweep grouping) depends only on the circuit, the mode's channel bounds, the
+// widths and the grouping's restarts, so calls that run the same circuit again (one state per call,
 // a serving loop, the autotuner's final choice) reuse it instead of fusing
 // again.  Keyed by the circuit's model-cache id.
 struct PlanKey {
     uint64_t hash;  // model id
-    int n, mode, f, tb;
+    int n, mode, f, tb, restarts;
     bool operator<(const PlanKey &o) const {
-        return std::tie(hash, n, mode, f, tb) < std::tie(o.hash, o.n, o.mode, o.f, o.tb);
+        return std::tie(hash, n, mode, f, tb, restarts) <
+               std::tie(o.hash, o.n, o.mode, o.f, o.tb, o.restarts);
     }
 };
 
@@ -1325,16 +1326,20 @@ qs_status circuit_model(const qs_circuit *c, std::shared_ptr<const ModelEntry> *
 // ---- sweep grouping effort and the per-segment cache
 // Every sweep saved is one read and one write of the state per trajectory, so
 // the default plan's grouping is searched in proportion to the sweep work of
-// the call that plans it (n_traj states of 2^n amplitudes; about 40 ms for
-// 4096 restarts on a 24-qubit plan), and always hard from 26 qubits on, where
-// one trajectory's sweeps take tens of milliseconds.  The plan is cached, so
-// later calls on the same circuit reuse it.  A trajectory whose channels need
-// inner products regroups the blocks of each segment between such channels;
-// those groupings are cached per segment.
+// the call (n_traj states of 2^n amplitudes; about 10 ms for 4096 restarts on
+// a 24-qubit plan), and always hard from 26 qubits on, where one trajectory's
+// sweeps take tens of milliseconds.  Blocks on disjoint qubits commute but
+// round differently, so the grouping is part of the results: the count is a
+// part of every key that a plan is kept under, and one of four, so that a
+// circuit run with varying trajectory counts has at most four plans.  A
+// trajectory whose channels need inner products regroups the blocks of each
+// segment between such channels; those groupings are cached per segment.
 int plan_restarts(int n, int64_t n_traj) {
     if (n >= 26) return 4096;
     const double w = std::ldexp(double(std::max<int64_t>(n_traj, 1)), n - 20);
-    return int(std::min(4096.0, std::max(64.0, w)));
+    int restarts = 64;
+    while (restarts < 4096 && restarts < w) restarts *= 4;
+    return restarts;
 }
 // Below 24 qubits a sweep costs a few microseconds, about as much as a
 // dozen restarts on a segment's blocks, and a segment with fewer than 16
@@ -1706,7 +1711,8 @@ struct Runner {
                 default_mats[o] = fast_pick_matrix(c, c.default_pick);
             }
         }
-        const PlanKey key{chash, m.n, p.mode, max_fuse, plan_tile_bits()};
+        const int restarts = plan_restarts(m.n, call_traj);
+        const PlanKey key{chash, m.n, p.mode, max_fuse, plan_tile_bits(), restarts};
         std::shared_ptr<const PlanEntry> cached;
         if (chash) plan_lookup(key, &cached);
         if (cached) return cached;
@@ -1728,7 +1734,7 @@ struct Runner {
         if (T >= 10 && m.n >= qs::kTileMinQubits) {
             e->sweeps = qs::group_sweeps_best(m.n, e->blocks, std::min(T, m.n), qs::kTileLowBits, qs::kMaxTileGates,
                                               qs::tile_mat_budget(std::min(T, m.n)), tile_slots(),
-                                              plan_restarts(m.n, p.n_traj), kGroupSeed);
+                                              restarts, kGroupSeed);
         } else {
             for (size_t b = 0; b < e->blocks.size(); ++b) {
                 qs::Sweep sw;
@@ -1746,7 +1752,8 @@ struct Runner {
     qs_status plan_delayed() {
         if (!tuning) QS_CHECK(upload_channels());
         // a plan from the cache is fixed by its key: the state keeps its
-        // matrices from one call to the next
+        // matrices from one call to the next (they do not depend on how the
+        // blocks are grouped)
         const uint64_t tag = chash ? (chash << 16) | (uint64_t(p.mode & 3) << 12) |
                                          (uint64_t(max_fuse) << 8) | uint64_t(plan_tile_bits())
                                    : 0;
@@ -3509,12 +3516,15 @@ namespace {
 constexpr int kBatchDefaultFuse = 3;
 
 // Per-circuit fusion and sweep grouping of the batched launch, cached by
-// circuit hash and fusion width (a batch of the same circuits is planned
+// circuit, fusion width and grouping restarts (a batch of the same circuits is planned
 // once; only the per-trajectory draws and patched blocks are redone).
 struct BatchPlanKey {
     uint64_t hash;  // model id
     int f;
-    bool operator<(const BatchPlanKey &o) const { return std::tie(hash, f) < std::tie(o.hash, o.f); }
+    int restarts;   // of the sweep grouping (0: resident, not grouped)
+    bool operator<(const BatchPlanKey &o) const {
+        return std::tie(hash, f, restarts) < std::tie(o.hash, o.f, o.restarts);
+    }
 };
 struct BatchPlanEntry {
     std::vector<qs::BatchSweep> sweeps;     // gate ranges local to the circuit
@@ -3664,7 +3674,7 @@ std::vector<qs::Sweep> cut_sweeps(const std::vector<qs::Sweep> &order, const std
 // device needs to redo a block for other picks: the channel table and, for
 // each block holding a channel, its operations with FP64 matrices.
 qs_status plan_batched_circuit(const CircuitModel &m, const std::vector<const cd *> &default_mats,
-                               int f, bool resident, int64_t n_traj, BatchPlanEntry &e) {
+                               int f, bool resident, int restarts, BatchPlanEntry &e) {
     const int n = m.n;
     std::vector<int> op_block;
     const std::vector<qs::Block> blocks = qs::fuse_greedy(n, m.ops, f, &op_block);
@@ -3678,7 +3688,7 @@ qs_status plan_batched_circuit(const CircuitModel &m, const std::vector<const cd
     } else {
         static const int no_budget[6] = {0, 0, 0, 0, 0, 0};
         const auto order = qs::group_sweeps_best(n, blocks, qs::kBatchOrderBits, qs::kBatchOrderLowBits, 1 << 30,
-                                                 1 << 30, no_budget, plan_restarts(n, n_traj), kGroupSeed);
+                                                 1 << 30, no_budget, restarts, kGroupSeed);
         sw = cut_sweeps(order, blocks);
     }
     std::vector<char> has_channel(blocks.size(), 0);
@@ -3862,8 +3872,10 @@ void plan_waves(std::vector<qs::BatchJob> &jobs, const std::vector<qs::BatchCirc
     }
 }
 
-qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_batch_params *bp,
-                           int f, qs_batch_result *r) {
+// `sized`: the items whose trajectory counts the plans are searched for (an
+// autotuner trial runs fewer trajectories on the plans of the whole batch).
+qs_status run_batched_impl(const qs_batch_item *items, const qs_batch_item *sized, int n_items,
+                           const qs_batch_params *bp, int f, qs_batch_result *r) {
     const auto t0 = std::chrono::steady_clock::now();
     hipStream_t st = static_cast<hipStream_t>(bp->hip_stream);
     std::memset(r, 0, sizeof(*r));
@@ -3929,7 +3941,8 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
             for (int q = 0; q < n; ++q) X.readout.push_back(ro.e0[q]);
             for (int q = 0; q < n; ++q) X.readout.push_back(ro.e1[q]);
         }
-        const BatchPlanKey bkey{P.me->id, f};
+        const int restarts = P.resident ? 0 : plan_restarts(n, sized[it].n_traj);
+        const BatchPlanKey bkey{P.me->id, f, restarts};
         batch_plan_lookup(bkey, &P.plan);
         if (!P.plan) {
             const int n_ops = int(P.m->ops.size());
@@ -3942,7 +3955,7 @@ qs_status run_batched_impl(const qs_batch_item *items, int n_items, const qs_bat
                 }
             }
             auto e = std::make_shared<BatchPlanEntry>();
-            const qs_status ps = plan_batched_circuit(*P.m, default_mats, f, P.resident, I.n_traj, *e);
+            const qs_status ps = plan_batched_circuit(*P.m, default_mats, f, P.resident, restarts, *e);
             if (ps != QS_OK) {
                 X.status = ps;
                 X.error = g_last_error;
@@ -4270,7 +4283,7 @@ extern "C" qs_status qs_run_batched(const qs_batch_item *items, int n_items,
     if (!items || n_items < 0 || !bp || !r) return fail(QS_ERR_INVALID_ARGUMENT, "null argument");
     if (bp->max_fuse < 0 || bp->max_fuse > qs::kMaxGateQubits)
         return fail(QS_ERR_INVALID_ARGUMENT, "max_fuse outside 0..5");
-    if (bp->max_fuse > 0) return run_batched_impl(items, n_items, bp, bp->max_fuse, r);
+    if (bp->max_fuse > 0) return run_batched_impl(items, items, n_items, bp, bp->max_fuse, r);
     for (int it = 0; it < n_items; ++it)
         if (!items[it].circuit || !items[it].circuit->ops || !items[it].circuit->mat_pool ||
             items[it].circuit->n_ops < 0 || items[it].circuit->pool_len < 0)
@@ -4305,7 +4318,7 @@ extern "C" qs_status qs_run_batched(const qs_batch_item *items, int n_items,
             double best = 1e300, t_default = -1.0;
             for (int cand : {2, 3, 4, 5}) {
                 qs_batch_result tr;
-                QS_CHECK(run_batched_impl(trial.data(), n_items, &tp, cand, &tr));
+                QS_CHECK(run_batched_impl(trial.data(), items, n_items, &tp, cand, &tr));
                 if (cand == kBatchDefaultFuse) t_default = tr.host_seconds;
                 if (tr.host_seconds < best) {
                     best = tr.host_seconds;
@@ -4317,7 +4330,7 @@ extern "C" qs_status qs_run_batched(const qs_batch_item *items, int n_items,
             tune_ms = 1e3 * std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
         }
     }
-    const qs_status st = run_batched_impl(items, n_items, bp, f, r);
+    const qs_status st = run_batched_impl(items, items, n_items, bp, f, r);
     r->tune_ms = tune_ms;
     return st;
 }

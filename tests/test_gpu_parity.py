@@ -601,3 +601,17 @@ def test_autotuner_times_trajectories_when_inner_products_are_frequent(qs, orc):
         mism = np.nonzero(tuned["samples"][t] != ref["samples"])[0]
         assert np.all(ref["sample_margins"][mism] < SAMPLE_TIE)
     assert ties <= 1
+
+
+def test_plans_do_not_depend_on_earlier_calls(qs):
+    """A call's sweep grouping is searched for its own trajectory count: after
+    a call of one trajectory a longer one has the sweeps it has as a first
+    call (24 qubits at depth 20: 17 after 64 restarts, 16 after 1024)."""
+    sweeps = []
+    with qs.State(24) as st:
+        for seed, counts in ((1, (1, 17)), (2, (17,))):
+            c = W.generic_grid_circuit(24, 20, seed=seed)  # the same structure, other gates
+            for n_traj in counts:
+                r = qs.qs_run_trajectories(st.h, c, n_traj, max_fuse=4)
+                sweeps.append(r["gate_sweeps"] / n_traj)
+    assert sweeps[0] > sweeps[1] == sweeps[2]
