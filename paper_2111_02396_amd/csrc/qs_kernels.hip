@@ -267,6 +267,18 @@ __global__ __launch_bounds__(kBlock) void apply_direct_mfma(MatArg<(K <= 4 ? K :
 
 __host__ __device__ constexpr int ilog2(int x) { return x <= 1 ? 0 : 1 + ilog2(x / 2); }
 
+// Orders a wavefront's LDS accesses before this point against those behind it.
+// The hardware keeps them in order (the lanes run in lockstep); the fences keep
+// the compiler from moving accesses that one work-item does not see overlap.
+__device__ __forceinline__ void wave_lds_order() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// LDS that is read as 16-byte vectors is declared so aligned.
+#define QS_LDS_VECTORS(array) static_assert(__alignof__(array) % 16 == 0, "read as 16-byte vectors")
+
 // Issue priority from the batches a wavefront still has to do in this gate:
 // the arbiter favours older wavefronts, so without this the younger ones
 // finish a gate late and the rest of the workgroup idles at the barrier.
@@ -1147,7 +1159,8 @@ __global__ __launch_bounds__(NT) void apply_tile(float2 *__restrict__ amp, Idx n
     // that folds into the LDS instructions' offsets); the launch's matrices
     // follow it in dynamic LDS.
     __shared__ float2 sd[1 << TB];
-    extern __shared__ float2 sm[];
+    alignas(16) extern __shared__ float2 sm[];
+    QS_LDS_VECTORS(sm);
     tile_sweep<TB, Idx, K5, NT, RK, false, SP>(amp, Idx(blockIdx.x), Idx(gridDim.x), n_tiles, ArgSweep{a}, sd, sm);
 }
 
@@ -1171,7 +1184,8 @@ template <int TB, typename Idx>
 __global__ __launch_bounds__(kBlock) void apply_tile_one(MatArg<4>, float2 *__restrict__ amp, Idx n_tiles,
                                                          TileOneArgs a) {
     __shared__ float2 sd[1 << TB];
-    __shared__ float2 sm[416];  // tile_mat_slots(4)
+    __shared__ alignas(16) float2 sm[416];  // tile_mat_slots(4)
+    QS_LDS_VECTORS(sm);
     tile_sweep<TB, Idx, false, kBlock, false, false, false>(amp, Idx(blockIdx.x), Idx(gridDim.x), n_tiles, OneGate{a}, sd,
                                                      sm);
 }
@@ -1517,12 +1531,11 @@ __device__ void fuse_patched(const BatchArgs &A, const BatchJob &J, const BatchC
                 const int k = __builtin_amdgcn_readlane(mk, i), lpp = __builtin_amdgcn_readlane(mlpp, i);
                 const double2 u_next = i + 1 < count ? fetch(i + 1) : u;
                 if (k >= 1 && k <= 3) {
-                    // the wavefront's lanes run in lockstep: the previous
-                    // operator's reads precede these writes, and these writes
-                    // precede the reads below
-                    __builtin_amdgcn_wave_barrier();
+                    // the previous operator's reads precede these writes, and
+                    // these writes precede the reads below
+                    wave_lds_order();
                     if (lane < (1 << (2 * k))) ush[lane] = u;
-                    __builtin_amdgcn_wave_barrier();
+                    wave_lds_order();
                     if (on) {
                         if (k == 1) fuse_member_small<1>(col, D, lpp, ush);
                         else if (k == 2) fuse_member_small<2>(col, D, lpp, ush);
@@ -1701,7 +1714,8 @@ __device__ __forceinline__ void batched_sample(const BatchArgs &A, const BatchJo
 // write-back and invalidate on gfx950) is needed.
 template <int NT>
 __global__ __launch_bounds__(NT) void run_batched(BatchArgs A) {
-    extern __shared__ float2 smem[];
+    alignas(16) extern __shared__ float2 smem[];
+    QS_LDS_VECTORS(smem);
     float2 *sd = smem;                                                   // 2^13 amplitudes
     float2 *wide = smem + (1 << kBatchLdsQubits);                        // a 5-qubit block's matrix
     float2 *raw = smem + (1 << kBatchLdsQubits) + 1024;                  // 2 x 256 entries
@@ -1743,7 +1757,8 @@ __global__ __launch_bounds__(NT) void run_batched(BatchArgs A) {
 // Per job of the wave: draws, rebuilt matrices, and the table of the job's
 // block matrices (default or rebuilt) its sweeps read.
 __global__ __launch_bounds__(kBlock) void batch_prepare(BatchArgs A, int job0) {
-    extern __shared__ float2 smem[];  // 4 x (1024 + 64) complex128
+    alignas(16) extern __shared__ float2 smem[];  // 4 x (1024 + 64) complex128
+    QS_LDS_VECTORS(smem);
     __shared__ uint32_t mask[kBatchMaxBlocks / 32];
     const BatchJob J = A.jobs[job0 + int(blockIdx.x)];
     const BatchCircuit C = A.circs[J.circuit];
@@ -1779,7 +1794,8 @@ struct JobSweep {
 template <bool K5>
 __global__ __launch_bounds__(kBatchWideThreads) void batch_sweep(BatchArgs A, const BatchPart *parts, int step) {
     __shared__ float2 sd[1 << kBatchTileBits];
-    extern __shared__ float2 sm[];
+    alignas(16) extern __shared__ float2 sm[];
+    QS_LDS_VECTORS(sm);
     typedef const __attribute__((address_space(4))) BatchPart *Parts;
     typedef const __attribute__((address_space(4))) BatchJob *Jobs;
     typedef const __attribute__((address_space(4))) BatchCircuit *Circs;
@@ -1893,7 +1909,8 @@ __device__ __forceinline__ void resident_rdm(const float2 *sd, int n, const int 
 // by side on as many CUs.
 template <int NT, int M3, int M4>
 __global__ __launch_bounds__(NT) void run_resident(TrajResidentArgs A) {
-    extern __shared__ float2 smem[];
+    alignas(16) extern __shared__ float2 smem[];
+    QS_LDS_VECTORS(smem);
     float2 *sd = smem;                    // 2^n amplitudes
     float2 *wide = smem + (1 << A.n);     // a 5-qubit block's matrix
     float2 *raw = wide + 1024;            // 2 x 256 entries
@@ -1952,7 +1969,8 @@ template <int NT>
 __global__ __launch_bounds__(NT, 4) void traj_sweep(const TrajSweep *sweeps, const TrajGate *gates,
                                                     uint32_t n_tiles) {
     __shared__ float2 sd[1 << kBatchTileBits];
-    extern __shared__ float2 sm[];
+    alignas(16) extern __shared__ float2 sm[];
+    QS_LDS_VECTORS(sm);
     TrajSweepSrc src;
     src.s = (const __attribute__((address_space(4))) TrajSweep *)(sweeps) + blockIdx.y;
     src.g = (const __attribute__((address_space(4))) TrajGate *)(gates) + src.s->g0;
@@ -2490,7 +2508,7 @@ __global__ __launch_bounds__(kBlock) void sample_draw(const float2 *__restrict__
                 mine[a + a / PER] = make_float2(in[i].x, in[i].y);
                 mine[a + a / PER + 1] = make_float2(in[i].z, in[i].w);
             }
-            __builtin_amdgcn_wave_barrier();  // a wavefront's LDS accesses keep their order
+            wave_lds_order();
 #pragma unroll
             for (int i = 0; i < PER; ++i) keep[i] = mine[lane * (PER + 1) + i];
 #pragma unroll
