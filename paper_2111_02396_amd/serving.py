@@ -1,9 +1,9 @@
 """Continuous-batching request loop over the C ABI.
 
 Requests arrive over time (each a circuit, trajectory count, seed and
-request id).  A request is admitted when its device footprint, 16 * 2^n
-bytes (the state plus room for a second state), fits the free budget, and
-runs on one of two lanes:
+request id).  A request is admitted when its device footprint (the state,
+and room for a second state or for the states that run beside it) fits the
+free budget, and runs on one of two lanes:
 
 * the batch lane takes every admitted request with at most 18 qubits whose
   channels are all mixtures of unitaries and packs whatever is waiting into
@@ -34,7 +34,19 @@ BATCH_MAX_QUBITS = 18
 
 
 def footprint_bytes(n: int) -> int:
-    return 16 * (1 << n)
+    """Device bytes of amplitudes that a request of n qubits may hold: its
+    state and a second one, or those of the trajectories run side by side
+    (qs_run_trajectories keeps up to 255 states of at most 13 qubits beside
+    its own, and up to 64 MiB of them, with 64 bytes of records per 2^13
+    amplitudes, from 14 to 21 qubits)."""
+    state = 8 << n
+    beside = state
+    if n <= 13:
+        beside = 255 * state
+    elif n <= 21:
+        states = min(max(1024 >> (n - 13), 2), 64)
+        beside = (states - 1) * state + states * (64 << (n - 13))
+    return state + beside
 
 
 def batchable(circuit) -> bool:

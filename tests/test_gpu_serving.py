@@ -81,3 +81,27 @@ def test_serving_top_of_the_range_32_qubits(qs):
         alone = serving.run_alone(r)
         assert np.array_equal(alone.samples, mix.samples), r.rid
         assert np.array_equal(alone.choices, mix.choices), r.rid
+
+
+@pytest.mark.parametrize("n,noise", [(13, 0.01), (14, 0.01), (17, 0.01), (19, 0.0), (21, 0.01), (22, 0.01)])
+def test_footprint_covers_what_a_request_holds(qs, n, noise):
+    """The device memory a state holds after a call of many trajectories is
+    within its footprint, but for the 12 MiB or less of staging, reduction and
+    sampling buffers that do not grow with the state."""
+    from paper_2111_02396_amd import serving
+
+    c = W.generic_grid_circuit(n, 3, p_dep=0.01, gamma=noise or None, seed=1)
+    kw = dict(seed=1, max_fuse=3, n_samples=2)
+
+    def run(st):
+        qs.qs_run_trajectories(st.h, c, 300 if n < 17 else 20, **kw)
+        torch.cuda.synchronize()
+
+    with qs.State(n) as st:
+        run(st)  # kernels and library workspaces are loaded
+    before = torch.cuda.mem_get_info()[0]
+    with qs.State(n) as st:
+        run(st)
+        held = before - torch.cuda.mem_get_info()[0]
+    assert held <= serving.footprint_bytes(n) + (12 << 20)
+    assert serving.footprint_bytes(n) <= 16 * (1 << n) + (80 << 20)
