@@ -692,7 +692,10 @@ __device__ __forceinline__ void staged_gate_mfma4(float2 *__restrict__ sd, const
 
 // ---- k = 4 on BF16 MFMA with FP32 operands split in three
 // x = h + m + l with h, m, l BF16 (8 significant bits each, rounded to
-// nearest), exactly for every FP32 x away from the exponent's lower end.  Of
+// nearest), exactly for FP32 |x| from 2^-110 (below, l leaves BF16's range) to
+// 3.39e38 (BF16's largest number).  An infinite component leaves no number in
+// its group, as in the FP32 form, whose sums of real and imaginary parts spread
+// it.  Of
 // the nine products of a split operand pair the three below 2^-26 of the
 // largest are left out; the other six are exact in FP32 and are accumulated
 // in FP32 from the smallest up, 32 terms per instruction.  Against the FP32

@@ -615,3 +615,58 @@ def test_plans_do_not_depend_on_earlier_calls(qs):
                 r = qs.qs_run_trajectories(st.h, c, n_traj, max_fuse=4)
                 sweeps.append(r["gate_sweeps"] / n_traj)
     assert sweeps[0] > sweeps[1] == sweeps[2]
+
+
+# The 4-qubit blocks of sweeps multiply operands split into three BF16 parts.
+# A block rounds each output at most once per accumulation step (six of them)
+# and its matrix once, each 2^-24 of the block's largest term: an error below
+# 8 * 2^-24 a block, in norm and, where one product dominates, per amplitude.
+SPLIT_TOL = 8.0 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("n_traj", [1, 3])
+@pytest.mark.parametrize("log10_norm", [-9.5, 0.0, 15.0])
+def test_split_blocks_far_from_unit_norm(qs, orc, n_traj, log10_norm):
+    """Sweeps on states whose norm is just above where the driver would
+    renormalise (norm^2 1e-19), 1 and 1e30: the scales of the first layer's
+    gates multiply to 10^log10_norm."""
+    n = 15
+    rng = np.random.Generator(np.random.PCG64(17))
+    ops = [W.Op(W.GATE, (q,), [W.random_unitary(1, rng) * 10.0 ** (log10_norm / n)], 0, "scaled") for q in range(n)]
+    for layer in range(1, 4):
+        order = rng.permutation(n)
+        for i in range(0, n - 1, 2):
+            ops.append(W.Op(W.GATE, tuple(int(q) for q in order[i:i + 2]), [W.random_unitary(2, rng)], layer, "pair"))
+    c = W.Circuit(n, ops, "scaled")
+    with qs.State(n) as st:
+        got = qs.qs_run_trajectories(st.h, c, n_traj, max_fuse=4, return_state=True)
+    assert got["gate_k_launches"][4] > 0
+    assert abs(np.log10(np.linalg.norm(got["state"].astype(np.complex128))) - log10_norm) < 1e-3
+    ref = orc.run_trajectory(c, 0, seed=0, return_state=True)["state"]
+    assert rel_l2(got["state"], ref) < SPLIT_TOL * got["gate_k_launches"][4] / n_traj
+
+
+@pytest.mark.parametrize("n_traj", [1, 2])
+def test_split_blocks_keep_small_amplitudes(qs, n_traj):
+    """A product state whose amplitudes fall from 1 to 2^-98: each stays within
+    the blocks' relative error of its exact value, not only of the norm."""
+    n = 14
+    theta = 2.0 ** -7 * (1.0 + 0.05 * np.arange(n))
+    rot = [np.array([[np.cos(t), -np.sin(t)], [np.sin(t), np.cos(t)]], dtype=np.complex128) for t in theta]
+    ops = []
+    for lo, hi in ((0, 4), (4, 8), (8, 12), (12, 14)):
+        m = np.eye(1, dtype=np.complex128)
+        for q in range(lo, hi):
+            m = np.kron(rot[q], m)
+        ops.append(W.Op(W.GATE, tuple(range(lo, hi)), [m], 0, "product"))
+    c = W.Circuit(n, ops, "product")
+    with qs.State(n) as st:
+        got = qs.qs_run_trajectories(st.h, c, n_traj, max_fuse=4, return_state=True)
+    blocks = sum(got["gate_k_launches"]) / n_traj
+    assert got["gate_k_launches"][4] > 0
+    exact = np.ones(1)
+    for q in range(n):
+        exact = np.kron(rot[q][:, 0].real, exact)
+    assert exact.min() < 2.0 ** -90
+    err = np.abs(got["state"].astype(np.complex128) - exact) / exact
+    assert err.max() < SPLIT_TOL * blocks
