@@ -94,7 +94,11 @@ typedef struct {
 enum {
     QS_TRAJ_RETURN_STATE = 1u, /* copy the last trajectory's final amplitudes to final_state */
     QS_TRAJ_TIME_KERNELS = 2u, /* bracket every fused-gate launch with HIP events on the
-                                  state's stream and report their summed durations */
+                                  state's stream and report their summed durations; the
+                                  trajectories then run one by one (an untimed call of up
+                                  to 21 qubits runs them side by side, several times as
+                                  fast; results differ by rounding below 10 qubits and
+                                  for 5-qubit blocks of 11..13) */
     QS_TRAJ_NO_GRAPH = 4u,     /* launch every sweep directly (the default; overrides
                                   QS_TRAJ_GRAPH) */
     QS_TRAJ_GRAPH = 8u         /* replay the default plan's sweeps from a HIP graph where
@@ -307,7 +311,9 @@ qs_status qs_sample_measurements_noalloc(qs_state s, uint64_t seed, uint32_t tra
  * and replays the graph, instead of launching the sweeps one by one.  The
  * results are those of the direct launches (the same kernels on the same
  * matrices).  Off by default: on MI355X with ROCm 7 the replays measured a
- * few percent slower than direct launches of the same sweeps.
+ * few percent slower than direct launches of the same sweeps, and they take
+ * the trajectories one by one (20 qubits: 4.2k against 9.7k trajectories/s
+ * side by side).
  * The circuit's n_qubits must equal the state's.  Results are written to the
  * caller's host arrays in r.  On return the state holds the last trajectory's
  * final vector (lazily normalised; what QS_TRAJ_RETURN_STATE copies out), or

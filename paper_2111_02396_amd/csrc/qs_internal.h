@@ -130,9 +130,6 @@ struct BatchTileGate {
                              // of a resident state, else tile-local bits)
     uint32_t tab2[kMaxTileBits / 2];  // LDS byte offset per logical bit, two per word
     int lofs;                // sweeps: float2 offset in the staged matrices
-    __host__ __device__ int k() const { return int(head & 7u); }
-    __host__ __device__ int lt(int j) const { return int((head >> (4 + 4 * j)) & 15u); }
-    __host__ __device__ int tab(int b) const { return int((tab2[b >> 1] >> (16 * (b & 1))) & 0xffffu); }
 };
 
 struct BatchSweep {          // circuits of n > kBatchLdsQubits
@@ -145,8 +142,6 @@ struct BatchPart {
     int job, tile0, tiles;
 };
 
-struct BatchGate;
-struct BatchTileGate;
 struct BatchChannel;
 struct BatchMember;
 
@@ -162,7 +157,6 @@ struct BatchCircuit {
     const BatchMember *members;
     const double2 *fmats;    // FP64 gate and channel matrices for the members
     int n;
-    int resident;
     int n_gates, nch;
     int n_samples;
     int readout;             // offset of 2n doubles (e0[], e1[]) in the readout pool, or -1

@@ -1041,16 +1041,16 @@ __device__ __forceinline__ void tile_sweep(float2 *__restrict__ amp, Idx first, 
                 case 1: tile_gate_small<1, SwizzledTile, NT>(sd, a.mat(gi), lt, tab, TB); break;
                 case 2: tile_gate_small<2, SwizzledTile, NT>(sd, a.mat(gi), lt, tab, TB); break;
                 case 3:
-                    staged_gate_mfma3<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)),
-                                                      tab, TB);
+                    staged_gate_mfma3<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)), tab,
+                                                        TB);
                     break;
                 case 4:
-if constexpr (SP)
+                    if constexpr (SP)
                         tile_gate_split4<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)), tab,
                                                            TB);
                     else
-                        staged_gate_mfma4<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)),
-                                                      tab, TB);
+                        staged_gate_mfma4<SwizzledTile, NT>(sd, reinterpret_cast<const float *>(sm + a.lofs(gi)), tab,
+                                                            TB);
                     break;
                 default:
                     if constexpr (K5 && K5_MFMA)
@@ -1755,7 +1755,7 @@ __global__ __launch_bounds__(NT) void run_batched(BatchArgs A) {
 // of its blocks bound it, as there).  What a sweep applies, and in which
 // order, is fixed by the circuit's plan, so a job's state does not depend on
 // the jobs beside it.  64 circuits of 12..18 qubits x 16 trajectories: 51 ms
-// with a workgroup per job, 7.8 ms like this (5.5 ms of it sweeps).
+// with a workgroup per job, 5.7 ms like this (5.3 ms of it sweeps).
 
 // Per job of the wave: draws, rebuilt matrices, and the table of the job's
 // block matrices (default or rebuilt) its sweeps read.
@@ -1907,9 +1907,9 @@ __device__ __forceinline__ void resident_rdm(const float2 *sd, int n, const int 
 
 // One trajectory per workgroup, its state in LDS from |0...0> to the end: the
 // blocks in launch order, each selection where its channel stands in the
-// circuit (between the blocks of the operations before it and after it).  Bound by the chain of blocks on one CU (LDS round trip,
-// barrier, a few MFMAs each: about 1 us), so a call's trajectories run side
-// by side on as many CUs.
+// circuit (between the blocks of the operations before it and after it).
+// Bound by the chain of blocks on one CU (LDS round trip, barrier, a few MFMAs
+// each: about 1 us), so a call's trajectories run side by side on as many CUs.
 template <int NT, int M3, int M4>
 __global__ __launch_bounds__(NT) void run_resident(TrajResidentArgs A) {
     alignas(16) extern __shared__ float2 smem[];
@@ -2939,8 +2939,11 @@ hipError_t gate_k(float2 *amp, int n, const GateDesc &g, const float2 *dev, hipS
         if (g.t[0] >= kMfmaTarget) {  // then n - K >= 4: sixteen groups
             const uint64_t batches = uint64_t(1) << (n - K - 4);
             // a few batches per wavefront: the A operands are loaded once for
-            // them (k = 5, 22 qubits: 22.3 us at 8 workgroups per CU, 21.2 at
-            // 4, 19.7 at 2, 20.8 at 1; k = 3 12.2, 11.4, 12.1, 15.6)
+            // them (us a gate on high targets at 1 / 2 / 4 / 8 workgroups per
+            // CU: k = 3, 22 qubits 10.9, 9.8, 9.6, 9.4, 26 qubits 347, 228,
+            // 193, 206; k = 4 14.3, 12.7, 12.4, 12.8 and 279, 200, 205, 209;
+            // k = 5, 24 qubits 60, 59, 64, 69, 26 qubits 259, 224, 242, 247;
+            // up to 20 qubits the same at any)
             const uint64_t cap = uint64_t(device_cus()) * (K == 5 ? 2 : 4);
             const uint64_t grid = std::min<uint64_t>((batches + 3) / 4, cap);
             apply_direct_mfma<K, Idx><<<unsigned(grid), kBlock, 0, st>>>(m, amp, Idx(batches), dev, ta);

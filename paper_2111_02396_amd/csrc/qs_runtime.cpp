@@ -96,7 +96,7 @@ struct qs_state_s {
     // trajectory-driver buffers kept across calls (allocated on first use)
     float2 *side_buf = nullptr;      // states beside this one, and sweep records
     size_t side_cap = 0;             // bytes
-    int *sel_choice_dev = nullptr;   // device-side picks [kChoiceCap] + error flag
+    int *sel_choice_dev = nullptr;   // an error flag, then the device-side picks [kChoiceCap]
     int *sel_choice_host = nullptr;  // pinned mirror
     double *sel_rdm = nullptr;       // the pending channel's reduced density matrix
     float2 *static_buf = nullptr;    // default-plan matrices
@@ -1417,7 +1417,12 @@ struct TrajPlan {
 
 // Side by side, trajectories of n > kBatchLdsQubits share sweep launches of up
 // to this many 2^13-amplitude tiles (64 MiB of states; 512 workgroups are
-// resident at once).  From 22 qubits on one trajectory fills the GPU.
+// resident at once).  Calls of the noisy grid at 256 / 512 / 1024 / 2048 / 4096
+// tiles: 20 trajectories of 15 qubits 0.77, 0.62, 0.62, 0.65, 0.66 ms; 64 of 17
+// 1.93, 1.47, 1.27, 1.25, 1.28; 20 of 20 3.58, 2.56, 2.09, 1.92, 1.96; 20 of 21
+// 4.43, 4.26, 3.61, 3.34, 3.23: beyond 1024 up to a tenth is left at 20 and 21
+// qubits, for twice the memory a step.  From 22 qubits on one trajectory fills
+// the GPU.
 constexpr int kSideTiles = 1024;
 constexpr int kSideMaxQubits = 21;
 // Samples and Z records a call holds on the device at once.
@@ -2389,8 +2394,11 @@ struct Runner {
         };
         for (size_t si = 0;; ++si) {
             const int seg_end = si < slow.size() ? m.channels[slow[si]].op : n_ops;
-            // the one-by-one path's order of the blocks (a resident state too:
-            // the same trajectory rounds alike whichever way it runs)
+            // the one-by-one path's order of the blocks, also for a resident
+            // state: from 10 qubits on the same trajectory then rounds alike
+            // whichever way it runs, but for 5-qubit blocks of 11 to 13 qubits
+            // (VALU in a workgroup, MFMA one by one); below 10 qubits the
+            // kernels differ
             segment_sweeps(seg_start, seg_end, slow.empty(), store, seg);
             for (const SegSweep &ss : seg) {
                 const size_t g0 = P.gates.size();
@@ -3508,7 +3516,7 @@ qs_status qs_sweep_plan(const qs_circuit *c, int max_fuse, int tile_bits, int32_
 }  // extern "C"
 
 // --------------------------------------------------------------------------
-// Batched persistent launch: host planning.
+// Batched launches: host planning.
 // --------------------------------------------------------------------------
 
 namespace {
@@ -3820,8 +3828,8 @@ struct BatchWave {
 
 // States of a wave (1 GiB at most): every launch ends with a partly filled
 // round of workgroups, so few large waves beat cache-sized ones (64 circuits
-// of 12..18 qubits x 16 trajectories: 9.0 ms a batch with 128 MiB waves, 8.6
-// with 256 MiB, 8.2 with all 570 MiB in one).
+// of 12..18 qubits x 16 trajectories: 6.87 ms a batch with 128 MiB waves, 6.01
+// with 256 MiB, 5.72 with all 570 MiB in one).
 constexpr size_t kWaveAmps = size_t(1) << 27;
 constexpr size_t kWavePatched = size_t(1) << 25;  // float2 of rebuilt matrices
 
@@ -3852,8 +3860,10 @@ void plan_waves(std::vector<qs::BatchJob> &jobs, const std::vector<qs::BatchCirc
         }
         // two tiles per workgroup share the staging of the sweep's matrices
         // once that leaves four rounds of workgroups (two per CU); more than
-        // two make the launch's last round longer than they save (the same
-        // batch: 8.95 ms at eight tiles, 8.15 at four, 7.81 at two)
+        // two make the launch's last round longer than they save (at 1 / 2 / 4
+        // / 8 tiles the same batch takes 5.91, 5.66, 5.85, 6.52 ms, 512
+        // trajectories of 18 qubits 7.69, 7.23, 7.29, 7.18, 1024 of 14 0.94,
+        // 0.87, 0.87, 0.87; 16 of 16 qubits, 128 tiles, 0.26, 0.35, 0.54, 0.92)
         const size_t tiles = amps >> qs::kBatchTileBits;
         const int per = tiles >= 4096 ? 2 : 1;
         for (int i = 0; i < w.count; ++i) {
@@ -3933,7 +3943,6 @@ qs_status run_batched_impl(const qs_batch_item *items, const qs_batch_item *size
         qs::BatchCircuit &C = circs[it];
         std::memset(&C, 0, sizeof(C));
         C.n = n;
-        C.resident = P.resident ? 1 : 0;
         C.n_samples = I.n_samples;
         C.readout = -1;
         if (ro.enabled) {

@@ -186,3 +186,20 @@ def test_tuner_times_the_kind_of_call_it_tunes(qs):
         four = qs.qs_run_trajectories(st.h, c, 4, seed=1, max_fuse=0)
     assert one["tune_ms"] > 0.0 and four["tune_ms"] == 0.0
     assert (one["max_fuse_used"], one["tile_bits_used"]) == (four["max_fuse_used"], four["tile_bits_used"])
+
+
+@pytest.mark.parametrize("n,f", [(5, 4), (9, 4), (11, 5), (12, 5), (13, 5)])
+def test_both_ways_round_within_the_blocks_errors(qs, n, f):
+    """Where the workgroup's kernels differ from the one-by-one path's (below
+    10 qubits, and 5-qubit blocks of 11 to 13), the states differ by no more
+    than the two paths' rounding: an output of a block sums 2^f products of
+    complex numbers in FP32, so at most 2^f + 2 roundings of 2^-24 of its norm
+    a block and path."""
+    c = W.generic_grid_circuit(n, 10, p_dep=0.02, seed=n)
+    kw = dict(seed=3, max_fuse=f, return_state=True)
+    with qs.State(n) as st:
+        side = qs.qs_run_trajectories(st.h, c, 6, **kw)
+        alone = qs.qs_run_trajectories(st.h, c, 6, time_kernels=True, **kw)
+    assert np.array_equal(side["choices"], alone["choices"])
+    blocks = sum(alone["gate_k_launches"]) / 6
+    assert rel_l2(side["state"], alone["state"]) < 2 * blocks * (2 ** f + 2) * 2.0 ** -24
