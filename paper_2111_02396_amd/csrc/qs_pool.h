@@ -19,9 +19,10 @@ namespace qs {
 // chunks of a concurrent call plan at the same time, and with one loop at a
 // time they waited for one another (four states of two 11-qubit trajectories
 // each 200 us a call, now 110; of two noisy 14-qubit ones 1.33 ms, now 0.82).
-// A loop wakes no more helpers than it has pieces, or all of them with one
-// system call (two noiseless trajectories of one qubit, planned by the caller
-// alone: 55 us a call with fifteen threads woken, now 29).
+// A loop of up to three threads wakes only those it has room for (two
+// noiseless trajectories of one qubit, planned by the caller alone: 55 us a
+// call with fifteen threads woken, now 29); a longer one wakes all with one
+// system call, and the first of them take its places.
 class HostPool {
   public:
     static HostPool &get() {
@@ -48,7 +49,7 @@ class HostPool {
             std::lock_guard<std::mutex> lock(mu_);
             open_.push_back(&loop);
         }
-        if (2 * width > size()) cv_.notify_all();  // one system call
+        if (width >= 4) cv_.notify_all();  // the first to wake take the places
         else
             for (unsigned i = 1; i < width; ++i) cv_.notify_one();
         loop.drain();
