@@ -246,3 +246,22 @@ def test_batched_waves_agree_with_short_ranges(qs):
         part = run(first, 6)
         assert np.array_equal(full["choices"][first:first + 6], part["choices"])
         assert np.array_equal(full["samples"][first:first + 6], part["samples"])
+
+
+def test_batched_ranges_planned_on_their_own(qs):
+    """The trajectories of a long call equal those of a short one whose plan
+    was made for it: the same circuit with every matrix stored twice is another
+    entry of the caches."""
+    c = W.generic_grid_circuit(18, 3, p_dep=0.02, seed=6)
+    twin = W.Circuit(c.n, [W.Op(o.kind, o.qubits, [m.copy() for m in o.mats], o.moment, o.name) for o in c.ops], "twin")
+
+    def run(circuit, offset, count):
+        w = TrajectoryWorkload("w", circuit, n_traj=count, seed=9, circuit_id=1, n_samples=4)
+        w.traj_offset = offset
+        res, _ = qs.qs_run_batched([w], max_fuse=3)
+        return res[0]
+
+    part = run(twin, 300, 5)
+    full = run(c, 0, 320)
+    assert np.array_equal(full["choices"][300:305], part["choices"])
+    assert np.array_equal(full["samples"][300:305], part["samples"])
